@@ -1,16 +1,16 @@
 #!/usr/bin/env python3
 """Benchmark of the radix top-k hot path on one MI355X.
 
-A "step" is one complete selection (every kernel of the path: sample histogram, the sweep over X, later digit
-passes, single-workgroup finish) over one batch of synthetic input that is already resident in HBM.  The
-workload is the benchmark's headline case that fits one GPU:
+A "step" is one complete selection (every kernel of the path: the bound from a sample, the sweep over X into a list, the
+list into buckets, the buckets in order) over one batch of synthetic input that is already resident in HBM.  The
+workload is the headline case that fits one GPU:
 
     config 4: single query, n = 2^28 fp32 keys i.i.d. uniform in [-1e6, 1e6), k = 2^20, largest
 
 Prints ONE JSON line: keys/sec over the timed region, the roofline of the dominant kernel (measured live with HIP
 events recorded by the library on the launch stream), the CPU oracle timed on a bounded sample, and -- after the
 timed region of the headline, so that it is not disturbed -- one row per (config, k, direction, scaling) of
-the benchmark's other configurations (`configs`), each with its time, keys/s, the bytes its passes moved and the
+the other configurations (`configs`), each with its time, keys/s, the bytes its passes moved and the
 fraction of HBM peak that is.
 """
 from __future__ import annotations
@@ -37,6 +37,9 @@ def bytes_moved(tr, n, es, k):
         return 0, "skipped"
     if ps[0].where == 4:                                   # one-sweep row kernel: X once (+ its first part again, cached)
         return es * n + out, "one sweep"
+    if ps[0].where == 5:                                   # sample, one sweep into a list, the list in order (a long list is
+        listed = tr.pre_kept                               # moved once more, into buckets); crowded rows list next to nothing
+        return es * (tr.pre_elems + n) + (32 if listed > 8192 else 16) * listed + out, "sample + one sweep into a list"
     def pass_bytes(i):
         """read of pass i's source + write of its candidates (an in-place pass writes none; after in-place passes
         that began over X the source is still X)"""
@@ -177,7 +180,7 @@ def main() -> int:
     if prefilter:
         hist_bytes = es * tr.pre_elems                 # the sample
         sweep_bytes = es * n + 8 * tr.pre_kept         # X once, what is kept written once
-        names = ("hist_keys_sample", "prefilter_keys")
+        names = ("list_bound", "list_sweep") if tr.passes[0].where == 5 else ("hist_keys_sample", "prefilter_keys")
     else:
         p0 = tr.passes[0]
         hist_bytes = es * n
@@ -237,7 +240,7 @@ def main() -> int:
                        "passes": [[p.where, p.cand_before, p.cand_after, p.winners] for p in tr.passes]},
     }
 
-    # ---- every other (config, k, direction, scaling) of the benchmark spec, after the headline's timed region
+    # ---- every other (config, k, direction, scaling), after the headline's timed region
     def time_rows(xd, kk, largest, scaling, code, batch, nn, reps=10, sorted_out=False, wsb=None):
         vb = torch.empty((batch, kk), dtype=xd.dtype, device=dev)
         ib = torch.empty((batch, kk), dtype=torch.int64, device=dev)

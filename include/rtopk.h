@@ -50,7 +50,9 @@ enum {
      * subtracted (one fp32 rounding) from every element before digits are taken, which spreads
      * the exponents of keys clustered near a_s.  The rounded difference orders keys weakly, so
      * the library finishes the selection on the unscaled key; the result is identical with and
-     * without the flag and for every seed.  Ignored for 16-bit keys. */
+     * without the flag and for every seed.  Ignored for 16-bit keys.  (The list kernels, which the automatic
+     * choice takes for most calls, compare whole keys and need no digits to be spread: they draw and
+     * record a_s and do nothing else with it.) */
     RTOPK_FLAG_SCALING = 1u << 0,
     /* Accepted and without effect: the per-pass records (rtopk_row_trace below) are the library's own
      * loop state, so they are written on every call. */
@@ -233,7 +235,9 @@ typedef struct {
                                   pass 0 swept the row again instead of reading what was kept;
                                   2: the same on purpose -- the sample showed the keys crowded into the
                                   bins to keep (over 1/8 of the row; 1/16 for 16-bit keys), so the sweep kept nothing
-                                  (pre_bound is the bin count) and only counted                     */
+                                  (pre_bound is the bin count) and only counted.  List kernels: the
+                                  sample showed the keys crowded in the same sense; pre_kept then
+                                  stays 0 and the record counts the whole row as looked at          */
     uint32_t pre_merged;       /* 1: the prefilter's bound bin was the k-th key's bin, and pass 0 had no
                                   sweep of its own -- pass 1's sweep over what was kept classified by both
                                   digits at once (pass 0's record: its selectBin; winners are what lay above
@@ -246,7 +250,9 @@ typedef struct {
     uint32_t reserved[6];
     struct {
         uint32_t where;        /* 0 pass not run; 1 many workgroups; 2 single-workgroup finish;
-                                  3 fused one-workgroup-per-row kernel; 4 one-sweep row kernel       */
+                                  3 fused one-workgroup-per-row kernel; 4 one-sweep row kernel;
+                                  5 list: everything not below a key taken from a sample, ranked
+                                  directly (one record, source 3, stands for the whole selection)    */
         uint32_t bin;          /* chosen bin of this digit                                           */
         uint32_t k_after;      /* rank of the k-th key inside the bin (0 if the whole bin was taken) */
         uint32_t cand_after;   /* candidates passed on to the next digit (0: the row is finished)    */

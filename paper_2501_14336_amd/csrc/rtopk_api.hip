@@ -215,6 +215,68 @@ static Layout make_layout(int64_t batch, int64_t n, const Config& c) {
     return L;
 }
 
+// Does the call go through lists (rtopk_list.inl), and how?  The automatic choice only: a call with tuning knobs gets the
+// kernels it names.
+static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, const rtopk_tuning* tn, bool ragged, ListPlan* L) {
+    memset(L, 0, sizeof(*L));
+    if (tn && (tn->digit_bits || tn->path || tn->wgs_per_row || tn->small_threshold || tn->prefilter)) return false;
+    const int eb = elem_bytes(dt), E = 16 / eb;
+    // the smallest sample is 8 KB of a row, a quarter of 32 KB
+    if (n * eb < 32768) return false;
+    // the list is to stay below half the row (in a ragged batch: half the longest row, for every row)
+    if (k * 5 > (ragged ? n : n * 2)) return false;
+    const int64_t vecs = n * eb / 16;
+    L->sample = vecs >= (1 << 20) ? 4 : vecs >= (1 << 16) ? 3 : vecs >= (1 << 14) ? 2 : vecs >= (1 << 12) || batch <= 256 ? 1 : 0;
+    // one workgroup per row: rows of up to 256 KB, in large batches up to 1 MB
+    const bool by_row = n * eb <= (256 << 10) || (batch >= 256 && n * eb <= (1 << 20));
+    if (by_row && L->sample > 2) L->sample = 2;
+    double listed = 0.0, room = 0.0;  // expected length of the list, and with a margin
+    auto expect = [&]() {
+        const double elems = (double)((L->sample == 4 ? (eb == 4 ? 16384 : 8192) : L->sample == 3 ? 4096 : 512 << L->sample) * E);
+        const double ks = (double)k * elems / (double)n;
+        listed = (ks + 6.0 * __builtin_sqrt(ks) + 10.0) * 1.08 * (double)n / elems;
+        room = listed * 1.08 + 64.0;
+    };
+    expect();
+    if (by_row) {
+        // (a list that does not fit is put in order by k_list_redo: better a little too much room)
+        L->row_block = batch > 256 && room * 1.2 <= 2048.0 ? 256 : batch > 256 && room * 1.2 <= 4096.0 ? 512 : room <= 8192.0 ? 1024 : 0;
+        if (L->row_block == 1024 && L->sample == 0) L->sample = 1;
+    }
+    if (L->row_block == 0 && L->sample < 2) {  // (the kernels for many workgroups per row take larger samples)
+        if (vecs < 4096) return false;
+        L->sample = 2;
+    }
+    expect();
+    if (listed * 1.1 > 0.5 * (double)n) return false;
+    const bool is_long = L->row_block == 0 && room > 8192.0;
+    // one workgroup of 1024 threads per compute unit where the list's histogram is counted, else four of 512 (three for 16-bit keys)
+    const int64_t tile_elems = (int64_t)(is_long ? 1024 : kHostGridBlock) * 64 / eb;
+    const int64_t ntiles = (n + E - 1 + tile_elems - 1) / tile_elems;
+    int64_t G = (is_long ? 256 : eb == 4 ? 1024 : 768) / batch;
+    if (G < 1) G = 1;
+    if (G > ntiles) G = ntiles;
+    L->G = (int)G;
+    L->finish = room > 4096.0 ? 1024 : room > 2048.0 ? 512 : 256;
+    L->bucket_shift = 11;
+    while ((k >> L->bucket_shift) + 1 > (int64_t)kListMaxBuckets) ++L->bucket_shift;
+    L->nb = is_long ? (u32)((k >> L->bucket_shift) + 1) : 0u;
+    int64_t ties = n > 16384 ? 128 / batch : 0;
+    if (n > 16384 && ties < 1) ties = 1;
+    if (ties > ntiles) ties = ntiles;
+    L->ties = (int)ties;
+    if (batch * ((int64_t)L->nb + 1 + ties) >= ((int64_t)1 << 22) || batch * G >= ((int64_t)1 << 22)) return false;  // grid sizes
+    u64 off = 256;
+    auto take = [&](u64 bytes) { const u64 at = off; off = align_up(off + bytes, 16); return (u32)at; };
+    L->hist_off = take(is_long ? kMaxBins * 4 : 0);
+    L->cursor_off = take((u64)L->nb * 4);
+    L->first_off = take((u64)L->nb * 4);
+    L->seg_off = take((u64)G * 4);
+    L->tile_off = take((u64)((n + E - 1) / (kHostGridBlock * 64 / eb) + 1) * 4);  // (the smaller tiles' number)
+    L->stack_off = take(((u64)n / 256 + 64 + 16 * (u64)L->nb) * 16);
+    return off + 256 + 8 <= (u64)n * 4;  // (the upper half of a candidate array)
+}
+
 }  // namespace rtopk
 
 using namespace rtopk;
@@ -348,8 +410,17 @@ static rtopk_status select_impl(const void* keys, const int64_t* row_offsets, co
     for (int i = 0; i < c.npass; ++i) P.pass[i] = c.pass[i];
 
     hipStream_t st = (hipStream_t)hip_stream;
+    ListPlan list;
+    const bool by_list = make_list_plan(batch, n, k, dt, tuning, row_offsets != nullptr, &list);
     (void)hipGetLastError();  // an error left by earlier HIP calls of the process is not this call's
     const bool scaled = (flags & RTOPK_FLAG_SCALING) && dt == RTOPK_F32;
+    if (by_list) {
+        switch (dt) {
+            case RTOPK_F32: return launch_list_f32(P, list, st, events);
+            case RTOPK_F16: return launch_list_f16(P, list, st, events);
+            case RTOPK_BF16: return launch_list_bf16(P, list, st, events);
+        }
+    }
     switch (dt) {
         case RTOPK_F32: return launch_f32(P, c, scaled, st, events);
         case RTOPK_F16: return launch_f16(P, c, false, st, events);

@@ -25,6 +25,22 @@ rtopk_status launch_f32(const Params& P, const Config& c, bool scaled, hipStream
 rtopk_status launch_f16(const Params& P, const Config& c, bool scaled, hipStream_t st, void* const* events);
 rtopk_status launch_bf16(const Params& P, const Config& c, bool scaled, hipStream_t st, void* const* events);
 
+// Plan of a call that goes through lists (rtopk_list.inl).  Offsets: bytes from the start of a row's working memory.
+constexpr unsigned kListMaxBuckets = 4096;
+struct ListPlan {
+    int G;            // workgroups per row in the sweep
+    int row_block;    // one workgroup per row does everything: its threads (0: many workgroups per row)
+    int sample;       // which size of sample: 512, 1024, 2048, 4096 or 16384 (16-bit keys: 8192) vectors of 16 bytes
+    int finish;       // short lists: threads of the workgroup that puts a row's list in order
+    int ties;         // workgroups per row that fetch elements equal to the bound, where those are very many
+    u32 nb;           // long lists: buckets per row (0: short lists)
+    u32 bucket_shift; // ... of 2^bucket_shift ranks
+    u32 hist_off, cursor_off, first_off, seg_off, tile_off, stack_off;
+};
+rtopk_status launch_list_f32(const Params& P, const ListPlan& L, hipStream_t st, void* const* events);
+rtopk_status launch_list_f16(const Params& P, const ListPlan& L, hipStream_t st, void* const* events);
+rtopk_status launch_list_bf16(const Params& P, const ListPlan& L, hipStream_t st, void* const* events);
+
 // Launch geometry the host needs for sizing.
 constexpr int kHostHistBuffers = 6;  // global histograms per row: four in rotation, the sample's, the prefilter's second
 constexpr int kHostSwgBuffers = 4;   // per-workgroup record sets per row: three in rotation, the prefilter's second

@@ -1878,7 +1878,9 @@ __global__ void __launch_bounds__(kRowBlock) k_row(Params P, bool only_redo) {
     __shared__ Shared<kRowBlock> sm;
     const int row = blockIdx.x;
     rtopk_row_trace* st = row_state(P, row);
-    if (only_redo && st->redo != 1u) return;
+    const bool skip = only_redo && st->redo != 1u;
+    __syncthreads();  // (every wave has looked at the mark before init_row clears it)
+    if (skip) return;
     const RowShape rs = row_shape<KeyOf<DT>::kBytes>(P, row);
     const float drawn = init_row<DT>(P, row, st, rs, only_redo);
     if (rs.k == 0) return;  // (ragged batches: an empty row, or nothing wanted from it)
@@ -1924,7 +1926,9 @@ __global__ void __launch_bounds__(kRowBlock) k_row_resident(Params P, bool only_
     __shared__ Shared<kRowBlock> sm;
     typedef KeySource<DT, kRowBlock, key_vecs<DT>(), false> Source;
     constexpr int kTiles = kResidentVecs / key_vecs<DT>();
-    if (only_redo && row_state(P, blockIdx.x)->redo != 1u) return;
+    const bool skip = only_redo && row_state(P, blockIdx.x)->redo != 1u;
+    __syncthreads();  // (every wave has looked at the mark before init_row clears it)
+    if (skip) return;
 #ifdef RTOPK_X_AHEAD
     constexpr int kAhead = RTOPK_X_AHEAD;
 #else

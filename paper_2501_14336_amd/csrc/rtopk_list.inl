@@ -1,0 +1,1358 @@
+// Selection through a list: the automatic choice for rows of 8192 keys up while k is at most 0.4 n.
+//
+// selectBin (paper Section 2.3.1) applied to a sample of the row gives a key T that very probably lies at or below the
+// k-th key.  ONE sweep over X then does nothing but compare every element with T and append the few that are not below
+// it to a list; whenever the list holds at least k elements it contains the k-th key and is the top of the row,
+// exactly, so everything that follows (countBin, selectBin, filter, and the order of the output) works on the list.
+// Nothing is counted in the sweep, no digit decides what is kept, and the only thing that many workgroups have to
+// agree on is T.  The result never depends on the sample: a list that comes out short (the sample misled), or longer
+// than half the row, has the row done again by one workgroup that selects the k-th key from all of X (k_list_redo).
+//
+//   k_list_row      short rows, or many: one workgroup per row does all of the following
+//   k_list_bound    one workgroup per row: sample, T
+//   k_list_sweep    many workgroups per row: X -> list, one segment per workgroup
+//   k_list_finish   (short lists) one workgroup per row: the list, best first, is the output
+//   k_list_scatter  (long lists) many workgroups per row: the list into buckets of about 2048 ranks each,
+//   k_list_buckets  and one workgroup per bucket puts its ranks in order
+//   k_list_redo     rows whose list was no use (normally none: the launch finds nothing to do)
+//
+// List entries are 64-bit numbers, distinct within a row, whose descending order is the order of the output: the
+// ordered key (direction applied, 16 or 32 bits) above the inverted index (as many bits as n needs).  An entry holds
+// all there is to know about an element but a NaN's payload.
+//
+// Rows with very many elements equal to T (most of the row one value) would make a long list for nothing.  The sample
+// shows that; the sweep then keeps only what is better than T and counts the equal elements of every tile, and
+// the ones with the lowest positions are read from X again, straight into the output (ties_of_row).
+#include "rtopk_kernels.inl"
+
+namespace rtopk {
+
+constexpr u32 kListBins = 4096;                 // bins of a long list's histogram
+constexpr int kListStage = 256;                 // staged entries per wave (short lists)
+constexpr int kListStageLong = 512;             // ... (long lists)
+constexpr int kListBucketBlock = 512;          // threads per workgroup of the buckets' kernel (4096 entries in LDS)
+constexpr u32 kListRowTiles = 128;              // tiles of the longest row that one workgroup takes
+constexpr u32 kListTies = 16384;                // equal elements from which on they are counted, not listed
+
+// How a sweep deals a row: tiles of four 16-byte vectors per thread (16 elements, or 32 of 16 bits).
+constexpr int kLongBlock = 1024;                // threads per workgroup of a long list's sweep (one workgroup per compute unit)
+template <int DT, bool LONG, bool NT = false>
+using ListSource = KeySource<DT, LONG ? kLongBlock : kGridBlock, 4, NT>;
+
+enum : u32 { kListSkip = 0, kListPlain = 1, kListTied = 2 };
+
+// What k_list_bound decides about a row.
+struct ListRow {
+    u32 mode;      // kListSkip: nothing wanted; kListPlain: list what is >= T; kListTied: list what is > T, count == T
+    u32 T;         // key, direction applied
+    u32 exact;     // 1: compare keys; 0: compare the element with the number t
+    float t;
+    u64 lo;        // long lists: bin of an entry = min((entry - lo) >> sh, kListBins - 1)
+    u32 sh;
+    u32 total;     // entries (long lists, and short ones that do not fit one workgroup's LDS)
+    u32 end;       // long lists: entries in bins that begin below rank k
+    u32 pad;
+};
+static_assert(sizeof(ListRow) % 8 == 0, "read by words");
+// Bits of rtopk_row_trace::redo that the list kernels set and k_list_redo looks at: the list is no use; it was too long to
+// put in order in LDS (it is all in array `end`); so were some of its buckets.
+enum : u32 { kRedoRow = 1, kRedoList = 2, kRedoBuckets = 4 };
+
+// row_shape, in scalar registers (a ragged batch's comes from memory).
+template <int DT>
+__device__ __forceinline__ RowShape row_shape_scalar(const Params& P, int row) {
+    RowShape r = row_shape<KeyOf<DT>::kBytes>(P, row);
+    const u64 x = (u64)(uintptr_t)r.x;
+    const u32 lo = (u32)__builtin_amdgcn_readfirstlane((u32)x), hi = (u32)__builtin_amdgcn_readfirstlane((u32)(x >> 32));
+    r.x = (const char*)(uintptr_t)(((u64)hi << 32) | lo);  // (the builtin's result is signed: no widening of it)
+    r.n = __builtin_amdgcn_readfirstlane(r.n);
+    r.k = __builtin_amdgcn_readfirstlane(r.k);
+    return r;
+}
+
+// A row's decision, read into scalar registers (it is the same for every lane, which a load does not know).
+__device__ __forceinline__ ListRow list_row_scalar(const ListRow* p) {
+    ListRow r;
+    constexpr int kWords = sizeof(ListRow) / 4;
+    u32 w[kWords];
+#pragma unroll
+    for (int i = 0; i < kWords; ++i) w[i] = __builtin_amdgcn_readfirstlane(((const u32*)p)[i]);
+    __builtin_memcpy(&r, w, sizeof(r));
+    return r;
+}
+
+// Per-row working memory beside the list: the upper half of the row's first candidate array (the list proper is at
+// most half a row).  Offsets in bytes from its 256-byte-aligned start come from the host (ListPlan).
+__device__ __forceinline__ char* list_meta(const Params& P, int row) {
+    const uintptr_t a = (uintptr_t)(P.cand[0] + (size_t)row * P.cand_stride + (size_t)((P.n + 1) / 2));
+    return (char*)((a + 255) & ~(uintptr_t)255);
+}
+__device__ __forceinline__ ListRow* list_row(const Params& P, int row) { return (ListRow*)list_meta(P, row); }
+template <class T>
+__device__ __forceinline__ T* list_part(const Params& P, int row, u32 off) { return (T*)(list_meta(P, row) + off); }
+__device__ __forceinline__ u64* list_array(const Params& P, u32 which, int row) {
+    return (u64*)(P.cand[which] + (size_t)row * P.cand_stride);
+}
+
+// Entry of an element, and back.
+struct ListEntry {
+    u32 kshift, ib, dirmask, idx_max;  // kshift: 16 for 16-bit keys, which are kept in the upper half of their word
+    __device__ __forceinline__ u64 of(u32 key, u32 idx) const { return ((u64)(key >> kshift) << ib) | (u64)(idx_max - idx); }
+    __device__ __forceinline__ u32 idx(u64 e) const { return idx_max - ((u32)e & idx_max); }
+    __device__ __forceinline__ u32 key(u64 e) const { return (u32)(e >> ib) << kshift; }
+};
+template <int DT>
+__device__ __forceinline__ ListEntry list_entry(const Params& P) {
+    ListEntry c;
+    c.kshift = DT == RTOPK_F32 ? 0u : 16u;
+    c.ib = (u32)__builtin_popcount(P.idx_max);
+    c.dirmask = P.dirmask;
+    c.idx_max = P.idx_max;
+    return c;
+}
+// The element's own bits from its key; a NaN's are fetched from the row.
+template <int DT>
+__device__ __forceinline__ u32 raw_of_key(u32 key, u32 idx, const RowShape& rs, u32 dirmask) {
+    const u32 o = key ^ dirmask;
+    const u32 nan = DT == RTOPK_F32 ? 0xffffffffu : 0xffff0000u;
+    if (o == nan) return load_value<DT>(rs.x, idx);
+    const u32 b = (o & 0x80000000u) ? (o ^ 0x80000000u) : ~o;
+    return DT == RTOPK_F32 ? b : b >> 16;
+}
+
+// ------------------------------------------------------------------------------------------------
+// T from a sample
+// ------------------------------------------------------------------------------------------------
+
+// The rank-th largest (or a little less) of the values that each(f) hands to f, over all threads of the workgroup; it lies in
+// [lo, hi], and values below lo are passed over.  2048 bins divide [lo, hi] evenly; the bin in question is divided again
+// until it holds few values, and its lower edge is returned (*exact: until it was one value).
+struct RankShared {
+    u32 hist[2 * 2049];  // two copies, a word apart (see HistSlot)
+    u32 wsum[16], selv[3];
+};
+template <int B, class Each>
+__device__ __forceinline__ u32 sample_rank(Each&& each, u32 rank, u32 lo, u32 hi, RankShared& sm, bool* exact) {
+    constexpr int kPer = 2048 / B;
+    const u32 tid = threadIdx.x;
+    u32* mine = sm.hist + (lane_id() & 1u) * 2049u;
+    u32 left = rank;
+    for (;;) {
+        const u32 width = hi > lo ? 32u - (u32)__builtin_clz(hi - lo) : 0u, sh = width > 11u ? width - 11u : 0u;
+        for (u32 j = tid; j < 2u * 2049u; j += B) sm.hist[j] = 0;
+        if (tid == 0) sm.selv[0] = sm.selv[1] = sm.selv[2] = 0;
+        __syncthreads();
+        each([&](u32 v) __attribute__((always_inline)) {
+            if (v >= lo && v <= hi) atomicAdd(&mine[(v - lo) >> sh], 1u);
+        });
+        __syncthreads();
+        u32 c[kPer], s = 0;
+        const u32 r0 = tid * kPer;  // position counted from the top bin
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const u32 b = 2047u - (r0 + i);
+            c[i] = sm.hist[b] + sm.hist[2049u + b];
+            s += c[i];
+        }
+        const u32 incl = block_inclusive_scan<B>(s, sm.wsum);
+        u32 run = incl - s;
+        if (run < left && left <= incl) {
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                if (run < left && left <= run + c[i]) {
+                    sm.selv[0] = 2047u - (r0 + i);
+                    sm.selv[1] = run;
+                    sm.selv[2] = c[i];
+                }
+                run += c[i];
+            }
+        }
+        __syncthreads();
+        const u32 bin = sm.selv[0], inside = sm.selv[2];
+        left -= sm.selv[1];
+        __syncthreads();
+        lo += bin << sh;
+        hi = sh == 0u ? lo : lo + ((1u << sh) - 1u);
+        *exact = sh == 0u;
+        if (sh == 0u || inside <= 1u + rank / 16u) return lo;
+    }
+}
+
+__device__ __forceinline__ u32 mix32(u32 z) {
+    z ^= z >> 16; z *= 0x7feb352du;
+    z ^= z >> 15; z *= 0x846ca68bu;
+    return z ^ (z >> 16);
+}
+
+// A vector's elements -> their keys (direction applied), in place; and the key of element j of such a vector.
+template <int DT>
+__device__ __forceinline__ void keys_of_vector(uint4& q, u32 dirmask) {
+    u32* w = (u32*)&q;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (DT == RTOPK_F32) {
+            w[i] = KeyOf<DT>::key(w[i]) ^ dirmask;
+        } else {  // two 16-bit keys per word (see KeySource::digits)
+            const u32 thr = DT == RTOPK_F16 ? 0x03ff03ffu : 0x007f007fu;
+            const u32 x = w[i], sb = x & 0x80008000u;
+            u32 key = x ^ ((sb - (sb >> 15)) | 0x80008000u);
+            const u32 nb = ((x & 0x7fff7fffu) + thr) & 0x80008000u;
+            key |= (nb - (nb >> 15)) | nb;
+            w[i] = dirmask ? ~key : key;
+        }
+    }
+}
+template <int DT>
+__device__ __forceinline__ u32 key_in_vector(const uint4& q, int j) {
+    const u32 w[4] = {q.x, q.y, q.z, q.w};
+    if constexpr (DT == RTOPK_F32) return w[j % 4];
+    else return (j & 1) ? w[j / 2 % 4] & 0xffff0000u : w[j / 2 % 4] << 16;
+}
+
+// Bound by latency: V independent loads per lane, then a few phases with barriers, on one compute unit.  The sample is
+// B * V vectors of 16 bytes, in runs of 8 (one 128-byte line), one run from a hashed place in each of B * V / 8 equal
+// stretches of the row: a trend along the row, or any period in it, cannot line up with that.
+// The rank is taken among the MAXIMA of vectors (or of all a lane's vectors) while it is small against their number:
+// neighbouring elements that are alike then count once, so that a row whose best elements lie together does not look
+// richer than it is, and there are fewer values to rank.  The rank that stands for the row's k-th key is its share
+// ks = k * sample / n, plus six standard deviations of a Poisson count, plus 8.
+// te: counters of ties per tile, nt of them, cleared if they will be used.  Thread 0 fills in *lr.
+template <int DT, int B, int V>
+__device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L, int row, const RowShape& rs, rtopk_row_trace* st,
+                                             ListRow* lr, u32* te, u32 nt, RankShared& sm, u32* red) {
+    constexpr int E = 16 / KeyOf<DT>::kBytes;
+    constexpr u32 kRun = 8;
+    const u32 tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    KeySource<DT, kGridBlock, key_vecs<DT>(), false> src;
+    src.init(rs);
+    const u32 v0 = src.lead != 0 ? 1u : 0u;
+    const u32 v1 = (u32)(((u64)src.lead + (u64)rs.n) / E);
+    const u32 groups = v1 > v0 ? (v1 - v0) / kRun : 0u;  // whole runs inside the row
+    constexpr u32 kRuns = (u32)(B * V) / kRun;
+    const ListEntry ent = list_entry<DT>(P);
+    const bool sampled = groups >= kRuns + kRuns / 2u && (u64)rs.k * 5u <= (u64)rs.n * 2u;
+    uint4 q[V];
+    if (sampled) {
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+            const u32 j = (u32)u * B + tid, c = j / kRun;
+            const u32 g = (u32)((((u64)c << 16 | (mix32(c) >> 16)) * groups / kRuns) >> 16);
+            q[u] = load16<false>(src.abase + (v0 + g * kRun + j % kRun));
+        }
+    }
+    init_row<DT>(P, row, st, rs);
+    if (rs.k == 0) {
+        if (tid == 0) lr->mode = kListSkip;
+        return;
+    }
+    if (L.nb != 0) {  // a long list: its histogram and the buckets' write positions
+        u32* gh = list_part<u32>(P, row, L.hist_off);
+        for (u32 j = tid; j < kListBins; j += B) gh[j] = 0;
+        u32* cur = list_part<u32>(P, row, L.cursor_off);
+        for (u32 j = tid; j < L.nb; j += B) cur[j] = 0;
+    }
+    if (!sampled) {  // (ragged batches: a row that is short against the batch's longest one: everything is listed)
+        if (tid == 0) {
+            lr->mode = kListPlain;
+            lr->T = 0;
+            lr->exact = 1;
+            lr->t = 0.0f;
+            lr->lo = 0;
+            const u32 top = ent.ib + (DT == RTOPK_F32 ? 32u : 16u);
+            lr->sh = top > 12u ? top - 12u : 0u;
+        }
+        return;
+    }
+    constexpr u32 kVecsTotal = (u32)(B * V), kElems = kVecsTotal * E;
+    const u32 ks = (u32)(((u64)rs.k * kElems + rs.n - 1u) / rs.n);
+    const u32 rank = ks + (u32)(6.0f * __builtin_sqrtf((float)ks)) + 8u;
+    u32 vmax[V], lmax = 0;
+#pragma unroll
+    for (int u = 0; u < V; ++u) {
+        keys_of_vector<DT>(q[u], P.dirmask);
+        vmax[u] = 0;
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            const u32 k = key_in_vector<DT>(q[u], j);
+            vmax[u] = vmax[u] > k ? vmax[u] : k;
+        }
+        lmax = lmax > vmax[u] ? lmax : vmax[u];
+    }
+    // the best of the sample, and the worst of the lanes' best (at least B elements are not below it)
+    u32 top = lmax, low = lmax;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const u32 a = __shfl_xor(top, o, 64), b = __shfl_xor(low, o, 64);
+        top = top > a ? top : a;
+        low = low < b ? low : b;
+    }
+    if (lane == 0) {
+        red[2 * wave] = top;
+        red[2 * wave + 1] = low;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < B / 64; ++w) {
+        top = top > red[2 * w] ? top : red[2 * w];
+        low = low < red[2 * w + 1] ? low : red[2 * w + 1];
+    }
+    __syncthreads();
+    u32 T;
+    bool exact;
+    if (rank <= (u32)B / 4u) {
+        T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) { f(lmax); }, rank, low, top, sm, &exact);
+    } else if (rank <= kVecsTotal / 4u) {
+        T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < V; ++u) f(vmax[u]);
+        }, rank, rank <= (u32)B ? low : 0u, top, sm, &exact);
+    } else {
+        T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < V; ++u)
+#pragma unroll
+                for (int j = 0; j < E; ++j) f(key_in_vector<DT>(q[u], j));
+        }, rank, rank <= (u32)B ? low : 0u, top, sm, &exact);
+    }
+    // of the sample: how many equal T (which matters if T is one key and not the edge of a range), how many share the first
+    // digit of T or have a better one
+    const u32 d0 = P.pass[0].bits, edge = (T >> (32u - d0)) << (32u - d0);
+    u32 eq = 0, crowd = 0;
+    if (exact || low >= edge) {  // (else some lane has no element that good: far from crowded)
+#pragma unroll
+        for (int u = 0; u < V; ++u)
+#pragma unroll
+            for (int j = 0; j < E; ++j) {
+                const u32 k = key_in_vector<DT>(q[u], j);
+                eq += k == T ? 1u : 0u;
+                crowd += k >= edge ? 1u : 0u;
+            }
+        block_sum2<B>(eq, crowd, red);
+    }
+    const u64 eq_row = (u64)eq * rs.n / kElems;
+    const bool tied = eq_row > (u64)kListTies && eq_row > (u64)rs.k;
+    if (tied) {
+        for (u32 j = tid; j < nt; j += B) te[j] = 0;
+    }
+    if (tid == 0) {
+        lr->mode = tied ? kListTied : kListPlain;
+        lr->T = T;
+        // as a number: not below the number whose key is T ("largest"), or below the one whose key is the next
+        // ("smallest": keys are complemented)
+        const bool largest = P.dirmask == 0;
+        const u64 o = T ^ P.dirmask;
+        float t = 0.0f;
+        lr->exact = tied || !threshold_number<DT>(largest ? o : o + (DT == RTOPK_F32 ? 1u : 0x10000u), &t);
+        lr->t = t;
+        const u64 lo = (u64)(T >> ent.kshift) << ent.ib, hi = ((u64)(top >> ent.kshift) << ent.ib) | ent.idx_max;
+        const u64 range = hi > lo ? hi - lo : 1u;
+        const u32 width = 64u - (u32)__builtin_clzll(range);
+        lr->lo = lo;
+        lr->sh = width > 12u ? width - 12u : 0u;
+        st->pre_elems = kElems;
+        // (crowded keys: what a first digit could tell apart is less than an eighth of the row)
+        const bool crowded = (u64)crowd * 8u > (u64)kElems;
+        st->pre_bound = crowded ? 1u << d0 : T >> (32u - d0);
+        st->pre_missed = crowded ? 2u : 0u;
+    }
+}
+
+template <int DT, int B, int V>
+__global__ void __launch_bounds__(B) k_list_bound(Params P, ListPlan L) {
+    __shared__ RankShared sm;
+    __shared__ u32 red[2 * (B / 64)];
+    const int row = blockIdx.x;
+    const RowShape rs = row_shape_scalar<DT>(P, row);
+    ListSource<DT, false> src;  // (the smaller of the two sweeps' tiles: the larger number of them)
+    src.init(rs);
+    bound_of_row<DT, B, V>(P, L, row, rs, row_state(P, row), list_row(P, row), list_part<u32>(P, row, L.tile_off), src.ntiles(), sm, red);
+}
+
+// ------------------------------------------------------------------------------------------------
+// the sweep
+// ------------------------------------------------------------------------------------------------
+
+// Where workgroup wg's segment of the list begins: as many entries in as the tiles of the workgroups before it have
+// elements (tiles are dealt round-robin; the first and the last of a row may be short).
+template <class Source>
+__device__ __forceinline__ u32 list_segment(const Source& src, u32 wg, u32 G, u32 ntiles) {
+    const u32 te = (u32)Source::kTileVecs * (u32)Source::E;
+    const u32 q = ntiles / G, r = ntiles % G;
+    u64 at = (u64)(wg * q + (wg < r ? wg : r)) * te;
+    if (wg > 0) at -= src.lead;
+    if (ntiles > 0 && (ntiles - 1u) % G < wg) at -= (u64)ntiles * te - src.lead - src.n;  // (the last tile's missing end)
+    return (u32)at;
+}
+
+// Staged (raw bits, index) pairs -> entries at the workgroup's next free positions; LONG: counted into the histogram.
+// (Expanded in place: around a call the compiler keeps the tiles in flight in memory.)
+template <int DT, bool LONG>
+__device__ __forceinline__ void list_flush(u64* seg, Lds<u64>* buf, Lds<u32>* run, u32 fill, Lds<u32>* hist, const ListEntry& c,
+                                           u64 lo, u32 sh, u32 lane) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    u32 base = 0;
+    if (lane == 0) base = __hip_atomic_fetch_add(run, fill, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    base = __builtin_amdgcn_readfirstlane(base);
+    for (u32 i = lane; i < fill; i += 64) {
+        const u64 v = buf[i];
+        const u64 e = c.of(KeyOf<DT>::key((u32)v) ^ c.dirmask, (u32)(v >> 32));
+        ((Glb<u64>*)seg)[base + i] = e;
+        if (LONG) {
+            const u64 b = (e - lo) >> sh;
+            __hip_atomic_fetch_add(hist + (b < kListBins ? (u32)b : kListBins - 1u), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// Element s (0 .. kSlots - 1, different in every lane) of a tile that is held in registers: a tree of selects.  (An index
+// that varies would put the tile into scratch memory.)
+template <class Source>
+__device__ __forceinline__ u32 pick(const typename Source::Tile& t, u32 s) {
+    const u32 w = Source::E == 4 ? s : s >> 1;  // which of the 16 words
+    auto of4 = [&](const uint4& q) __attribute__((always_inline)) {
+        const u32 lo = (w & 1u) ? q.y : q.x, hi = (w & 1u) ? q.w : q.z;
+        return (w & 2u) ? hi : lo;
+    };
+    const u32 c0 = of4(t.r[0]), c1 = of4(t.r[1]), c2 = of4(t.r[2]), c3 = of4(t.r[3]);
+    const u32 d0 = (w & 4u) ? c1 : c0, d1 = (w & 4u) ? c3 : c2;
+    const u32 x = (w & 8u) ? d1 : d0;
+    if constexpr (Source::E == 4) return x;
+    else return (s & 1u) ? x >> 16 : x & 0xffffu;
+}
+
+// bits = 2 * bits + (x < t) over the elements of a full tile, the first element's bit on top: compare into carry, add with
+// carry.  (False for a NaN: inverted for "largest", where NaNs are wanted, as it is for "smallest".)
+template <class Source>
+__device__ __forceinline__ u32 below_mask(const Source& src, const typename Source::Tile& t, float thr) {
+    u32 bits = 0;
+#pragma unroll
+    for (int s = 0; s < Source::kSlots; ++s) {
+        const float x = src.template value<SRC_KEY>(t, s, 0.0f);
+        asm("v_cmp_gt_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(thr), "v"(x) : "vcc");
+    }
+    return bits;
+}
+
+// Position in the row of a lane's element s.
+template <class Source>
+__device__ __forceinline__ u32 element_index(const Source& src, u32 tile, u32 s) {
+    constexpr u32 E = Source::E, B = (u32)Source::kTileVecs / (Source::kSlots / E);
+    return (tile * (u32)Source::kTileVecs + (s / E) * B + threadIdx.x) * E + s % E - src.lead;
+}
+
+// Workgroup wg of the G that share the row: what is not below the row's bound goes to append(tile, mask), bit
+// kSlots - 1 - s of a lane's mask standing for its element s; where ties are counted, tile j's go to te[j].
+// Bound by HBM.  Per element: a compare and an add-with-carry (and the unpacking of a 16-bit key), into one mask per lane
+// and tile.  A branch per 64 elements, or a store, would cost more than the row's trip from memory (see stream_tile).
+template <int DT, class Source, class Append>
+__device__ __forceinline__ void sweep_row(const Source& src, u32 wg, u32 G, const ListRow& lr, u32* te, u32 dirmask, Append&& append) {
+    const u32 ntiles = src.ntiles(), tid = threadIdx.x, lane = lane_id(), T = lr.T;
+    const bool tied = lr.mode == kListTied;
+    u32 f0, f1;  // tiles [f0, f1) are full
+    src.full_range(f0, f1);
+    if (lr.exact == 0u) {
+        // full tiles, one in flight while one is processed
+        const float t = lr.t;
+        u32 first = wg;
+        if (first < f0) first += G;  // (f0 is 0 or 1)
+        const u32 m = first < f1 ? (f1 - first + G - 1) / G : 0u;
+        if (m != 0u) {
+            const u32 flip = dirmask == 0 ? 0xffffffffu >> (32 - Source::kSlots) : 0u;
+            typename Source::Tile a, b;
+            src.load_full(first, tid, a);
+            for (u32 i = 0;;) {
+                if (i + 1 < m) src.load_full(first + (i + 1) * G, tid, b);
+                append(a, below_mask(src, a, t) ^ flip);
+                if (++i >= m) break;
+                if (i + 1 < m) src.load_full(first + (i + 1) * G, tid, a);
+                append(b, below_mask(src, b, t) ^ flip);
+                if (++i >= m) break;
+            }
+        }
+    } else {
+        f1 = f0;  // (all tiles by key)
+    }
+    // the rest, by key: short tiles, and every tile where T is not a number to compare with or ties are counted
+    for (u32 next = wg; next < ntiles; next += G) {
+        if (next >= f0 && next < f1) {
+            next += (f1 - 1u - next) / G * G;  // (on to the last full tile of this workgroup's)
+            continue;
+        }
+        typename Source::Tile cur;
+        src.load(next, tid, cur);
+        constexpr u32 E = Source::E;
+        u32 m = 0, eq = 0;
+#pragma unroll
+        for (int u = 0; u < Source::kSlots / (int)E; ++u) {
+            uint4 q = cur.r[u];
+            keys_of_vector<DT>(q, dirmask);
+            const u32 idx = element_index(src, next, (u32)u * E);  // (a lead-in element's wraps to a huge number)
+#pragma unroll
+            for (u32 j = 0; j < E; ++j) {
+                const u32 key = key_in_vector<DT>(q, (int)j);
+                const bool valid = idx + j < src.n;
+                m = m + m + ((valid && (tied ? key > T : key >= T)) ? 1u : 0u);
+                eq += (valid && key == T) ? 1u : 0u;
+            }
+            __builtin_amdgcn_sched_barrier(0);  // (one vector's keys at a time: registers)
+        }
+        append(cur, m);
+        if (tied) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) eq += __shfl_down(eq, o, 64);
+            if (lane == 0 && eq != 0u) atomicAdd(&te[next], eq);
+        }
+    }
+}
+// X -> list.  A wave takes one noted element per lane at a time until no lane has any left, stages them in LDS, and writes
+// a full stage to the workgroup's segment.
+// NT: the input is far larger than the last-level cache.  LONG: the list's histogram is counted as it is written; then one
+// workgroup of 1024 threads has a compute unit, so that there are no more than 256 histograms to add up (512
+// workgroups of 512: adding up took longer than it saved; see the table).
+template <int DT, bool NT, bool LONG>
+__global__ void __launch_bounds__(LONG ? kLongBlock : kGridBlock, LONG ? 4 : DT == RTOPK_F32 ? 8 : 6) k_list_sweep(Params P, ListPlan L) {
+    constexpr int B = LONG ? kLongBlock : kGridBlock, ST = LONG ? kListStageLong : kListStage;
+    __shared__ uint2 stage[B / 64][ST];
+    __shared__ u32 hist[LONG ? kListBins : 1];
+    __shared__ u32 run;
+    typedef ListSource<DT, LONG, NT> Source;
+    const u32 G = (u32)L.G;
+    const int row = (int)(blockIdx.x / G);
+    const u32 wg = blockIdx.x % G;
+    const ListRow lr = list_row_scalar(list_row(P, row));
+    if (lr.mode == kListSkip) return;
+    const RowShape rs = row_shape_scalar<DT>(P, row);
+    Source src;
+    src.init(rs);
+    const u32 tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    u64* seg = list_array(P, 1u, row) + list_segment(src, wg, G, src.ntiles());
+    if (LONG)
+        for (u32 j = tid; j < kListBins; j += B) hist[j] = 0;
+    if (tid == 0) run = 0;
+    __syncthreads();
+    const ListEntry ent = list_entry<DT>(P);
+    uint2* buf = stage[wave];
+    u32 fill = 0;
+    auto flush = [&]() __attribute__((always_inline)) {
+        list_flush<DT, LONG>(seg, lds_words(buf), lds_word(&run), fill, lds_word(hist), ent, lr.lo, lr.sh, lane);
+        fill = 0;
+    };
+    sweep_row<DT>(src, wg, G, lr, list_part<u32>(P, row, L.tile_off), P.dirmask, [&](const typename Source::Tile& cur, u32 m) __attribute__((always_inline)) {
+        for (;;) {
+            const u64 have = ballot64(m != 0u);
+            if (have == 0) break;
+            if (fill > (u32)(ST - 64)) flush();
+            if (m != 0u) {
+                const u32 bit = 31u - (u32)__builtin_clz(m), s = (u32)Source::kSlots - 1u - bit;
+                m ^= 1u << bit;
+                buf[fill + mbcnt64(have)] = make_uint2(pick<Source>(cur, s), element_index(src, cur.tile, s));
+            }
+            fill += (u32)__popcll(have);
+        }
+    });
+    if (fill != 0u) flush();
+    __syncthreads();
+    if (tid == 0) list_part<u32>(P, row, L.seg_off)[wg] = run;
+    if (LONG) {
+        u32* gh = list_part<u32>(P, row, L.hist_off);
+        for (u32 j = tid; j < kListBins; j += B) {
+            const u32 c = hist[j];
+            if (c) atomicAdd(&gh[j], c);
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// putting entries in order
+// ------------------------------------------------------------------------------------------------
+
+// A workgroup of B threads puts up to 8 B entries in order in LDS: 4 B bins that divide the range from the best entry to
+// the worst evenly, positions within a bin by arrival, and then every entry's rank among its bin's.  Entries are
+// distinct and bins hold one or two of them unless the keys are very uneven; a bin of more than kOrderCrowd sends the whole lot
+// through a bitonic network instead.
+constexpr u32 kOrderCrowd = 128;
+template <int B>
+struct OrderShared {
+    u64 buf[8 * B];
+    u32 hist[4 * B + 1];
+    u32 wsum[B / 64];
+    u64 red[2 * (B / 64)];
+    u32 flag, sp;
+};
+
+template <int B>
+__device__ __forceinline__ void order_range(u64& mn, u64& mx, OrderShared<B>& sm) {
+    const u32 lane = lane_id(), wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const u64 a = __shfl_xor(mn, o, 64), b = __shfl_xor(mx, o, 64);
+        mn = mn < a ? mn : a;
+        mx = mx > b ? mx : b;
+    }
+    if (lane == 0) { sm.red[2 * wave] = mn; sm.red[2 * wave + 1] = mx; }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < B / 64; ++w) {
+        mn = mn < sm.red[2 * w] ? mn : sm.red[2 * w];
+        mx = mx > sm.red[2 * w + 1] ? mx : sm.red[2 * w + 1];
+    }
+}
+template <int B>
+__device__ __forceinline__ u32 order_shift(u64 range) {
+    constexpr u32 kBits = 31u - (u32)__builtin_clz(4 * B);
+    const u32 width = range ? 64u - (u32)__builtin_clzll(range) : 0u;
+    return width > kBits ? width - kBits : 0u;
+}
+// h[0 .. 4 B): counts -> exclusive prefix sums; the largest count, if a crowd, into sm.flag; into sm.sp the bin that holds
+// rank want - 1.  Two barriers.
+template <int B>
+__device__ __forceinline__ void order_scan(u32* h, u32 want, OrderShared<B>& sm) {
+    const u32 tid = threadIdx.x;
+    u32 c[4], s = 0, most = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        c[i] = h[4 * tid + i];
+        s += c[i];
+        most = most > c[i] ? most : c[i];
+    }
+    const u32 incl = block_inclusive_scan<B>(s, sm.wsum);
+    u32 r = incl - s;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        h[4 * tid + i] = r;
+        if (r < want && r + c[i] >= want) sm.sp = 4 * tid + i;
+        r += c[i];
+    }
+    if (most > kOrderCrowd) atomicMax(&sm.flag, most);
+    __syncthreads();
+}
+
+// C entries, load(0) .. load(C - 1) (1 <= C <= 8 B), which are the row's ranks rank0 .. rank0 + C - 1: write those below
+// row_k to the output.  load() may read sm.buf.
+template <int DT, int B, class Load>
+__device__ __forceinline__ void order_in_lds(const Params& P, int row, const RowShape& rs, OrderShared<B>& sm, u32 C, u32 rank0,
+                                             Load&& load) {
+    const u32 tid = threadIdx.x;
+    const u32 want = rs.k - rank0 < C ? rs.k - rank0 : C;
+    const ListEntry ent = list_entry<DT>(P);
+    u64 e[8], mn = ~0ull, mx = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        e[j] = 0;
+        if ((u32)j * B < C) {  // (the same for the whole workgroup; lanes beyond the end read the last entry)
+            const u32 i = tid + (u32)j * B;
+            e[j] = load(i < C ? i : C - 1u);
+        }
+    }
+    for (u32 j = tid; j <= 4u * B; j += B) sm.hist[j] = 0;
+    if (tid == 0) sm.flag = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        if ((u32)j * B < C) {
+            mn = mn < e[j] ? mn : e[j];
+            mx = mx > e[j] ? mx : e[j];
+        }
+    }
+    order_range<B>(mn, mx, sm);
+    const u32 sh = order_shift<B>(mx - mn);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if (tid + (u32)j * B < C) atomicAdd(&sm.hist[(u32)((mx - e[j]) >> sh) + 1u], 1u);  // (the bins' counts, one place up)
+    __syncthreads();
+    order_scan<B>(sm.hist + 1, want, sm);
+    if (sm.flag == 0u) {
+        // hist[b + 1]: where bin b begins, and once its entries are in place, where it ends; hist[b] is then where it begins
+        const u32 last = sm.sp;  // (nothing beyond this bin is wanted)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const u32 bin = (u32)((mx - e[j]) >> sh);
+            if (tid + (u32)j * B < C && bin <= last) sm.buf[atomicAdd(&sm.hist[bin + 1u], 1u)] = e[j];
+            else e[j] = ~0ull;  // (not an entry: those have at most 63 bits)
+        }
+        __syncthreads();
+        u32 rank[4];  // two to a word
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            u32 r = 0xffffu;
+            if ((u32)j * B < C && e[j] != ~0ull) {
+                const u32 b = (u32)((mx - e[j]) >> sh);
+                const u32 s1 = sm.hist[b + 1u];
+                r = sm.hist[b];
+#pragma unroll 1
+                for (u32 i = sm.hist[b]; i < s1; ++i) r += sm.buf[i] > e[j] ? 1u : 0u;
+            }
+            rank[j / 2] = (j & 1) ? rank[j / 2] | r << 16 : r;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const u32 r = (j & 1) ? rank[j / 2] >> 16 : rank[j / 2] & 0xffffu;
+            if (r < want) sm.buf[r] = e[j];
+        }
+    } else {
+        u32 m = 64;
+        while (m < C) m <<= 1;
+        // (the network sorts upwards: complements; padding sorts last)
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (tid + (u32)j * B < C) sm.buf[tid + (u32)j * B] = ~e[j];
+        for (u32 i = C + tid; i < m; i += B) sm.buf[i] = ~0ull;
+        bitonic_sort<B>(sm.buf, m, tid);
+        __syncthreads();
+        for (u32 i = tid; i < want; i += B) sm.buf[i] = ~sm.buf[i];
+    }
+    __syncthreads();
+    char* out_v = (char*)P.out_values + (size_t)row * (size_t)P.k * KeyOf<DT>::kBytes;
+    long long* out_i = P.out_indices + (size_t)row * (size_t)P.k;
+    for (u32 i = tid; i < want; i += B) {
+        const u64 v = sm.buf[i];
+        const u32 idx = ent.idx(v);
+        out_i[rank0 + i] = (long long)idx;
+        store_value<DT>(out_v, rank0 + i, raw_of_key<DT>(ent.key(v), idx, rs, P.dirmask));
+    }
+}
+
+// The same for `count` entries at positions rank0 .. of list array `which`, however many: what LDS does not hold is
+// first spread over bins in the other array (same positions; the bins divide the range evenly, so this ends after a
+// few levels at most), and runs of bins of about 4 B entries are then taken one after the other.  `stack`: room for
+// count / B + 16 records of this workgroup's own.
+struct OrderRange { u32 at, count, which, pad; };
+template <int DT, int B>
+__device__ void order_entries(const Params& P, int row, const RowShape& rs, OrderShared<B>& sm, u32 rank0, u32 count, u32 which,
+                              OrderRange* stack) {
+    constexpr u32 kCap = 8 * B;
+    const u32 tid = threadIdx.x;
+    u32 sp = 0;  // records on the stack (uniform)
+    OrderRange cur{rank0, count, which, 0u};
+    for (;;) {
+        const u64* src = list_array(P, cur.which, row) + cur.at;
+        __syncthreads();
+        if (cur.count == 0) {  // (an empty bin and a large one that begin at the same rank)
+        } else if (cur.count <= kCap) {
+            order_in_lds<DT, B>(P, row, rs, sm, cur.count, cur.at, [&](u32 i) __attribute__((always_inline)) { return src[i]; });
+        } else {
+            u64* dst = list_array(P, 1u - cur.which, row) + cur.at;
+            for (u32 j = tid; j < 4u * B; j += B) sm.hist[j] = 0;
+            u64 mn = ~0ull, mx = 0;
+#pragma unroll 1
+            for (u32 i = tid; i < cur.count; i += B) {
+                const u64 e = src[i];
+                mn = mn < e ? mn : e;
+                mx = mx > e ? mx : e;
+            }
+            order_range<B>(mn, mx, sm);  // (its barrier also covers the clearing)
+            const u32 sh = order_shift<B>(mx - mn);
+#pragma unroll 1
+            for (u32 i = tid; i < cur.count; i += B) atomicAdd(&sm.hist[(u32)((mx - src[i]) >> sh)], 1u);
+            __syncthreads();
+            const u32 want = rs.k - cur.at < cur.count ? rs.k - cur.at : cur.count;
+            order_scan<B>(sm.hist, want, sm);
+            const u32 end = (sm.sp + 1u < 4u * B) ? sm.hist[sm.sp + 1u] : cur.count;  // what begins below `want` ends here
+            // runs of bins: a run begins at the first bin that starts beyond the next multiple of run_len, and at a bin
+            // that alone holds more than run_len (so a run is one bin, whose range is a small part of this one, or
+            // has at most 2 run_len entries: every round is strictly smaller than the one before)
+            u32 run_len = kCap / 2u;
+            while ((u64)run_len * (kCap / 2u) < (u64)cur.count) run_len *= 2u;  // (the list of beginnings fits sm.buf)
+            u32 begins = 0, mask = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const u32 b = 4 * tid + i, s = sm.hist[b];
+                const u32 n1 = b + 1u < 4u * B ? sm.hist[b + 1u] : cur.count;
+                const bool first = s < want && (b == 0 || s / run_len > sm.hist[b - 1] / run_len || n1 - s > run_len);
+                mask |= (first ? 1u : 0u) << i;
+                begins += first ? 1u : 0u;
+            }
+            u32 slot = block_inclusive_scan<B>(begins, sm.wsum) - begins;  // (and everybody has read sm.sp)
+            u32* beg = (u32*)sm.buf;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if ((mask >> i) & 1u) beg[slot++] = sm.hist[4 * tid + i];
+            if (tid == B - 1) sm.sp = slot;
+            __syncthreads();
+            const u32 nrun = sm.sp;
+            for (u32 i = tid; i < nrun; i += B) {
+                const u32 b = beg[i], n1 = i + 1 < nrun ? beg[i + 1] : end;
+                stack[sp + i] = OrderRange{cur.at + b, n1 - b, 1u - cur.which, 0u};
+            }
+            __syncthreads();
+#pragma unroll 1
+            for (u32 i = tid; i < cur.count; i += B) {
+                const u64 e = src[i];
+                dst[atomicAdd(&sm.hist[(u32)((mx - e) >> sh)], 1u)] = e;
+            }
+            sp += nrun;
+        }
+        __syncthreads();
+        if (sp == 0) return;
+        cur = stack[--sp];
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// short lists
+// ------------------------------------------------------------------------------------------------
+
+// One row's record: how many were listed, all ranked directly.
+__device__ __forceinline__ void list_record(rtopk_row_trace* st, const RowShape& rs, u32 listed, u32 where) {
+    st->pass_rec[0].bin = 0;
+    st->pass_rec[0].k_after = 0;
+    st->pass_rec[0].cand_after = 0;
+    st->pass_rec[0].winners = rs.k;
+    st->pass_rec[0].out_before = 0;
+    st->pass_rec[0].cand_before = st->pre_missed == 2u ? rs.n : listed;
+    st->pass_rec[0].window = SRC_RANK;
+    st->pass_rec[0].where = where;
+    if (st->pre_missed != 2u) st->pre_kept = listed;
+}
+
+// Elements equal to T, lowest positions first, to the output behind the `listed` better ones.  Workgroup w of nw takes the
+// tiles w, w + nw, ... as far as they are needed.  te: how many every tile has (counted by atomics, and read past the
+// vector cache, which does not see those).  Returns false if the row has too few of them.
+template <int DT, int B, class Source>
+__device__ bool ties_of_row(const Params& P, const u32* te, int row, const RowShape& rs, u32 listed, u32 T, u32 w, u32 nw,
+                            u32* before, u32* wsum) {
+    constexpr u32 E = Source::E, kStep = 2;
+    static_assert(Source::kTileVecs % (kStep * B) == 0, "whole steps");
+    Source src;
+    src.init(rs);
+    const u32 ntiles = src.ntiles(), tid = threadIdx.x, want = rs.k - listed;
+    char* out_v = (char*)P.out_values + (size_t)row * (size_t)P.k * KeyOf<DT>::kBytes;
+    long long* out_i = P.out_indices + (size_t)row * (size_t)P.k;
+    u32 base = 0;  // equal elements in the tiles before this block of B tiles
+    for (u32 t0 = 0; t0 < ntiles; t0 += B) {
+        const u32 c = t0 + tid < ntiles ? __hip_atomic_load(&te[t0 + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        __syncthreads();
+        const u32 incl = block_inclusive_scan<B>(c, wsum);
+        before[tid] = base + incl - c;
+        if (tid == B - 1) before[B] = base + incl;
+        __syncthreads();
+        const u32 next = before[B];
+        for (u32 k = (w + nw - t0 % nw) % nw; k < (u32)B && t0 + k < ntiles; k += nw) {
+            const u32 at = before[k];
+            if (at >= want) break;
+            if (before[k + 1] == at) continue;
+            // this tile, in steps of kStep neighbouring vectors per thread, so that thread order is index order
+            u32 begin = at;
+            for (u32 v0 = 0; v0 < (u32)Source::kTileVecs; v0 += kStep * (u32)B) {
+                const u64 v = (u64)(t0 + k) * Source::kTileVecs + v0 + (u64)tid * kStep;
+                u32 hit = 0;
+#pragma unroll
+                for (u32 u = 0; u < kStep; ++u) {
+                    uint4 q = v + u < src.nvec ? load16<false>(src.abase + (v + u)) : make_uint4(0, 0, 0, 0);
+                    keys_of_vector<DT>(q, P.dirmask);
+#pragma unroll
+                    for (u32 j = 0; j < E; ++j) {
+                        const bool is = (u32)(v + u) * E + j - src.lead < rs.n && key_in_vector<DT>(q, (int)j) == T;
+                        hit |= (is ? 1u : 0u) << (u * E + j);
+                    }
+                }
+                const u32 n = (u32)__builtin_popcount(hit);
+                __syncthreads();  // (wsum's last readers are done)
+                const u32 incl = block_inclusive_scan<B>(n, wsum);
+                u32 pos = begin + incl - n;
+#pragma unroll
+                for (u32 w = 0; w < (u32)(B / 64); ++w) begin += wsum[w];  // (the scan leaves every wave's sum there)
+                for (; hit != 0u && pos < want; hit &= hit - 1u, ++pos) {
+                    const u32 idx = (u32)v * E + (u32)__builtin_ctz(hit) - src.lead;
+                    out_i[listed + pos] = (long long)idx;
+                    store_value<DT>(out_v, listed + pos, raw_of_key<DT>(T, idx, rs, P.dirmask));
+                }
+            }
+        }
+        base = next;
+        if (base >= want) return true;
+        __syncthreads();
+    }
+    return false;
+}
+
+// The list of one row into the output.  Blocks [0, batch): a row each.  Blocks beyond: L.ties per row, for rows whose
+// equal elements were counted.
+template <int DT, int B>
+__global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
+    __shared__ OrderShared<B> sm;
+    __shared__ u32 segs[1025];
+    const u32 tid = threadIdx.x;
+    const bool for_ties = blockIdx.x >= (u32)P.batch;
+    const int row = for_ties ? (int)((blockIdx.x - (u32)P.batch) / (u32)L.ties) : (int)blockIdx.x;
+    const ListRow* lr = list_row(P, row);
+    const u32 mode = lr->mode;
+    if (mode == kListSkip || (for_ties && mode != kListTied)) return;
+    const RowShape rs = row_shape_scalar<DT>(P, row);
+    rtopk_row_trace* st = row_state(P, row);
+    // the segments' beginnings in the list
+    const u32* counts = list_part<u32>(P, row, L.seg_off);
+    u32 total = 0;
+    for (u32 s0 = 0; s0 < (u32)L.G; s0 += B) {
+        const u32 c = s0 + tid < (u32)L.G ? counts[s0 + tid] : 0u;
+        const u32 incl = block_inclusive_scan<B>(c, sm.wsum);
+        if (s0 + tid < (u32)L.G) segs[s0 + tid] = total + incl - c;
+        if (tid == B - 1) segs[1024] = total + incl;
+        __syncthreads();
+        total = segs[1024];
+        __syncthreads();
+    }
+    if (for_ties) {
+        const u32 w = (blockIdx.x - (u32)P.batch) % (u32)L.ties;
+        if (total < rs.k && !ties_of_row<DT, B, ListSource<DT, false>>(P, list_part<u32>(P, row, L.tile_off), row, rs, total, lr->T, w, (u32)L.ties,
+                                                               sm.hist, sm.wsum) && w == 0 && tid == 0) {
+            st->redo_why = 8u;
+            atomicOr(&st->redo, kRedoRow);
+        }
+        return;
+    }
+    if ((mode == kListPlain && total < rs.k) || total > (u32)((P.n + 1) / 2)) {
+        if (tid == 0) {
+            st->redo_why = total < rs.k ? 8u : 5u;
+            atomicOr(&st->redo, kRedoRow);
+        }
+        return;
+    }
+    if (tid == 0) list_record(st, rs, total, 5u);
+    if (total == 0) return;
+    ListSource<DT, false> src;
+    src.init(rs);
+    const u32 ntiles = src.ntiles();
+    u64* dst = list_array(P, 0u, row);
+    const u64* from = list_array(P, 1u, row);
+    auto entry = [&](u32 i) __attribute__((always_inline)) {
+        u32 a = 0, b = (u32)L.G;  // the segment that holds entry i: the last one that begins at or before it
+        while (b - a > 1u) {
+            const u32 m = (a + b) / 2u;
+            if (segs[m] <= i) a = m; else b = m;
+        }
+        return from[list_segment(src, a, (u32)L.G, ntiles) + (i - segs[a])];
+    };
+    if (total <= 8u * B) {
+        order_in_lds<DT, B>(P, row, rs, sm, total, 0u, entry);
+    } else {
+        for (u32 i = tid; i < total; i += B) dst[i] = entry(i);
+        if (tid == 0) {
+            list_row(P, row)->total = total;
+            list_row(P, row)->end = 0u;
+            atomicOr(&st->redo, kRedoList);
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// one workgroup per row
+// ------------------------------------------------------------------------------------------------
+
+// Bound, sweep and order in one kernel: the list is gathered in LDS (what does not fit there goes to the list array).
+// For rows so short, or so many, that sharing one out gains nothing.  Several of these workgroups share a compute unit, so that one
+// row's trip from memory overlaps the others' ranking.
+template <int DT, int B, int V>
+__global__ void __launch_bounds__(B, 4) k_list_row(Params P, ListPlan L) {
+    __shared__ union { OrderShared<B> ord; RankShared rank; } sm;
+    __shared__ ListRow lr;
+    __shared__ u32 red[2 * (B / 64)], te[kListRowTiles], run;
+    constexpr u32 kCap = 8 * B;
+    typedef KeySource<DT, B, 4, false> Source;
+    const int row = blockIdx.x;
+    const u32 tid = threadIdx.x, lane = lane_id();
+    const RowShape rs = row_shape_scalar<DT>(P, row);
+    rtopk_row_trace* st = row_state(P, row);
+    Source src;
+    src.init(rs);
+    bound_of_row<DT, B, V>(P, L, row, rs, st, &lr, te, src.ntiles(), sm.rank, red);
+    if (tid == 0) run = 0;
+    __syncthreads();
+    if (lr.mode == kListSkip) return;
+    const ListRow b = list_row_scalar(&lr);
+    const ListEntry ent = list_entry<DT>(P);
+    u64* list = list_array(P, 1u, row);
+    const u32 room = (u32)((P.n + 1) / 2);
+    sweep_row<DT>(src, 0u, 1u, b, te, P.dirmask, [&](const typename Source::Tile& cur, u32 m) __attribute__((always_inline)) {
+        for (;;) {
+            const u64 have = ballot64(m != 0u);
+            if (have == 0) break;
+            u32 base = 0;
+            if (lane == 0) base = atomicAdd(&run, (u32)__popcll(have));
+            base = __builtin_amdgcn_readfirstlane(base);
+            if (m != 0u) {
+                const u32 bit = 31u - (u32)__builtin_clz(m), s = (u32)Source::kSlots - 1u - bit;
+                m ^= 1u << bit;
+                const u32 pos = base + mbcnt64(have);
+                const u64 e = ent.of(KeyOf<DT>::key(pick<Source>(cur, s)) ^ P.dirmask, element_index(src, cur.tile, s));
+                if (pos < kCap) sm.ord.buf[pos] = e;
+                else if (pos < room) list[pos] = e;
+            }
+        }
+    });
+    __syncthreads();
+    const u32 total = run;
+    if ((b.mode == kListPlain && total < rs.k) || total > room) {
+        if (tid == 0) {
+            st->redo_why = total < rs.k ? 8u : 5u;
+            atomicOr(&st->redo, kRedoRow);
+        }
+        return;
+    }
+    if (tid == 0) list_record(st, rs, total, 4u);
+    if (total > kCap) {
+        for (u32 i = tid; i < kCap; i += B) list[i] = sm.ord.buf[i];
+        if (tid == 0) {
+            list_row(P, row)->total = total;
+            list_row(P, row)->end = 1u;
+            atomicOr(&st->redo, kRedoList);
+        }
+    } else if (total != 0u) {
+        order_in_lds<DT, B>(P, row, rs, sm.ord, total, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.ord.buf[i]; });
+    }
+    if (b.mode == kListTied && total < rs.k) {
+        __syncthreads();
+        if (!ties_of_row<DT, B, Source>(P, te, row, rs, total, b.T, 0u, 1u, sm.ord.hist, sm.ord.wsum) && tid == 0) {
+            st->redo_why = 8u;
+            atomicOr(&st->redo, kRedoRow);
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// long lists
+// ------------------------------------------------------------------------------------------------
+
+// Workgroup w moves segment w into buckets.  A bin's rank is the number of entries in better bins; a bucket is the run of
+// bins whose ranks share rank >> L.bucket_shift, its place in the array its first bin's rank.  Bins that begin at rank k or
+// beyond are dropped.  One atomic per bucket reserves all of a workgroup's places in it; what the registers do not hold
+// of a segment is read twice.
+template <int DT>
+__global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan L) {
+    constexpr int B = kLongBlock, kPer = kListBins / B;
+    __shared__ u32 start[kListBins];         // rank of every bin
+    __shared__ u32 place[kListMaxBuckets];   // of every bucket: this workgroup's entries, then their next place
+    __shared__ u32 wsum[B / 64];
+    __shared__ u32 s_end;
+    const u32 G = (u32)L.G, tid = threadIdx.x;
+    const int row = (int)(blockIdx.x / G);
+    const u32 wg = blockIdx.x % G;
+    ListRow* lr = list_row(P, row);
+    const u32 mode = lr->mode;
+    if (mode == kListSkip) return;
+    const RowShape rs = row_shape_scalar<DT>(P, row);
+    rtopk_row_trace* st = row_state(P, row);
+    const u64 lo = lr->lo;
+    const u32 sh = lr->sh;
+    ListSource<DT, true> src;
+    src.init(rs);
+    const u64* from = list_array(P, 1u, row) + list_segment(src, wg, G, src.ntiles());
+    const u32 mine = list_part<u32>(P, row, L.seg_off)[wg];
+    constexpr int kHeld = 8;
+    u64 held[kHeld];
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i) held[i] = tid + (u32)i * B < mine ? from[tid + (u32)i * B] : 0ull;
+    const u32* gh = list_part<u32>(P, row, L.hist_off);
+    const u32 bs = L.bucket_shift, nb = L.nb;
+    u32 c[kPer], s = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        c[i] = gh[kListBins - 1u - (tid * kPer + i)];  // from the best bin down
+        s += c[i];
+    }
+    for (u32 j = tid; j < nb; j += B) place[j] = 0;
+    if (tid == 0) s_end = 0;
+    const u32 incl = block_inclusive_scan<B>(s, wsum);
+    u32 total = 0;
+    {
+        u32 r = incl - s;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            start[kListBins - 1u - (tid * kPer + i)] = r;
+            if (r < rs.k && r + c[i] >= rs.k) s_end = r + c[i];
+            r += c[i];
+        }
+    }
+    __syncthreads();
+    // (start[0] is the worst bin's rank: its end is the total)
+    total = start[0] + gh[0];
+    const bool few = total < rs.k;
+    const u32 end = few ? total : s_end;
+    if ((mode == kListPlain && few) || total > (u32)((P.n + 1) / 2)) {
+        if (wg == 0 && tid == 0) {
+            lr->mode = kListSkip;
+            st->redo_why = few ? 8u : 5u;
+            atomicOr(&st->redo, kRedoRow);
+        }
+        return;
+    }
+    if (wg == 0) {
+        if (tid == 0) {
+            lr->total = total;
+            lr->end = end;
+            list_record(st, rs, total, 5u);
+        }
+        // the buckets' first ranks
+        u32* first = list_part<u32>(P, row, L.first_off);
+        for (u32 j = tid; j < nb; j += B) first[j] = 0xffffffffu;
+        __syncthreads();
+        for (u32 j = tid; j < kListBins; j += B) {  // j counts from the best bin
+            const u32 r = start[kListBins - 1u - j];
+            if (r < end && (j == 0 || (r >> bs) > (start[kListBins - j] >> bs))) first[r >> bs] = r;
+        }
+    }
+    auto bucket_of = [&](u64 e) __attribute__((always_inline)) {
+        const u64 b = (e - lo) >> sh;
+        const u32 r = start[b < kListBins ? (u32)b : kListBins - 1u];
+        return r < end ? r >> bs : 0xffffffffu;
+    };
+    // (what the registers hold of the segment is on its way before the ranks are known)
+    u32 bk[kHeld];
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i) {
+        bk[i] = 0xffffffffu;
+        if (tid + (u32)i * B < mine) bk[i] = bucket_of(held[i]);
+        if (bk[i] != 0xffffffffu) atomicAdd(&place[bk[i]], 1u);
+    }
+    for (u32 i = tid + kHeld * B; i < mine; i += B) {
+        const u32 b = bucket_of(from[i]);
+        if (b != 0xffffffffu) atomicAdd(&place[b], 1u);
+    }
+    __syncthreads();
+    u32* cursor = list_part<u32>(P, row, L.cursor_off);
+    // a bucket's own beginning is added by the bin that begins it
+    for (u32 j = tid; j < nb; j += B) {
+        const u32 n = place[j];
+        if (n != 0) place[j] = atomicAdd(&cursor[j], n);
+    }
+    __syncthreads();
+    for (u32 j = tid; j < kListBins; j += B) {
+        const u32 r = start[kListBins - 1u - j];
+        if (r < end && (j == 0 || (r >> bs) > (start[kListBins - j] >> bs))) place[r >> bs] += r;
+    }
+    __syncthreads();
+    u64* dst = list_array(P, 0u, row);
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i)
+        if (bk[i] != 0xffffffffu) dst[atomicAdd(&place[bk[i]], 1u)] = held[i];
+    for (u32 i = tid + kHeld * B; i < mine; i += B) {
+        const u64 e = from[i];
+        const u32 b = bucket_of(e);
+        if (b != 0xffffffffu) dst[atomicAdd(&place[b], 1u)] = e;
+    }
+}
+
+// Where bucket j of a row begins and how many entries it has; false if there is no such bucket, or nothing is wanted from it.
+// Contains two barriers (not if it returns at once, the same for every thread).
+template <int B>
+__device__ __forceinline__ bool bucket_range(const Params& P, const ListPlan& L, int row, const RowShape& rs, u32 end, u32 j, u32* at,
+                                             u32* count, u32* shared) {
+    const u32* first = list_part<u32>(P, row, L.first_off);
+    *at = first[j];
+    if (*at == 0xffffffffu || *at >= rs.k || *at >= end) return false;
+    // the next bucket that exists begins where this one ends
+    if (threadIdx.x == 0) *shared = end;
+    __syncthreads();
+    for (u32 i = j + 1u + threadIdx.x; i < L.nb; i += B) {
+        const u32 f = first[i];
+        if (f != 0xffffffffu) {
+            atomicMin(shared, f);
+            break;
+        }
+    }
+    __syncthreads();
+    *count = *shared - *at;
+    return true;
+}
+
+// One workgroup per bucket (blocks [0, nb) of a row) puts its entries in order; the other L.ties blocks of the row are for
+// the elements equal to T.
+template <int DT>
+__global__ void __launch_bounds__(kListBucketBlock) k_list_buckets(Params P, ListPlan L) {
+    constexpr int B = kListBucketBlock;
+    __shared__ OrderShared<B> sm;
+    const u32 per = L.nb + (u32)L.ties, tid = threadIdx.x;
+    const int row = (int)(blockIdx.x / per);
+    const u32 j = blockIdx.x % per;
+    const ListRow* lr = list_row(P, row);
+    const u32 mode = lr->mode;
+    if (mode == kListSkip) return;
+    const RowShape rs = row_shape_scalar<DT>(P, row);
+    if (j >= L.nb) {
+        if (mode != kListTied || lr->total >= rs.k) return;
+        if (!ties_of_row<DT, B, ListSource<DT, true>>(P, list_part<u32>(P, row, L.tile_off), row, rs, lr->total, lr->T, j - L.nb,
+                                                      (u32)L.ties, sm.hist, sm.wsum) && j == L.nb && tid == 0) {
+            rtopk_row_trace* st = row_state(P, row);
+            st->redo_why = 8u;
+            atomicOr(&st->redo, kRedoRow);
+        }
+        return;
+    }
+    u32 at, count;
+    if (!bucket_range<B>(P, L, row, rs, lr->end, j, &at, &count, &sm.sp)) return;
+    if (count <= 8u * B) {
+        const u64* src = list_array(P, 0u, row) + at;
+        order_in_lds<DT, B>(P, row, rs, sm, count, at, [&](u32 i) __attribute__((always_inline)) { return src[i]; });
+    } else if (tid == 0) {
+        atomicOr(&row_state(P, row)->redo, kRedoBuckets);
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// rows whose list was no use
+// ------------------------------------------------------------------------------------------------
+// kRedoRow: one workgroup selects the row's k-th key from all of X (three or four sweeps), lists what is better, counts what
+// is equal, and goes on as usual.
+template <int DT, int B>
+__device__ __forceinline__ void redo_row(const Params& P, const ListPlan& L, int row, const RowShape& rs, rtopk_row_trace* st,
+                                         RankShared& rank, u32* run, u32* hist, u32* wsum, u32* listed_out) {
+    typedef ListSource<DT, false> Source;
+    constexpr u32 E = Source::E;
+    const u32 tid = threadIdx.x, lane = lane_id();
+    Source src;
+    src.init(rs);
+    const u32 nvec = (u32)src.nvec;
+    bool exact;
+    const u32 T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) {
+        for (u32 v = tid; v < nvec; v += B) {
+            uint4 q = load16<false>(src.abase + v);
+            keys_of_vector<DT>(q, P.dirmask);
+#pragma unroll
+            for (u32 j = 0; j < E; ++j)
+                if (v * E + j - src.lead < rs.n) f(key_in_vector<DT>(q, (int)j));
+        }
+    }, rs.k, 0u, 0xffffffffu, rank, &exact);
+    u32* te = list_part<u32>(P, row, L.tile_off);
+    const u32 nt = src.ntiles();
+    for (u32 j = tid; j < nt; j += B) te[j] = 0;
+    if (tid == 0) *run = 0;
+    __syncthreads();
+    const ListEntry ent = list_entry<DT>(P);
+    u64* list = list_array(P, 1u, row);
+    const u32 room = (u32)((P.n + 1) / 2);
+    for (u32 b = 0; b < nvec; b += B) {  // (whole waves: a wave's 64 vectors lie in one tile)
+        const u32 v = b + tid;
+        uint4 q = v < nvec ? load16<false>(src.abase + v) : make_uint4(0, 0, 0, 0);
+        keys_of_vector<DT>(q, P.dirmask);
+        u32 eq = 0;
+#pragma unroll
+        for (u32 j = 0; j < E; ++j) {
+            const u32 key = key_in_vector<DT>(q, (int)j), idx = v * E + j - src.lead;
+            const bool valid = v < nvec && idx < rs.n;
+            eq += valid && key == T ? 1u : 0u;
+            if (valid && key > T) {
+                const u32 at = atomicAdd(run, 1u);
+                if (at < room) list[at] = ent.of(key, idx);
+            }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) eq += __shfl_down(eq, o, 64);
+        if (lane == 0 && eq != 0u) atomicAdd(&te[v / (u32)Source::kTileVecs], eq);
+    }
+    __syncthreads();
+    const u32 listed = *run;
+    *listed_out = 0;
+    if (listed > room) {
+        if (tid == 0) st->error |= 4u;  // never expected: little more than k are better than T
+        return;
+    }
+    if (tid == 0) list_record(st, rs, listed, 5u);
+    if (listed < rs.k) {
+        __syncthreads();
+        ties_of_row<DT, B, Source>(P, te, row, rs, listed, T, 0u, 1u, hist, wsum);
+        __syncthreads();
+    }
+    *listed_out = listed;
+}
+
+// What the kernels before left over; normally nothing.  Rows (kRedoRow, kRedoList) are dealt to the workgroups, buckets of
+// one row likewise.
+template <int DT>
+__global__ void __launch_bounds__(kListBucketBlock) k_list_redo(Params P, ListPlan L) {
+    constexpr int B = kListBucketBlock;
+    __shared__ union { OrderShared<B> ord; RankShared rank; } sm;
+    __shared__ u32 run, marked[B], nmarked;
+    const u32 tid = threadIdx.x;
+    for (int r0 = 0; r0 < P.batch; r0 += B) {
+        const u32 mark = r0 + (int)tid < P.batch ? row_state(P, r0 + (int)tid)->redo : 0u;
+        if (__syncthreads_or((int)mark) == 0) continue;
+        if (tid == 0) nmarked = 0;
+        __syncthreads();
+        if (mark != 0u) marked[atomicAdd(&nmarked, 1u)] = tid;
+        __syncthreads();
+        const u32 nm = nmarked;
+        for (u32 i = 0; i < nm; ++i) {
+            // (the order of `marked` differs between workgroups: who takes a row is decided by its number)
+            const int row = r0 + (int)marked[i];
+            rtopk_row_trace* st = row_state(P, row);
+            const u32 why = st->redo;
+            const bool mine = (u32)row % gridDim.x == blockIdx.x;
+            const RowShape rs = row_shape_scalar<DT>(P, row);
+            OrderRange* stack = list_part<OrderRange>(P, row, L.stack_off);
+            // one task (the row's list), or one per bucket that is too large
+            const bool buckets = (why & (kRedoRow | kRedoList)) == 0u;
+            const u32 tasks = buckets ? L.nb : 1u;
+            for (u32 j = buckets ? blockIdx.x : 0u; j < tasks; j += gridDim.x) {
+                u32 at = 0, count = 0, which = 0;
+                if (buckets) {
+                    if (!bucket_range<B>(P, L, row, rs, list_row(P, row)->end, j, &at, &count, &run)) continue;
+                    if (count <= 8u * B) count = 0;  // (done)
+                    stack += at / (u32)B + 16u * j;
+                } else if (mine && (why & kRedoRow)) {
+                    redo_row<DT, B>(P, L, row, rs, st, sm.rank, &run, sm.ord.hist, sm.ord.wsum, &count);
+                    which = 1;
+                } else if (mine) {
+                    count = list_row(P, row)->total;
+                    which = list_row(P, row)->end;
+                }
+                __syncthreads();
+                if (count != 0u) order_entries<DT, B>(P, row, rs, sm.ord, at, count, which, stack);
+                __syncthreads();
+                stack = list_part<OrderRange>(P, row, L.stack_off);
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+template <int DT>
+static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStream_t st, void* const* events) {
+    mark(events, 0, st);
+    mark(events, 1, st);
+    const dim3 rows((unsigned)P.batch);
+    const unsigned redo = L.nb != 0 ? 64u : (unsigned)(P.batch < 256 ? P.batch : 256);
+    if (L.row_block != 0) {
+        mark(events, 2, st);
+        mark(events, 3, st);
+        if (L.row_block == 1024 && L.sample == 2) hipLaunchKernelGGL((k_list_row<DT, 1024, 2>), rows, dim3(1024), 0, st, P, L);
+        else if (L.row_block == 1024) hipLaunchKernelGGL((k_list_row<DT, 1024, 1>), rows, dim3(1024), 0, st, P, L);
+        else if (L.row_block == 512 && L.sample == 2) hipLaunchKernelGGL((k_list_row<DT, 512, 4>), rows, dim3(512), 0, st, P, L);
+        else if (L.row_block == 512 && L.sample == 1) hipLaunchKernelGGL((k_list_row<DT, 512, 2>), rows, dim3(512), 0, st, P, L);
+        else if (L.row_block == 512) hipLaunchKernelGGL((k_list_row<DT, 512, 1>), rows, dim3(512), 0, st, P, L);
+        else if (L.sample == 2) hipLaunchKernelGGL((k_list_row<DT, 256, 8>), rows, dim3(256), 0, st, P, L);
+        else if (L.sample == 1) hipLaunchKernelGGL((k_list_row<DT, 256, 4>), rows, dim3(256), 0, st, P, L);
+        else hipLaunchKernelGGL((k_list_row<DT, 256, 2>), rows, dim3(256), 0, st, P, L);
+        hipLaunchKernelGGL((k_list_redo<DT>), dim3(redo), dim3(kListBucketBlock), 0, st, P, L);
+        mark(events, 4, st);
+        return hipGetLastError() == hipSuccess ? RTOPK_OK : RTOPK_ERR_HIP;
+    }
+    switch (L.sample) {
+        case 2: hipLaunchKernelGGL((k_list_bound<DT, 512, 4>), rows, dim3(512), 0, st, P, L); break;
+        case 3: hipLaunchKernelGGL((k_list_bound<DT, 1024, 4>), rows, dim3(1024), 0, st, P, L); break;
+        default: hipLaunchKernelGGL((k_list_bound<DT, 1024, DT == RTOPK_F32 ? 16 : 8>), rows, dim3(1024), 0, st, P, L); break;
+    }
+    mark(events, 2, st);
+    const bool nt = (P.flags & kInternalStream) != 0, is_long = L.nb != 0;
+    const dim3 grid((unsigned)P.batch * (unsigned)L.G), block(is_long ? kLongBlock : kGridBlock);
+    if (is_long && nt) hipLaunchKernelGGL((k_list_sweep<DT, true, true>), grid, block, 0, st, P, L);
+    else if (is_long) hipLaunchKernelGGL((k_list_sweep<DT, false, true>), grid, block, 0, st, P, L);
+    else if (nt) hipLaunchKernelGGL((k_list_sweep<DT, true, false>), grid, block, 0, st, P, L);
+    else hipLaunchKernelGGL((k_list_sweep<DT, false, false>), grid, block, 0, st, P, L);
+    mark(events, 3, st);
+    if (is_long) {
+        hipLaunchKernelGGL((k_list_scatter<DT>), grid, block, 0, st, P, L);
+        hipLaunchKernelGGL((k_list_buckets<DT>), dim3((unsigned)P.batch * (L.nb + (unsigned)L.ties)), dim3(kListBucketBlock), 0, st, P, L);
+    } else {
+        const dim3 g((unsigned)P.batch * (1u + (unsigned)L.ties));
+        if (L.finish == 256) hipLaunchKernelGGL((k_list_finish<DT, 256>), g, dim3(256), 0, st, P, L);
+        else if (L.finish == 512) hipLaunchKernelGGL((k_list_finish<DT, 512>), g, dim3(512), 0, st, P, L);
+        else hipLaunchKernelGGL((k_list_finish<DT, 1024>), g, dim3(1024), 0, st, P, L);
+    }
+    hipLaunchKernelGGL((k_list_redo<DT>), dim3(redo), dim3(kListBucketBlock), 0, st, P, L);
+    mark(events, 4, st);
+    return hipGetLastError() == hipSuccess ? RTOPK_OK : RTOPK_ERR_HIP;
+}
+
+}  // namespace rtopk

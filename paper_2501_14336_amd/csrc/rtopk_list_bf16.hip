@@ -1,0 +1,8 @@
+// List kernels for RTOPK_BF16 keys.
+#include "rtopk_list.inl"
+
+namespace rtopk {
+rtopk_status launch_list_bf16(const Params& P, const ListPlan& L, hipStream_t st, void* const* events) {
+    return launch_list_all<RTOPK_BF16>(P, L, st, events);
+}
+}  // namespace rtopk

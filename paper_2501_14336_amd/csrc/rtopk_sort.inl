@@ -41,11 +41,11 @@ __device__ __forceinline__ u32 load_value(const void* v, size_t i) {
 // the 2^L elements that these levels connect -- h apart, starting at a multiple of 2 S plus an offset below h -- are
 // held by one thread, which exchanges among them in registers.  One barrier and one trip through LDS per group of
 // levels instead of one per level.  (All of a group's elements lie in one block of `size` elements: one direction.)
-template <int L>
+template <int L, int B>
 __device__ __forceinline__ void bitonic_levels(u64* buf, u32 m, u32 size, u32 S, u32 tid) {
     constexpr u32 N = 1u << L;
     const u32 h = S >> (L - 1);
-    for (u32 g = tid; g < (m >> L); g += kRowBlock) {
+    for (u32 g = tid; g < (m >> L); g += B) {
         const u32 base = (g / h) * (h << L) + (g & (h - 1u));
         const bool up = (base & size) == 0;
         u64 e[N];
@@ -67,6 +67,25 @@ __device__ __forceinline__ void bitonic_levels(u64* buf, u32 m, u32 size, u32 S,
     }
 }
 
+// The whole network over m (a power of two, at least 8) keys in LDS, upwards.  Begins with a barrier, ends without one.
+template <int B>
+__device__ __forceinline__ void bitonic_sort(u64* buf, u32 m, u32 tid) {
+    for (u32 size = 2, levels = 1; size <= m; size <<= 1, ++levels) {
+        // the levels of this size, largest stride first: a first group of levels % 3 (if any), then groups of three,
+        // so that the group with the smallest strides -- the one whose threads touch neighbouring words -- is a full one
+        u32 stride = size >> 1, left = levels;
+        while (left > 0) {
+            const u32 L = left % 3u ? left % 3u : 3u;
+            __syncthreads();
+            if (L == 1) bitonic_levels<1, B>(buf, m, size, stride, tid);
+            else if (L == 2) bitonic_levels<2, B>(buf, m, size, stride, tid);
+            else bitonic_levels<3, B>(buf, m, size, stride, tid);
+            stride >>= L;
+            left -= L;
+        }
+    }
+}
+
 // k <= kSortSmall: bitonic sort of one row's keys in LDS.
 template <int DT>
 __global__ void __launch_bounds__(kRowBlock) k_sort_small(Params P) {
@@ -84,20 +103,7 @@ __global__ void __launch_bounds__(kRowBlock) k_sort_small(Params P) {
     while (m < k) m <<= 1;
     for (u32 i = tid; i < m; i += B)
         buf[i] = i < k ? sort_key_of<DT>(load_value<DT>(out_v, i), (u32)out_i[i], P.dirmask) : ~0ull;  // padding sorts last
-    for (u32 size = 2, levels = 1; size <= m; size <<= 1, ++levels) {
-        // the levels of this size, largest stride first: a first group of levels % 3 (if any), then groups of three,
-        // so that the group with the smallest strides -- the one whose threads touch neighbouring words -- is a full one
-        u32 stride = size >> 1, left = levels;
-        while (left > 0) {
-            const u32 L = left % 3u ? left % 3u : 3u;
-            __syncthreads();
-            if (L == 1) bitonic_levels<1>(buf, m, size, stride, tid);
-            else if (L == 2) bitonic_levels<2>(buf, m, size, stride, tid);
-            else bitonic_levels<3>(buf, m, size, stride, tid);
-            stride >>= L;
-            left -= L;
-        }
-    }
+    bitonic_sort<B>(buf, m, tid);
     __syncthreads();
     for (u32 i = tid; i < k; i += B) {
         const u32 idx = (u32)buf[i];

@@ -1,0 +1,120 @@
+"""The list kernels (the automatic choice for rows of 32 KB up while k is at most 0.4 n) against the sort oracle,
+position by position: sizes around the tiles, the samples and the list capacities, ties, specials, crowded rows,
+ragged rows and rows whose sample misleads."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2501_14336_amd import workloads as W
+from tests import verify
+from tests.gpu_util import BF16, F16, F32, gpu_topk, to_device
+from tests.test_gpu_ragged import _check_ragged
+
+pytestmark = pytest.mark.gpu
+LIST = (4, 5)  # rtopk_row_trace: where
+
+
+def _bits(x, dtype):
+    with np.errstate(over="ignore"):
+        return x.view(np.uint32) if dtype == F32 else x.astype(np.float16).view(np.uint16) if dtype == F16 else W.to_bf16_bits(x)
+
+
+def _check(name, x, dtype, k, largest=True, sorted=True, batch=1, by_list=True, why=0):
+    bits = _bits(np.asarray(x, np.float32), dtype).reshape(batch, -1)
+    print("list:", name, bits.shape, "dtype", dtype, "k", k, "largest", largest, "sorted", sorted, flush=True)
+    gv, gi, tr, _ = gpu_topk(to_device(bits, dtype), dtype, k, largest, sorted=sorted)
+    wv, wi = oracle.topk(bits, dtype, k, largest)
+    for r in range(batch):
+        assert tr[r].error == 0 and tr[r].done and tr[r].redo_why == why, (r, tr[r].error, tr[r].redo_why)
+        assert (tr[r].passes[0].where in LIST) == by_list
+        if sorted:
+            assert np.array_equal(gi[r], wi[r]) and np.array_equal(gv[r], wv[r]), "row %d" % r
+        else:
+            verify.assert_same_selection(bits[r], gv[r], gi[r], wv[r], wi[r])
+    return tr
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+def test_sizes_and_ks(dtype):
+    least = 8192 if dtype == F32 else 16384
+    for n in (least, least + 1, 30011, 65535, 65536, 65537, 131072 + 5, (1 << 18) + 3, (1 << 20) + 7):
+        x = W.normal(n, seed=n, sigma=3.0)
+        for k in sorted({1, 50, 1000, 2500, n // 10, n // 5}):
+            _check("normal", x, dtype, k, largest=(k % 3 != 1), by_list=n >= least)
+        _check("unsorted", x, dtype, n // 100, sorted=False)
+    # k at the upper end (with larger margins than half a row allows, the call goes elsewhere)
+    x = W.normal(300007, 5)
+    for k, by_list in ((100000, True), (2 * 300007 // 5, False)):
+        _check("large k", x, dtype, k, by_list=by_list)
+        _check("large k", x, dtype, k, largest=False, sorted=False, by_list=by_list)
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+@pytest.mark.parametrize("n", [40003, 300001])
+def test_ties_specials_and_crowds(dtype, n):
+    u = W.uniform01(n, 3)
+    data = {
+        "duplicates": W.duplicates(n, 1),                       # counted, not listed (long row)
+        "constant": np.full(n, np.float32(-1.5)),
+        "five values": np.floor(u * 5).astype(np.float32) - 2,
+        "clipped": np.minimum(W.normal(n, 4), np.float32(1.5)),  # many equal elements above the bound
+        "grid": np.floor(u * 300).astype(np.float32),
+        "narrow": W.narrow(n, 6),
+        "specials": W.specials_ramp(n, 7, with_nan=True),
+        "outlier": np.where(np.arange(n) == n // 3, np.float32(1e30), W.normal(n, 8)).astype(np.float32),
+        "mostly NaN": np.where(u < 0.9, np.float32(np.nan), W.normal(n, 9)).astype(np.float32),
+        "zeros": np.where(u < 0.6, np.float32(0.0), np.where(u < 0.8, np.float32(-0.0), W.normal(n, 10))).astype(np.float32),
+        "ascending": np.arange(n, dtype=np.float32) - n / 3,
+        "descending": n / 3 - np.arange(n, dtype=np.float32),
+    }
+    for name, x in data.items():
+        for k in (1, 100, 3000, n // 5):
+            for largest in (True, False):
+                _check(name, x, dtype, k, largest)
+
+
+def test_batches_and_odd_rows():
+    for dtype in (F32, F16, BF16):
+        for batch, n in ((3, 20011), (7, 100003), (140, 16387), (600, 16384)):
+            x = W.normal(batch * n, 11, sigma=3.0)
+            for k in (1, 77, 1500):
+                _check("batch", x, dtype, k, largest=k != 77, batch=batch)
+    _check("logits", W.bf16_bits_to_f32(W.llm_logits(40, 131072, 12)).reshape(-1), BF16, 1024, batch=40)
+
+
+def test_ragged_rows_short_and_long():
+    lens = [1, 0, 63, 5000, 8193, 40000, 100003, 200001, 65536, 199999, 100001]
+    for dtype in (F32, BF16):
+        rows = [_bits(W.normal(n, 20 + r, sigma=3.0) if r % 4 else W.duplicates(n, 20 + r), dtype) for r, n in enumerate(lens)]
+        for kk in (50, 4000):
+            ks = [min(n, kk) for n in lens]
+            for srt in (False, True):
+                _check_ragged("list", rows, dtype, ks, True, None, srt)
+                _check_ragged("list", rows, dtype, ks, False, None, srt)
+
+
+def _sampled(n, vectors, elems):
+    """Positions of a row (starting on a 16-byte boundary) that the sample covers: runs of 8 vectors of 16 bytes."""
+    def mix(z):
+        z = z.astype(np.uint32)
+        z ^= z >> np.uint32(16); z *= np.uint32(0x7feb352d)
+        z ^= z >> np.uint32(15); z *= np.uint32(0x846ca68b)
+        return z ^ (z >> np.uint32(16))
+    runs, groups = vectors // 8, (n // elems) // 8
+    c = np.arange(runs, dtype=np.uint64)
+    with np.errstate(over="ignore"):
+        h = (mix(c) >> np.uint32(16)).astype(np.uint64)
+    g = (((c << np.uint64(16)) | h) * np.uint64(groups) // np.uint64(runs)) >> np.uint64(16)
+    return (g[:, None] * np.uint64(8 * elems) + np.arange(8 * elems, dtype=np.uint64)[None, :]).reshape(-1).astype(np.int64)
+
+
+@pytest.mark.parametrize("k", [300, 9000])
+def test_rows_whose_sample_misleads_are_done_again(k):
+    # the sampled positions hold the row's best elements, fewer than k of them count: the list comes out short
+    n = 400000
+    pos = _sampled(n, 4096, 4)
+    for largest in (True, False):
+        x = W.normal(n, 31)
+        x[pos] = 100.0 + W.uniform01(len(pos), 32)
+        for srt in (False, True):
+            _check("misled", x if largest else -x, F32, k, largest, srt, why=8)
