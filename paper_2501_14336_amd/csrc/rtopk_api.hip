@@ -221,6 +221,20 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     memset(L, 0, sizeof(*L));
     if (tn && (tn->digit_bits || tn->path || tn->wgs_per_row || tn->small_threshold || tn->prefilter)) return false;
     const int eb = elem_bytes(dt), E = 16 / eb;
+    // rows that one workgroup can hold in registers
+    if (batch <= ((int64_t)1 << 22)) {
+        static const struct { int block, vecs; int64_t rows; } held[] = {
+            {128, 4, 1 << 22}, {256, 4, 1 << 22}, {256, 8, 1 << 22}, {512, 8, 1 << 22}, {512, 16, 512}, {1024, 16, 256}};
+        for (const auto& h : held) {
+            if (n * eb > (int64_t)h.block * h.vecs * 16) continue;
+            if (n > 8 * h.block && k + k / 16 + 2 > 8 * h.block) continue;  // the list's room
+            if (n > 8 * h.block && h.vecs == 16 && k > h.block / 2) continue;  // (bounded by the lanes' best elements only)
+            if (batch > h.rows) break;
+            L->row_block = h.block;
+            L->held = h.vecs;
+            return true;
+        }
+    }
     // the smallest sample is 8 KB of a row, a quarter of 32 KB
     if (n * eb < 32768) return false;
     // the list is to stay below half the row (in a ragged batch: half the longest row, for every row)

@@ -30,6 +30,7 @@ constexpr unsigned kListMaxBuckets = 4096;
 struct ListPlan {
     int G;            // workgroups per row in the sweep
     int row_block;    // one workgroup per row does everything: its threads (0: many workgroups per row)
+    int held;         // ... holding the row in registers: 16-byte vectors per thread (0: the row is swept)
     int sample;       // which size of sample: 512, 1024, 2048, 4096 or 16384 (16-bit keys: 8192) vectors of 16 bytes
     int finish;       // short lists: threads of the workgroup that puts a row's list in order
     int ties;         // workgroups per row that fetch elements equal to the bound, where those are very many

@@ -8,7 +8,8 @@
 // agree on is T.  The result never depends on the sample: a list that comes out short (the sample misled), or longer
 // than half the row, has the row done again by one workgroup that selects the k-th key from all of X (k_list_redo).
 //
-//   k_list_row      short rows, or many: one workgroup per row does all of the following
+//   k_list_held     rows of up to 256 KB: one workgroup per row, which holds the row in registers and needs no sample
+//   k_list_row      longer rows, or many: one workgroup per row does all of the following
 //   k_list_bound    one workgroup per row: sample, T
 //   k_list_sweep    many workgroups per row: X -> list, one segment per workgroup
 //   k_list_finish   (short lists) one workgroup per row: the list, best first, is the output
@@ -119,6 +120,46 @@ __device__ __forceinline__ u32 raw_of_key(u32 key, u32 idx, const RowShape& rs, 
     const u32 b = (o & 0x80000000u) ? (o ^ 0x80000000u) : ~o;
     return DT == RTOPK_F32 ? b : b >> 16;
 }
+
+// f(0), f(1), ... f(N - 1) with constants: a row in registers must stay a named set of registers (see each_resident_tile).
+template <int C, int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (C < N) {
+        f(std::integral_constant<int, C>{});
+        static_for<C + 1, N>(f);
+    }
+}
+
+// Reductions over a wave on the lane network (see wave_inclusive_scan); the result is in lane 63.  A lane without a
+// source keeps its own value.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ u32 lane_move(u32 v) {
+    return (u32)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROWS, 0xf, false);
+}
+template <class Op>
+__device__ __forceinline__ u32 wave_reduce(u32 v, Op&& op) {
+    v = op(v, lane_move<0x111, 0xf>(v));
+    v = op(v, lane_move<0x112, 0xf>(v));
+    v = op(v, lane_move<0x114, 0xf>(v));
+    v = op(v, lane_move<0x118, 0xf>(v));
+    v = op(v, lane_move<0x142, 0xa>(v));
+    return op(v, lane_move<0x143, 0xc>(v));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ u64 lane_move64(u64 v) {
+    return ((u64)lane_move<CTRL, ROWS>((u32)(v >> 32)) << 32) | lane_move<CTRL, ROWS>((u32)v);
+}
+template <class Op>
+__device__ __forceinline__ u64 wave_reduce64(u64 v, Op&& op) {
+    v = op(v, lane_move64<0x111, 0xf>(v));
+    v = op(v, lane_move64<0x112, 0xf>(v));
+    v = op(v, lane_move64<0x114, 0xf>(v));
+    v = op(v, lane_move64<0x118, 0xf>(v));
+    v = op(v, lane_move64<0x142, 0xa>(v));
+    return op(v, lane_move64<0x143, 0xc>(v));
+}
+struct MaxOf { template <class T> __device__ __forceinline__ T operator()(T a, T b) const { return a > b ? a : b; } };
+struct MinOf { template <class T> __device__ __forceinline__ T operator()(T a, T b) const { return a < b ? a : b; } };
 
 // ------------------------------------------------------------------------------------------------
 // T from a sample
@@ -279,41 +320,40 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
         lmax = lmax > vmax[u] ? lmax : vmax[u];
     }
     // the best of the sample, and the worst of the lanes' best (at least B elements are not below it)
-    u32 top = lmax, low = lmax;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const u32 a = __shfl_xor(top, o, 64), b = __shfl_xor(low, o, 64);
-        top = top > a ? top : a;
-        low = low < b ? low : b;
-    }
-    if (lane == 0) {
+    u32 top = wave_reduce(lmax, MaxOf()), low = wave_reduce(lmax, MinOf());
+    if (lane == 63u) {
         red[2 * wave] = top;
         red[2 * wave + 1] = low;
     }
     __syncthreads();
+    top = red[0];
+    low = red[1];
 #pragma unroll
-    for (int w = 0; w < B / 64; ++w) {
+    for (int w = 1; w < B / 64; ++w) {
         top = top > red[2 * w] ? top : red[2 * w];
         low = low < red[2 * w + 1] ? low : red[2 * w + 1];
     }
     __syncthreads();
+    // (16-bit keys are ranked on the 16 bits they have: fewer rounds)
+    constexpr u32 ksh = DT == RTOPK_F32 ? 0u : 16u;
     u32 T;
     bool exact;
     if (rank <= (u32)B / 4u) {
-        T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) { f(lmax); }, rank, low, top, sm, &exact);
+        T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) { f(lmax >> ksh); }, rank, low >> ksh, top >> ksh, sm, &exact);
     } else if (rank <= kVecsTotal / 4u) {
         T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < V; ++u) f(vmax[u]);
-        }, rank, rank <= (u32)B ? low : 0u, top, sm, &exact);
+            for (int u = 0; u < V; ++u) f(vmax[u] >> ksh);
+        }, rank, rank <= (u32)B ? low >> ksh : 0u, top >> ksh, sm, &exact);
     } else {
         T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) {
 #pragma unroll
             for (int u = 0; u < V; ++u)
 #pragma unroll
-                for (int j = 0; j < E; ++j) f(key_in_vector<DT>(q[u], j));
-        }, rank, rank <= (u32)B ? low : 0u, top, sm, &exact);
+                for (int j = 0; j < E; ++j) f(key_in_vector<DT>(q[u], j) >> ksh);
+        }, rank, rank <= (u32)B ? low >> ksh : 0u, top >> ksh, sm, &exact);
     }
+    T <<= ksh;
     // of the sample: how many equal T (which matters if T is one key and not the edge of a range), how many share the first
     // digit of T or have a better one
     const u32 d0 = P.pass[0].bits, edge = (T >> (32u - d0)) << (32u - d0);
@@ -421,16 +461,18 @@ __device__ __forceinline__ u32 pick(const typename Source::Tile& t, u32 s) {
     else return (s & 1u) ? x >> 16 : x & 0xffffu;
 }
 
-// bits = 2 * bits + (x < t) over the elements of a full tile, the first element's bit on top: compare into carry, add with
-// carry.  (False for a NaN: inverted for "largest", where NaNs are wanted, as it is for "smallest".)
+// 2 * bits + (x < t): compare into carry, add with carry -- two instructions.  (False where x or t is a NaN.)
+__device__ __forceinline__ u32 shift_in_below(u32 bits, float x, float t) {
+    asm("v_cmp_gt_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(t), "v"(x) : "vcc");
+    return bits;
+}
+// That for the elements of a full tile, the first element's bit on top.  (Inverted for "largest", where NaNs are wanted; as
+// it is for "smallest".)
 template <class Source>
 __device__ __forceinline__ u32 below_mask(const Source& src, const typename Source::Tile& t, float thr) {
     u32 bits = 0;
 #pragma unroll
-    for (int s = 0; s < Source::kSlots; ++s) {
-        const float x = src.template value<SRC_KEY>(t, s, 0.0f);
-        asm("v_cmp_gt_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(thr), "v"(x) : "vcc");
-    }
+    for (int s = 0; s < Source::kSlots; ++s) bits = shift_in_below(bits, src.template value<SRC_KEY>(t, s, 0.0f), thr);
     return bits;
 }
 
@@ -584,16 +626,14 @@ struct OrderShared {
 template <int B>
 __device__ __forceinline__ void order_range(u64& mn, u64& mx, OrderShared<B>& sm) {
     const u32 lane = lane_id(), wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const u64 a = __shfl_xor(mn, o, 64), b = __shfl_xor(mx, o, 64);
-        mn = mn < a ? mn : a;
-        mx = mx > b ? mx : b;
-    }
-    if (lane == 0) { sm.red[2 * wave] = mn; sm.red[2 * wave + 1] = mx; }
+    mn = wave_reduce64(mn, MinOf());
+    mx = wave_reduce64(mx, MaxOf());
+    if (lane == 63u) { sm.red[2 * wave] = mn; sm.red[2 * wave + 1] = mx; }
     __syncthreads();
+    mn = sm.red[0];
+    mx = sm.red[1];
 #pragma unroll
-    for (int w = 0; w < B / 64; ++w) {
+    for (int w = 1; w < B / 64; ++w) {
         mn = mn < sm.red[2 * w] ? mn : sm.red[2 * w];
         mx = mx > sm.red[2 * w + 1] ? mx : sm.red[2 * w + 1];
     }
@@ -719,7 +759,7 @@ __device__ __forceinline__ void order_in_lds(const Params& P, int row, const Row
 // count / B + 16 records of this workgroup's own.
 struct OrderRange { u32 at, count, which, pad; };
 template <int DT, int B>
-__device__ void order_entries(const Params& P, int row, const RowShape& rs, OrderShared<B>& sm, u32 rank0, u32 count, u32 which,
+__device__ __forceinline__ void order_entries(const Params& P, int row, const RowShape& rs, OrderShared<B>& sm, u32 rank0, u32 count, u32 which,
                               OrderRange* stack) {
     constexpr u32 kCap = 8 * B;
     const u32 tid = threadIdx.x;
@@ -810,7 +850,7 @@ __device__ __forceinline__ void list_record(rtopk_row_trace* st, const RowShape&
 // tiles w, w + nw, ... as far as they are needed.  te: how many every tile has (counted by atomics, and read past the
 // vector cache, which does not see those).  Returns false if the row has too few of them.
 template <int DT, int B, class Source>
-__device__ bool ties_of_row(const Params& P, const u32* te, int row, const RowShape& rs, u32 listed, u32 T, u32 w, u32 nw,
+__device__ __forceinline__ bool ties_of_row(const Params& P, const u32* te, int row, const RowShape& rs, u32 listed, u32 T, u32 w, u32 nw,
                             u32* before, u32* wsum) {
     constexpr u32 E = Source::E, kStep = 2;
     static_assert(Source::kTileVecs % (kStep * B) == 0, "whole steps");
@@ -940,12 +980,216 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
 // one workgroup per row
 // ------------------------------------------------------------------------------------------------
 
+// A row that B lanes can hold, NV vectors of 16 bytes each: X is read once, in one go, and everything else works on
+// registers.  The bound needs no sample: the best element of every lane is known, and the k-th best of those is a number
+// that at least k elements reach -- hardly more than k while k is small against B (k = B / 2: 1.4 k on independent
+// draws).  For larger k the maxima of vectors take the place of the lanes', then the elements.
+// Bound by latency: one trip to memory, then about ten phases with barriers (the first four waves alone put a short list
+// in order: a barrier among 16 waves takes 1 us, among 4 waves 0.5).
+// A list that comes out too long (crowded keys) is bounded again by the exact k-th key, and if it is still too long, equal
+// elements are counted and not listed; no row is left over.
+template <int DT, int B, int NV>
+__global__ void __launch_bounds__(B, 4) k_list_held(Params P, ListPlan L) {
+    constexpr int kGroups = NV / 4;  // the row as tiles of four vectors per lane
+    constexpr u32 kCap = 8 * B;
+    constexpr int OB = B < 256 ? B : 256;  // threads that order a short list
+    typedef KeySource<DT, B, 4, false> Source;
+    constexpr u32 E = Source::E;
+    __shared__ union { OrderShared<B> ord; OrderShared<OB> few; RankShared rank; } sm;  // (both lists at the same place)
+    __shared__ u32 red[2 * (B / 64)], te[kGroups + 1], run;  // (a full row off the 16-byte grid ends in one more tile)
+    const int row = blockIdx.x;
+    const u32 tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    const RowShape rs = row_shape_scalar<DT>(P, row);
+    rtopk_row_trace* st = row_state(P, row);
+    Source src;
+    src.init(rs);
+    const bool largest = P.dirmask == 0;
+    // Whole vectors of the row are held; lanes without one hold the worst number there is.  The few elements before the
+    // first and after the last whole vector (a row may begin and end anywhere) go to the list unseen.
+    const u32 worst = (DT == RTOPK_F32 ? 0x7f800000u : DT == RTOPK_F16 ? 0x7c007c00u : 0x7f807f80u) |
+                      (largest ? (DT == RTOPK_F32 ? 0x80000000u : 0x80008000u) : 0u);
+    typename Source::Tile t[kGroups];
+    const u32 nvec = (u32)src.nvec, v0 = src.lead != 0u ? 1u : 0u, v1 = (u32)(((u64)src.lead + rs.n) / E);
+    static_for<0, kGroups>([&](auto gc) __attribute__((always_inline)) {
+        constexpr int g = decltype(gc)::value;
+        static_for<0, 4>([&](auto uc) __attribute__((always_inline)) {
+            constexpr int u = decltype(uc)::value;
+            const u32 v = (u32)(4 * g + u) * B + tid;
+            t[g].r[u] = make_uint4(worst, worst, worst, worst);
+            if (v >= v0 && v < v1) t[g].r[u] = load16<false>(src.abase + v);
+        });
+    });
+    const u32 head = src.lead != 0u ? (E - src.lead < rs.n ? E - src.lead : rs.n) : 0u;
+    const u32 odd = rs.n - (v1 > v0 ? (v1 - v0) * E : 0u);  // how many elements those are: `head` first ones, the others last ones
+    const u32 odd_idx = tid < head ? tid : rs.n - odd + tid;
+    u32 odd_raw = 0;
+    if (tid < odd) odd_raw = load_value<DT>(rs.x, odd_idx);
+    init_row<DT>(P, row, st, rs);
+    if (rs.k == 0) return;
+    if (tid == 0) run = 0;
+    // (nothing computed from the elements in one phase is worth keeping for the next: unpacked, they would take twice the
+    // registers)
+    auto forget = [&]() __attribute__((always_inline)) {
+        static_for<0, kGroups>([&](auto gc) __attribute__((always_inline)) {
+            constexpr int g = decltype(gc)::value;
+            static_for<0, 4>([&](auto uc) __attribute__((always_inline)) {
+                uint4& q = t[g].r[decltype(uc)::value];
+                asm volatile("" : "+v"(q.x), "+v"(q.y), "+v"(q.z), "+v"(q.w));
+            });
+        });
+    };
+    auto better = [&](float a, float b) __attribute__((always_inline)) { return largest ? __builtin_fmaxf(a, b) : __builtin_fminf(a, b); };
+    auto best_of_vector = [&](const typename Source::Tile& tile, auto uc) __attribute__((always_inline)) {
+        constexpr int u = decltype(uc)::value;
+        float m = src.template value<SRC_KEY>(tile, u * (int)E, 0.0f);
+        static_for<1, (int)E>([&](auto jc) __attribute__((always_inline)) {
+            m = better(m, src.template value<SRC_KEY>(tile, u * (int)E + decltype(jc)::value, 0.0f));
+        });
+        return m;
+    };
+    // the order of numbers as 32-bit keys (those of fp32, for every type)
+    auto key_of_number = [&](float x) __attribute__((always_inline)) { return KeyOf<RTOPK_F32>::key(__float_as_uint(x)) ^ (largest ? 0u : 0xffffffffu); };
+    u32 T;
+    bool exact;
+    {
+        float m = best_of_vector(t[0], std::integral_constant<int, 0>{});
+        static_for<0, kGroups>([&](auto gc) __attribute__((always_inline)) {
+            constexpr int g = decltype(gc)::value;
+            static_for<0, 4>([&](auto uc) __attribute__((always_inline)) {
+                m = better(m, best_of_vector(t[g], uc));
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+        forget();
+        const u32 lmax = key_of_number(m);
+        u32 top = wave_reduce(lmax, MaxOf()), low = wave_reduce(lmax, MinOf());
+        if (lane == 63u) {
+            red[2 * wave] = top;
+            red[2 * wave + 1] = low;
+        }
+        __syncthreads();
+        top = red[0];
+        low = red[1];
+#pragma unroll
+        for (int w = 1; w < B / 64; ++w) {
+            top = top > red[2 * w] ? top : red[2 * w];
+            low = low < red[2 * w + 1] ? low : red[2 * w + 1];
+        }
+        __syncthreads();
+        if (rs.k <= (u32)B / 2u) {
+            T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) { f(lmax); }, rs.k, low, top, sm.rank, &exact);
+        } else if (NV < 16 && rs.k <= (u32)(B * NV) / 2u) {  // (with 16 vectors the registers do not allow it)
+            T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) {
+                static_for<0, kGroups>([&](auto gc) __attribute__((always_inline)) {
+                    constexpr int g = decltype(gc)::value;
+                    static_for<0, 4>([&](auto uc) __attribute__((always_inline)) {
+                        f(key_of_number(best_of_vector(t[g], uc)));
+                        __builtin_amdgcn_sched_barrier(0);
+                    });
+                });
+            }, rs.k, 0u, top, sm.rank, &exact);
+        } else {
+            T = 0;
+        }
+    }
+    forget();
+    // masks of what is not worse than the number T stands for; it has to be better than what lies outside the row
+    u32 m[kGroups], mine = 0;
+    const float x = __uint_as_float(largest ? ((T & 0x80000000u) ? T ^ 0x80000000u : ~T) : ((T & 0x80000000u) ? T : T ^ 0x7fffffffu));
+    const bool bounded = T != 0u && odd < (u32)B && (largest ? x > -__builtin_inff() : x < __builtin_inff());
+    static_for<0, kGroups>([&](auto gc) __attribute__((always_inline)) {
+        constexpr int g = decltype(gc)::value;
+        u32 worse = 0;
+        static_for<0, Source::kSlots>([&](auto sc) __attribute__((always_inline)) {
+            const float v = src.template value<SRC_KEY>(t[g], decltype(sc)::value, 0.0f);
+            worse = largest ? shift_in_below(worse, v, x) : shift_in_below(worse, x, v);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+        m[g] = worse ^ (0xffffffffu >> (32 - Source::kSlots));
+        mine += (u32)__builtin_popcount(m[g]);
+    });
+    u32 pos = odd + block_inclusive_scan<B>(mine, red) - mine;  // this lane's place in the list
+    u32 listed = odd, Tk = 0;
+#pragma unroll
+    for (int w = 0; w < B / 64; ++w) listed += red[w];
+    bool tied = false;
+    const ListEntry ent = list_entry<DT>(P);
+    __syncthreads();  // (the counting arrays are done with)
+    if (listed <= kCap && bounded) {
+        if (tid < odd) sm.ord.buf[tid] = ent.of(KeyOf<DT>::key(odd_raw) ^ P.dirmask, odd_idx);
+        static_for<0, kGroups>([&](auto gc) __attribute__((always_inline)) {
+            constexpr int g = decltype(gc)::value;
+            while (ballot64(m[g] != 0u) != 0) {
+                if (m[g] != 0u) {
+                    const u32 bit = 31u - (u32)__builtin_clz(m[g]), s = (u32)Source::kSlots - 1u - bit;
+                    m[g] ^= 1u << bit;
+                    sm.ord.buf[pos++] = ent.of(KeyOf<DT>::key(pick<Source>(t[g], s)) ^ P.dirmask, element_index(src, (u32)g, s));
+                }
+            }
+        });
+        __syncthreads();
+    } else {
+        // crowded, or k close to n: the k-th key itself, of all elements (which are read again: the caches have them, and the
+        // registers stay free of what this rare way needs)
+        auto all = [&](auto&& f) __attribute__((always_inline)) {
+#pragma unroll 1
+            for (u32 v = tid; v < nvec; v += B) {
+                uint4 q = load16<false>(src.abase + v);
+                keys_of_vector<DT>(q, P.dirmask);
+#pragma unroll
+                for (u32 j = 0; j < E; ++j) {
+                    const u32 idx = v * E + j - src.lead;
+                    if (idx < rs.n) f(key_in_vector<DT>(q, (int)j), idx, v);
+                }
+            }
+        };
+        // (a row that the list holds whole needs no bound)
+        if (rs.n > kCap)
+            Tk = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) { all([&](u32 key, u32, u32) __attribute__((always_inline)) { f(key); }); },
+                                rs.k, 0u, 0xffffffffu, sm.rank, &exact);
+        for (;;) {  // what is not below it; if that is too much, what is above it, and the others counted
+            if (tid == 0) run = 0;
+            if (tid <= (u32)kGroups) te[tid] = 0;
+            __syncthreads();
+            all([&](u32 key, u32 idx, u32 v) __attribute__((always_inline)) {
+                if (key > Tk || (key == Tk && !tied)) {
+                    const u32 at = atomicAdd(&run, 1u);
+                    if (at < kCap) sm.ord.buf[at] = ent.of(key, idx);
+                } else if (key == Tk) {
+                    atomicAdd(&te[v / (4u * B)], 1u);
+                }
+            });
+            __syncthreads();
+            listed = run;
+            if (listed <= kCap || tied) break;
+            tied = true;
+            __syncthreads();
+        }
+    }
+    if (tid == 0) list_record(st, rs, listed, 4u);
+    if (listed != 0u && listed <= 8u * OB && !tied) {
+        if (tid >= (u32)OB) return;  // (a barrier waits for the waves that are left)
+        order_in_lds<DT, OB>(P, row, rs, sm.few, listed, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.few.buf[i]; });
+    } else if (listed != 0u) {
+        if (listed > kCap) {  // never expected: the k-th key bounds the list
+            if (tid == 0) st->error |= 4u;
+            return;
+        }
+        order_in_lds<DT, B>(P, row, rs, sm.ord, listed, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.ord.buf[i]; });
+    }
+    if (tied && listed < rs.k) {
+        __syncthreads();
+        if (!ties_of_row<DT, B, Source>(P, te, row, rs, listed, Tk, 0u, 1u, sm.ord.hist, sm.ord.wsum) && tid == 0) st->error |= 4u;
+    }
+}
+
 // Bound, sweep and order in one kernel: the list is gathered in LDS (what does not fit there goes to the list array).
 // For rows so short, or so many, that sharing one out gains nothing.  Several of these workgroups share a compute unit, so that one
 // row's trip from memory overlaps the others' ranking.
 template <int DT, int B, int V>
 __global__ void __launch_bounds__(B, 4) k_list_row(Params P, ListPlan L) {
-    __shared__ union { OrderShared<B> ord; RankShared rank; } sm;
+    constexpr int OB = B < 256 ? B : 256;  // threads that order a short list (see k_list_held)
+    __shared__ union { OrderShared<B> ord; OrderShared<OB> few; RankShared rank; } sm;
     __shared__ ListRow lr;
     __shared__ u32 red[2 * (B / 64)], te[kListRowTiles], run;
     constexpr u32 kCap = 8 * B;
@@ -998,6 +1242,9 @@ __global__ void __launch_bounds__(B, 4) k_list_row(Params P, ListPlan L) {
             list_row(P, row)->end = 1u;
             atomicOr(&st->redo, kRedoList);
         }
+    } else if (total != 0u && total <= 8u * OB && b.mode != kListTied) {
+        if (tid >= (u32)OB) return;  // (a barrier waits for the waves that are left)
+        order_in_lds<DT, OB>(P, row, rs, sm.few, total, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.few.buf[i]; });
     } else if (total != 0u) {
         order_in_lds<DT, B>(P, row, rs, sm.ord, total, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.ord.buf[i]; });
     }
@@ -1316,6 +1563,18 @@ static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStrea
     if (L.row_block != 0) {
         mark(events, 2, st);
         mark(events, 3, st);
+    }
+    if (L.held != 0) {
+        if (L.row_block == 128) hipLaunchKernelGGL((k_list_held<DT, 128, 4>), rows, dim3(128), 0, st, P, L);
+        else if (L.row_block == 256 && L.held == 4) hipLaunchKernelGGL((k_list_held<DT, 256, 4>), rows, dim3(256), 0, st, P, L);
+        else if (L.row_block == 256) hipLaunchKernelGGL((k_list_held<DT, 256, 8>), rows, dim3(256), 0, st, P, L);
+        else if (L.row_block == 512 && L.held == 8) hipLaunchKernelGGL((k_list_held<DT, 512, 8>), rows, dim3(512), 0, st, P, L);
+        else if (L.row_block == 512) hipLaunchKernelGGL((k_list_held<DT, 512, 16>), rows, dim3(512), 0, st, P, L);
+        else hipLaunchKernelGGL((k_list_held<DT, 1024, 16>), rows, dim3(1024), 0, st, P, L);
+        mark(events, 4, st);
+        return hipGetLastError() == hipSuccess ? RTOPK_OK : RTOPK_ERR_HIP;
+    }
+    if (L.row_block != 0) {
         if (L.row_block == 1024 && L.sample == 2) hipLaunchKernelGGL((k_list_row<DT, 1024, 2>), rows, dim3(1024), 0, st, P, L);
         else if (L.row_block == 1024) hipLaunchKernelGGL((k_list_row<DT, 1024, 1>), rows, dim3(1024), 0, st, P, L);
         else if (L.row_block == 512 && L.sample == 2) hipLaunchKernelGGL((k_list_row<DT, 512, 4>), rows, dim3(512), 0, st, P, L);

@@ -35,6 +35,27 @@ def _check(name, x, dtype, k, largest=True, sorted=True, batch=1, by_list=True, 
 
 
 @pytest.mark.parametrize("dtype", [F32, F16, BF16])
+def test_rows_held_in_registers(dtype):
+    # around the capacities of every variant, any k the list has room for; whole and broken first and last vectors
+    for n in (1, 2, 7, 8, 9, 63, 65, 1000, 2047, 2049, 4096, 4097, 8191, 8200, 16384, 16389, 32768, 32771):
+        x = W.normal(3 * n, seed=n, sigma=3.0)
+        for k in sorted({1, min(n, 50), min(n, 300), max(1, n // 3), n - n // 7, n}):
+            if n <= 8192 or k <= 1900:
+                _check("held", x, dtype, k, largest=k % 2 == 0, batch=3)
+        y = np.where(W.uniform01(3 * n, 1) < 0.7, np.float32(2.5), x).astype(np.float32)     # crowded
+        y[:: max(1, n // 3)] = np.nan
+        for k in sorted({1, max(1, n // 5), max(1, n // 2), n}):
+            if n <= 8192 or k <= 1900:
+                _check("held, crowded", y, dtype, k, largest=k % 2 == 1, batch=3)
+                _check("held, crowded", y, dtype, k, largest=k % 2 == 0, batch=3, sorted=False)
+    z = np.full(5000, np.float32(-np.inf))
+    z[::9] = np.nan
+    for k in (1, 600, 4999):
+        for largest in (True, False):
+            _check("held, worst numbers only", z, dtype, k, largest)
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
 def test_sizes_and_ks(dtype):
     least = 8192 if dtype == F32 else 16384
     for n in (least, least + 1, 30011, 65535, 65536, 65537, 131072 + 5, (1 << 18) + 3, (1 << 20) + 7):
