@@ -221,6 +221,19 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     memset(L, 0, sizeof(*L));
     if (tn && (tn->digit_bits || tn->path || tn->wgs_per_row || tn->small_threshold || tn->prefilter)) return false;
     const int eb = elem_bytes(dt), E = 16 / eb;
+    // few rows, small k: stretches of 32 KB, each listing its best k
+    {
+        const int64_t part = (int64_t)kListPartBlock * kListPartVecs * 16, G = (n * eb + 16 + part - 1) / part;
+        const int64_t stride = k * 2 + 64;
+        if (n * eb > (64 << 10) && batch <= 256 && batch * G <= 1024 && G * stride <= 8192 && G * stride <= n / 2 &&
+            stride <= 8 * kListPartBlock) {
+            L->G = (int)G;
+            L->seg_stride = (u32)stride;
+            L->finish = G * stride <= 2048 ? 256 : 1024;
+            L->seg_off = 256;
+            return true;
+        }
+    }
     // rows that one workgroup can hold in registers
     if (batch <= ((int64_t)1 << 22)) {
         static const struct { int block, vecs; int64_t rows; } held[] = {
@@ -243,12 +256,12 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     L->sample = vecs >= (1 << 20) ? 4 : vecs >= (1 << 16) ? 3 : vecs >= (1 << 14) ? 2 : vecs >= (1 << 12) || batch <= 256 ? 1 : 0;
     // one workgroup per row: rows of up to 256 KB, in large batches up to 1 MB
     const bool by_row = n * eb <= (256 << 10) || (batch >= 256 && n * eb <= (1 << 20));
-    if (by_row && L->sample > 2) L->sample = 2;
+    if (by_row && L->sample > 1) L->sample = 1;
     double listed = 0.0, room = 0.0;  // expected length of the list, and with a margin
     auto expect = [&]() {
         const double elems = (double)((L->sample == 4 ? (eb == 4 ? 16384 : 8192) : L->sample == 3 ? 4096 : 512 << L->sample) * E);
         const double ks = (double)k * elems / (double)n;
-        listed = (ks + 6.0 * __builtin_sqrt(ks) + 10.0) * 1.08 * (double)n / elems;
+        listed = (ks + 6.0 * __builtin_sqrt(ks) + 7.0) * 1.08 * (double)n / elems;
         room = listed * 1.08 + 64.0;
     };
     expect();
@@ -271,7 +284,11 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     if (G < 1) G = 1;
     if (G > ntiles) G = ntiles;
     L->G = (int)G;
-    L->finish = room > 4096.0 ? 1024 : room > 2048.0 ? 512 : 256;
+    // (one sweep: nothing is read twice.  2^26 fp32 keys, k = n / 100 as a mask, 133 us with ordinary loads, 121 past the
+    // caches; 1024 rows of 2^17 bf16 keys, k = 50, 64 against 57.5; 2^24 fp32 keys, which the last-level cache holds, 36.7
+    // against 37.8)
+    L->stream = batch * n * eb > ((int64_t)128 << 20);
+    L->finish = room > 2048.0 ? 1024 : 256;
     L->bucket_shift = 11;
     while ((k >> L->bucket_shift) + 1 > (int64_t)kListMaxBuckets) ++L->bucket_shift;
     L->nb = is_long ? (u32)((k >> L->bucket_shift) + 1) : 0u;
@@ -284,7 +301,7 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     auto take = [&](u64 bytes) { const u64 at = off; off = align_up(off + bytes, 16); return (u32)at; };
     L->hist_off = take(is_long ? kMaxBins * 4 : 0);
     L->cursor_off = take((u64)L->nb * 4);
-    L->first_off = take((u64)L->nb * 4);
+    L->first_off = take((u64)L->nb * 8);
     L->seg_off = take((u64)G * 4);
     L->tile_off = take((u64)((n + E - 1) / (kHostGridBlock * 64 / eb) + 1) * 4);  // (the smaller tiles' number)
     L->stack_off = take(((u64)n / 256 + 64 + 16 * (u64)L->nb) * 16);

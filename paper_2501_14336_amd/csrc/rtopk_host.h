@@ -27,13 +27,16 @@ rtopk_status launch_bf16(const Params& P, const Config& c, bool scaled, hipStrea
 
 // Plan of a call that goes through lists (rtopk_list.inl).  Offsets: bytes from the start of a row's working memory.
 constexpr unsigned kListMaxBuckets = 4096;
+constexpr int kListPartBlock = 256, kListPartVecs = 8;  // a stretch of a row that one workgroup holds: 32 KB
 struct ListPlan {
     int G;            // workgroups per row in the sweep
     int row_block;    // one workgroup per row does everything: its threads (0: many workgroups per row)
     int held;         // ... holding the row in registers: 16-byte vectors per thread (0: the row is swept)
     int sample;       // which size of sample: 512, 1024, 2048, 4096 or 16384 (16-bit keys: 8192) vectors of 16 bytes
+    int stream;       // the input is too large for the caches to keep: read past them
     int finish;       // short lists: threads of the workgroup that puts a row's list in order
     int ties;         // workgroups per row that fetch elements equal to the bound, where those are very many
+    u32 seg_stride;   // the row's stretches are held by G workgroups that list at most this many each (0: the row is swept)
     u32 nb;           // long lists: buckets per row (0: short lists)
     u32 bucket_shift; // ... of 2^bucket_shift ranks
     u32 hist_off, cursor_off, first_off, seg_off, tile_off, stack_off;

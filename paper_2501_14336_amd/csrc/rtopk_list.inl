@@ -9,6 +9,7 @@
 // than half the row, has the row done again by one workgroup that selects the k-th key from all of X (k_list_redo).
 //
 //   k_list_held     rows of up to 256 KB: one workgroup per row, which holds the row in registers and needs no sample
+//   k_list_part     few rows and a small k: several workgroups hold a row and list their stretches' best (k_list_finish follows)
 //   k_list_row      longer rows, or many: one workgroup per row does all of the following
 //   k_list_bound    one workgroup per row: sample, T
 //   k_list_sweep    many workgroups per row: X -> list, one segment per workgroup
@@ -219,6 +220,44 @@ __device__ __forceinline__ u32 sample_rank(Each&& each, u32 rank, u32 lo, u32 hi
     }
 }
 
+// The same for one value per thread, in LDS: the first wave halves [lo, hi] until the values from lo up are at least `rank`
+// and few more, counting with a compare and a scalar population count per 64 of them -- no barriers among many waves
+// (1024 values: 1.3 us against 4.4 with sample_rank).  At least `rank` values are not below lo.  Contains two barriers; `v`
+// may be written again after it.
+template <int B>
+__device__ __forceinline__ u32 rank_by_one_wave(u32 value, u32 rank, u32 lo, u32 hi, u32* v, u32* result, bool* exact) {
+    const u32 tid = threadIdx.x;
+    v[tid] = value;
+    __syncthreads();
+    if (tid < 64u) {
+        constexpr int kPer = B / 64;
+        u32 mine[kPer];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) mine[i] = v[i * 64 + tid];
+        const u32 slack = rank + 1u + rank / 16u;
+        u32 end = hi;  // fewer than `rank` values lie above it
+        while (lo < end) {
+            const u32 mid = lo + (end - lo + 1u) / 2u;
+            u32 c = 0;
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) c += (u32)__popcll(ballot64(mine[i] >= mid));
+            if (c >= rank) {
+                lo = mid;
+                if (c <= slack) break;
+            } else {
+                end = mid - 1u;
+            }
+        }
+        if (tid == 0) {
+            result[0] = lo;
+            result[1] = lo == end ? 1u : 0u;
+        }
+    }
+    __syncthreads();
+    *exact = result[1] != 0u;
+    return result[0];
+}
+
 __device__ __forceinline__ u32 mix32(u32 z) {
     z ^= z >> 16; z *= 0x7feb352du;
     z ^= z >> 15; z *= 0x846ca68bu;
@@ -256,7 +295,8 @@ __device__ __forceinline__ u32 key_in_vector(const uint4& q, int j) {
 // The rank is taken among the MAXIMA of vectors (or of all a lane's vectors) while it is small against their number:
 // neighbouring elements that are alike then count once, so that a row whose best elements lie together does not look
 // richer than it is, and there are fewer values to rank.  The rank that stands for the row's k-th key is its share
-// ks = k * sample / n, plus six standard deviations of a Poisson count, plus 8.
+// ks = k * sample / n, plus six standard deviations of a Poisson count, plus 6 (ks = 0.1, 1, 10, 100: more than
+// that many are seen with a probability of 1e-13, 1e-9, 1e-8, 1e-8; the row is then done again).
 // te: counters of ties per tile, nt of them, cleared if they will be used.  Thread 0 fills in *lr.
 template <int DT, int B, int V>
 __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L, int row, const RowShape& rs, rtopk_row_trace* st,
@@ -305,8 +345,8 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
         return;
     }
     constexpr u32 kVecsTotal = (u32)(B * V), kElems = kVecsTotal * E;
-    const u32 ks = (u32)(((u64)rs.k * kElems + rs.n - 1u) / rs.n);
-    const u32 rank = ks + (u32)(6.0f * __builtin_sqrtf((float)ks)) + 8u;
+    const float ks = (float)rs.k * ((float)kElems / (float)rs.n);
+    const u32 rank = (u32)(ks + 6.0f * __builtin_sqrtf(ks) + 6.0f);
     u32 vmax[V], lmax = 0;
 #pragma unroll
     for (int u = 0; u < V; ++u) {
@@ -339,7 +379,7 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
     u32 T;
     bool exact;
     if (rank <= (u32)B / 4u) {
-        T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) { f(lmax >> ksh); }, rank, low >> ksh, top >> ksh, sm, &exact);
+        T = rank_by_one_wave<B>(lmax >> ksh, rank, low >> ksh, top >> ksh, sm.hist, sm.selv, &exact);
     } else if (rank <= kVecsTotal / 4u) {
         T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) {
 #pragma unroll
@@ -962,9 +1002,17 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
             const u32 m = (a + b) / 2u;
             if (segs[m] <= i) a = m; else b = m;
         }
-        return from[list_segment(src, a, (u32)L.G, ntiles) + (i - segs[a])];
+        const u32 at = L.seg_stride != 0u ? a * L.seg_stride : list_segment(src, a, (u32)L.G, ntiles);
+        return from[at + (i - segs[a])];
     };
-    if (total <= 8u * B) {
+    // (a list that fewer waves can put in order is left to them: barriers)
+    if (B > 256 && total <= 8u * 256u) {
+        if (tid >= 256u) return;
+        order_in_lds<DT, 256>(P, row, rs, *(OrderShared<256>*)&sm, total, 0u, entry);
+    } else if (B > 512 && total <= 8u * 512u) {
+        if (tid >= 512u) return;
+        order_in_lds<DT, 512>(P, row, rs, *(OrderShared<512>*)&sm, total, 0u, entry);
+    } else if (total <= 8u * B) {
         order_in_lds<DT, B>(P, row, rs, sm, total, 0u, entry);
     } else {
         for (u32 i = tid; i < total; i += B) dst[i] = entry(i);
@@ -980,27 +1028,28 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
 // one workgroup per row
 // ------------------------------------------------------------------------------------------------
 
-// A row that B lanes can hold, NV vectors of 16 bytes each: X is read once, in one go, and everything else works on
-// registers.  The bound needs no sample: the best element of every lane is known, and the k-th best of those is a number
-// that at least k elements reach -- hardly more than k while k is small against B (k = B / 2: 1.4 k on independent
-// draws).  For larger k the maxima of vectors take the place of the lanes', then the elements.
-// Bound by latency: one trip to memory, then about ten phases with barriers (the first four waves alone put a short list
-// in order: a barrier among 16 waves takes 1 us, among 4 waves 0.5).
+// B lanes hold a stretch of a row, NV vectors of 16 bytes each from vector p0 on (a multiple of B * NV; `last`: it is the
+// row's last stretch): read once, in one go, and everything else works on registers.  Leaves a list in sm.ord.buf that
+// contains the best min(k, size) elements of the stretch, and returns its length, at most `limit` (at least k + k / 16 + 2, or
+// the stretch's size).  after_load() runs while the loads are under way.  Ends with a barrier.
+// The bound needs no sample: the best element of every lane is known, and the k-th best of those is a number that at least
+// k elements reach -- hardly more than k while k is small against B (k = B / 2: 1.4 k on independent draws).  For
+// larger k the maxima of vectors take the place of the lanes'.
 // A list that comes out too long (crowded keys) is bounded again by the exact k-th key, and if it is still too long, equal
-// elements are counted and not listed; no row is left over.
-template <int DT, int B, int NV>
-__global__ void __launch_bounds__(B, 4) k_list_held(Params P, ListPlan L) {
-    constexpr int kGroups = NV / 4;  // the row as tiles of four vectors per lane
-    constexpr u32 kCap = 8 * B;
-    constexpr int OB = B < 256 ? B : 256;  // threads that order a short list
+// elements are added in the order of their positions until there are k.
+template <int B>
+struct HeldShared {
+    static constexpr int OB = B < 256 ? B : 256;  // threads that order a short list
+    union { OrderShared<B> ord; OrderShared<OB> few; RankShared rank; };  // (both lists at the same place)
+    u32 part[2 * (B / 64)], run;
+};
+template <int DT, int B, int NV, class AfterLoad>
+__device__ __forceinline__ u32 hold_and_list(const Params& P, const RowShape& rs, u32 p0, bool last, u32 limit, HeldShared<B>& sm,
+                                             AfterLoad&& after_load) {
+    constexpr int kGroups = NV / 4;  // the stretch as tiles of four vectors per lane
     typedef KeySource<DT, B, 4, false> Source;
     constexpr u32 E = Source::E;
-    __shared__ union { OrderShared<B> ord; OrderShared<OB> few; RankShared rank; } sm;  // (both lists at the same place)
-    __shared__ u32 red[2 * (B / 64)], te[kGroups + 1], run;  // (a full row off the 16-byte grid ends in one more tile)
-    const int row = blockIdx.x;
     const u32 tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-    const RowShape rs = row_shape_scalar<DT>(P, row);
-    rtopk_row_trace* st = row_state(P, row);
     Source src;
     src.init(rs);
     const bool largest = P.dirmask == 0;
@@ -1014,19 +1063,19 @@ __global__ void __launch_bounds__(B, 4) k_list_held(Params P, ListPlan L) {
         constexpr int g = decltype(gc)::value;
         static_for<0, 4>([&](auto uc) __attribute__((always_inline)) {
             constexpr int u = decltype(uc)::value;
-            const u32 v = (u32)(4 * g + u) * B + tid;
+            const u32 v = p0 + (u32)(4 * g + u) * B + tid;
             t[g].r[u] = make_uint4(worst, worst, worst, worst);
             if (v >= v0 && v < v1) t[g].r[u] = load16<false>(src.abase + v);
         });
     });
-    const u32 head = src.lead != 0u ? (E - src.lead < rs.n ? E - src.lead : rs.n) : 0u;
-    const u32 odd = rs.n - (v1 > v0 ? (v1 - v0) * E : 0u);  // how many elements those are: `head` first ones, the others last ones
+    // (the elements before the first whole vector belong to the first stretch, those after the last one to the last)
+    const u32 before = src.lead != 0u ? (E - src.lead < rs.n ? E - src.lead : rs.n) : 0u;
+    const u32 behind = rs.n - before - (v1 > v0 ? (v1 - v0) * E : 0u);
+    const u32 head = p0 == 0u ? before : 0u, odd = head + (last ? behind : 0u);
     const u32 odd_idx = tid < head ? tid : rs.n - odd + tid;
     u32 odd_raw = 0;
     if (tid < odd) odd_raw = load_value<DT>(rs.x, odd_idx);
-    init_row<DT>(P, row, st, rs);
-    if (rs.k == 0) return;
-    if (tid == 0) run = 0;
+    after_load();
     // (nothing computed from the elements in one phase is worth keeping for the next: unpacked, they would take twice the
     // registers)
     auto forget = [&]() __attribute__((always_inline)) {
@@ -1064,20 +1113,20 @@ __global__ void __launch_bounds__(B, 4) k_list_held(Params P, ListPlan L) {
         const u32 lmax = key_of_number(m);
         u32 top = wave_reduce(lmax, MaxOf()), low = wave_reduce(lmax, MinOf());
         if (lane == 63u) {
-            red[2 * wave] = top;
-            red[2 * wave + 1] = low;
+            sm.part[2 * wave] = top;
+            sm.part[2 * wave + 1] = low;
         }
         __syncthreads();
-        top = red[0];
-        low = red[1];
+        top = sm.part[0];
+        low = sm.part[1];
 #pragma unroll
         for (int w = 1; w < B / 64; ++w) {
-            top = top > red[2 * w] ? top : red[2 * w];
-            low = low < red[2 * w + 1] ? low : red[2 * w + 1];
+            top = top > sm.part[2 * w] ? top : sm.part[2 * w];
+            low = low < sm.part[2 * w + 1] ? low : sm.part[2 * w + 1];
         }
         __syncthreads();
         if (rs.k <= (u32)B / 2u) {
-            T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) { f(lmax); }, rs.k, low, top, sm.rank, &exact);
+            T = rank_by_one_wave<B>(lmax, rs.k, low, top, sm.rank.hist, sm.rank.selv, &exact);
         } else if (NV < 16 && rs.k <= (u32)(B * NV) / 2u) {  // (with 16 vectors the registers do not allow it)
             T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) {
                 static_for<0, kGroups>([&](auto gc) __attribute__((always_inline)) {
@@ -1096,7 +1145,7 @@ __global__ void __launch_bounds__(B, 4) k_list_held(Params P, ListPlan L) {
     // masks of what is not worse than the number T stands for; it has to be better than what lies outside the row
     u32 m[kGroups], mine = 0;
     const float x = __uint_as_float(largest ? ((T & 0x80000000u) ? T ^ 0x80000000u : ~T) : ((T & 0x80000000u) ? T : T ^ 0x7fffffffu));
-    const bool bounded = T != 0u && odd < (u32)B && (largest ? x > -__builtin_inff() : x < __builtin_inff());
+    const bool bounded = T != 0u && (largest ? x > -__builtin_inff() : x < __builtin_inff());
     static_for<0, kGroups>([&](auto gc) __attribute__((always_inline)) {
         constexpr int g = decltype(gc)::value;
         u32 worse = 0;
@@ -1108,92 +1157,165 @@ __global__ void __launch_bounds__(B, 4) k_list_held(Params P, ListPlan L) {
         m[g] = worse ^ (0xffffffffu >> (32 - Source::kSlots));
         mine += (u32)__builtin_popcount(m[g]);
     });
-    u32 pos = odd + block_inclusive_scan<B>(mine, red) - mine;  // this lane's place in the list
-    u32 listed = odd, Tk = 0;
+    u32 pos = odd + block_inclusive_scan<B>(mine, sm.part) - mine;  // this lane's place in the list
+    u32 listed = odd;
 #pragma unroll
-    for (int w = 0; w < B / 64; ++w) listed += red[w];
-    bool tied = false;
+    for (int w = 0; w < B / 64; ++w) listed += sm.part[w];
     const ListEntry ent = list_entry<DT>(P);
     __syncthreads();  // (the counting arrays are done with)
-    if (listed <= kCap && bounded) {
+    if (listed <= limit && bounded) {
         if (tid < odd) sm.ord.buf[tid] = ent.of(KeyOf<DT>::key(odd_raw) ^ P.dirmask, odd_idx);
-        static_for<0, kGroups>([&](auto gc) __attribute__((always_inline)) {
-            constexpr int g = decltype(gc)::value;
-            while (ballot64(m[g] != 0u) != 0) {
-                if (m[g] != 0u) {
-                    const u32 bit = 31u - (u32)__builtin_clz(m[g]), s = (u32)Source::kSlots - 1u - bit;
-                    m[g] ^= 1u << bit;
-                    sm.ord.buf[pos++] = ent.of(KeyOf<DT>::key(pick<Source>(t[g], s)) ^ P.dirmask, element_index(src, (u32)g, s));
-                }
+        // (the few are fetched again: to select one of 64 registers by a number takes longer than the caches do)
+        for (;;) {
+            u32 left = 0, group = 0;
+            static_for<0, kGroups>([&](auto gc) __attribute__((always_inline)) {
+                constexpr int g = kGroups - 1 - decltype(gc)::value;
+                if (m[g] != 0u) { left = m[g]; group = (u32)g; }
+            });
+            if (ballot64(left != 0u) == 0) break;
+            const u32 bit = 31u - (u32)__builtin_clz(left | 1u), s = (u32)Source::kSlots - 1u - bit;
+            static_for<0, kGroups>([&](auto gc) __attribute__((always_inline)) {
+                constexpr int g = decltype(gc)::value;
+                if (left != 0u && group == (u32)g) m[g] ^= 1u << bit;
+            });
+            if (left != 0u) {
+                const u32 idx = element_index(src, p0 / (4u * B) + group, s);
+                sm.ord.buf[pos++] = ent.of(KeyOf<DT>::key(load_value<DT>(rs.x, idx)) ^ P.dirmask, idx);
+            }
+        }
+        __syncthreads();
+        return listed;
+    }
+    // Crowded, or k close to the stretch's size: the k-th key itself, of all elements (which are read again: the caches have
+    // them, and the registers stay free of what this rare way needs).
+    const u32 pend = last || p0 + (u32)(B * NV) > nvec ? nvec : p0 + (u32)(B * NV);
+    auto all = [&](auto&& f) __attribute__((always_inline)) {
+#pragma unroll 1
+        for (u32 v = p0 + tid; v < pend; v += B) {
+            uint4 q = load16<false>(src.abase + v);
+            keys_of_vector<DT>(q, P.dirmask);
+#pragma unroll
+            for (u32 j = 0; j < E; ++j) {
+                const u32 idx = v * E + j - src.lead;
+                if (idx < rs.n) f(key_in_vector<DT>(q, (int)j), idx);
+            }
+        }
+    };
+    const u32 from = p0 == 0u ? 0u : p0 * E - src.lead, to = pend * E - src.lead < rs.n ? pend * E - src.lead : rs.n;
+    const u32 size = pend > p0 ? to - from : 0u;
+    u32 Tk = 0;
+    if (size > limit)  // (a stretch that the list holds whole needs no bound)
+        Tk = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) { all([&](u32 key, u32) __attribute__((always_inline)) { f(key); }); }, rs.k,
+                            0u, 0xffffffffu, sm.rank, &exact);
+    bool tied = false;
+    for (;;) {  // what is not below it; if that is too much, what is above it
+        if (tid == 0) sm.run = 0;
+        __syncthreads();
+        all([&](u32 key, u32 idx) __attribute__((always_inline)) {
+            if (key > Tk || (key == Tk && !tied)) {
+                const u32 at = atomicAdd(&sm.run, 1u);
+                if (at < limit) sm.ord.buf[at] = ent.of(key, idx);
             }
         });
         __syncthreads();
-    } else {
-        // crowded, or k close to n: the k-th key itself, of all elements (which are read again: the caches have them, and the
-        // registers stay free of what this rare way needs)
-        auto all = [&](auto&& f) __attribute__((always_inline)) {
-#pragma unroll 1
-            for (u32 v = tid; v < nvec; v += B) {
-                uint4 q = load16<false>(src.abase + v);
-                keys_of_vector<DT>(q, P.dirmask);
-#pragma unroll
-                for (u32 j = 0; j < E; ++j) {
-                    const u32 idx = v * E + j - src.lead;
-                    if (idx < rs.n) f(key_in_vector<DT>(q, (int)j), idx, v);
-                }
-            }
-        };
-        // (a row that the list holds whole needs no bound)
-        if (rs.n > kCap)
-            Tk = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) { all([&](u32 key, u32, u32) __attribute__((always_inline)) { f(key); }); },
-                                rs.k, 0u, 0xffffffffu, sm.rank, &exact);
-        for (;;) {  // what is not below it; if that is too much, what is above it, and the others counted
-            if (tid == 0) run = 0;
-            if (tid <= (u32)kGroups) te[tid] = 0;
-            __syncthreads();
-            all([&](u32 key, u32 idx, u32 v) __attribute__((always_inline)) {
-                if (key > Tk || (key == Tk && !tied)) {
-                    const u32 at = atomicAdd(&run, 1u);
-                    if (at < kCap) sm.ord.buf[at] = ent.of(key, idx);
-                } else if (key == Tk) {
-                    atomicAdd(&te[v / (4u * B)], 1u);
-                }
-            });
-            __syncthreads();
-            listed = run;
-            if (listed <= kCap || tied) break;
-            tied = true;
-            __syncthreads();
-        }
+        listed = sm.run;
+        if (listed <= limit || tied) break;
+        tied = true;
+        __syncthreads();
     }
+    // equal elements, a vector per thread at a time: thread order is position order
+    for (u32 b = p0; tied && listed < rs.k && b < pend; b += B) {
+        const u32 v = b + tid;
+        u32 hit = 0;
+        if (v < pend) {
+            uint4 q = load16<false>(src.abase + v);
+            keys_of_vector<DT>(q, P.dirmask);
+#pragma unroll
+            for (u32 j = 0; j < E; ++j) hit |= (v * E + j - src.lead < rs.n && key_in_vector<DT>(q, (int)j) == Tk ? 1u : 0u) << j;
+        }
+        const u32 n = (u32)__builtin_popcount(hit);
+        u32 at = listed + block_inclusive_scan<B>(n, sm.part) - n;
+        for (; hit != 0u && at < rs.k; hit &= hit - 1u, ++at) sm.ord.buf[at] = ent.of(Tk, v * E + (u32)__builtin_ctz(hit) - src.lead);
+#pragma unroll
+        for (int w = 0; w < B / 64; ++w) listed += sm.part[w];
+        if (listed > rs.k) listed = rs.k;
+        __syncthreads();
+    }
+    return listed;
+}
+
+// A row that one workgroup can hold: no sample, one launch, no row left over.
+// Bound by latency: one trip to memory, then about ten phases with barriers (the first four waves alone put a short list
+// in order: a barrier among 16 waves takes 1 us, among 4 waves 0.5).
+template <int DT, int B, int NV>
+__global__ void __launch_bounds__(B, 4) k_list_held(Params P, ListPlan L) {
+    constexpr u32 kCap = 8 * B;
+    constexpr int OB = HeldShared<B>::OB;
+    __shared__ HeldShared<B> sm;
+    const int row = blockIdx.x;
+    const u32 tid = threadIdx.x;
+    const RowShape rs = row_shape_scalar<DT>(P, row);
+    rtopk_row_trace* st = row_state(P, row);
+    if (rs.k == 0) {
+        init_row<DT>(P, row, st, rs);
+        return;
+    }
+    const u32 listed = hold_and_list<DT, B, NV>(P, rs, 0u, true, kCap, sm, [&]() __attribute__((always_inline)) { init_row<DT>(P, row, st, rs); });
     if (tid == 0) list_record(st, rs, listed, 4u);
-    if (listed != 0u && listed <= 8u * OB && !tied) {
+    if (listed > kCap) {  // never expected: the k-th key bounds the list
+        if (tid == 0) st->error |= 4u;
+    } else if (listed <= 8u * OB) {
         if (tid >= (u32)OB) return;  // (a barrier waits for the waves that are left)
         order_in_lds<DT, OB>(P, row, rs, sm.few, listed, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.few.buf[i]; });
-    } else if (listed != 0u) {
-        if (listed > kCap) {  // never expected: the k-th key bounds the list
-            if (tid == 0) st->error |= 4u;
-            return;
-        }
+    } else {
         order_in_lds<DT, B>(P, row, rs, sm.ord, listed, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.ord.buf[i]; });
     }
-    if (tied && listed < rs.k) {
-        __syncthreads();
-        if (!ties_of_row<DT, B, Source>(P, te, row, rs, listed, Tk, 0u, 1u, sm.ord.hist, sm.ord.wsum) && tid == 0) st->error |= 4u;
+}
+
+// Few rows, small k: a row's stretches of 32 KB are held by a workgroup each, which list their best k; k_list_finish puts a
+// row's L.G lists of at most L.seg_stride entries in order.  Two launches, no sample, no row left over.
+constexpr int kPartBlock = kListPartBlock, kPartVecs = kListPartVecs;
+template <int DT>
+__global__ void __launch_bounds__(kPartBlock, 4) k_list_part(Params P, ListPlan L) {
+    constexpr int B = kPartBlock;
+    __shared__ HeldShared<B> sm;
+    const u32 G = (u32)L.G, tid = threadIdx.x;
+    const int row = (int)(blockIdx.x / G);
+    const u32 g = blockIdx.x % G;
+    const RowShape rs = row_shape_scalar<DT>(P, row);
+    rtopk_row_trace* st = row_state(P, row);
+    KeySource<DT, B, 4, false> src;
+    src.init(rs);
+    constexpr u32 kHeld = (u32)B * (u32)kPartVecs;
+    const u32 p0 = g * kHeld, nvec = (u32)src.nvec;
+    u32 listed = 0;
+    auto first = [&]() __attribute__((always_inline)) {
+        if (g == 0u) {
+            init_row<DT>(P, row, st, rs);
+            if (tid == 0) list_row(P, row)->mode = rs.k == 0u ? kListSkip : kListPlain;
+        }
+    };
+    if (rs.k == 0u || p0 >= nvec) {
+        first();
+    } else {
+        listed = hold_and_list<DT, B, kPartVecs>(P, rs, p0, p0 + kHeld >= nvec, L.seg_stride, sm, first);
+        u64* seg = list_array(P, 1u, row) + (size_t)g * L.seg_stride;
+        for (u32 i = tid; i < listed && i < L.seg_stride; i += B) seg[i] = sm.ord.buf[i];
     }
+    if (tid == 0) list_part<u32>(P, row, L.seg_off)[g] = listed < L.seg_stride ? listed : L.seg_stride;
 }
 
 // Bound, sweep and order in one kernel: the list is gathered in LDS (what does not fit there goes to the list array).
 // For rows so short, or so many, that sharing one out gains nothing.  Several of these workgroups share a compute unit, so that one
 // row's trip from memory overlaps the others' ranking.
-template <int DT, int B, int V>
+template <int DT, int B, int V, bool NT>
 __global__ void __launch_bounds__(B, 4) k_list_row(Params P, ListPlan L) {
     constexpr int OB = B < 256 ? B : 256;  // threads that order a short list (see k_list_held)
     __shared__ union { OrderShared<B> ord; OrderShared<OB> few; RankShared rank; } sm;
     __shared__ ListRow lr;
     __shared__ u32 red[2 * (B / 64)], te[kListRowTiles], run;
     constexpr u32 kCap = 8 * B;
-    typedef KeySource<DT, B, 4, false> Source;
+    typedef KeySource<DT, B, 4, NT> Source;
     const int row = blockIdx.x;
     const u32 tid = threadIdx.x, lane = lane_id();
     const RowShape rs = row_shape_scalar<DT>(P, row);
@@ -1330,14 +1452,24 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
             lr->end = end;
             list_record(st, rs, total, 5u);
         }
-        // the buckets' first ranks
+        // the buckets' first ranks and sizes
         u32* first = list_part<u32>(P, row, L.first_off);
-        for (u32 j = tid; j < nb; j += B) first[j] = 0xffffffffu;
+        for (u32 j = tid; j < nb; j += B) place[j] = 0xffffffffu;
         __syncthreads();
         for (u32 j = tid; j < kListBins; j += B) {  // j counts from the best bin
             const u32 r = start[kListBins - 1u - j];
-            if (r < end && (j == 0 || (r >> bs) > (start[kListBins - j] >> bs))) first[r >> bs] = r;
+            if (r < end && (j == 0 || (r >> bs) > (start[kListBins - j] >> bs))) place[r >> bs] = r;
         }
+        __syncthreads();
+        for (u32 j = tid; j < nb; j += B) {
+            u32 i = j + 1u;
+            while (i < nb && place[i] == 0xffffffffu) ++i;
+            first[2u * j] = place[j];
+            first[2u * j + 1u] = (i < nb ? place[i] : end) - place[j];
+        }
+        __syncthreads();
+        for (u32 j = tid; j < nb; j += B) place[j] = 0;
+        __syncthreads();
     }
     auto bucket_of = [&](u64 e) __attribute__((always_inline)) {
         const u64 b = (e - lo) >> sh;
@@ -1381,26 +1513,11 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
 }
 
 // Where bucket j of a row begins and how many entries it has; false if there is no such bucket, or nothing is wanted from it.
-// Contains two barriers (not if it returns at once, the same for every thread).
-template <int B>
-__device__ __forceinline__ bool bucket_range(const Params& P, const ListPlan& L, int row, const RowShape& rs, u32 end, u32 j, u32* at,
-                                             u32* count, u32* shared) {
-    const u32* first = list_part<u32>(P, row, L.first_off);
-    *at = first[j];
-    if (*at == 0xffffffffu || *at >= rs.k || *at >= end) return false;
-    // the next bucket that exists begins where this one ends
-    if (threadIdx.x == 0) *shared = end;
-    __syncthreads();
-    for (u32 i = j + 1u + threadIdx.x; i < L.nb; i += B) {
-        const u32 f = first[i];
-        if (f != 0xffffffffu) {
-            atomicMin(shared, f);
-            break;
-        }
-    }
-    __syncthreads();
-    *count = *shared - *at;
-    return true;
+__device__ __forceinline__ bool bucket_range(const Params& P, const ListPlan& L, int row, const RowShape& rs, u32 j, u32* at, u32* count) {
+    const uint2 f = list_part<uint2>(P, row, L.first_off)[j];
+    *at = f.x;
+    *count = f.y;
+    return f.x != 0xffffffffu && f.x < rs.k;
 }
 
 // One workgroup per bucket (blocks [0, nb) of a row) puts its entries in order; the other L.ties blocks of the row are for
@@ -1427,7 +1544,7 @@ __global__ void __launch_bounds__(kListBucketBlock) k_list_buckets(Params P, Lis
         return;
     }
     u32 at, count;
-    if (!bucket_range<B>(P, L, row, rs, lr->end, j, &at, &count, &sm.sp)) return;
+    if (!bucket_range(P, L, row, rs, j, &at, &count)) return;
     if (count <= 8u * B) {
         const u64* src = list_array(P, 0u, row) + at;
         order_in_lds<DT, B>(P, row, rs, sm, count, at, [&](u32 i) __attribute__((always_inline)) { return src[i]; });
@@ -1533,7 +1650,7 @@ __global__ void __launch_bounds__(kListBucketBlock) k_list_redo(Params P, ListPl
             for (u32 j = buckets ? blockIdx.x : 0u; j < tasks; j += gridDim.x) {
                 u32 at = 0, count = 0, which = 0;
                 if (buckets) {
-                    if (!bucket_range<B>(P, L, row, rs, list_row(P, row)->end, j, &at, &count, &run)) continue;
+                    if (!bucket_range(P, L, row, rs, j, &at, &count)) continue;
                     if (count <= 8u * B) count = 0;  // (done)
                     stack += at / (u32)B + 16u * j;
                 } else if (mine && (why & kRedoRow)) {
@@ -1554,6 +1671,15 @@ __global__ void __launch_bounds__(kListBucketBlock) k_list_redo(Params P, ListPl
 }
 
 // ------------------------------------------------------------------------------------------------
+template <int DT, bool NT>
+static void launch_list_row(const Params& P, const ListPlan& L, hipStream_t st) {
+    const dim3 rows((unsigned)P.batch);
+    if (L.row_block == 1024) hipLaunchKernelGGL((k_list_row<DT, 1024, 1, NT>), rows, dim3(1024), 0, st, P, L);
+    else if (L.row_block == 512 && L.sample == 1) hipLaunchKernelGGL((k_list_row<DT, 512, 2, NT>), rows, dim3(512), 0, st, P, L);
+    else if (L.row_block == 512) hipLaunchKernelGGL((k_list_row<DT, 512, 1, NT>), rows, dim3(512), 0, st, P, L);
+    else if (L.sample == 1) hipLaunchKernelGGL((k_list_row<DT, 256, 4, NT>), rows, dim3(256), 0, st, P, L);
+    else hipLaunchKernelGGL((k_list_row<DT, 256, 2, NT>), rows, dim3(256), 0, st, P, L);
+}
 template <int DT>
 static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStream_t st, void* const* events) {
     mark(events, 0, st);
@@ -1575,15 +1701,18 @@ static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStrea
         return hipGetLastError() == hipSuccess ? RTOPK_OK : RTOPK_ERR_HIP;
     }
     if (L.row_block != 0) {
-        if (L.row_block == 1024 && L.sample == 2) hipLaunchKernelGGL((k_list_row<DT, 1024, 2>), rows, dim3(1024), 0, st, P, L);
-        else if (L.row_block == 1024) hipLaunchKernelGGL((k_list_row<DT, 1024, 1>), rows, dim3(1024), 0, st, P, L);
-        else if (L.row_block == 512 && L.sample == 2) hipLaunchKernelGGL((k_list_row<DT, 512, 4>), rows, dim3(512), 0, st, P, L);
-        else if (L.row_block == 512 && L.sample == 1) hipLaunchKernelGGL((k_list_row<DT, 512, 2>), rows, dim3(512), 0, st, P, L);
-        else if (L.row_block == 512) hipLaunchKernelGGL((k_list_row<DT, 512, 1>), rows, dim3(512), 0, st, P, L);
-        else if (L.sample == 2) hipLaunchKernelGGL((k_list_row<DT, 256, 8>), rows, dim3(256), 0, st, P, L);
-        else if (L.sample == 1) hipLaunchKernelGGL((k_list_row<DT, 256, 4>), rows, dim3(256), 0, st, P, L);
-        else hipLaunchKernelGGL((k_list_row<DT, 256, 2>), rows, dim3(256), 0, st, P, L);
+        if (L.stream) launch_list_row<DT, true>(P, L, st);
+        else launch_list_row<DT, false>(P, L, st);
         hipLaunchKernelGGL((k_list_redo<DT>), dim3(redo), dim3(kListBucketBlock), 0, st, P, L);
+        mark(events, 4, st);
+        return hipGetLastError() == hipSuccess ? RTOPK_OK : RTOPK_ERR_HIP;
+    }
+    if (L.seg_stride != 0) {
+        hipLaunchKernelGGL((k_list_part<DT>), dim3((unsigned)P.batch * (unsigned)L.G), dim3(kPartBlock), 0, st, P, L);
+        mark(events, 2, st);
+        mark(events, 3, st);
+        if (L.finish == 256) hipLaunchKernelGGL((k_list_finish<DT, 256>), rows, dim3(256), 0, st, P, L);
+        else hipLaunchKernelGGL((k_list_finish<DT, 1024>), rows, dim3(1024), 0, st, P, L);
         mark(events, 4, st);
         return hipGetLastError() == hipSuccess ? RTOPK_OK : RTOPK_ERR_HIP;
     }
@@ -1593,7 +1722,7 @@ static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStrea
         default: hipLaunchKernelGGL((k_list_bound<DT, 1024, DT == RTOPK_F32 ? 16 : 8>), rows, dim3(1024), 0, st, P, L); break;
     }
     mark(events, 2, st);
-    const bool nt = (P.flags & kInternalStream) != 0, is_long = L.nb != 0;
+    const bool nt = L.stream != 0, is_long = L.nb != 0;
     const dim3 grid((unsigned)P.batch * (unsigned)L.G), block(is_long ? kLongBlock : kGridBlock);
     if (is_long && nt) hipLaunchKernelGGL((k_list_sweep<DT, true, true>), grid, block, 0, st, P, L);
     else if (is_long) hipLaunchKernelGGL((k_list_sweep<DT, false, true>), grid, block, 0, st, P, L);
@@ -1606,7 +1735,6 @@ static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStrea
     } else {
         const dim3 g((unsigned)P.batch * (1u + (unsigned)L.ties));
         if (L.finish == 256) hipLaunchKernelGGL((k_list_finish<DT, 256>), g, dim3(256), 0, st, P, L);
-        else if (L.finish == 512) hipLaunchKernelGGL((k_list_finish<DT, 512>), g, dim3(512), 0, st, P, L);
         else hipLaunchKernelGGL((k_list_finish<DT, 1024>), g, dim3(1024), 0, st, P, L);
     }
     hipLaunchKernelGGL((k_list_redo<DT>), dim3(redo), dim3(kListBucketBlock), 0, st, P, L);
