@@ -221,12 +221,18 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     memset(L, 0, sizeof(*L));
     if (tn && (tn->digit_bits || tn->path || tn->wgs_per_row || tn->small_threshold || tn->prefilter)) return false;
     const int eb = elem_bytes(dt), E = 16 / eb;
-    // few rows, small k: stretches of 32 KB, each listing its best k
+    // Few rows above 128 KB, k of at most 64: stretches of 32 KB, each listing its best k.  us, rows held whole / in stretches:
+    // 16 rows of 2^17 bf16 keys, k = 50, 23.8 / 15.2, 96 rows 27.3 / 21.1, one fp32 row of 2^16, k = 10, 14.0 / 11.9.  With a
+    // large k the stretches' lists are most of the work (16 rows of 2^16 fp32 keys, k = 300, 16.7 / 20.2; 96 rows of 2^17
+    // bf16 keys 28.7 / 30.6), and a short row is held by 256 or 512 threads, in one launch (16 fp32 rows of 20000, k = 10, 11.5 / 12.5;
+    // 48 bf16 rows of 50257, k = 50, 18.9 / 21.2).  Rows off the 16-byte grid have stretches with lanes that are partly empty and
+    // bound less: 16 fp32 rows of 50000, k = 32, 15.0 / 12.8, but of 50257 16.1 / 18.6; 16-bit keys have more to a lane and win
+    // up to k = 50 (48 bf16 rows of 100003 27.2 / 23.3; a single one, k = 64, 22.2 / 23.4).
     {
         const int64_t part = (int64_t)kListPartBlock * kListPartVecs * 16, G = (n * eb + 16 + part - 1) / part;
         const int64_t stride = k * 2 + 64;
-        if (n * eb > (64 << 10) && batch <= 256 && batch * G <= 1024 && G * stride <= 8192 && G * stride <= n / 2 &&
-            stride <= 8 * kListPartBlock) {
+        const bool whole = !ragged && n % E == 0;
+        if (k <= (whole ? 64 : eb == 2 ? 48 : 0) && n * eb > (128 << 10) && batch * G <= 1024 && G * stride <= 8192) {
             L->G = (int)G;
             L->seg_stride = (u32)stride;
             L->finish = G * stride <= 2048 ? 256 : 1024;

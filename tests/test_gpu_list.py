@@ -95,18 +95,19 @@ def test_ties_specials_and_crowds(dtype, n):
 
 
 def test_rows_shared_out_in_held_stretches():
-    # few rows, small k: stretches of 32 KB; rows that end just before, at and after a stretch, crowds in some stretches only
+    # few rows above 128 KB, k up to 64: stretches of 32 KB; rows that end just before, at and after a stretch, crowds in some
+    # stretches only; on both sides of the rule's lines
     for dtype, per in ((F32, 8192), (F16, 16384), (BF16, 16384)):
-        for n in (2 * per + 1, 3 * per - 7, 3 * per, 3 * per + 1, 3 * per + 9, 8 * per + 5):
+        for n in (2 * per + 1, 4 * per, 4 * per + 8, 5 * per - 7, 5 * per, 5 * per + 1, 8 * per + 8):
             for batch in (1, 5):
                 x = W.normal(batch * n, seed=n, sigma=3.0)
                 y = x.copy()
                 y[n // 3: n // 3 + per + 100] = 7.0       # one value over more than a stretch
                 z = np.where(W.uniform01(batch * n, 2) < 0.8, np.float32(np.nan), x).astype(np.float32)
-                for k in (1, 50, 128, 129, 400):
+                for k in (1, 48, 50, 64, 65, 400):
                     _check("stretches", x, dtype, k, largest=k != 50, batch=batch)
-                    _check("stretches, flat", y, dtype, k, largest=k != 128, batch=batch, sorted=k != 1)
-                    _check("stretches, NaN", z, dtype, k, largest=k != 129, batch=batch)
+                    _check("stretches, flat", y, dtype, k, largest=k != 64, batch=batch, sorted=k != 1)
+                    _check("stretches, NaN", z, dtype, k, largest=k != 65, batch=batch)
 
 
 def test_batches_and_odd_rows():
