@@ -94,6 +94,22 @@ def test_ties_specials_and_crowds(dtype, n):
                 _check(name, x, dtype, k, largest)
 
 
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+@pytest.mark.parametrize("value", [1.5, -1.5, 0.0, -0.0, 2.0 ** -24, np.inf, -np.inf, np.nan])
+def test_crowd_of_one_value(dtype, value):
+    # the k-th best is one value that most of the row holds: compared as a number where equal numbers have one key (the smallest
+    # fp16 denormal among them), by key for the zeros and NaNs; NaNs and the other zero beside it; short tiles at both ends
+    n = 300007
+    u, x = W.uniform01(n, 31), W.normal(n, 32)
+    y = np.where(u < 0.9, np.float32(value), x).astype(np.float32)
+    y[u > 0.9995] = np.nan
+    y[(u > 0.9990) & (u <= 0.9995)] = -0.0 if value == 0.0 and not np.signbit(value) else 0.0
+    for largest in (True, False):
+        # (beyond what is better than the crowd on either side)
+        for k in (20, 33000, 40000):
+            _check("crowd of %r" % value, y, dtype, k, largest=largest)
+
+
 def test_rows_shared_out_in_held_stretches():
     # few rows above 128 KB, k up to 64: stretches of 32 KB; rows that end just before, at and after a stretch, crowds in some
     # stretches only; on both sides of the rule's lines
