@@ -177,8 +177,8 @@ rtopk_status rtopk_select_ragged(const void* keys, const int64_t* row_offsets, c
  *
  * Limits: rtopk_workspace_bytes(batch, n, k, dt, flags) must not exceed RTOPK_STATIC_SCRATCH_BYTES --
  * otherwise RTOPK_ERR_STATIC_SCRATCH is returned and nothing is launched.  The workspace holds two candidate
- * arrays of 8 bytes per key, so that admits inputs of up to about 4 million keys in total (batch * n), of any
- * shape: 32 rows of 2^17 logits, one row of 2^22 keys.
+ * arrays of 8 bytes per key and per-workgroup records, so that admits inputs of up to about 2.9 million keys in
+ * total (batch * n): 16 rows of 2^17 logits, one row of 2^21 keys.
  * All calls on one GPU share that GPU's buffer: two calls that may overlap in time on the same GPU (different
  * streams, different host threads) race; the caller orders them.  The buffer keeps the previous call's
  * contents; every call clears what it needs cleared itself.
@@ -220,7 +220,8 @@ typedef struct {
     uint32_t error;            /* 0, or a bit set if the device saw an impossible state              */
     uint32_t redo;             /* 1: the one-sweep row kernel left this row to the two-sweep kernel
                                   (which clears the record, redo_why excepted, when it takes the row
-                                  over)                                                              */
+                                  over).  List kernels, bits: 1 the list was no use and the row was
+                                  selected anew, 2 the list, 4 some of its buckets did not fit LDS   */
     uint32_t redo_why;         /* diagnostic; non-zero: the one-sweep kernel handed the row over.
                                   1 inf/NaN in the part counted first, 2 that part shorter than k,
                                   3 bin edge not a number, 5 list full, 6 too many candidates in the

@@ -217,7 +217,8 @@ static Layout make_layout(int64_t batch, int64_t n, const Config& c) {
 
 // Does the call go through lists (rtopk_list.inl), and how?  The automatic choice only: a call with tuning knobs gets the
 // kernels it names.
-static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, const rtopk_tuning* tn, bool ragged, ListPlan* L) {
+static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, const rtopk_tuning* tn, bool ragged, bool sorted,
+                           ListPlan* L) {
     memset(L, 0, sizeof(*L));
     if (tn && (tn->digit_bits || tn->path || tn->wgs_per_row || tn->small_threshold || tn->prefilter)) return false;
     const int eb = elem_bytes(dt), E = 16 / eb;
@@ -258,6 +259,10 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     if (n * eb < 32768) return false;
     // the list is to stay below half the row (in a ragged batch: half the longest row, for every row)
     if (k * 5 > (ragged ? n : n * 2)) return false;
+    // A list's 4096 bins hold more than a workgroup puts in order once k is in the millions.  Digit passes / list, us, 2^28 fp32
+    // keys: sorted, k = 2^22, 1120 / 317, 2^23 1479 / 1370, 2^24 2460 / 2362; unsorted, k = 2^21, 456 / 356, 2^22 442 / 487,
+    // 2^24 586 / 2694.
+    if (k > ((int64_t)1 << (sorted ? 22 : 21))) return false;
     const int64_t vecs = n * eb / 16;
     L->sample = vecs >= (1 << 20) ? 4 : vecs >= (1 << 16) ? 3 : vecs >= (1 << 14) ? 2 : vecs >= (1 << 12) || batch <= 256 ? 1 : 0;
     // one workgroup per row: rows of up to 256 KB, in large batches up to 1 MB
@@ -283,6 +288,11 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     expect();
     if (listed * 1.1 > 0.5 * (double)n) return false;
     const bool is_long = L->row_block == 0 && room > 8192.0;
+    // A long list is put in order whether that was asked for or not.  Unsorted output pays for it where keys lie in order
+    // along the row and crowd the bins: a ramp with infinities, us, digit passes / list: 2^22 fp32 keys, k = 2^13, 75 / 105,
+    // k = 2^20, 77 / 159; 2^26 fp16 keys, k = 2^16, 162 / 234, k = 2^20, 154 / 388.  Long fp32 rows gain more than they can
+    // lose: 2^26 keys, k = 2^16, uniform 149 / 104, the ramp 154 / 162.
+    if (is_long && !sorted && (eb != 4 || n < ((int64_t)1 << 25))) return false;
     // one workgroup of 1024 threads per compute unit where the list's histogram is counted, else four of 512 (three for 16-bit keys)
     const int64_t tile_elems = (int64_t)(is_long ? 1024 : kHostGridBlock) * 64 / eb;
     const int64_t ntiles = (n + E - 1 + tile_elems - 1) / tile_elems;
@@ -448,7 +458,7 @@ static rtopk_status select_impl(const void* keys, const int64_t* row_offsets, co
 
     hipStream_t st = (hipStream_t)hip_stream;
     ListPlan list;
-    const bool by_list = make_list_plan(batch, n, k, dt, tuning, row_offsets != nullptr, &list);
+    const bool by_list = make_list_plan(batch, n, k, dt, tuning, row_offsets != nullptr, (flags & RTOPK_FLAG_SORTED) != 0, &list);
     (void)hipGetLastError();  // an error left by earlier HIP calls of the process is not this call's
     const bool scaled = (flags & RTOPK_FLAG_SCALING) && dt == RTOPK_F32;
     if (by_list) {

@@ -49,11 +49,12 @@ struct ListRow {
     u32 T;         // key, direction applied
     u32 exact;     // 1: compare keys; 0: compare the element with the number t
     float t;
-    u64 lo;        // long lists: bin of an entry = min((entry - lo) >> sh, kListBins - 1)
+    u64 lo;        // long lists: see list_bin
     u32 sh;
     u32 total;     // entries (long lists, and short ones that do not fit one workgroup's LDS)
     u32 end;       // long lists: entries in bins that begin below rank k
-    u32 pad;
+    u32 finite;    // bins for entries below `special`
+    u64 special;   // the first entry that is an infinity or NaN on the better side; ~0: bins are not set aside for those
 };
 static_assert(sizeof(ListRow) % 8 == 0, "read by words");
 // Bits of rtopk_row_trace::redo that the list kernels set and k_list_redo looks at: the list is no use; it was too long to
@@ -81,6 +82,18 @@ __device__ __forceinline__ ListRow list_row_scalar(const ListRow* p) {
     for (int i = 0; i < kWords; ++i) w[i] = __builtin_amdgcn_readfirstlane(((const u32*)p)[i]);
     __builtin_memcpy(&r, w, sizeof(r));
     return r;
+}
+
+// Bin of an entry of a long list, in the entries' order.  The bins divide the range of what the sample showed evenly; infinities
+// would stretch that range until all numbers shared a bin or two, which one workgroup each then puts in order.  Where the
+// sample holds any, the last quarter of the bins divides the infinities by position.  us per call, one range / two: 2^26
+// fp32 keys, a ramp with an infinity in every 2048, k = 2^16, sorted, 927 / 133, k = 2^20, 2909 / 174.
+constexpr u32 kListFinite = 3072;
+__device__ __forceinline__ u32 list_bin(u64 e, u64 lo, u32 sh, u64 special, u32 finite, u32 ib) {
+    const bool sp = e >= special;
+    const u64 b = (e - (sp ? special : lo)) >> (sp ? (ib > 10u ? ib - 10u : 0u) : sh);
+    const u32 room = sp ? kListBins - finite : finite;
+    return (sp ? finite : 0u) + (b < room ? (u32)b : room - 1u);
 }
 
 // Per-row working memory beside the list: the upper half of the row's first candidate array (the list proper is at
@@ -348,6 +361,8 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
             lr->lo = 0;
             const u32 top = ent.ib + (DT == RTOPK_F32 ? 32u : 16u);
             lr->sh = top > 12u ? top - 12u : 0u;
+            lr->finite = kListBins;
+            lr->special = ~0ull;
         }
         return;
     }
@@ -416,6 +431,26 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
             }
         block_sum2<B>(eq, crowd, red);
     }
+    // the best finite key, where bins are set aside for infinities
+    constexpr u32 kSpecial = DT == RTOPK_F16 ? 0xfc000000u : 0xff800000u;  // (either direction)
+    const bool apart = L.nb != 0u && top >= kSpecial;
+    if (apart) {
+        u32 f = 0;
+#pragma unroll
+        for (int u = 0; u < V; ++u)
+#pragma unroll
+            for (int j = 0; j < E; ++j) {
+                const u32 k = key_in_vector<DT>(q[u], j);
+                f = k < kSpecial && k > f ? k : f;
+            }
+        f = wave_reduce(f, MaxOf());
+        __syncthreads();
+        if (lane == 63u) red[wave] = f;
+        __syncthreads();
+        top = red[0];
+#pragma unroll
+        for (int w = 1; w < B / 64; ++w) top = top > red[w] ? top : red[w];
+    }
     const u64 eq_row = (u64)eq * rs.n / kElems;
     const bool tied = eq_row > (u64)kListTies && eq_row > (u64)rs.k;
     if (tied) {
@@ -441,7 +476,11 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
         const u64 range = hi > lo ? hi - lo : 1u;
         const u32 width = 64u - (u32)__builtin_clzll(range);
         lr->lo = lo;
-        lr->sh = width > 12u ? width - 12u : 0u;
+        u32 sh = width > 12u ? width - 12u : 0u;
+        if (apart && (range >> sh) >= kListFinite) ++sh;
+        lr->sh = sh;
+        lr->finite = apart ? kListFinite : kListBins;
+        lr->special = apart ? (u64)(kSpecial >> ent.kshift) << ent.ib : ~0ull;
         st->pre_elems = kElems;
         // (crowded keys: what a first digit could tell apart is less than an eighth of the row)
         const bool crowded = (u64)crowd * 8u > (u64)kElems;
@@ -481,7 +520,7 @@ __device__ __forceinline__ u32 list_segment(const Source& src, u32 wg, u32 G, u3
 // (Expanded in place: around a call the compiler keeps the tiles in flight in memory.)
 template <int DT, bool LONG>
 __device__ __forceinline__ void list_flush(u64* seg, Lds<u64>* buf, Lds<u32>* run, u32 fill, Lds<u32>* hist, const ListEntry& c,
-                                           u64 lo, u32 sh, u32 lane) {
+                                           const ListRow& lr, u32 lane) {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     u32 base = 0;
     if (lane == 0) base = __hip_atomic_fetch_add(run, fill, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -491,8 +530,8 @@ __device__ __forceinline__ void list_flush(u64* seg, Lds<u64>* buf, Lds<u32>* ru
         const u64 e = c.of(KeyOf<DT>::key((u32)v) ^ c.dirmask, (u32)(v >> 32));
         ((Glb<u64>*)seg)[base + i] = e;
         if (LONG) {
-            const u64 b = (e - lo) >> sh;
-            __hip_atomic_fetch_add(hist + (b < kListBins ? (u32)b : kListBins - 1u), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_fetch_add(hist + list_bin(e, lr.lo, lr.sh, lr.special, lr.finite, c.ib), 1u, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
         }
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -616,7 +655,7 @@ __device__ __forceinline__ void sweep_row(const Source& src, u32 wg, u32 G, cons
 // a full stage to the workgroup's segment.
 // NT: the input is far larger than the last-level cache.  LONG: the list's histogram is counted as it is written; then one
 // workgroup of 1024 threads has a compute unit, so that there are no more than 256 histograms to add up (512
-// workgroups of 512: adding up took longer than it saved; see the table).
+// workgroups of 512: adding up took longer than it saved).
 template <int DT, bool NT, bool LONG>
 __global__ void __launch_bounds__(LONG ? kLongBlock : kGridBlock, LONG ? 4 : DT == RTOPK_F32 ? 8 : 6) k_list_sweep(Params P, ListPlan L) {
     constexpr int B = LONG ? kLongBlock : kGridBlock, ST = LONG ? kListStageLong : kListStage;
@@ -642,7 +681,7 @@ __global__ void __launch_bounds__(LONG ? kLongBlock : kGridBlock, LONG ? 4 : DT 
     uint2* buf = stage[wave];
     u32 fill = 0;
     auto flush = [&]() __attribute__((always_inline)) {
-        list_flush<DT, LONG>(seg, lds_words(buf), lds_word(&run), fill, lds_word(hist), ent, lr.lo, lr.sh, lane);
+        list_flush<DT, LONG>(seg, lds_words(buf), lds_word(&run), fill, lds_word(hist), ent, lr, lane);
         fill = 0;
     };
     sweep_row<DT>(src, wg, G, lr, list_part<u32>(P, row, L.tile_off), P.dirmask, [&](const typename Source::Tile& cur, u32 m) __attribute__((always_inline)) {
@@ -1427,8 +1466,8 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     if (mode == kListSkip) return;
     const RowShape rs = row_shape_scalar<DT>(P, row);
     rtopk_row_trace* st = row_state(P, row);
-    const u64 lo = lr->lo;
-    const u32 sh = lr->sh;
+    const u64 lo = lr->lo, special = lr->special;
+    const u32 sh = lr->sh, finite = lr->finite, ib = list_entry<DT>(P).ib;
     ListSource<DT, true> src;
     src.init(rs);
     const u64* from = list_array(P, 1u, row) + list_segment(src, wg, G, src.ntiles());
@@ -1497,8 +1536,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
         __syncthreads();
     }
     auto bucket_of = [&](u64 e) __attribute__((always_inline)) {
-        const u64 b = (e - lo) >> sh;
-        const u32 r = start[b < kListBins ? (u32)b : kListBins - 1u];
+        const u32 r = start[list_bin(e, lo, sh, special, finite, ib)];
         return r < end ? r >> bs : 0xffffffffu;
     };
     // (what the registers hold of the segment is on its way before the ranks are known)
