@@ -51,12 +51,20 @@ struct ListRow {
     float t;
     u64 lo;        // long lists: see list_bin
     u32 sh;
-    u32 total;     // entries (long lists, and short ones that do not fit one workgroup's LDS)
-    u32 end;       // long lists: entries in bins that begin below rank k
     u32 finite;    // bins for entries below `special`
     u64 special;   // the first entry that is an infinity or NaN on the better side; ~0: bins are not set aside for those
 };
 static_assert(sizeof(ListRow) % 8 == 0, "read by words");
+// What became of a row's list.  A record of its own: the kernel that writes it has workgroups that still read the decision, and a
+// wave that found the decision changed would leave the others of its workgroup alone with sums it never wrote.
+struct ListDone {
+    u32 total;     // entries (long lists, and short ones that do not fit one workgroup's LDS)
+    u32 end;       // long lists: entries in bins that begin below rank k; short ones: the array that holds the list
+    u32 drop;      // long lists: 1: the list was no use, the buckets are not filled
+    u32 pad;
+};
+constexpr u32 kListDoneOff = 128;
+static_assert(sizeof(ListRow) <= kListDoneOff && kListDoneOff + sizeof(ListDone) <= 256, "both lie before the plan's first offset");
 // Bits of rtopk_row_trace::redo that the list kernels set and k_list_redo looks at: the list is no use; it was too long to
 // put in order in LDS (it is all in array `end`); so were some of its buckets.
 enum : u32 { kRedoRow = 1, kRedoList = 2, kRedoBuckets = 4 };
@@ -102,7 +110,10 @@ __device__ __forceinline__ char* list_meta(const Params& P, int row) {
     const uintptr_t a = (uintptr_t)(P.cand[0] + (size_t)row * P.cand_stride + (size_t)((P.n + 1) / 2));
     return (char*)((a + 255) & ~(uintptr_t)255);
 }
-__device__ __forceinline__ ListRow* list_row(const Params& P, int row) { return (ListRow*)list_meta(P, row); }
+// (written by k_list_bound and k_list_part, through list_row_out; constant for every kernel after them)
+__device__ __forceinline__ const ListRow* list_row(const Params& P, int row) { return (const ListRow*)list_meta(P, row); }
+__device__ __forceinline__ ListRow* list_row_out(const Params& P, int row) { return (ListRow*)list_meta(P, row); }
+__device__ __forceinline__ ListDone* list_done(const Params& P, int row) { return (ListDone*)(list_meta(P, row) + kListDoneOff); }
 template <class T>
 __device__ __forceinline__ T* list_part(const Params& P, int row, u32 off) { return (T*)(list_meta(P, row) + off); }
 __device__ __forceinline__ u64* list_array(const Params& P, u32 which, int row) {
@@ -497,7 +508,7 @@ __global__ void __launch_bounds__(B) k_list_bound(Params P, ListPlan L) {
     const RowShape rs = row_shape_scalar<DT>(P, row);
     ListSource<DT, false> src;  // (the smaller of the two sweeps' tiles: the larger number of them)
     src.init(rs);
-    bound_of_row<DT, B, V>(P, L, row, rs, row_state(P, row), list_row(P, row), list_part<u32>(P, row, L.tile_off), src.ntiles(), sm, red);
+    bound_of_row<DT, B, V>(P, L, row, rs, row_state(P, row), list_row_out(P, row), list_part<u32>(P, row, L.tile_off), src.ntiles(), sm, red);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1081,8 +1092,8 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     } else {
         for (u32 i = tid; i < total; i += B) dst[i] = entry(i);
         if (tid == 0) {
-            list_row(P, row)->total = total;
-            list_row(P, row)->end = 0u;
+            list_done(P, row)->total = total;
+            list_done(P, row)->end = 0u;
             atomicOr(&st->redo, kRedoList);
         }
     }
@@ -1356,7 +1367,7 @@ __global__ void __launch_bounds__(kPartBlock, 4) k_list_part(Params P, ListPlan 
     auto first = [&]() __attribute__((always_inline)) {
         if (g == 0u) {
             init_row<DT>(P, row, st, rs);
-            if (tid == 0) list_row(P, row)->mode = rs.k == 0u ? kListSkip : kListPlain;
+            if (tid == 0) list_row_out(P, row)->mode = rs.k == 0u ? kListSkip : kListPlain;
         }
     };
     if (rs.k == 0u || p0 >= nvec) {
@@ -1424,8 +1435,8 @@ __global__ void __launch_bounds__(B, 4) k_list_row(Params P, ListPlan L) {
     if (total > kCap) {
         for (u32 i = tid; i < kCap; i += B) list[i] = sm.ord.buf[i];
         if (tid == 0) {
-            list_row(P, row)->total = total;
-            list_row(P, row)->end = 1u;
+            list_done(P, row)->total = total;
+            list_done(P, row)->end = 1u;
             atomicOr(&st->redo, kRedoList);
         }
     } else if (total != 0u && total <= 8u * OB && b.mode != kListTied) {
@@ -1461,7 +1472,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     const u32 G = (u32)L.G, tid = threadIdx.x;
     const int row = (int)(blockIdx.x / G);
     const u32 wg = blockIdx.x % G;
-    ListRow* lr = list_row(P, row);
+    const ListRow* lr = list_row(P, row);
     const u32 mode = lr->mode;
     if (mode == kListSkip) return;
     const RowShape rs = row_shape_scalar<DT>(P, row);
@@ -1502,20 +1513,17 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     total = start[0] + gh[0];
     const bool few = total < rs.k;
     const u32 end = few ? total : s_end;
-    if ((mode == kListPlain && few) || total > (u32)((P.n + 1) / 2)) {
+    const bool drop = (mode == kListPlain && few) || total > (u32)((P.n + 1) / 2);
+    if (wg == 0 && tid == 0) *list_done(P, row) = ListDone{total, end, drop ? 1u : 0u, 0u};
+    if (drop) {
         if (wg == 0 && tid == 0) {
-            lr->mode = kListSkip;
             st->redo_why = few ? 8u : 5u;
             atomicOr(&st->redo, kRedoRow);
         }
         return;
     }
     if (wg == 0) {
-        if (tid == 0) {
-            lr->total = total;
-            lr->end = end;
-            list_record(st, rs, total, 5u);
-        }
+        if (tid == 0) list_record(st, rs, total, 5u);
         // the buckets' first ranks and sizes
         u32* first = list_part<u32>(P, row, L.first_off);
         for (u32 j = tid; j < nb; j += B) place[j] = 0xffffffffu;
@@ -1595,10 +1603,12 @@ __global__ void __launch_bounds__(kListBucketBlock) k_list_buckets(Params P, Lis
     const ListRow* lr = list_row(P, row);
     const u32 mode = lr->mode;
     if (mode == kListSkip) return;
+    const ListDone done = *list_done(P, row);
+    if (done.drop != 0u) return;
     const RowShape rs = row_shape_scalar<DT>(P, row);
     if (j >= L.nb) {
-        if (mode != kListTied || lr->total >= rs.k) return;
-        if (!ties_of_row<DT, B, ListSource<DT, true>>(P, list_part<u32>(P, row, L.tile_off), row, rs, lr->total, lr->T, j - L.nb,
+        if (mode != kListTied || done.total >= rs.k) return;
+        if (!ties_of_row<DT, B, ListSource<DT, true>>(P, list_part<u32>(P, row, L.tile_off), row, rs, done.total, lr->T, j - L.nb,
                                                       (u32)L.ties, sm.hist, sm.wsum) && j == L.nb && tid == 0) {
             rtopk_row_trace* st = row_state(P, row);
             st->redo_why = 8u;
@@ -1720,8 +1730,8 @@ __global__ void __launch_bounds__(kListBucketBlock) k_list_redo(Params P, ListPl
                     redo_row<DT, B>(P, L, row, rs, st, sm.rank, &run, sm.ord.hist, sm.ord.wsum, &count);
                     which = 1;
                 } else if (mine) {
-                    count = list_row(P, row)->total;
-                    which = list_row(P, row)->end;
+                    count = list_done(P, row)->total;
+                    which = list_done(P, row)->end;
                 }
                 __syncthreads();
                 if (count != 0u) order_entries<DT, B>(P, row, rs, sm.ord, at, count, which, stack);

@@ -188,3 +188,19 @@ def test_rows_whose_sample_misleads_are_done_again(k):
         x[pos] = 100.0 + W.uniform01(len(pos), 32)
         for srt in (False, True):
             _check("misled", x if largest else -x, F32, k, largest, srt, why=8)
+
+
+def test_misled_rows_beside_others():
+    # long lists, several workgroups per row, and every second row's list is no use: its buckets stay empty, its record says so,
+    # and the rows beside it are not touched
+    n, batch, k = 400000, 6, 9000
+    pos = _sampled(n, 4096, 4)
+    x = W.normal(batch * n, 33).reshape(batch, n)
+    for r in range(0, batch, 2):
+        x[r, pos] = 100.0 + W.uniform01(len(pos), 34 + r)
+    for largest in (True, False):
+        bits = (x if largest else -x).view(np.uint32)
+        gv, gi, tr, _ = gpu_topk(to_device(bits, F32), F32, k, largest, sorted=True)
+        wv, wi = oracle.topk(bits, F32, k, largest)
+        assert np.array_equal(gi, wi) and np.array_equal(gv, wv)
+        assert [t.redo & 1 for t in tr] == [1, 0] * (batch // 2) and all(t.error == 0 for t in tr)

@@ -160,3 +160,14 @@ def test_workload_shapes_and_structure():
     assert 2.5 < logits.std() < 3.6
     c4 = W.config4(n=1 << 16)
     assert c4.min() >= -1e6 and c4.max() <= 1e6 and abs(c4.mean()) < 2e4
+
+
+def test_a_rows_decision_is_written_before_the_kernels_that_share_it():
+    # k_list_scatter and the kernels after it are run by many workgroups of a row, each of whose waves reads the row's decision
+    # before any barrier: none of them may write it (a wave that sees the change leaves its workgroup's sums unwritten)
+    text = open(os.path.join(ROOT, "paper_2501_14336_amd", "csrc", "rtopk_list.inl")).read()
+    kernels = re.split(r"(?=template <int DT[^>]*>\n(?:__global__|__device__|static))", text)
+    writers = [re.search(r"\b(k_list_\w+|bound_of_row)\(", k).group(1) for k in kernels
+               if re.search(r"\b(k_list_\w+|bound_of_row)\(", k) and
+               (re.search(r"\blr->\w+ = ", k) or re.search(r"list_row(_out)?\(P, row\)->\w+ = ", k))]
+    assert sorted(writers) == ["bound_of_row", "k_list_part"], writers
