@@ -312,6 +312,8 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     if (n > 16384 && ties < 1) ties = 1;
     if (ties > ntiles) ties = ntiles;
     L->ties = (int)ties;
+    L->redo_wgs = L->row_block != 0 || batch >= 256 ? 1 : (int)(256 / batch);
+    if (!is_long && L->redo_wgs > 4) L->redo_wgs = 4;  // (a short list's k ranks are at most so many parts)
     if (batch * ((int64_t)L->nb + 1 + ties) >= ((int64_t)1 << 22) || batch * G >= ((int64_t)1 << 22)) return false;  // grid sizes
     u64 off = 256;
     auto take = [&](u64 bytes) { const u64 at = off; off = align_up(off + bytes, 16); return (u32)at; };

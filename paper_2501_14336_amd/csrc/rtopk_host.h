@@ -36,6 +36,7 @@ struct ListPlan {
     int stream;       // the input is too large for the caches to keep: read past them
     int finish;       // short lists: threads of the workgroup that puts a row's list in order
     int ties;         // workgroups per row that fetch elements equal to the bound, where those are very many
+    int redo_wgs;     // workgroups per row of the kernel that does what the others leave over
     u32 seg_stride;   // the row's stretches are held by G workgroups that list at most this many each (0: the row is swept)
     u32 nb;           // long lists: buckets per row (0: short lists)
     u32 bucket_shift; // ... of 2^bucket_shift ranks

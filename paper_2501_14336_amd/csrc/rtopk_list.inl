@@ -726,17 +726,66 @@ __global__ void __launch_bounds__(LONG ? kLongBlock : kGridBlock, LONG ? 4 : DT 
 
 // A workgroup of B threads puts up to 8 B entries in order in LDS: 4 B bins that divide the range from the best entry to
 // the worst evenly, positions within a bin by arrival, and then every entry's rank among its bin's.  Entries are
-// distinct and bins hold one or two of them unless the keys are very uneven; a bin of more than kOrderCrowd sends the whole lot
-// through a bitonic network instead.
-constexpr u32 kOrderCrowd = 128;
+// distinct and bins hold one or two of them unless the keys are very uneven.  If a bin that matters has more than kOrderCrowd,
+// over the number of entries per thread (equal keys; one key far from the others), the bins are laid anew between 255 of the entries themselves: equal keys then
+// differ by their positions, and no distance between keys matters.  Only entries that defeat that as well (more than
+// kSplitCrowd in one bin) go through a bitonic network.
+constexpr u32 kOrderCrowd = 256, kSplitCrowd = 256;
 template <int B>
 struct OrderShared {
     u64 buf[8 * B];
-    u32 hist[4 * B + 1];
+    u32 hist[4 * B + 2];
     u32 wsum[B / 64];
     u64 red[2 * (B / 64)];
     u32 flag, sp;
 };
+
+// Bins between splitters: edge[0] (above every entry) > edge[1] > ... > edge[N] (at or below every entry), N intervals
+// of 2^Q bins each, which divide it evenly; bin 0 is the best.
+template <int B>
+struct SplitBins {
+    static constexpr int N = B < 256 ? B : 256;  // intervals
+    static constexpr u32 Q = 31u - (u32)__builtin_clz(4 * B / N);
+    __device__ static __forceinline__ u32 shift(u64 upper, u64 lower) {
+        const u64 span = upper - lower - (upper > lower ? 1u : 0u);
+        const u32 width = span ? 64u - (u32)__builtin_clzll(span) : 0u;
+        return width > Q ? width - Q : 0u;
+    }
+    __device__ static __forceinline__ u32 bin(const u64* edge, u64 e) {
+        u32 p = 0;
+#pragma unroll
+        for (u32 step = N / 2; step > 0; step /= 2) p += edge[p + step] > e ? step : 0u;
+        const u64 upper = edge[p];
+        return (p << Q) | (u32)((upper - 1u - e) >> shift(upper, edge[p + 1u]));
+    }
+    // The least number that belongs to bin b.
+    __device__ static __forceinline__ u64 floor_of(const u64* edge, u32 b) {
+        const u64 upper = edge[b >> Q], lower = edge[(b >> Q) + 1u];
+        const u64 down = (u64)((b & ((1u << Q) - 1u)) + 1u) << shift(upper, lower);
+        return upper - lower > down ? upper - down : lower;
+    }
+};
+// Edges from N - 1 entries, one per thread from thread 1 on (in any order), and the two ends.  Contains three barriers; edge may be
+// written and read again after it.
+template <int B>
+__device__ __forceinline__ void make_edges(u64* edge, u64 mine, u64 best, u64 worst) {
+    constexpr u32 N = SplitBins<B>::N;
+    const u32 tid = threadIdx.x;
+    if (tid >= 1u && tid < N) edge[tid] = mine;
+    __syncthreads();
+    u32 r = 1;
+    if (tid >= 1u && tid < N) {
+#pragma unroll 8
+        for (u32 i = 1; i < N; ++i) r += (edge[i] > mine || (edge[i] == mine && i < tid)) ? 1u : 0u;
+    }
+    __syncthreads();
+    if (tid >= 1u && tid < N) edge[r] = mine;
+    if (tid == 0) {
+        edge[0] = best + 1u;
+        edge[N] = worst;
+    }
+    __syncthreads();
+}
 
 template <int B>
 __device__ __forceinline__ void order_range(u64& mn, u64& mx, OrderShared<B>& sm) {
@@ -759,37 +808,54 @@ __device__ __forceinline__ u32 order_shift(u64 range) {
     const u32 width = range ? 64u - (u32)__builtin_clzll(range) : 0u;
     return width > kBits ? width - kBits : 0u;
 }
-// h[0 .. 4 B): counts -> exclusive prefix sums; the largest count, if a crowd, into sm.flag; into sm.sp the bin that holds
-// rank want - 1.  Two barriers.
+// h[0 .. 4 B): counts -> exclusive prefix sums; into sm.sp the bin that holds rank want - 1; into sm.flag a 1 if a bin whose
+// order matters (`sorted`: any up to that one; else that one alone) has more than `crowd`.  Two barriers.
 template <int B>
-__device__ __forceinline__ void order_scan(u32* h, u32 want, OrderShared<B>& sm) {
+__device__ __forceinline__ void order_scan(u32* h, u32 want, u32 crowd, bool sorted, OrderShared<B>& sm) {
     const u32 tid = threadIdx.x;
-    u32 c[4], s = 0, most = 0;
+    u32 c[4], s = 0;
+    bool most = false;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         c[i] = h[4 * tid + i];
         s += c[i];
-        most = most > c[i] ? most : c[i];
     }
     const u32 incl = block_inclusive_scan<B>(s, sm.wsum);
     u32 r = incl - s;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         h[4 * tid + i] = r;
-        if (r < want && r + c[i] >= want) sm.sp = 4 * tid + i;
+        const bool last = r < want && r + c[i] >= want;
+        if (last) sm.sp = 4 * tid + i;
+        most = most || (c[i] > crowd && (last || (sorted && r < want)));
         r += c[i];
     }
-    if (most > kOrderCrowd) atomicMax(&sm.flag, most);
+    if (most) sm.flag = 1u;
     __syncthreads();
 }
 
+// buf[0 .. want) to the row's output, from rank0 on.
+template <int DT, int B>
+__device__ __forceinline__ void order_output(const Params& P, int row, const RowShape& rs, const OrderShared<B>& sm, u32 want, u32 rank0,
+                                             const ListEntry& ent) {
+    char* out_v = (char*)P.out_values + (size_t)row * (size_t)P.k * KeyOf<DT>::kBytes;
+    long long* out_i = P.out_indices + (size_t)row * (size_t)P.k;
+    for (u32 i = threadIdx.x; i < want; i += B) {
+        const u64 v = sm.buf[i];
+        const u32 idx = ent.idx(v);
+        out_i[rank0 + i] = (long long)idx;
+        store_value<DT>(out_v, rank0 + i, raw_of_key<DT>(ent.key(v), idx, rs, P.dirmask));
+    }
+}
+
 // C entries, load(0) .. load(C - 1) (1 <= C <= 8 B), which are the row's ranks rank0 .. rank0 + C - 1: write those below
-// row_k to the output.  load() may read sm.buf.
+// row_k to the output, in order if the call asked for that.  load() may read sm.buf.
 template <int DT, int B, class Load>
 __device__ __forceinline__ void order_in_lds(const Params& P, int row, const RowShape& rs, OrderShared<B>& sm, u32 C, u32 rank0,
                                              Load&& load) {
     const u32 tid = threadIdx.x;
     const u32 want = rs.k - rank0 < C ? rs.k - rank0 : C;
+    const bool sorted = (P.flags & RTOPK_FLAG_SORTED) != 0u;
     const ListEntry ent = list_entry<DT>(P);
     u64 e[8], mn = ~0ull, mx = 0;
 #pragma unroll
@@ -815,27 +881,18 @@ __device__ __forceinline__ void order_in_lds(const Params& P, int row, const Row
     for (int j = 0; j < 8; ++j)
         if (tid + (u32)j * B < C) atomicAdd(&sm.hist[(u32)((mx - e[j]) >> sh) + 1u], 1u);  // (the bins' counts, one place up)
     __syncthreads();
-    order_scan<B>(sm.hist + 1, want, sm);
-    if (sm.flag == 0u) {
-        // hist[b + 1]: where bin b begins, and once its entries are in place, where it ends; hist[b] is then where it begins
-        const u32 last = sm.sp;  // (nothing beyond this bin is wanted)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const u32 bin = (u32)((mx - e[j]) >> sh);
-            if (tid + (u32)j * B < C && bin <= last) sm.buf[atomicAdd(&sm.hist[bin + 1u], 1u)] = e[j];
-            else e[j] = ~0ull;  // (not an entry: those have at most 63 bits)
-        }
-        __syncthreads();
+    order_scan<B>(sm.hist + 1, want, kOrderCrowd / ((C + (u32)B - 1u) / (u32)B), sorted, sm);
+    // entry j's rank, if it is wanted, among the entries of its bin, which are buf[from .. to); then every one to its place
+    auto rank_and_place = [&](auto&& from, auto&& to) __attribute__((always_inline)) {
         u32 rank[4];  // two to a word
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             u32 r = 0xffffu;
             if ((u32)j * B < C && e[j] != ~0ull) {
-                const u32 b = (u32)((mx - e[j]) >> sh);
-                const u32 s1 = sm.hist[b + 1u];
-                r = sm.hist[b];
+                const u32 s0 = from(j), s1 = to(j);
+                r = s0;
 #pragma unroll 1
-                for (u32 i = sm.hist[b]; i < s1; ++i) r += sm.buf[i] > e[j] ? 1u : 0u;
+                for (u32 i = s0; i < s1; ++i) r += sm.buf[i] > e[j] ? 1u : 0u;
             }
             rank[j / 2] = (j & 1) ? rank[j / 2] | r << 16 : r;
         }
@@ -845,6 +902,58 @@ __device__ __forceinline__ void order_in_lds(const Params& P, int row, const Row
             const u32 r = (j & 1) ? rank[j / 2] >> 16 : rank[j / 2] & 0xffffu;
             if (r < want) sm.buf[r] = e[j];
         }
+    };
+    if (sm.flag == 0u) {
+        // hist[b + 1]: where bin b begins, and once its entries are in place, where it ends; hist[b] is then where it begins
+        const u32 last = sm.sp;  // (nothing beyond this bin is wanted)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const u32 bin = (u32)((mx - e[j]) >> sh);
+            const bool is = tid + (u32)j * B < C && bin <= last;
+            if (is) sm.buf[atomicAdd(&sm.hist[bin + 1u], 1u)] = e[j];
+            if (!is || (!sorted && bin < last)) e[j] = ~0ull;  // (not an entry: those have at most 63 bits; nothing left to do with it)
+        }
+        __syncthreads();
+        rank_and_place([&](int j) { return sm.hist[(u32)((mx - e[j]) >> sh)]; }, [&](int j) { return sm.hist[(u32)((mx - e[j]) >> sh) + 1u]; });
+        __syncthreads();
+        order_output<DT, B>(P, row, rs, sm, want, rank0, ent);
+        return;
+    }
+    // crowded: bins between splitters, which are taken from the entries at equal distances
+    typedef SplitBins<B> Split;
+    __syncthreads();  // (everybody has seen the flag)
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if (tid + (u32)j * B < C) sm.buf[tid + (u32)j * B] = e[j];
+    for (u32 j = tid; j < 4u * B + 2u; j += B) sm.hist[j] = 0;
+    if (tid == 0) sm.flag = 0;
+    __syncthreads();
+    const u64 mine = tid < (u32)Split::N ? sm.buf[(u32)((u64)tid * C / (u32)Split::N)] : 0ull;
+    __syncthreads();
+    make_edges<B>(sm.buf, mine, mx, mn);
+    u32 at[8];  // bin, and which of its entries this one is
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        at[j] = 0;
+        if (tid + (u32)j * B < C) {
+            const u32 bin = Split::bin(sm.buf, e[j]);
+            at[j] = bin << 16 | atomicAdd(&sm.hist[bin], 1u);
+        }
+    }
+    __syncthreads();
+    order_scan<B>(sm.hist, want, kSplitCrowd, sorted, sm);
+    if (sm.flag == 0u) {
+        const u32 last = sm.sp;
+        if (tid == 0) sm.hist[4 * B] = C;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const u32 bin = at[j] >> 16;
+            const bool is = tid + (u32)j * B < C && bin <= last;
+            if (is) sm.buf[sm.hist[bin] + (at[j] & 0xffffu)] = e[j];
+            if (!is || (!sorted && bin < last)) e[j] = ~0ull;
+        }
+        __syncthreads();
+        rank_and_place([&](int j) { return sm.hist[at[j] >> 16]; }, [&](int j) { return sm.hist[(at[j] >> 16) + 1u]; });
     } else {
         u32 m = 64;
         while (m < C) m <<= 1;
@@ -858,14 +967,7 @@ __device__ __forceinline__ void order_in_lds(const Params& P, int row, const Row
         for (u32 i = tid; i < want; i += B) sm.buf[i] = ~sm.buf[i];
     }
     __syncthreads();
-    char* out_v = (char*)P.out_values + (size_t)row * (size_t)P.k * KeyOf<DT>::kBytes;
-    long long* out_i = P.out_indices + (size_t)row * (size_t)P.k;
-    for (u32 i = tid; i < want; i += B) {
-        const u64 v = sm.buf[i];
-        const u32 idx = ent.idx(v);
-        out_i[rank0 + i] = (long long)idx;
-        store_value<DT>(out_v, rank0 + i, raw_of_key<DT>(ent.key(v), idx, rs, P.dirmask));
-    }
+    order_output<DT, B>(P, row, rs, sm, want, rank0, ent);
 }
 
 // The same for `count` entries at positions rank0 .. of list array `which`, however many: what LDS does not hold is
@@ -902,7 +1004,7 @@ __device__ __forceinline__ void order_entries(const Params& P, int row, const Ro
             for (u32 i = tid; i < cur.count; i += B) atomicAdd(&sm.hist[(u32)((mx - src[i]) >> sh)], 1u);
             __syncthreads();
             const u32 want = rs.k - cur.at < cur.count ? rs.k - cur.at : cur.count;
-            order_scan<B>(sm.hist, want, sm);
+            order_scan<B>(sm.hist, want, ~0u, false, sm);
             const u32 end = (sm.sp + 1u < 4u * B) ? sm.hist[sm.sp + 1u] : cur.count;  // what begins below `want` ends here
             // runs of bins: a run begins at the first bin that starts beyond the next multiple of run_len, and at a bin
             // that alone holds more than run_len (so a run is one bin, whose range is a small part of this one, or
@@ -941,6 +1043,139 @@ __device__ __forceinline__ void order_entries(const Params& P, int row, const Ro
         __syncthreads();
         if (sp == 0) return;
         cur = stack[--sp];
+    }
+}
+
+// Entries of src[0 .. count) in [lo, hi) to buf; returns how many there are (up to 8 B are kept).  Begins and ends with a barrier.
+template <int B>
+__device__ __forceinline__ u32 order_gather(const u64* src, u32 count, u64 lo, u64 hi, OrderShared<B>& sm, u32* run) {
+    const u32 tid = threadIdx.x;
+    __syncthreads();
+    if (tid == 0) *run = 0;
+    __syncthreads();
+#pragma unroll 4
+    for (u32 i = tid; i < count; i += B) {
+        const u64 e = src[i];
+        if (e >= lo && e < hi) {
+            const u32 at = atomicAdd(run, 1u);
+            if (at < 8u * B) sm.buf[at] = e;
+        }
+    }
+    __syncthreads();
+    return *run;
+}
+
+// The entries of src in [lo, hi), which are the row's ranks from rank0 on, a chunk that LDS holds after the other; where the
+// chunk ends is found by dividing the range evenly, as often as it takes (entries are distinct).
+template <int DT, int B>
+__device__ __forceinline__ void order_in_chunks(const Params& P, int row, const RowShape& rs, OrderShared<B>& sm, const u64* src, u32 count,
+                                                u32 rank0, u64 lo, u64 hi, u32* run) {
+    const u32 tid = threadIdx.x;
+    while (hi > lo && rank0 < rs.k) {
+        u64 a = lo, cut;
+        for (;;) {
+            const u32 sh = order_shift<B>(hi - a - 1u);
+            __syncthreads();
+            for (u32 j = tid; j < 4u * B; j += B) sm.hist[j] = 0;
+            if (tid == 0) sm.sp = 4u * B;
+            __syncthreads();
+#pragma unroll 4
+            for (u32 i = tid; i < count; i += B) {
+                const u64 e = src[i];
+                if (e >= a && e < hi) atomicAdd(&sm.hist[(u32)((hi - 1u - e) >> sh)], 1u);
+            }
+            __syncthreads();
+            order_scan<B>(sm.hist, 8u * B + 1u, ~0u, false, sm);  // sp: the first bin whose end lies beyond 8 B entries
+            const u32 bins = sm.sp;
+            const u64 down = (u64)bins << sh;
+            cut = bins < 4u * B && hi - a > down ? hi - down : a;
+            if (bins != 0u) break;
+            if (hi - a > (1ull << sh)) a = hi - (1ull << sh);
+        }
+        const u32 n = order_gather<B>(src, count, cut, hi, sm, run);
+        if (n != 0u) order_in_lds<DT, B>(P, row, rs, sm, n, rank0, [&](u32 i) __attribute__((always_inline)) { return sm.buf[i]; });
+        rank0 += n;
+        hi = cut;
+    }
+}
+
+// One of `parts` workgroups that put src[0 .. count) in order, the row's ranks from rank0 on.  Each reads all of it once and counts
+// it into bins between splitters, which are entries at equal distances, so that all of them see the same bins; runs of bins that LDS
+// holds are dealt to them, and each reads all of it again for every run of its own.  Nobody waits for anybody and
+// nothing is moved in memory.  One workgroup reads about 0.1 TB/s, so 2^20 entries take 256 of them about 0.2 ms.
+constexpr u32 kOrderRuns = 128;  // runs that a workgroup notes at a time
+template <int B>
+struct OrderParts {
+    u64 edge[SplitBins<B>::N + 1];
+    u64 lo[kOrderRuns], hi[kOrderRuns];
+    u32 start[kOrderRuns], size[kOrderRuns];
+    u32 bin[4 * B];  // the runs' first bins
+    u32 nrun, run;
+};
+template <int DT, int B>
+__device__ __forceinline__ void order_shared(const Params& P, int row, const RowShape& rs, OrderShared<B>& sm, OrderParts<B>& sp, const u64* src,
+                                             u32 count, u32 rank0, u32 part, u32 parts) {
+    typedef SplitBins<B> Split;
+    constexpr u32 kCap = 8 * B, kRun = kCap * 3 / 4, kBig = kCap / 4;
+    const u32 tid = threadIdx.x, want = rs.k - rank0 < count ? rs.k - rank0 : count;
+    __syncthreads();
+    if (count <= kCap) {
+        if (part == 0u) order_in_lds<DT, B>(P, row, rs, sm, count, rank0, [&](u32 i) __attribute__((always_inline)) { return src[i]; });
+        return;
+    }
+    // (the ends: nothing is known of the best and the worst entry but that they fit)
+    make_edges<B>(sp.edge, tid < (u32)Split::N ? src[(u64)tid * count / (u32)Split::N] : 0ull, (1ull << 63) - 1u, 0ull);
+    for (u32 done = 0;;) {
+        for (u32 j = tid; j < 4u * B + 2u; j += B) sm.hist[j] = 0;
+        __syncthreads();
+#pragma unroll 4
+        for (u32 i = tid; i < count; i += B) atomicAdd(&sm.hist[Split::bin(sp.edge, src[i])], 1u);
+        __syncthreads();
+        order_scan<B>(sm.hist, want, ~0u, false, sm);
+        if (tid == 0) sm.hist[4 * B] = count;
+        __syncthreads();
+        // A run begins at the first bin beyond a multiple of kRun, and at and after a bin of more than kBig: so it is such a bin
+        // or has at most kRun + kBig entries.
+        u32 begins = 0, mask = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const u32 b = 4 * tid + i, s = sm.hist[b], before = b == 0u ? 0u : sm.hist[b - 1];
+            const bool first = s < want && (b == 0u || s / kRun != before / kRun || sm.hist[b + 1] - s > kBig || s - before > kBig);
+            mask |= (first ? 1u : 0u) << i;
+            begins += first ? 1u : 0u;
+        }
+        u32 slot = block_inclusive_scan<B>(begins, sm.wsum) - begins;
+        const u32 last = sm.sp;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if ((mask >> i) & 1u) sp.bin[slot++] = 4 * tid + i;
+        if (tid == B - 1) sp.nrun = slot;
+        __syncthreads();
+        const u32 nrun = sp.nrun;
+        // this workgroup's next runs: part, part + parts, ...
+        for (u32 i = tid; i < kOrderRuns; i += B) {
+            const u64 r64 = (u64)part + (u64)(done + i) * parts;
+            if (r64 < nrun) {
+                const u32 r = (u32)r64, b0 = sp.bin[r], b1 = r + 1u < nrun ? sp.bin[r + 1u] - 1u : last;
+                sp.hi[i] = b0 == 0u ? 1ull << 63 : Split::floor_of(sp.edge, b0 - 1u);
+                sp.lo[i] = Split::floor_of(sp.edge, b1);
+                sp.start[i] = sm.hist[b0];
+                sp.size[i] = sm.hist[b1 + 1u] - sm.hist[b0];
+            }
+        }
+        __syncthreads();
+        for (u32 i = 0; i < kOrderRuns; ++i) {
+            if ((u64)part + (u64)(done + i) * parts >= nrun) return;
+            const u32 n = sp.size[i], r0 = rank0 + sp.start[i];
+            if (n > kCap) {
+                order_in_chunks<DT, B>(P, row, rs, sm, src, count, r0, sp.lo[i], sp.hi[i], &sp.run);
+            } else if (n != 0u) {
+                order_gather<B>(src, count, sp.lo[i], sp.hi[i], sm, &sp.run);
+                order_in_lds<DT, B>(P, row, rs, sm, n, r0, [&](u32 i) __attribute__((always_inline)) { return sm.buf[i]; });
+            }
+        }
+        done += kOrderRuns;
+        __syncthreads();
     }
 }
 
@@ -1693,51 +1928,67 @@ __device__ __forceinline__ void redo_row(const Params& P, const ListPlan& L, int
     *listed_out = listed;
 }
 
-// What the kernels before left over; normally nothing.  Rows (kRedoRow, kRedoList) are dealt to the workgroups, buckets of
-// one row likewise.
+// What the kernels before left over; normally nothing.  Every row has L.redo_wgs workgroups, which share what has to be put in
+// order; where that is one, a workgroup has several rows.
 template <int DT>
 __global__ void __launch_bounds__(kListBucketBlock) k_list_redo(Params P, ListPlan L) {
     constexpr int B = kListBucketBlock;
     __shared__ union { OrderShared<B> ord; RankShared rank; } sm;
-    __shared__ u32 run, marked[B], nmarked;
-    const u32 tid = threadIdx.x;
-    for (int r0 = 0; r0 < P.batch; r0 += B) {
-        const u32 mark = r0 + (int)tid < P.batch ? row_state(P, r0 + (int)tid)->redo : 0u;
+    __shared__ OrderParts<B> parts;
+    __shared__ u32 before[B], run, marked[B], nmarked;
+    const u32 tid = threadIdx.x, W = (u32)L.redo_wgs, w = blockIdx.x % W;
+    const u32 step = gridDim.x / W, first = blockIdx.x / W;  // (the grid is a multiple of W)
+    for (u64 r0 = first; r0 < (u64)P.batch; r0 += (u64)step * B) {
+        const u64 r = r0 + (u64)tid * step;
+        const u32 mark = r < (u64)P.batch ? row_state(P, (int)r)->redo : 0u;
         if (__syncthreads_or((int)mark) == 0) continue;
         if (tid == 0) nmarked = 0;
         __syncthreads();
-        if (mark != 0u) marked[atomicAdd(&nmarked, 1u)] = tid;
+        if (mark != 0u) marked[atomicAdd(&nmarked, 1u)] = (u32)r;
         __syncthreads();
         const u32 nm = nmarked;
         for (u32 i = 0; i < nm; ++i) {
-            // (the order of `marked` differs between workgroups: who takes a row is decided by its number)
-            const int row = r0 + (int)marked[i];
+            const int row = (int)marked[i];
             rtopk_row_trace* st = row_state(P, row);
             const u32 why = st->redo;
-            const bool mine = (u32)row % gridDim.x == blockIdx.x;
             const RowShape rs = row_shape_scalar<DT>(P, row);
-            OrderRange* stack = list_part<OrderRange>(P, row, L.stack_off);
-            // one task (the row's list), or one per bucket that is too large
-            const bool buckets = (why & (kRedoRow | kRedoList)) == 0u;
-            const u32 tasks = buckets ? L.nb : 1u;
-            for (u32 j = buckets ? blockIdx.x : 0u; j < tasks; j += gridDim.x) {
-                u32 at = 0, count = 0, which = 0;
-                if (buckets) {
-                    if (!bucket_range(P, L, row, rs, j, &at, &count)) continue;
-                    if (count <= 8u * B) count = 0;  // (done)
-                    stack += at / (u32)B + 16u * j;
-                } else if (mine && (why & kRedoRow)) {
-                    redo_row<DT, B>(P, L, row, rs, st, sm.rank, &run, sm.ord.hist, sm.ord.wsum, &count);
-                    which = 1;
-                } else if (mine) {
-                    count = list_done(P, row)->total;
-                    which = list_done(P, row)->end;
+            __syncthreads();
+            if (why & kRedoRow) {
+                if (w != 0u) continue;
+                u32 count;
+                redo_row<DT, B>(P, L, row, rs, st, sm.rank, &run, sm.ord.hist, sm.ord.wsum, &count);
+                __syncthreads();
+                if (count != 0u) order_entries<DT, B>(P, row, rs, sm.ord, 0u, count, 1u, list_part<OrderRange>(P, row, L.stack_off));
+            } else if (why & kRedoList) {
+                const ListDone done = *list_done(P, row);
+                const u32 want = rs.k < done.total ? rs.k : done.total, n = (want + 4u * B - 1u) / (4u * B), np = n < W ? n : W;
+                if (w < np) order_shared<DT, B>(P, row, rs, sm.ord, parts, list_array(P, done.end, row), done.total, 0u, w, np);
+            } else {
+                // every bucket that is too large is cut into parts of about half of what LDS holds; all of the row's parts are dealt to its
+                // workgroups
+                u32 base = 0;
+                for (u32 j0 = 0; j0 < L.nb; j0 += B) {
+                    u32 at = 0, count = 0, n = 0;
+                    if (j0 + tid < L.nb && bucket_range(P, L, row, rs, j0 + tid, &at, &count) && count > 8u * B) n = (count + 4u * B - 1u) / (4u * B);
+                    __syncthreads();
+                    const u32 incl = block_inclusive_scan<B>(n, sm.ord.wsum);
+                    before[tid] = incl - n;
+                    if (tid == B - 1) run = incl;
+                    __syncthreads();
+                    const u32 total = run;
+                    for (u32 s = (w + W - base % W) % W; s < total; s += W) {
+                        u32 a = 0, b = B;  // the bucket that part s belongs to: the last one that begins at or before it
+                        while (b - a > 1u) {
+                            const u32 m = (a + b) / 2u;
+                            if (before[m] <= s) a = m; else b = m;
+                        }
+                        bucket_range(P, L, row, rs, j0 + a, &at, &count);
+                        order_shared<DT, B>(P, row, rs, sm.ord, parts, list_array(P, 0u, row) + at, count, at, s - before[a], (count + 4u * B - 1u) / (4u * B));
+                    }
+                    base += total;
                 }
-                __syncthreads();
-                if (count != 0u) order_entries<DT, B>(P, row, rs, sm.ord, at, count, which, stack);
-                __syncthreads();
-                stack = list_part<OrderRange>(P, row, L.stack_off);
             }
+            __syncthreads();
         }
         __syncthreads();
     }
@@ -1758,7 +2009,7 @@ static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStrea
     mark(events, 0, st);
     mark(events, 1, st);
     const dim3 rows((unsigned)P.batch);
-    const unsigned redo = L.nb != 0 ? 64u : (unsigned)(P.batch < 256 ? P.batch : 256);
+    const unsigned redo = (unsigned)((L.redo_wgs > 1 ? P.batch * L.redo_wgs : P.batch < 512 ? P.batch : 512));
     if (L.row_block != 0) {
         mark(events, 2, st);
         mark(events, 3, st);

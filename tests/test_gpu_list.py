@@ -28,7 +28,7 @@ def _check(name, x, dtype, k, largest=True, sorted=True, batch=1, by_list=True, 
         assert tr[r].error == 0 and tr[r].done, (r, tr[r].error)
         if sorted:  # (unsorted, the route depends on the list's length as well)
             assert tr[r].redo_why == why, (r, tr[r].redo_why)
-            assert (tr[r].passes[0].where in LIST) == by_list
+            assert by_list is None or (tr[r].passes[0].where in LIST) == by_list
             assert np.array_equal(gi[r], wi[r]) and np.array_equal(gv[r], wv[r]), "row %d" % r
         else:
             verify.assert_same_selection(bits[r], gv[r], gi[r], wv[r], wi[r])
@@ -204,3 +204,54 @@ def test_misled_rows_beside_others():
         wv, wi = oracle.topk(bits, F32, k, largest)
         assert np.array_equal(gi, wi) and np.array_equal(gv, wv)
         assert [t.redo & 1 for t in tr] == [1, 0] * (batch // 2) and all(t.error == 0 for t in tr)
+
+
+def test_lists_and_buckets_that_do_not_fit_are_shared_out():
+    # a trend along the row: more is listed than one workgroup orders in LDS (bit 2); crowds that the sample does not show: a bucket
+    # that holds most of the list (bit 4), of one value and of neighbouring keys; one workgroup per row, and several
+    n = 1 << 20
+    for dtype, k in ((F32, 1000), (F16, 1000), (F32, 3000)):
+        x = np.linspace(6.0e4, -6.0e4, n, dtype=np.float32)
+        for largest in (True, False):
+            for srt in (True, False):
+                tr = _check("trend", x, dtype, k, largest, sorted=srt)
+                assert all(t.redo & 2 for t in tr), [t.redo for t in tr]
+    x = np.stack([np.linspace(1.0, -1.0, 131072, dtype=np.float32)] * 260)
+    tr = _check("trend, many rows", x, BF16, 1000, batch=260)
+    assert any(t.redo & 2 for t in tr)
+    n, k = 400000, 9000
+    hidden = np.setdiff1d(np.arange(n), _sampled(n, 4096, 4))
+    u = W.uniform01(n, 61)
+    for crowd in (np.float32(9.0), (9.0 + u * 1e-3).astype(np.float32)):
+        for count in (5000, 8000, 30000):
+            y = W.normal(n, 62)
+            where = hidden[:: len(hidden) // count][:count]
+            y[where] = crowd if np.ndim(crowd) == 0 else crowd[where]
+            for largest in (True, False):
+                tr = _check("hidden crowd", y if largest else -y, F32, k, largest)
+                assert tr[0].redo == 4
+
+
+def test_lists_longer_than_half_the_row_are_selected_anew():
+    # six elements in ten are one value that the sample does not show: everything listed, reason 5; a short list and a long one
+    n = 400000
+    hidden = np.setdiff1d(np.arange(n), _sampled(n, 4096, 4))
+    y = W.normal(n, 63)
+    y[hidden[W.uniform01(len(hidden), 64) < 0.65]] = 9.0
+    for k in (300, 9000):
+        for largest in (True, False):
+            tr = _check("hidden majority", y if largest else -y, F32, k, largest, why=5)
+            assert tr[0].redo & 1
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+def test_crowds_in_order(dtype):
+    # what LDS holds of a list, with few values in it, or one far above the rest: bins between splitters; every size of workgroup
+    for n, ks in ((1000, (1, 100, 300, 1000)), (4096, (100, 409, 1556)), (16384, (100, 1000)), (60000, (300, 2000))):
+        u = W.uniform01(2 * n, 65)
+        for name, x in (("two", np.floor(u * 2)), ("ten", np.floor(u * 10)), ("hundred", np.floor(u * 100)),
+                        ("far", np.where(u < 0.001, np.float32(6.0e4), np.floor(u * 30) / 1024)), ("half", np.maximum(W.normal(2 * n, 66), 0))):
+            for k in ks:
+                for largest in (True, False):
+                    _check("crowd of " + name, x.astype(np.float32), dtype, k, largest, batch=2, sorted=True)
+                    _check("crowd of " + name, x.astype(np.float32), dtype, k, largest, batch=2, sorted=False)
