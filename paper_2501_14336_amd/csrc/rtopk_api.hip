@@ -308,8 +308,8 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     L->bucket_shift = 11;
     while ((k >> L->bucket_shift) + 1 > (int64_t)kListMaxBuckets) ++L->bucket_shift;
     L->nb = is_long ? (u32)((k >> L->bucket_shift) + 1) : 0u;
-    int64_t ties = n > 16384 ? 128 / batch : 0;
-    if (n > 16384 && ties < 1) ties = 1;
+    int64_t ties = 128 / batch;
+    if (ties < 1) ties = 1;
     if (ties > ntiles) ties = ntiles;
     L->ties = (int)ties;
     L->redo_wgs = L->row_block != 0 || batch >= 256 ? 1 : (int)(256 / batch);
@@ -320,6 +320,7 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     L->hist_off = take(is_long ? kMaxBins * 4 : 0);
     L->cursor_off = take((u64)L->nb * 4);
     L->first_off = take((u64)L->nb * 8);
+    L->split_off = take(is_long ? (kListSplits + 1) * 8 : 0);
     L->seg_off = take((u64)G * 4);
     L->tile_off = take((u64)((n + E - 1) / (kHostGridBlock * 64 / eb) + 1) * 4);  // (the smaller tiles' number)
     L->stack_off = take(((u64)n / 256 + 64 + 16 * (u64)L->nb) * 16);

@@ -27,6 +27,7 @@ rtopk_status launch_bf16(const Params& P, const Config& c, bool scaled, hipStrea
 
 // Plan of a call that goes through lists (rtopk_list.inl).  Offsets: bytes from the start of a row's working memory.
 constexpr unsigned kListMaxBuckets = 4096;
+constexpr unsigned kListSplits = 256;                  // intervals between splitters
 constexpr int kListPartBlock = 256, kListPartVecs = 8;  // a stretch of a row that one workgroup holds: 32 KB
 struct ListPlan {
     int G;            // workgroups per row in the sweep
@@ -40,7 +41,7 @@ struct ListPlan {
     u32 seg_stride;   // the row's stretches are held by G workgroups that list at most this many each (0: the row is swept)
     u32 nb;           // long lists: buckets per row (0: short lists)
     u32 bucket_shift; // ... of 2^bucket_shift ranks
-    u32 hist_off, cursor_off, first_off, seg_off, tile_off, stack_off;
+    u32 hist_off, cursor_off, first_off, split_off, seg_off, tile_off, stack_off;
 };
 rtopk_status launch_list_f32(const Params& P, const ListPlan& L, hipStream_t st, void* const* events);
 rtopk_status launch_list_f16(const Params& P, const ListPlan& L, hipStream_t st, void* const* events);

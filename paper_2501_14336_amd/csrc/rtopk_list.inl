@@ -51,8 +51,7 @@ struct ListRow {
     float t;
     u64 lo;        // long lists: see list_bin
     u32 sh;
-    u32 finite;    // bins for entries below `special`
-    u64 special;   // the first entry that is an infinity or NaN on the better side; ~0: bins are not set aside for those
+    u32 split;     // long lists, 1: the bins lie between splitters
 };
 static_assert(sizeof(ListRow) % 8 == 0, "read by words");
 // What became of a row's list.  A record of its own: the kernel that writes it has workgroups that still read the decision, and a
@@ -92,16 +91,22 @@ __device__ __forceinline__ ListRow list_row_scalar(const ListRow* p) {
     return r;
 }
 
-// Bin of an entry of a long list, in the entries' order.  The bins divide the range of what the sample showed evenly; infinities
-// would stretch that range until all numbers shared a bin or two, which one workgroup each then puts in order.  Where the
-// sample holds any, the last quarter of the bins divides the infinities by position.  us per call, one range / two: 2^26
-// fp32 keys, a ramp with an infinity in every 2048, k = 2^16, sorted, 927 / 133, k = 2^20, 2909 / 174.
-constexpr u32 kListFinite = 3072;
-__device__ __forceinline__ u32 list_bin(u64 e, u64 lo, u32 sh, u64 special, u32 finite, u32 ib) {
-    const bool sp = e >= special;
-    const u64 b = (e - (sp ? special : lo)) >> (sp ? (ib > 10u ? ib - 10u : 0u) : sh);
-    const u32 room = sp ? kListBins - finite : finite;
-    return (sp ? finite : 0u) + (b < room ? (u32)b : room - 1u);
+// Bin of an entry of a long list, in the entries' order.  The bins divide the range of what the sample showed evenly, one shift per
+// entry; where the sample shows a crowd in one of those bins (equal keys, or one key far above the others: infinities, a mask
+// value), they lie between 255 entries of the sample at equal ranks, 16 to an interval: equal keys then differ by position, and
+// no distance between keys matters.  split: the intervals' edges, ascending, kListSplits + 1 of them, in LDS.
+__device__ __forceinline__ u32 list_bin(u64 e, u64 lo, u32 sh) {
+    const u64 b = (e - lo) >> sh;
+    return b < kListBins ? (u32)b : kListBins - 1u;
+}
+__device__ __forceinline__ u32 list_bin_split(u64 e, const u64* split) {
+    constexpr u32 Q = 31u - (u32)__builtin_clz(kListBins / kListSplits);
+    u32 p = 0;
+#pragma unroll
+    for (u32 step = kListSplits / 2; step > 0; step /= 2) p += split[p + step] <= e ? step : 0u;
+    const u64 lower = split[p], span = split[p + 1u] - lower;
+    const u32 width = span > 1u ? 64u - (u32)__builtin_clzll(span - 1u) : 0u;
+    return (p << Q) | (u32)((e - lower) >> (width > Q ? width - Q : 0u));
 }
 
 // Per-row working memory beside the list: the upper half of the row's first candidate array (the list proper is at
@@ -153,6 +158,22 @@ __device__ __forceinline__ u32 raw_of_key(u32 key, u32 idx, const RowShape& rs, 
     return DT == RTOPK_F32 ? b : b >> 16;
 }
 
+// block_inclusive_scan for the larger workgroups: the waves' sums are added up on the lane network, not by a loop over them.  (It is
+// the same where there are few waves.)
+template <int B>
+__device__ __forceinline__ u32 block_scan(u32 v, u32* wsum) {
+    if constexpr (B < 512) {
+        return block_inclusive_scan<B>(v, wsum);
+    } else {
+        const u32 lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        v = wave_inclusive_scan(v);
+        if (lane == 63) wsum[wave] = v;
+        __syncthreads();
+        const u32 x = wave_inclusive_scan(lane < wave ? wsum[lane % (u32)(B / 64)] : 0u);
+        return v + (u32)__builtin_amdgcn_readlane((int)x, 63);
+    }
+}
+
 // f(0), f(1), ... f(N - 1) with constants: a row in registers must stay a named set of registers (see each_resident_tile).
 template <int C, int N, class F>
 __device__ __forceinline__ void static_for(F&& f) {
@@ -201,8 +222,8 @@ struct MinOf { template <class T> __device__ __forceinline__ T operator()(T a, T
 // [lo, hi], and values below lo are passed over.  2048 bins divide [lo, hi] evenly; the bin in question is divided again
 // until it holds few values, and its lower edge is returned (*exact: until it was one value).
 struct RankShared {
-    u32 hist[2 * 2049];  // two copies, a word apart (see HistSlot)
-    u32 wsum[16], selv[3];
+    alignas(16) u32 hist[2 * 2049];  // two copies, a word apart (see HistSlot)
+    u32 wsum[16], selv[4];
 };
 template <int B, class Each>
 __device__ __forceinline__ u32 sample_rank(Each&& each, u32 rank, u32 lo, u32 hi, RankShared& sm, bool* exact) {
@@ -227,7 +248,7 @@ __device__ __forceinline__ u32 sample_rank(Each&& each, u32 rank, u32 lo, u32 hi
             c[i] = sm.hist[b] + sm.hist[2049u + b];
             s += c[i];
         }
-        const u32 incl = block_inclusive_scan<B>(s, sm.wsum);
+        const u32 incl = block_scan<B>(s, sm.wsum);
         u32 run = incl - s;
         if (run < left && left <= incl) {
 #pragma unroll
@@ -245,7 +266,7 @@ __device__ __forceinline__ u32 sample_rank(Each&& each, u32 rank, u32 lo, u32 hi
         left -= sm.selv[1];
         __syncthreads();
         lo += bin << sh;
-        hi = sh == 0u ? lo : lo + ((1u << sh) - 1u);
+        hi = hi - lo > (1u << sh) - 1u ? lo + ((1u << sh) - 1u) : hi;  // (the last bin may reach beyond the range, and beyond 32 bits)
         *exact = sh == 0u;
         if (sh == 0u || inside <= 1u + rank / 16u) return lo;
     }
@@ -254,8 +275,9 @@ __device__ __forceinline__ u32 sample_rank(Each&& each, u32 rank, u32 lo, u32 hi
 // The same for one value per thread, in LDS: the first wave halves [lo, hi] until the values from lo up are at least `rank`
 // and few more, counting with a compare and a scalar population count per 64 of them -- no barriers among many waves
 // (1024 values: 1.3 us against 4.4 with sample_rank).  At least `rank` values are not below lo.  Contains two barriers; `v`
-// may be written again after it.
-template <int B>
+// may be written again after it.  RUNS: result[2] is how many values that are, result[3] the sum of squares of how many every eight
+// neighbouring threads have.
+template <int B, bool RUNS = false>
 __device__ __forceinline__ u32 rank_by_one_wave(u32 value, u32 rank, u32 lo, u32 hi, u32* v, u32* result, bool* exact) {
     const u32 tid = threadIdx.x;
     v[tid] = value;
@@ -268,7 +290,7 @@ __device__ __forceinline__ u32 rank_by_one_wave(u32 value, u32 rank, u32 lo, u32
         const u32 slack = rank + 1u + rank / 16u;
         u32 end = hi;  // fewer than `rank` values lie above it
         while (lo < end) {
-            const u32 mid = lo + (end - lo + 1u) / 2u;
+            const u32 mid = end - (end - lo) / 2u;
             u32 c = 0;
 #pragma unroll
             for (int i = 0; i < kPer; ++i) c += (u32)__popcll(ballot64(mine[i] >= mid));
@@ -282,6 +304,27 @@ __device__ __forceinline__ u32 rank_by_one_wave(u32 value, u32 rank, u32 lo, u32
         if (tid == 0) {
             result[0] = lo;
             result[1] = lo == end ? 1u : 0u;
+        }
+        if constexpr (RUNS) {
+            u32 word = 0, sq = 0;  // lane 2 i, 2 i + 1: which of the values i * 64 .. i * 64 + 63 they are
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                const u64 m = ballot64(mine[i] >= lo);
+                word = tid == 2u * (u32)i ? (u32)m : word;
+                word = tid == 2u * (u32)i + 1u ? (u32)(m >> 32) : word;
+            }
+            u32 all = (u32)__builtin_popcount(word);
+#pragma unroll
+            for (u32 b = 0; b < 32u; b += 8u) {
+                const u32 c = (u32)__builtin_popcount((word >> b) & 0xffu);
+                sq += c * c;
+            }
+            all = wave_inclusive_scan(all);
+            sq = wave_inclusive_scan(sq);
+            if (tid == 63u) {
+                result[2] = all;
+                result[3] = sq;
+            }
         }
     }
     __syncthreads();
@@ -320,36 +363,77 @@ __device__ __forceinline__ u32 key_in_vector(const uint4& q, int j) {
     else return (j & 1) ? w[j / 2 % 4] & 0xffff0000u : w[j / 2 % 4] << 16;
 }
 
+// What the B / 64 waves of a workgroup left in v[0], v[stride], ...: their sum, or the best of them, in every lane.  (One read and six
+// steps on the lane network; a loop over 16 waves' words, run by all 16 waves, takes most of 1 us.)
+template <int B>
+__device__ __forceinline__ u32 sum_of_waves(const u32* v, u32 stride) {
+    const u32 x = lane_id() < (u32)(B / 64) ? v[stride * lane_id()] : 0u;
+    return (u32)__builtin_amdgcn_readlane((int)wave_inclusive_scan(x), 63);
+}
+template <int B, class Op>
+__device__ __forceinline__ u32 best_of_waves(const u32* v, u32 stride, Op&& op) {
+    return (u32)__builtin_amdgcn_readlane((int)wave_reduce(v[stride * (lane_id() % (u32)(B / 64))], op), 63);
+}
+
 // Bound by latency: V independent loads per lane, then a few phases with barriers, on one compute unit.  The sample is
 // B * V vectors of 16 bytes, in runs of 8 (one 128-byte line), one run from a hashed place in each of B * V / 8 equal
-// stretches of the row: a trend along the row, or any period in it, cannot line up with that.
+// stretches of the row: a trend along the row, or any period in it, cannot line up with that.  (A stretch is at least 1.5 runs
+// long and may begin inside one, so that neighbours meet in one run now and then, at most once in nine: it then counts twice.)
+// A row that is too short for that has a smaller sample, half as many runs until they fit.
 // The rank is taken among the MAXIMA of vectors (or of all a lane's vectors) while it is small against their number:
 // neighbouring elements that are alike then count once, so that a row whose best elements lie together does not look
 // richer than it is, and there are fewer values to rank.  The rank that stands for the row's k-th key is its share
-// ks = k * sample / n, plus six standard deviations of a Poisson count, plus 6 (ks = 0.1, 1, 10, 100: more than
-// that many are seen with a probability of 1e-13, 1e-9, 1e-8, 1e-8; the row is then done again).
-// te: counters of ties per tile, nt of them, cleared if they will be used.  Thread 0 fills in *lr.
-template <int DT, int B, int V>
+// ks = k * sample / n, plus six standard deviations of a Poisson count, plus 6 (independent draws: ks = 0.1, 1, 10, 100: more than
+// that many are seen with a probability of about 1e-13, 1e-9, 1e-8, 1e-8; the row is then done again).
+// Runs whose elements are alike (blocks of one value, a trend) are fewer draws than they have elements: their counts of
+// elements not below T show by how much (v), and where T has too few such elements for that, it is taken again, lower.
+// For many workgroups per row (a row done again is dear there, and so is a bin that holds much of a long list) what the sample has of
+// the list is gathered in LDS first, of every run or of every 2^thin-th.
+// te: counters of ties per tile, nt of them, cleared if they will be used.  room: how long a list may be that is put in order
+// in LDS.  Thread 0 fills in *lr.
+constexpr u32 kSampleList = 8192, kLeastThinned = 128;
+struct SampleList {
+    // place: (run * 8 + vector of the run) * elements per vector + element
+    // (two arrays: a 64-bit store of both would put a loaded vector's words into register pairs, and the kernel into scratch memory)
+    u32 key[kSampleList], place[kSampleList];
+    u32 run[2048];       // how many of them each run has
+    u32 bin[kListBins];  // how many of them, of those better than T, lie in each bin of a long list
+    u32 n, next;
+};
+template <int DT, int B, int V, bool GATHER>
 __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L, int row, const RowShape& rs, rtopk_row_trace* st,
-                                             ListRow* lr, u32* te, u32 nt, RankShared& sm, u32* red) {
+                                             ListRow* lr, u32* te, u32 nt, u32 room, RankShared& sm, SampleList* sl, u32* red) {
     constexpr int E = 16 / KeyOf<DT>::kBytes;
-    constexpr u32 kRun = 8;
+    constexpr u32 kRun = 8, kRuns = (u32)(B * V) / kRun, kLeastRuns = 16;
     const u32 tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     KeySource<DT, kGridBlock, key_vecs<DT>(), false> src;
     src.init(rs);
     const u32 v0 = src.lead != 0 ? 1u : 0u;
     const u32 v1 = (u32)(((u64)src.lead + (u64)rs.n) / E);
     const u32 groups = v1 > v0 ? (v1 - v0) / kRun : 0u;  // whole runs inside the row
-    constexpr u32 kRuns = (u32)(B * V) / kRun;
+    u32 lruns = 31u - (u32)__builtin_clz(kRuns);  // (their logarithm)
+    while ((1u << lruns) > kLeastRuns && groups < (1u << lruns) + (1u << lruns) / 2u) --lruns;
+    const u32 runs = 1u << lruns;
     const ListEntry ent = list_entry<DT>(P);
-    const bool sampled = groups >= kRuns + kRuns / 2u && (u64)rs.k * 5u <= (u64)rs.n * 2u;
+    const bool sampled = groups >= runs + runs / 2u;
+    // (where more than 0.4 of the row is wanted -- ragged batches -- everything is listed)
+    const bool whole = !sampled || (u64)rs.k * 5u > (u64)rs.n * 2u;
+    const bool bins = GATHER && L.nb != 0u;  // a long list
+    // Lane t's vector u is the t % 8-th of this run: the runs of a lane lie far apart (its best element would else stand for
+    // V neighbouring runs where the row has a trend), and so do the runs of any u.
+    static_assert((V & (V - 1)) == 0 && (B & (B - 1)) == 0, "one to one");
+    auto run_of = [&](u32 t, u32 u) __attribute__((always_inline)) { return t / kRun + (u32)B / kRun * ((u + t / kRun) % (u32)V); };
+    auto vector_of = [&](u32 c, u32 i) __attribute__((always_inline)) {  // which vector of the row is the i-th of run c
+        // (c << 16 | hash) * groups / runs >> 16, as the upper half of a 32-bit product
+        const u32 g = __umulhi((c << 16 | (mix32(c) >> 16)) << (16u - lruns), groups);
+        return v0 + g * kRun + i;
+    };
     uint4 q[V];
-    if (sampled) {
+    if (sampled && (bins || !whole)) {
 #pragma unroll
         for (int u = 0; u < V; ++u) {
-            const u32 j = (u32)u * B + tid, c = j / kRun;
-            const u32 g = (u32)((((u64)c << 16 | (mix32(c) >> 16)) * groups / kRuns) >> 16);
-            q[u] = load16<false>(src.abase + (v0 + g * kRun + j % kRun));
+            // (lanes beyond a smaller sample: some of it again, and ignored)
+            q[u] = load16<false>(src.abase + vector_of(run_of(tid, (u32)u) & (runs - 1u), tid % kRun));
         }
     }
     init_row<DT>(P, row, st, rs);
@@ -357,13 +441,19 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
         if (tid == 0) lr->mode = kListSkip;
         return;
     }
-    if (L.nb != 0) {  // a long list: its histogram and the buckets' write positions
+    if constexpr (GATHER) {
+        for (u32 r = tid; r < runs; r += B) sl->run[r] = 0;
+        if (tid == 0) sl->n = sl->next = 0;
+        if (bins)
+            for (u32 j = tid; j < kListBins; j += B) sl->bin[j] = 0;
+    }
+    if (bins) {  // its histogram and the buckets' write positions
         u32* gh = list_part<u32>(P, row, L.hist_off);
         for (u32 j = tid; j < kListBins; j += B) gh[j] = 0;
         u32* cur = list_part<u32>(P, row, L.cursor_off);
         for (u32 j = tid; j < L.nb; j += B) cur[j] = 0;
     }
-    if (!sampled) {  // (ragged batches: a row that is short against the batch's longest one: everything is listed)
+    if (whole && !(bins && sampled)) {
         if (tid == 0) {
             lr->mode = kListPlain;
             lr->T = 0;
@@ -372,26 +462,43 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
             lr->lo = 0;
             const u32 top = ent.ib + (DT == RTOPK_F32 ? 32u : 16u);
             lr->sh = top > 12u ? top - 12u : 0u;
-            lr->finite = kListBins;
-            lr->special = ~0ull;
+            lr->split = 0;
         }
         return;
     }
-    constexpr u32 kVecsTotal = (u32)(B * V), kElems = kVecsTotal * E;
-    const float ks = (float)rs.k * ((float)kElems / (float)rs.n);
-    const u32 rank = (u32)(ks + 6.0f * __builtin_sqrtf(ks) + 6.0f);
-    u32 vmax[V], lmax = 0;
+    const u32 vecs = runs * kRun, elems = vecs * E, lanes = vecs < (u32)B ? vecs : (u32)B;
+    const float ks = (float)rs.k * ((float)elems / (float)rs.n);
+    u32 rank = (u32)(ks + 6.0f * __builtin_sqrtf(ks) + 6.0f);
+    auto best_of = [&](const uint4& v) __attribute__((always_inline)) {
+        u32 m = 0;
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            const u32 k = key_in_vector<DT>(v, j);
+            m = m > k ? m : k;
+        }
+        return m;
+    };
+    u32 lmax = 0;
 #pragma unroll
     for (int u = 0; u < V; ++u) {
         keys_of_vector<DT>(q[u], P.dirmask);
-        vmax[u] = 0;
-#pragma unroll
-        for (int j = 0; j < E; ++j) {
-            const u32 k = key_in_vector<DT>(q[u], j);
-            vmax[u] = vmax[u] > k ? vmax[u] : k;
-        }
-        lmax = lmax > vmax[u] ? lmax : vmax[u];
+        const u32 m = best_of(q[u]);
+        lmax = lmax > m ? lmax : m;
     }
+    if (runs != kRuns) {  // (beyond a smaller sample: no key is below these)
+        lmax = 0;
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+            if (run_of(tid, (u32)u) >= runs) q[u] = make_uint4(0, 0, 0, 0);
+            const u32 m = best_of(q[u]);
+            lmax = lmax > m ? lmax : m;
+        }
+    }
+    auto forget = [&]() __attribute__((always_inline)) {  // (nothing worked out from the elements is kept: registers)
+#pragma unroll
+        for (int u = 0; u < V; ++u) asm volatile("" : "+v"(q[u].x), "+v"(q[u].y), "+v"(q[u].z), "+v"(q[u].w));
+    };
+    forget();
     // the best of the sample, and the worst of the lanes' best (at least B elements are not below it)
     u32 top = wave_reduce(lmax, MaxOf()), low = wave_reduce(lmax, MinOf());
     if (lane == 63u) {
@@ -399,73 +506,225 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
         red[2 * wave + 1] = low;
     }
     __syncthreads();
-    top = red[0];
-    low = red[1];
-#pragma unroll
-    for (int w = 1; w < B / 64; ++w) {
-        top = top > red[2 * w] ? top : red[2 * w];
-        low = low < red[2 * w + 1] ? low : red[2 * w + 1];
-    }
+    top = best_of_waves<B>(red, 2, MaxOf());
+    low = best_of_waves<B>(red + 1, 2, MinOf());
     __syncthreads();
     // (16-bit keys are ranked on the 16 bits they have: fewer rounds)
     constexpr u32 ksh = DT == RTOPK_F32 ? 0u : 16u;
-    u32 T;
-    bool exact;
-    if (rank <= (u32)B / 4u) {
-        T = rank_by_one_wave<B>(lmax >> ksh, rank, low >> ksh, top >> ksh, sm.hist, sm.selv, &exact);
-    } else if (rank <= kVecsTotal / 4u) {
+    u32 T = 0, cnt = 0, eq = 0, thin = 0, got = 0, eq_got = 0;
+    bool exact = false;
+    auto all = [&](auto&& f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < V; ++u)
+#pragma unroll
+            for (int j = 0; j < E; ++j) f(key_in_vector<DT>(q[u], j) >> ksh);
+    };
+    bool elements = false;  // T is ranked among the elements
+    bool alike = true;      // runs may be fewer draws than they have elements
+    if (whole) {
+    } else if (rank <= lanes / 4u) {
+        T = rank_by_one_wave<B, GATHER>(lmax >> ksh, rank, low >> ksh, top >> ksh, sm.hist, sm.selv, &exact);
+        if constexpr (GATHER) {
+            const float c = (float)sm.selv[2];
+            alike = (float)sm.selv[3] > (2.0f + c / (float)(lanes / kRun)) * c;
+            if (sm.selv[2] > lanes / 2u)  // (T is what most of the sample equals)
+                while ((runs >> thin) > kLeastThinned) ++thin;
+        }
+    } else if (rank <= vecs / 4u) {
         T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < V; ++u) f(vmax[u] >> ksh);
-        }, rank, rank <= (u32)B ? low >> ksh : 0u, top >> ksh, sm, &exact);
+            for (int u = 0; u < V; ++u) f(best_of(q[u]) >> ksh);
+        }, rank, rank <= lanes ? low >> ksh : 0u, top >> ksh, sm, &exact);
     } else {
-        T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) {
-#pragma unroll
-            for (int u = 0; u < V; ++u)
-#pragma unroll
-                for (int j = 0; j < E; ++j) f(key_in_vector<DT>(q[u], j) >> ksh);
-        }, rank, rank <= (u32)B ? low >> ksh : 0u, top >> ksh, sm, &exact);
+        elements = true;
     }
-    T <<= ksh;
-    // of the sample: how many equal T (which matters if T is one key and not the edge of a range), how many share the first
-    // digit of T or have a better one
-    const u32 d0 = P.pass[0].bits, edge = (T >> (32u - d0)) << (32u - d0);
-    u32 eq = 0, crowd = 0;
-    if (exact || low >= edge) {  // (else some lane has no element that good: far from crowded)
+    const bool gather = GATHER && (bins || alike);
+    // a long list's bins, while they divide the range evenly
+    u64 lo = 0;
+    u32 sh = 0, most = 0;  // ... and what the fullest of them has of the sample
+    auto even_shift = [&](u64 from) __attribute__((always_inline)) {
+        const u64 hi = ((u64)(top >> ent.kshift) << ent.ib) | ent.idx_max, range = hi > from ? hi - from : 1u;
+        const u32 width = 64u - (u32)__builtin_clzll(range);
+        return width > 12u ? width - 12u : 0u;
+    };
+    auto entry_at = [&](u32 i) __attribute__((always_inline)) {  // of what was gathered
+        const u32 at = sl->place[i], v = at / E;
+        return ent.of(sl->key[i], vector_of(v / kRun, v % kRun) * E + at % E - src.lead);
+    };
+    if (!gather) {
+        if (elements) T = sample_rank<B>(all, rank, rank <= lanes ? low >> ksh : 0u, top >> ksh, sm, &exact);
+        T <<= ksh;
+        if (exact) {  // (else T is no key with a crowd)
 #pragma unroll
-        for (int u = 0; u < V; ++u)
+            for (int u = 0; u < V; ++u) {
+                u32 c = 0;
 #pragma unroll
-            for (int j = 0; j < E; ++j) {
-                const u32 k = key_in_vector<DT>(q[u], j);
-                eq += k == T ? 1u : 0u;
-                crowd += k >= edge ? 1u : 0u;
+                for (int j = 0; j < E; ++j) {
+                    const u32 k = key_in_vector<DT>(q[u], j);
+                    eq += k == T ? 1u : 0u;
+                    c += k >= T ? 1u : 0u;
+                }
+                cnt += run_of(tid, (u32)u) < runs ? c : 0u;
             }
-        block_sum2<B>(eq, crowd, red);
+            cnt = wave_inclusive_scan(cnt);
+            eq = wave_inclusive_scan(eq);
+            if (lane == 63u) { red[2 * wave] = cnt; red[2 * wave + 1] = eq; }
+            __syncthreads();
+            cnt = sum_of_waves<B>(red, 2);
+            eq = sum_of_waves<B>(red + 1, 2);
+        }
     }
-    // the best finite key, where bins are set aside for infinities
-    constexpr u32 kSpecial = DT == RTOPK_F16 ? 0xfc000000u : 0xff800000u;  // (either direction)
-    const bool apart = L.nb != 0u && top >= kSpecial;
-    if (apart) {
-        u32 f = 0;
-#pragma unroll
-        for (int u = 0; u < V; ++u)
-#pragma unroll
-            for (int j = 0; j < E; ++j) {
-                const u32 k = key_in_vector<DT>(q[u], j);
-                f = k < kSpecial && k > f ? k : f;
+    if constexpr (GATHER) if (gather) {
+        static_assert(kRuns <= sizeof(sl->run) / 4, "a counter per run");
+        static_assert(kLeastThinned * kRun * E <= kSampleList, "thinned far enough");
+        while ((rank >> thin) > 128u && (runs >> thin) > kLeastThinned) ++thin;
+        bool fresh = true, again = false, dense = false;
+#pragma unroll 1
+        for (bool first = true;; first = false) {
+            if (elements && fresh) T = sample_rank<B>(all, rank, rank <= lanes && !again ? low >> ksh : 0u, top >> ksh, sm, &exact);
+            if (fresh && (elements || !again)) T <<= ksh;
+            const u32 every = (1u << thin) - 1u;
+            if (!first) {
+                __syncthreads();
+                for (u32 r = tid; r < runs; r += B) sl->run[r] = 0;
+                for (u32 j = tid; j < kListBins; j += B) sl->bin[j] = 0;
+                if (tid == 0) sl->n = 0;
+                __syncthreads();
             }
-        f = wave_reduce(f, MaxOf());
-        __syncthreads();
-        if (lane == 63u) red[wave] = f;
-        __syncthreads();
-        top = red[0];
+            u32 t0 = tid;
+            // (what follows from these is worked out here and not kept for the whole kernel: registers)
+            asm volatile("" : "+v"(t0));
+            forget();
+            if (ballot64(lmax >= T) != 0u) {
+                // f(vector, how many of its elements are not below T) for the runs that are kept
+                auto kept = [&](auto&& f) __attribute__((always_inline)) {
+                    static_for<0, V>([&](auto uc) __attribute__((always_inline)) {
+                        constexpr u32 u = (u32)decltype(uc)::value;
+                        __builtin_amdgcn_sched_barrier(0);  // (one vector at a time: registers)
+                        if ((u & every) != every / 2u) return;
+                        u32 c = 0;
 #pragma unroll
-        for (int w = 1; w < B / 64; ++w) top = top > red[w] ? top : red[w];
+                        for (int j = 0; j < E; ++j) c += key_in_vector<DT>(q[u], j) >= T ? 1u : 0u;
+                        f(uc, run_of(t0, u) < runs ? c : 0u);
+                    });
+                };
+                u32 mine = 0;
+                kept([&](auto, u32 c) __attribute__((always_inline)) { mine += c; });
+                const u32 incl = wave_inclusive_scan(mine);
+                u32 at = 0;
+                if (lane == 63u) at = atomicAdd(&sl->n, incl);
+                at = (u32)__builtin_amdgcn_readlane((int)at, 63) + incl - mine;
+                kept([&](auto uc, u32 c) __attribute__((always_inline)) {
+                    constexpr int u = decltype(uc)::value;
+                    if (ballot64(c != 0u) == 0) return;
+                    const u32 run = run_of(t0, (u32)u);
+                    u32 r = c;
+                    r += (u32)__builtin_amdgcn_update_dpp(0, (int)r, 0xb1, 0xf, 0xf, false);   // the neighbour's
+                    r += (u32)__builtin_amdgcn_update_dpp(0, (int)r, 0x4e, 0xf, 0xf, false);   // the other pair's
+                    r += (u32)__builtin_amdgcn_update_dpp(0, (int)r, 0x141, 0xf, 0xf, false);  // the other four's
+                    if (lane % kRun == 0u && r != 0u) sl->run[run] = r;
+#pragma unroll
+                    for (int j = 0; j < E; ++j) {
+                        const u32 k = key_in_vector<DT>(q[u], j);
+                        if (c != 0u && k >= T) {
+                            if (at < kSampleList) {
+                                sl->key[at] = k;
+                                sl->place[at] = (run * kRun + t0 % kRun) * (u32)E + (u32)j;
+                            }
+                            ++at;
+                        }
+                    }
+                });
+            }
+            __syncthreads();
+            got = sl->n;
+            fresh = false;
+            if (got > kSampleList) {
+                do { got >>= 1; ++thin; } while (got > kSampleList);
+                while ((runs >> thin) < kLeastThinned) --thin;  // (so many runs always fit: more than this many are left)
+                continue;
+            }
+            // how many of them equal T, the sum of the runs' squares, and how many lie in each of a long list's bins
+            u32 sq = 0;
+            eq_got = most = 0;
+            for (u32 r = tid; r < runs; r += B) sq += sl->run[r] * sl->run[r];
+            lo = (u64)(T >> ent.kshift) << ent.ib;
+            sh = even_shift(lo);
+            for (u32 i = tid; i < got; i += B) {
+                const u32 k = sl->key[i];
+                eq_got += k == T ? 1u : 0u;
+                if (bins && k != T) {
+                    const u32 before = atomicAdd(&sl->bin[list_bin(entry_at(i), lo, sh)], 1u);
+                    most = most > before ? most : before + 1u;
+                }
+            }
+            eq_got = wave_inclusive_scan(eq_got);
+            sq = wave_inclusive_scan(sq);
+            most = wave_reduce(most, MaxOf());
+            if (lane == 63u) { red[3 * wave] = eq_got; red[3 * wave + 1] = sq; red[3 * wave + 2] = most; }
+            __syncthreads();
+            eq_got = sum_of_waves<B>(red, 3);
+            sq = sum_of_waves<B>(red + 1, 3);
+            most = best_of_waves<B>(red + 2, 3, MaxOf());
+            cnt = got << thin;
+            eq = eq_got << thin;
+            const float v = got != 0u ? (float)sq / (float)got - (float)cnt / (float)runs : 0.0f;
+            if (v > 2.0f && thin != 0u && !dense) {  // (few draws: all there are are needed, for T and for splitters)
+                dense = true;
+                thin = 0;
+                continue;
+            }
+            // (a list holds at least what the sample has of it: nothing can go wrong from k on, twice k where runs meet)
+            const float need = ks + 4.0f * __builtin_sqrtf(ks * v) + 3.0f * v;
+            const u32 have = thin == 0u ? cnt : rank;  // (thinned, cnt is an estimate; it is no less than the rank)
+            if (whole || again || !(v > 2.0f) || !((float)have < need) || have >= 2u * rs.k) break;
+            rank = need < (float)elems ? (u32)need : elems;
+            elements = fresh = again = true;
+        }
     }
-    const u64 eq_row = (u64)eq * rs.n / kElems;
-    const bool tied = eq_row > (u64)kListTies && eq_row > (u64)rs.k;
+    // Most of the row may equal T, or so much that the list would be longer than half the row or than what is put in order in
+    // LDS: then what is better is listed and the equal elements are counted.
+    const u64 eq_row = (u64)eq * rs.n / elems, est = (u64)cnt * rs.n / elems;
+    const bool tied = !whole && eq != 0u && ((eq_row > (u64)kListTies && eq_row > (u64)rs.k) ||
+                                             (cnt > elems / 20u * 9u && cnt - eq < elems / 5u * 2u) ||
+                                             (est + est / 8u > (u64)room && (est - eq_row) * 4u < (u64)room * 3u));
     if (tied) {
         for (u32 j = tid; j < nt; j += B) te[j] = 0;
+    }
+    bool split = false;
+    if constexpr (GATHER) if (bins) {
+        if (!tied && most < eq_got) most = eq_got;  // (so many with one key)
+        // (a bin of several buckets' ranks -- up to there k_list_redo has it in order in no time -- and more of them than fall together by
+        // chance: 4096 bins, 2^28 keys, k = 2^20: about 400 draws)
+        split = most > 5u && ((u64)most << thin) * rs.n / elems > 8192u;
+        if (split) {
+            static_assert(sizeof(sm.hist) >= kListSplits * 8, "room for the candidates");
+            u64* cand = (u64*)sm.hist;
+            if (tid < kListSplits) cand[tid] = ~0ull >> 1;
+            __syncthreads();
+            const u32 total = tied ? got - eq_got : got;
+            for (u32 i = tid; i < got; i += B) {
+                if (tied && sl->key[i] == T) continue;
+                // every total / 256-th
+                const u32 pos = atomicAdd(&sl->next, 1u);
+                const u32 s0 = total > kListSplits ? pos * kListSplits / total : pos;
+                const u32 s1 = total > kListSplits ? (pos + 1u) * kListSplits / total : pos + 1u;
+                if (s0 != s1) cand[s0] = entry_at(i);
+            }
+            __syncthreads();
+            if (tid < kListSplits) {
+                const u64 c = cand[tid];
+                u32 r = 0;
+#pragma unroll 8
+                for (u32 i = 0; i < kListSplits; ++i) r += (cand[i] < c || (cand[i] == c && i < tid)) ? 1u : 0u;
+                u64* edge = list_part<u64>(P, row, L.split_off);
+                if (r != 0u) edge[r] = c;
+                if (tid == 0) {
+                    edge[0] = lo;
+                    edge[kListSplits] = 1ull << 63;
+                }
+            }
+        }
     }
     if (tid == 0) {
         lr->mode = tied ? kListTied : kListPlain;
@@ -475,7 +734,9 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
         const bool largest = P.dirmask == 0;
         const u64 o = T ^ P.dirmask;
         float t = 0.0f;
-        if (tied) {
+        if (whole) {
+            lr->exact = 1;
+        } else if (tied) {
             // the number whose key is T; not where equal numbers have different keys (the zeros, NaNs)
             t = number_of_key<DT>((u32)o);
             lr->exact = t == 0.0f || t != t;
@@ -483,32 +744,25 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
             lr->exact = !threshold_number<DT>(largest ? o : o + (DT == RTOPK_F32 ? 1u : 0x10000u), &t);
         }
         lr->t = t;
-        const u64 lo = (u64)(T >> ent.kshift) << ent.ib, hi = ((u64)(top >> ent.kshift) << ent.ib) | ent.idx_max;
-        const u64 range = hi > lo ? hi - lo : 1u;
-        const u32 width = 64u - (u32)__builtin_clzll(range);
         lr->lo = lo;
-        u32 sh = width > 12u ? width - 12u : 0u;
-        if (apart && (range >> sh) >= kListFinite) ++sh;
         lr->sh = sh;
-        lr->finite = apart ? kListFinite : kListBins;
-        lr->special = apart ? (u64)(kSpecial >> ent.kshift) << ent.ib : ~0ull;
-        st->pre_elems = kElems;
-        // (crowded keys: what a first digit could tell apart is less than an eighth of the row)
-        const bool crowded = (u64)crowd * 8u > (u64)kElems;
-        st->pre_bound = crowded ? 1u << d0 : T >> (32u - d0);
-        st->pre_missed = crowded ? 2u : 0u;
+        lr->split = split ? 1u : 0u;
+        st->pre_elems = elems;
+        st->pre_bound = T >> (32u - P.pass[0].bits);
     }
 }
 
 template <int DT, int B, int V>
 __global__ void __launch_bounds__(B) k_list_bound(Params P, ListPlan L) {
     __shared__ RankShared sm;
-    __shared__ u32 red[2 * (B / 64)];
+    __shared__ SampleList sl;
+    __shared__ u32 red[3 * (B / 64)];
     const int row = blockIdx.x;
     const RowShape rs = row_shape_scalar<DT>(P, row);
     ListSource<DT, false> src;  // (the smaller of the two sweeps' tiles: the larger number of them)
     src.init(rs);
-    bound_of_row<DT, B, V>(P, L, row, rs, row_state(P, row), list_row_out(P, row), list_part<u32>(P, row, L.tile_off), src.ntiles(), sm, red);
+    bound_of_row<DT, B, V, true>(P, L, row, rs, row_state(P, row), list_row_out(P, row), list_part<u32>(P, row, L.tile_off), src.ntiles(),
+                           L.nb != 0u ? ~0u : 8u * (u32)L.finish, sm, &sl, red);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -530,8 +784,8 @@ __device__ __forceinline__ u32 list_segment(const Source& src, u32 wg, u32 G, u3
 // Staged (raw bits, index) pairs -> entries at the workgroup's next free positions; LONG: counted into the histogram.
 // (Expanded in place: around a call the compiler keeps the tiles in flight in memory.)
 template <int DT, bool LONG>
-__device__ __forceinline__ void list_flush(u64* seg, Lds<u64>* buf, Lds<u32>* run, u32 fill, Lds<u32>* hist, const ListEntry& c,
-                                           const ListRow& lr, u32 lane) {
+__device__ __forceinline__ void list_flush(u64* seg, Lds<u64>* buf, Lds<u32>* run, u32 fill, Lds<u32>* hist, const u64* split,
+                                           const ListEntry& c, const ListRow& lr, u32 lane) {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     u32 base = 0;
     if (lane == 0) base = __hip_atomic_fetch_add(run, fill, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -541,7 +795,7 @@ __device__ __forceinline__ void list_flush(u64* seg, Lds<u64>* buf, Lds<u32>* ru
         const u64 e = c.of(KeyOf<DT>::key((u32)v) ^ c.dirmask, (u32)(v >> 32));
         ((Glb<u64>*)seg)[base + i] = e;
         if (LONG) {
-            __hip_atomic_fetch_add(hist + list_bin(e, lr.lo, lr.sh, lr.special, lr.finite, c.ib), 1u, __ATOMIC_RELAXED,
+            __hip_atomic_fetch_add(hist + (lr.split != 0u ? list_bin_split(e, split) : list_bin(e, lr.lo, lr.sh)), 1u, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_WORKGROUP);
         }
     }
@@ -672,6 +926,7 @@ __global__ void __launch_bounds__(LONG ? kLongBlock : kGridBlock, LONG ? 4 : DT 
     constexpr int B = LONG ? kLongBlock : kGridBlock, ST = LONG ? kListStageLong : kListStage;
     __shared__ uint2 stage[B / 64][ST];
     __shared__ u32 hist[LONG ? kListBins : 1];
+    __shared__ u64 split[LONG ? kListSplits + 1 : 1];
     __shared__ u32 run;
     typedef ListSource<DT, LONG, NT> Source;
     const u32 G = (u32)L.G;
@@ -684,15 +939,17 @@ __global__ void __launch_bounds__(LONG ? kLongBlock : kGridBlock, LONG ? 4 : DT 
     src.init(rs);
     const u32 tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     u64* seg = list_array(P, 1u, row) + list_segment(src, wg, G, src.ntiles());
-    if (LONG)
+    if (LONG) {
         for (u32 j = tid; j < kListBins; j += B) hist[j] = 0;
+        if (lr.split != 0u && tid <= kListSplits) split[tid] = list_part<u64>(P, row, L.split_off)[tid];
+    }
     if (tid == 0) run = 0;
     __syncthreads();
     const ListEntry ent = list_entry<DT>(P);
     uint2* buf = stage[wave];
     u32 fill = 0;
     auto flush = [&]() __attribute__((always_inline)) {
-        list_flush<DT, LONG>(seg, lds_words(buf), lds_word(&run), fill, lds_word(hist), ent, lr, lane);
+        list_flush<DT, LONG>(seg, lds_words(buf), lds_word(&run), fill, lds_word(hist), split, ent, lr, lane);
         fill = 0;
     };
     sweep_row<DT>(src, wg, G, lr, list_part<u32>(P, row, L.tile_off), P.dirmask, [&](const typename Source::Tile& cur, u32 m) __attribute__((always_inline)) {
@@ -733,7 +990,7 @@ __global__ void __launch_bounds__(LONG ? kLongBlock : kGridBlock, LONG ? 4 : DT 
 constexpr u32 kOrderCrowd = 256, kSplitCrowd = 256;
 template <int B>
 struct OrderShared {
-    u64 buf[8 * B];
+    u64 buf[8 * B + 4];  // (four more: they are compared four at a time)
     u32 hist[4 * B + 2];
     u32 wsum[B / 64];
     u64 red[2 * (B / 64)];
@@ -820,7 +1077,7 @@ __device__ __forceinline__ void order_scan(u32* h, u32 want, u32 crowd, bool sor
         c[i] = h[4 * tid + i];
         s += c[i];
     }
-    const u32 incl = block_inclusive_scan<B>(s, sm.wsum);
+    const u32 incl = block_scan<B>(s, sm.wsum);
     u32 r = incl - s;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -892,7 +1149,13 @@ __device__ __forceinline__ void order_in_lds(const Params& P, int row, const Row
                 const u32 s0 = from(j), s1 = to(j);
                 r = s0;
 #pragma unroll 1
-                for (u32 i = s0; i < s1; ++i) r += sm.buf[i] > e[j] ? 1u : 0u;
+                for (u32 i = s0; i < s1; i += 4u) {
+                    u64 b[4];
+#pragma unroll
+                    for (u32 x = 0; x < 4u; ++x) b[x] = sm.buf[i + x];
+#pragma unroll
+                    for (u32 x = 0; x < 4u; ++x) r += (b[x] > e[j] && i + x < s1) ? 1u : 0u;
+                }
             }
             rank[j / 2] = (j & 1) ? rank[j / 2] | r << 16 : r;
         }
@@ -1020,7 +1283,7 @@ __device__ __forceinline__ void order_entries(const Params& P, int row, const Ro
                 mask |= (first ? 1u : 0u) << i;
                 begins += first ? 1u : 0u;
             }
-            u32 slot = block_inclusive_scan<B>(begins, sm.wsum) - begins;  // (and everybody has read sm.sp)
+            u32 slot = block_scan<B>(begins, sm.wsum) - begins;  // (and everybody has read sm.sp)
             u32* beg = (u32*)sm.buf;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
@@ -1046,6 +1309,29 @@ __device__ __forceinline__ void order_entries(const Params& P, int row, const Ro
     }
 }
 
+// f(entry, of(entry)) for all of src[0 .. count), eight loads in flight per thread (and eight chains of what `of` looks up in LDS).
+template <int B, class Of, class F>
+__device__ __forceinline__ void order_pass(const u64* src, u32 count, Of&& of, F&& f) {
+    constexpr u32 kAhead = 8;
+    u32 i = threadIdx.x;
+#pragma unroll 1
+    for (; (u64)i + (kAhead - 1u) * B < count; i += kAhead * B) {
+        u64 e[kAhead];
+#pragma unroll
+        for (u32 j = 0; j < kAhead; ++j) e[j] = src[i + j * B];
+        u32 x[kAhead];
+#pragma unroll
+        for (u32 j = 0; j < kAhead; ++j) x[j] = of(e[j]);
+#pragma unroll
+        for (u32 j = 0; j < kAhead; ++j) f(e[j], x[j]);
+    }
+#pragma unroll 1
+    for (; i < count; i += B) {
+        const u64 e = src[i];
+        f(e, of(e));
+    }
+}
+
 // Entries of src[0 .. count) in [lo, hi) to buf; returns how many there are (up to 8 B are kept).  Begins and ends with a barrier.
 template <int B>
 __device__ __forceinline__ u32 order_gather(const u64* src, u32 count, u64 lo, u64 hi, OrderShared<B>& sm, u32* run) {
@@ -1053,14 +1339,12 @@ __device__ __forceinline__ u32 order_gather(const u64* src, u32 count, u64 lo, u
     __syncthreads();
     if (tid == 0) *run = 0;
     __syncthreads();
-#pragma unroll 4
-    for (u32 i = tid; i < count; i += B) {
-        const u64 e = src[i];
+    order_pass<B>(src, count, [](u64) { return 0u; }, [&](u64 e, u32) __attribute__((always_inline)) {
         if (e >= lo && e < hi) {
             const u32 at = atomicAdd(run, 1u);
             if (at < 8u * B) sm.buf[at] = e;
         }
-    }
+    });
     __syncthreads();
     return *run;
 }
@@ -1079,11 +1363,9 @@ __device__ __forceinline__ void order_in_chunks(const Params& P, int row, const 
             for (u32 j = tid; j < 4u * B; j += B) sm.hist[j] = 0;
             if (tid == 0) sm.sp = 4u * B;
             __syncthreads();
-#pragma unroll 4
-            for (u32 i = tid; i < count; i += B) {
-                const u64 e = src[i];
+            order_pass<B>(src, count, [](u64) { return 0u; }, [&](u64 e, u32) __attribute__((always_inline)) {
                 if (e >= a && e < hi) atomicAdd(&sm.hist[(u32)((hi - 1u - e) >> sh)], 1u);
-            }
+            });
             __syncthreads();
             order_scan<B>(sm.hist, 8u * B + 1u, ~0u, false, sm);  // sp: the first bin whose end lies beyond 8 B entries
             const u32 bins = sm.sp;
@@ -1119,6 +1401,47 @@ __device__ __forceinline__ void order_shared(const Params& P, int row, const Row
     constexpr u32 kCap = 8 * B, kRun = kCap * 3 / 4, kBig = kCap / 4;
     const u32 tid = threadIdx.x, want = rs.k - rank0 < count ? rs.k - rank0 : count;
     __syncthreads();
+    // Little is wanted of much: a bound from 8 B entries at equal distances, and one pass that gathers what is not below it.
+    {
+        const float ks = (float)want * ((float)kCap / (float)count);
+        const u32 rank = (u32)(ks + 5.0f * __builtin_sqrtf(ks) + 5.0f);
+        if (count > kCap && (u64)rank * count < (u64)kCap * (kCap / 8u * 7u)) {
+            if (part != 0u) return;
+            u64 e[8], lo = ~0ull, hi = 0;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) e[j] = src[(u64)(tid + (u32)j * B) * count / kCap];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                lo = lo < e[j] ? lo : e[j];
+                hi = hi > e[j] ? hi : e[j];
+            }
+            order_range<B>(lo, hi, sm);
+            u32 left = rank;
+            for (;;) {  // [lo, hi] holds the entry in question
+                const u32 sh = order_shift<B>(hi - lo);
+                __syncthreads();
+                for (u32 j = tid; j < 4u * B; j += B) sm.hist[j] = 0;
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (e[j] >= lo && e[j] <= hi) atomicAdd(&sm.hist[(u32)((hi - e[j]) >> sh)], 1u);
+                __syncthreads();
+                order_scan<B>(sm.hist, left, ~0u, false, sm);
+                const u32 b = sm.sp, s0 = sm.hist[b], inside = b + 1u < 4u * B ? sm.hist[b + 1u] - s0 : 0u;
+                left -= s0;
+                hi -= (u64)b << sh;
+                lo = hi - lo > (1ull << sh) - 1u ? hi - ((1ull << sh) - 1u) : lo;
+                if (sh == 0u || (b + 1u < 4u * B && inside <= 4u + rank / 8u)) break;
+            }
+            const u32 n = order_gather<B>(src, count, lo, ~0ull, sm, &sp.run);
+            if (n >= want && n <= kCap) {
+                order_in_lds<DT, B>(P, row, rs, sm, n, rank0, [&](u32 i) __attribute__((always_inline)) { return sm.buf[i]; });
+                return;
+            }
+            __syncthreads();
+            parts = 1;  // (an unlucky draw: everything, alone)
+        }
+    }
     if (count <= kCap) {
         if (part == 0u) order_in_lds<DT, B>(P, row, rs, sm, count, rank0, [&](u32 i) __attribute__((always_inline)) { return src[i]; });
         return;
@@ -1128,8 +1451,8 @@ __device__ __forceinline__ void order_shared(const Params& P, int row, const Row
     for (u32 done = 0;;) {
         for (u32 j = tid; j < 4u * B + 2u; j += B) sm.hist[j] = 0;
         __syncthreads();
-#pragma unroll 4
-        for (u32 i = tid; i < count; i += B) atomicAdd(&sm.hist[Split::bin(sp.edge, src[i])], 1u);
+        order_pass<B>(src, count, [&](u64 e) __attribute__((always_inline)) { return Split::bin(sp.edge, e); },
+                      [&](u64, u32 bin) __attribute__((always_inline)) { atomicAdd(&sm.hist[bin], 1u); });
         __syncthreads();
         order_scan<B>(sm.hist, want, ~0u, false, sm);
         if (tid == 0) sm.hist[4 * B] = count;
@@ -1144,7 +1467,7 @@ __device__ __forceinline__ void order_shared(const Params& P, int row, const Row
             mask |= (first ? 1u : 0u) << i;
             begins += first ? 1u : 0u;
         }
-        u32 slot = block_inclusive_scan<B>(begins, sm.wsum) - begins;
+        u32 slot = block_scan<B>(begins, sm.wsum) - begins;
         const u32 last = sm.sp;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -1190,10 +1513,10 @@ __device__ __forceinline__ void list_record(rtopk_row_trace* st, const RowShape&
     st->pass_rec[0].cand_after = 0;
     st->pass_rec[0].winners = rs.k;
     st->pass_rec[0].out_before = 0;
-    st->pass_rec[0].cand_before = st->pre_missed == 2u ? rs.n : listed;
+    st->pass_rec[0].cand_before = listed;
     st->pass_rec[0].window = SRC_RANK;
     st->pass_rec[0].where = where;
-    if (st->pre_missed != 2u) st->pre_kept = listed;
+    st->pre_kept = listed;
 }
 
 // Elements equal to T, lowest positions first, to the output behind the `listed` better ones.  Workgroup w of nw takes the
@@ -1213,7 +1536,7 @@ __device__ __forceinline__ bool ties_of_row(const Params& P, const u32* te, int 
     for (u32 t0 = 0; t0 < ntiles; t0 += B) {
         const u32 c = t0 + tid < ntiles ? __hip_atomic_load(&te[t0 + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
         __syncthreads();
-        const u32 incl = block_inclusive_scan<B>(c, wsum);
+        const u32 incl = block_scan<B>(c, wsum);
         before[tid] = base + incl - c;
         if (tid == B - 1) before[B] = base + incl;
         __syncthreads();
@@ -1239,7 +1562,7 @@ __device__ __forceinline__ bool ties_of_row(const Params& P, const u32* te, int 
                 }
                 const u32 n = (u32)__builtin_popcount(hit);
                 __syncthreads();  // (wsum's last readers are done)
-                const u32 incl = block_inclusive_scan<B>(n, wsum);
+                const u32 incl = block_scan<B>(n, wsum);
                 u32 pos = begin + incl - n;
 #pragma unroll
                 for (u32 w = 0; w < (u32)(B / 64); ++w) begin += wsum[w];  // (the scan leaves every wave's sum there)
@@ -1258,7 +1581,7 @@ __device__ __forceinline__ bool ties_of_row(const Params& P, const u32* te, int 
 }
 
 // The list of one row into the output.  Blocks [0, batch): a row each.  Blocks beyond: L.ties per row, for rows whose
-// equal elements were counted.
+// equal elements were counted, and for lists that one workgroup cannot put in order in LDS.
 template <int DT, int B>
 __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     __shared__ OrderShared<B> sm;
@@ -1268,7 +1591,7 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     const int row = for_ties ? (int)((blockIdx.x - (u32)P.batch) / (u32)L.ties) : (int)blockIdx.x;
     const ListRow* lr = list_row(P, row);
     const u32 mode = lr->mode;
-    if (mode == kListSkip || (for_ties && mode != kListTied)) return;
+    if (mode == kListSkip) return;
     const RowShape rs = row_shape_scalar<DT>(P, row);
     rtopk_row_trace* st = row_state(P, row);
     // the segments' beginnings in the list
@@ -1276,31 +1599,14 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     u32 total = 0;
     for (u32 s0 = 0; s0 < (u32)L.G; s0 += B) {
         const u32 c = s0 + tid < (u32)L.G ? counts[s0 + tid] : 0u;
-        const u32 incl = block_inclusive_scan<B>(c, sm.wsum);
+        const u32 incl = block_scan<B>(c, sm.wsum);
         if (s0 + tid < (u32)L.G) segs[s0 + tid] = total + incl - c;
         if (tid == B - 1) segs[1024] = total + incl;
         __syncthreads();
         total = segs[1024];
         __syncthreads();
     }
-    if (for_ties) {
-        const u32 w = (blockIdx.x - (u32)P.batch) % (u32)L.ties;
-        if (total < rs.k && !ties_of_row<DT, B, ListSource<DT, false>>(P, list_part<u32>(P, row, L.tile_off), row, rs, total, lr->T, w, (u32)L.ties,
-                                                               sm.hist, sm.wsum) && w == 0 && tid == 0) {
-            st->redo_why = 8u;
-            atomicOr(&st->redo, kRedoRow);
-        }
-        return;
-    }
-    if ((mode == kListPlain && total < rs.k) || total > (u32)((P.n + 1) / 2)) {
-        if (tid == 0) {
-            st->redo_why = total < rs.k ? 8u : 5u;
-            atomicOr(&st->redo, kRedoRow);
-        }
-        return;
-    }
-    if (tid == 0) list_record(st, rs, total, 5u);
-    if (total == 0) return;
+    const bool useless = (mode == kListPlain && total < rs.k) || total > (u32)((P.n + 1) / 2);
     ListSource<DT, false> src;
     src.init(rs);
     const u32 ntiles = src.ntiles();
@@ -1315,6 +1621,26 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
         const u32 at = L.seg_stride != 0u ? a * L.seg_stride : list_segment(src, a, (u32)L.G, ntiles);
         return from[at + (i - segs[a])];
     };
+    if (for_ties) {
+        const u32 w = (blockIdx.x - (u32)P.batch) % (u32)L.ties;
+        if (total > 8u * B && !useless)  // more than LDS holds: the segments are put together for k_list_redo
+            for (u32 i = w * B + tid; i < total; i += (u32)L.ties * B) dst[i] = entry(i);
+        if (mode == kListTied && total < rs.k && !ties_of_row<DT, B, ListSource<DT, false>>(P, list_part<u32>(P, row, L.tile_off), row, rs, total, lr->T, w, (u32)L.ties,
+                                                               sm.hist, sm.wsum) && w == 0 && tid == 0) {
+            st->redo_why = 8u;
+            atomicOr(&st->redo, kRedoRow);
+        }
+        return;
+    }
+    if (useless) {
+        if (tid == 0) {
+            st->redo_why = total < rs.k ? 8u : 5u;
+            atomicOr(&st->redo, kRedoRow);
+        }
+        return;
+    }
+    if (tid == 0) list_record(st, rs, total, 5u);
+    if (total == 0) return;
     // (a list that fewer waves can put in order is left to them: barriers)
     if (B > 256 && total <= 8u * 256u) {
         if (tid >= 256u) return;
@@ -1325,7 +1651,6 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     } else if (total <= 8u * B) {
         order_in_lds<DT, B>(P, row, rs, sm, total, 0u, entry);
     } else {
-        for (u32 i = tid; i < total; i += B) dst[i] = entry(i);
         if (tid == 0) {
             list_done(P, row)->total = total;
             list_done(P, row)->end = 0u;
@@ -1467,7 +1792,7 @@ __device__ __forceinline__ u32 hold_and_list(const Params& P, const RowShape& rs
         m[g] = worse ^ (0xffffffffu >> (32 - Source::kSlots));
         mine += (u32)__builtin_popcount(m[g]);
     });
-    u32 pos = odd + block_inclusive_scan<B>(mine, sm.part) - mine;  // this lane's place in the list
+    u32 pos = odd + block_scan<B>(mine, sm.part) - mine;  // this lane's place in the list
     u32 listed = odd;
 #pragma unroll
     for (int w = 0; w < B / 64; ++w) listed += sm.part[w];
@@ -1544,7 +1869,7 @@ __device__ __forceinline__ u32 hold_and_list(const Params& P, const RowShape& rs
             for (u32 j = 0; j < E; ++j) hit |= (v * E + j - src.lead < rs.n && key_in_vector<DT>(q, (int)j) == Tk ? 1u : 0u) << j;
         }
         const u32 n = (u32)__builtin_popcount(hit);
-        u32 at = listed + block_inclusive_scan<B>(n, sm.part) - n;
+        u32 at = listed + block_scan<B>(n, sm.part) - n;
         for (; hit != 0u && at < rs.k; hit &= hit - 1u, ++at) sm.ord.buf[at] = ent.of(Tk, v * E + (u32)__builtin_ctz(hit) - src.lead);
 #pragma unroll
         for (int w = 0; w < B / 64; ++w) listed += sm.part[w];
@@ -1623,7 +1948,7 @@ __global__ void __launch_bounds__(B, 4) k_list_row(Params P, ListPlan L) {
     constexpr int OB = B < 256 ? B : 256;  // threads that order a short list (see k_list_held)
     __shared__ union { OrderShared<B> ord; OrderShared<OB> few; RankShared rank; } sm;
     __shared__ ListRow lr;
-    __shared__ u32 red[2 * (B / 64)], te[kListRowTiles], run;
+    __shared__ u32 red[3 * (B / 64)], te[kListRowTiles], run;
     constexpr u32 kCap = 8 * B;
     typedef KeySource<DT, B, 4, NT> Source;
     const int row = blockIdx.x;
@@ -1632,14 +1957,13 @@ __global__ void __launch_bounds__(B, 4) k_list_row(Params P, ListPlan L) {
     rtopk_row_trace* st = row_state(P, row);
     Source src;
     src.init(rs);
-    bound_of_row<DT, B, V>(P, L, row, rs, st, &lr, te, src.ntiles(), sm.rank, red);
+    bound_of_row<DT, B, V, false>(P, L, row, rs, st, &lr, te, src.ntiles(), kCap, sm.rank, nullptr, red);
     if (tid == 0) run = 0;
     __syncthreads();
     if (lr.mode == kListSkip) return;
     const ListRow b = list_row_scalar(&lr);
     const ListEntry ent = list_entry<DT>(P);
     u64* list = list_array(P, 1u, row);
-    const u32 room = (u32)((P.n + 1) / 2);
     sweep_row<DT>(src, 0u, 1u, b, te, P.dirmask, [&](const typename Source::Tile& cur, u32 m) __attribute__((always_inline)) {
         for (;;) {
             const u64 have = ballot64(m != 0u);
@@ -1653,15 +1977,15 @@ __global__ void __launch_bounds__(B, 4) k_list_row(Params P, ListPlan L) {
                 const u32 pos = base + mbcnt64(have);
                 const u64 e = ent.of(KeyOf<DT>::key(pick<Source>(cur, s)) ^ P.dirmask, element_index(src, cur.tile, s));
                 if (pos < kCap) sm.ord.buf[pos] = e;
-                else if (pos < room) list[pos] = e;
+                else list[pos] = e;
             }
         }
     });
     __syncthreads();
     const u32 total = run;
-    if ((b.mode == kListPlain && total < rs.k) || total > room) {
+    if (b.mode == kListPlain && total < rs.k) {
         if (tid == 0) {
-            st->redo_why = total < rs.k ? 8u : 5u;
+            st->redo_why = 8u;
             atomicOr(&st->redo, kRedoRow);
         }
         return;
@@ -1702,6 +2026,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     constexpr int B = kLongBlock, kPer = kListBins / B;
     __shared__ u32 start[kListBins];         // rank of every bin
     __shared__ u32 place[kListMaxBuckets];   // of every bucket: this workgroup's entries, then their next place
+    __shared__ u64 split[kListSplits + 1];
     __shared__ u32 wsum[B / 64];
     __shared__ u32 s_end;
     const u32 G = (u32)L.G, tid = threadIdx.x;
@@ -1712,8 +2037,9 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     if (mode == kListSkip) return;
     const RowShape rs = row_shape_scalar<DT>(P, row);
     rtopk_row_trace* st = row_state(P, row);
-    const u64 lo = lr->lo, special = lr->special;
-    const u32 sh = lr->sh, finite = lr->finite, ib = list_entry<DT>(P).ib;
+    const u64 lo = lr->lo;
+    const u32 sh = lr->sh, by_split = __builtin_amdgcn_readfirstlane(lr->split);
+    if (by_split != 0u && tid <= kListSplits) split[tid] = list_part<u64>(P, row, L.split_off)[tid];
     ListSource<DT, true> src;
     src.init(rs);
     const u64* from = list_array(P, 1u, row) + list_segment(src, wg, G, src.ntiles());
@@ -1732,7 +2058,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     }
     for (u32 j = tid; j < nb; j += B) place[j] = 0;
     if (tid == 0) s_end = 0;
-    const u32 incl = block_inclusive_scan<B>(s, wsum);
+    const u32 incl = block_scan<B>(s, wsum);
     u32 total = 0;
     {
         u32 r = incl - s;
@@ -1748,7 +2074,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     total = start[0] + gh[0];
     const bool few = total < rs.k;
     const u32 end = few ? total : s_end;
-    const bool drop = (mode == kListPlain && few) || total > (u32)((P.n + 1) / 2);
+    const bool drop = (mode == kListPlain && few) || end > (u32)((P.n + 1) / 2);  // (the buckets have half a candidate array)
     if (wg == 0 && tid == 0) *list_done(P, row) = ListDone{total, end, drop ? 1u : 0u, 0u};
     if (drop) {
         if (wg == 0 && tid == 0) {
@@ -1779,7 +2105,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
         __syncthreads();
     }
     auto bucket_of = [&](u64 e) __attribute__((always_inline)) {
-        const u32 r = start[list_bin(e, lo, sh, special, finite, ib)];
+        const u32 r = start[by_split != 0u ? list_bin_split(e, split) : list_bin(e, lo, sh)];
         return r < end ? r >> bs : 0xffffffffu;
     };
     // (what the registers hold of the segment is on its way before the ranks are known)
@@ -1971,7 +2297,7 @@ __global__ void __launch_bounds__(kListBucketBlock) k_list_redo(Params P, ListPl
                     u32 at = 0, count = 0, n = 0;
                     if (j0 + tid < L.nb && bucket_range(P, L, row, rs, j0 + tid, &at, &count) && count > 8u * B) n = (count + 4u * B - 1u) / (4u * B);
                     __syncthreads();
-                    const u32 incl = block_inclusive_scan<B>(n, sm.ord.wsum);
+                    const u32 incl = block_scan<B>(n, sm.ord.wsum);
                     before[tid] = incl - n;
                     if (tid == B - 1) run = incl;
                     __syncthreads();

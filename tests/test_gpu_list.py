@@ -8,7 +8,7 @@ import oracle
 from paper_2501_14336_amd import workloads as W
 from tests import verify
 from tests.gpu_util import BF16, F16, F32, gpu_topk, to_device
-from tests.test_gpu_ragged import _check_ragged
+from tests.test_gpu_ragged import _check_ragged, _run_ragged
 
 pytestmark = pytest.mark.gpu
 LIST = (4, 5)  # rtopk_row_trace: where
@@ -255,3 +255,82 @@ def test_crowds_in_order(dtype):
                 for largest in (True, False):
                     _check("crowd of " + name, x.astype(np.float32), dtype, k, largest, batch=2, sorted=True)
                     _check("crowd of " + name, x.astype(np.float32), dtype, k, largest, batch=2, sorted=False)
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+def test_crowds_around_what_the_samples_gathering_holds(dtype):
+    # the sampled positions hold one value, as many of them as the gathered list holds, one more, and so on up to all of them:
+    # the gathering is thinned until it fits, and ends
+    n, vectors = 400000, 4096 if dtype == F32 else 2048
+    elems = 4 if dtype == F32 else 8
+    pos = np.unique(_sampled(n, vectors, elems))
+    for crowd in (4096, 4097, 4098, 8191, 8192, 8193, 8200, 16000):
+        crowd = min(crowd, len(pos))
+        x = -np.abs(W.normal(n, 35)) - 1.0
+        x[pos[:crowd]] = 5.0
+        for k in (3, 9000):
+            for largest in (True, False):
+                gv, gi, tr, _ = gpu_topk(to_device(_bits(x if largest else -x, dtype), dtype), dtype, k, largest, sorted=True)
+                wv, wi = oracle.topk(_bits(x if largest else -x, dtype), dtype, k, largest)
+                print("crowd", dtype, crowd, k, largest, tr[0].redo, flush=True)
+                assert np.array_equal(gi, wi) and np.array_equal(gv, wv) and tr[0].error == 0
+
+
+@pytest.mark.parametrize("dtype", [F32, F16])
+@pytest.mark.parametrize("values", [2, 3, 4, 8])
+def test_few_values_never_fill_the_list(dtype, values):
+    # equally frequent values, k between them: better and equal elements together are more than half the row, though neither is
+    for n in (40000, 300007, 1 << 20):
+        x = np.floor(W.uniform01(n, 71) * values).astype(np.float32)
+        for share in (0.26, 0.3, 0.34, 0.38):
+            for largest in (True, False):
+                tr = _check("%d values" % values, x, dtype, int(share * n), largest, by_list=None)
+                assert tr[0].redo & 1 == 0
+
+
+@pytest.mark.parametrize("far", [np.float32(3.4e38), np.float32(1.0e9), np.float32(np.inf), np.float32(np.nan)])
+def test_bins_do_not_follow_the_distance_to_a_few_keys(far):
+    # one key in 2048 (NaN: in 200) lies far above the rest: the others share the long list's bins, so no bucket is too large
+    n = 1 << 22
+    u = W.uniform01(n, 72)
+    for x in (W.uniform01(n, 73), W.normal(n, 74)):
+        y = np.where(u < (1 / 200 if far != far else 1 / 2048), far, x).astype(np.float32)
+        for k in (1 << 16, 1 << 18):
+            tr = _check("far %r" % far, y, F32, k, by_list=True)
+            assert tr[0].redo == 0, tr[0].redo
+            if far == far:
+                tr = _check("far %r" % -far, -y, F32, k, largest=False)
+                assert tr[0].redo == 0, tr[0].redo
+
+
+def test_crowd_of_nans_at_the_top_is_counted():
+    # more NaNs than k: T is the NaNs' key, the last there is (the last of an even division's bins reaches beyond 32 bits)
+    n = 1 << 22
+    x = np.where(W.uniform01(n, 75) < 0.05, np.float32(np.nan), W.normal(n, 76)).astype(np.float32)
+    for k in (40000, 100000):
+        tr = _check("NaNs", x, F32, k)
+        assert tr[0].redo == 0 and tr[0].pre_kept == 0
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+def test_blocks_of_one_value_are_few_draws(dtype):
+    # 64 neighbours each have one value: the sample's lines are as many draws, not its elements; no row of these is done again
+    n = 1 << 21
+    for seed in range(6):
+        x = np.repeat(W.normal(n // 64, 80 + seed), 64)
+        for k in (3000, n // 100, n // 10, n // 3):
+            tr = _check("blocks", x, dtype, k, largest=seed % 2 == 0)
+            assert tr[0].redo & 1 == 0
+
+
+def test_rows_far_shorter_than_the_longest_have_samples_of_their_own():
+    # a ragged batch: the sample's size goes by the longest row, but a row that is short against it is not listed whole
+    lens = [50000] * 20 + [1 << 22] + [300, 1537, 3000, 12000, 98304, 98303]
+    for dtype in (F32, BF16):
+        rows = [_bits(W.normal(n, 90 + r, sigma=3.0), dtype) for r, n in enumerate(lens)]
+        for kk in (100, 2000):
+            ks = [min(n, kk) for n in lens]
+            for srt in (False, True):
+                _check_ragged("short rows", rows, dtype, ks, True, None, srt)
+                for tr, n in zip(_run_ragged(rows, dtype, ks, True, None, srt, False)[2], lens):
+                    assert tr.redo == 0 and (n < 20000 or tr.pre_kept < n // 3), (n, tr.redo, tr.pre_kept)
