@@ -831,6 +831,10 @@ __device__ __forceinline__ u32 shift_in_not_above(u32 bits, float x, float t) {
     asm("v_cmp_ge_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(t), "v"(x) : "vcc");
     return bits;
 }
+__device__ __forceinline__ u32 shift_in_not_up_to(u32 bits, float x, float t) {  // !(x <= t): true for NaNs
+    asm("v_cmp_nge_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(t), "v"(x) : "vcc");
+    return bits;
+}
 // That for the elements of a full tile, the first element's bit on top.  (Inverted for "largest", where NaNs are wanted; as
 // it is for "smallest".)
 template <class Source>
@@ -1733,7 +1737,7 @@ __device__ __forceinline__ u32 hold_and_list(const Params& P, const RowShape& rs
     };
     // the order of numbers as 32-bit keys (those of fp32, for every type)
     auto key_of_number = [&](float x) __attribute__((always_inline)) { return KeyOf<RTOPK_F32>::key(__float_as_uint(x)) ^ (largest ? 0u : 0xffffffffu); };
-    u32 T;
+    u32 T, top;
     bool exact;
     {
         float m = best_of_vector(t[0], std::integral_constant<int, 0>{});
@@ -1746,7 +1750,8 @@ __device__ __forceinline__ u32 hold_and_list(const Params& P, const RowShape& rs
         });
         forget();
         const u32 lmax = key_of_number(m);
-        u32 top = wave_reduce(lmax, MaxOf()), low = wave_reduce(lmax, MinOf());
+        top = wave_reduce(lmax, MaxOf());
+        u32 low = wave_reduce(lmax, MinOf());
         if (lane == 63u) {
             sm.part[2 * wave] = top;
             sm.part[2 * wave + 1] = low;
@@ -1786,7 +1791,7 @@ __device__ __forceinline__ u32 hold_and_list(const Params& P, const RowShape& rs
         u32 worse = 0;
         static_for<0, Source::kSlots>([&](auto sc) __attribute__((always_inline)) {
             const float v = src.template value<SRC_KEY>(t[g], decltype(sc)::value, 0.0f);
-            worse = largest ? shift_in_below(worse, v, x) : shift_in_below(worse, x, v);
+            worse = largest ? shift_in_below(worse, v, x) : shift_in_not_up_to(worse, v, x);  // (NaNs are the best, or the worst)
         });
         __builtin_amdgcn_sched_barrier(0);
         m[g] = worse ^ (0xffffffffu >> (32 - Source::kSlots));
@@ -1839,9 +1844,44 @@ __device__ __forceinline__ u32 hold_and_list(const Params& P, const RowShape& rs
     const u32 from = p0 == 0u ? 0u : p0 * E - src.lead, to = pend * E - src.lead < rs.n ? pend * E - src.lead : rs.n;
     const u32 size = pend > p0 ? to - from : 0u;
     u32 Tk = 0;
-    if (size > limit)  // (a stretch that the list holds whole needs no bound)
-        Tk = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) { all([&](u32 key, u32) __attribute__((always_inline)) { f(key); }); }, rs.k,
-                            0u, 0xffffffffu, sm.rank, &exact);
+    if (size > limit) {  // (a stretch that the list holds whole needs no bound)
+        // It lies between T and the best number (crowds: often the same, and there is nothing left to do), or among the NaNs, which
+        // were passed over.  Elements' keys; a fp16 number near T is rounded, hence one key lower.  (Elements outside
+        // whole vectors are no part of those: they count as better where they are.)
+        constexpr u32 ksh = DT == RTOPK_F32 ? 0u : 16u;
+        auto key_of = [&](u32 k32) __attribute__((always_inline)) {
+            if constexpr (DT != RTOPK_F16) {
+                return k32 >> ksh;
+            } else {
+                const u32 o = largest ? k32 : ~k32;
+                const float f = __uint_as_float((o & 0x80000000u) ? o ^ 0x80000000u : ~o);
+                return (KeyOf<DT>::key((u32)__builtin_bit_cast(uint16_t, (_Float16)f)) ^ P.dirmask) >> ksh;
+            }
+        };
+        const u32 last_key = 0xffffffffu >> ksh;
+        u32 lo = bounded ? key_of(T) : 0u, hi = key_of(top), rank = rs.k, above = 0;
+        if (DT == RTOPK_F16 && lo != 0u) --lo;
+        all([&](u32 key, u32) __attribute__((always_inline)) { above += (key >> ksh) > hi ? 1u : 0u; });
+        above = wave_inclusive_scan(above);
+        __syncthreads();
+        if (lane == 63u) sm.part[wave] = above;
+        __syncthreads();
+        above = sum_of_waves<B>(sm.part, 1);
+        if (above >= rank) {
+            lo = hi + 1u;
+            hi = last_key;
+        } else {
+            rank -= above;
+        }
+        if (lo >= hi) {
+            Tk = hi;
+            exact = true;
+        } else {
+            Tk = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) { all([&](u32 key, u32) __attribute__((always_inline)) { f(key >> ksh); }); },
+                                rank, lo, hi, sm.rank, &exact);
+        }
+        Tk <<= ksh;
+    }
     bool tied = false;
     for (;;) {  // what is not below it; if that is too much, what is above it
         if (tid == 0) sm.run = 0;

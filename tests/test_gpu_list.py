@@ -334,3 +334,18 @@ def test_rows_far_shorter_than_the_longest_have_samples_of_their_own():
                 _check_ragged("short rows", rows, dtype, ks, True, None, srt)
                 for tr, n in zip(_run_ragged(rows, dtype, ks, True, None, srt, False)[2], lens):
                     assert tr.redo == 0 and (n < 20000 or tr.pre_kept < n // 3), (n, tr.redo, tr.pre_kept)
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+def test_nans_are_no_part_of_the_smallest(dtype):
+    # held rows: a NaN is not below the bound on either side, so it has to be left out by name; otherwise every NaN is listed and ordered
+    for n in (4096, 16384, 30000):
+        x = np.where(W.uniform01(n, 77) < 0.05, np.float32(np.nan), W.normal(n, 78)).astype(np.float32)
+        tr = _check("NaNs", x, dtype, 30, largest=False)
+        assert tr[0].pre_kept < 100, tr[0].pre_kept
+        # fewer numbers than k: NaNs follow them, and held rows that crowd at their bound
+        z = np.where(W.uniform01(n, 79) < 0.9, np.float32(np.nan), W.normal(n, 78)).astype(np.float32)
+        for k in (50, n // 8):
+            for largest in (True, False):
+                _check("mostly NaNs", z, dtype, k, largest, sorted=True)
+                _check("crowd at the top", np.minimum(x, 1.0), dtype, k, largest, sorted=True)
