@@ -250,11 +250,21 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
             if (n > 8 * h.block && k + k / 16 + 2 > 8 * h.block) continue;  // the list's room
             if (n > 8 * h.block && h.vecs == 16 && k > h.block / 2) continue;  // (bounded by the lanes' best elements only)
             if (batch > h.rows) break;
+            // Unsorted output of a larger part of a row: the list is ranked for nothing, the digit passes write their winners as they
+            // find them (in one launch as well).  us, digit passes / list, normal keys: one fp32 row of 4096, k = 100 12 / 9, k = 409 13 / 12,
+            // k = 1000 13 / 17, of 16384, k = 1000 17 / 15, k = 4915 20 / 20; keys of 100 values, k = 1228 of 4096, 13 / 47.  16-bit keys, whose
+            // vectors' maxima bound less: 4096, k = 40 11 / 9, k = 100 11 / 13, k = 409 11 / 23; 16384, k = 100 12 / 11, k = 1638 15 / 31.  Many
+            // rows: a smaller workgroup per row wins by far up to a quarter of the row (1024 fp32 rows of 4096, k = 1228, 58 / 26; 1024 fp16
+            // rows of 16384, k = 1638, 69 / 54, k = 4915 61 / 88).
+            if (!sorted && (batch <= 512 ? k * (eb == 4 ? 16 : 64) > n : n > 8192 && k * 4 > n)) return false;
             L->row_block = h.block;
             L->held = h.vecs;
             return true;
         }
     }
+    // The same for rows that one workgroup sweeps: one fp32 row of 16384, k = 4915, 20 / 23, of 30000, k = 3000, 26 / 24; fp16 rows of 30000,
+    // k = 3000, 23 / 31, of 50257, k = 5025, 38 / 33.
+    if (!sorted && batch <= 512 && n <= 40000 && k * (eb == 4 ? 4 : 16) > n) return false;
     // the smallest sample is 8 KB of a row, a quarter of 32 KB
     if (n * eb < 32768) return false;
     // the list is to stay below half the row (in a ragged batch: half the longest row, for every row)

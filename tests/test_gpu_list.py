@@ -349,3 +349,15 @@ def test_nans_are_no_part_of_the_smallest(dtype):
             for largest in (True, False):
                 _check("mostly NaNs", z, dtype, k, largest, sorted=True)
                 _check("crowd at the top", np.minimum(x, 1.0), dtype, k, largest, sorted=True)
+
+
+def test_unsorted_calls_of_a_large_part_of_a_row_take_digit_passes():
+    # on both sides of the rule's lines: the selection is the same, and which kernels made it is in the record
+    for dtype, n, inside, beyond in ((F32, 4096, 256, 257), (F32, 16384, 1024, 1025), (F32, 20000, 1250, 5001),
+                                     (F16, 4096, 64, 65), (BF16, 16384, 256, 257), (F16, 30000, 468, 1876)):
+        x = W.normal(2 * n, 101)
+        for k in (inside, beyond):
+            for largest in (True, False):
+                tr = _check("unsorted", x, dtype, k, largest, batch=2, sorted=False)
+                assert all((t.passes[0].where in LIST) == (k == inside) for t in tr), (n, k, [t.passes[0].where for t in tr])
+                _check("sorted", x, dtype, k, largest, batch=2)
