@@ -37,8 +37,10 @@ def bytes_moved(tr, n, es, k):
         return 0, "skipped"
     if ps[0].where == 4:                                   # one-sweep row kernel: X once (+ its first part again, cached)
         return es * n + out, "one sweep"
+    if ps[0].where == 6:                                   # the same with the list in LDS, after a sample or with the row held
+        return es * (tr.pre_elems + n) + out, "one sweep, one workgroup per row"
     if ps[0].where == 5:                                   # sample, one sweep into a list, the list in order (a long list is
-        listed = tr.pre_kept                               # moved once more, into buckets); crowded rows list next to nothing
+        listed = tr.pre_kept                               # moved once more, into buckets)
         return es * (tr.pre_elems + n) + (32 if listed > 8192 else 16) * listed + out, "sample + one sweep into a list"
     def pass_bytes(i):
         """read of pass i's source + write of its candidates (an in-place pass writes none; after in-place passes

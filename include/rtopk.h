@@ -60,8 +60,9 @@ enum {
     /* Sorted output: every row's k outputs in the order best element first (descending for "largest",
      * ascending for "smallest"; NaN ranks above +inf, -0 below +0), lowest index first among equal elements.
      * The paper's output is unsorted by nature (Section 2.3.1); its evaluation sorts afterwards and counts
-     * that time (Section 5.2).  Costs a sort of the k pairs after the selection: in LDS for k <= 8192, a
-     * radix sort in the workspace beyond. */
+     * that time (Section 5.2).  The list kernels put their lists in order anyway and the flag costs little or nothing
+     * there; digit passes are followed by a sort of the k pairs, in LDS for k <= 8192, a radix sort in the workspace
+     * beyond. */
     RTOPK_FLAG_SORTED = 1u << 2
 };
 
@@ -77,8 +78,9 @@ typedef struct {
     int32_t digit_bits;      /* radix digit width d, 8..12 (default 12; 11 for 16-bit keys when one workgroup
                                 handles a row)                                                                  */
     int32_t path;            /* 0 auto, 1 one workgroup per row (fused kernel), 2 many workgroups per row,
-                                3 like 1, with the one-sweep kernel for small k first (auto picks it for
-                                batches of 64 rows up with k <= 256, k <= 512 on rows of 64K keys up)           */
+                                3 like 1, with the one-sweep kernel for small k first.  With every field 0 most
+                                calls go to the list kernels, which no knob reaches; with another field set, auto
+                                is 1 or 2, or 3 for batches of 64 rows up with k <= 256 (512 from 64K keys up)  */
     int32_t wgs_per_row;     /* workgroups cooperating on one row in path 2 (default: fill 256 CUs)            */
     int32_t small_threshold; /* candidate count at or below which one workgroup finishes a row by itself       */
     int32_t prefilter;       /* path 2: 0 auto, 1 always, -1 never: histogram of a sample of the row, then ONE
@@ -196,6 +198,8 @@ rtopk_status rtopk_select_static(const void* keys, int64_t batch, int64_t n, int
  *   events[0] before anything is enqueued          events[1] before the first-pass HIST kernel
  *   events[2] between first-pass HIST and CLASSIFY  events[3] after the first-pass CLASSIFY kernel
  *   events[4] after the last kernel
+ * List kernels: events[1] before the sample, events[2] between the sample and the sweep, events[3] after the sweep (a row's
+ * stretches held by several workgroups: both after the only sweep).
  * With one workgroup per row (a single fused kernel) events[1..3] are recorded together with events[0].
  * Nothing is synchronised; the caller reads the events after the stream has drained.
  */
@@ -220,25 +224,27 @@ typedef struct {
     uint32_t error;            /* 0, or a bit set if the device saw an impossible state              */
     uint32_t redo;             /* 1: the one-sweep row kernel left this row to the two-sweep kernel
                                   (which clears the record, redo_why excepted, when it takes the row
-                                  over).  List kernels, bits: 1 the list was no use and the row was
-                                  selected anew, 2 the list, 4 some of its buckets did not fit LDS   */
-    uint32_t redo_why;         /* diagnostic; non-zero: the one-sweep kernel handed the row over.
+                                  over).  List kernels, bits (any of them): 1 the list was no use and
+                                  the row was selected anew, 2 the list, 4 some of its buckets were too
+                                  long for one workgroup and were shared out                         */
+    uint32_t redo_why;         /* diagnostic; non-zero: the one-sweep kernel handed the row over, or
+                                  (list kernels: 5 and 8 only) the list was no use.
                                   1 inf/NaN in the part counted first, 2 that part shorter than k,
-                                  3 bin edge not a number, 5 list full, 6 too many candidates in the
+                                  3 bin edge not a number, 5 list full (list kernels: what has to be
+                                  kept of it is more than half the row), 6 too many candidates in the
                                   chosen bin, 7 list expected to overflow, 8 the sample misled (fewer
                                   than k elements at or above its bound)                              */
-    uint32_t pre_elems;        /* elements in the row's sample, counted before a prefilter sweep
-                                  (0: no prefilter, the whole row was counted)                       */
+    uint32_t pre_elems;        /* elements in the row's sample, counted before a prefilter sweep or
+                                  before a list's (0: no sample, the whole row was counted or held)  */
     uint32_t pre_bound;        /* with a prefilter: the bin taken from the sample; the sweep kept the
-                                  elements of this bin and the better ones                           */
-    uint32_t pre_kept;         /* how many elements that were                                        */
+                                  elements of this bin and the better ones.  List kernels: the bin of
+                                  the first digit that their bound lies in                           */
+    uint32_t pre_kept;         /* how many elements that were; how many were listed                  */
     uint32_t pre_missed;       /* 1: the k-th key's bin lies below pre_bound (the sample misled), so
                                   pass 0 swept the row again instead of reading what was kept;
                                   2: the same on purpose -- the sample showed the keys crowded into the
                                   bins to keep (over 1/8 of the row; 1/16 for 16-bit keys), so the sweep kept nothing
-                                  (pre_bound is the bin count) and only counted.  List kernels: the
-                                  sample showed the keys crowded in the same sense; pre_kept then
-                                  stays 0 and the record counts the whole row as looked at          */
+                                  (pre_bound is the bin count) and only counted.  List kernels: 0  */
     uint32_t pre_merged;       /* 1: the prefilter's bound bin was the k-th key's bin, and pass 0 had no
                                   sweep of its own -- pass 1's sweep over what was kept classified by both
                                   digits at once (pass 0's record: its selectBin; winners are what lay above
@@ -253,7 +259,8 @@ typedef struct {
         uint32_t where;        /* 0 pass not run; 1 many workgroups; 2 single-workgroup finish;
                                   3 fused one-workgroup-per-row kernel; 4 one-sweep row kernel;
                                   5 list: everything not below a key taken from a sample, ranked
-                                  directly (one record, source 3, stands for the whole selection)    */
+                                  directly (one record, source 3, stands for the whole selection);
+                                  6 the same by one workgroup per row                                */
         uint32_t bin;          /* chosen bin of this digit                                           */
         uint32_t k_after;      /* rank of the k-th key inside the bin (0 if the whole bin was taken) */
         uint32_t cand_after;   /* candidates passed on to the next digit (0: the row is finished)    */

@@ -59,7 +59,8 @@ static rtopk_status make_config(int64_t batch, int64_t n, int64_t k, rtopk_dtype
     }
     // The one-sweep kernel sets aside a few hundred elements of a row (its bound comes from the row's first
     // eighth, more for larger k) and holds 2048.  Rows it cannot finish go to the two-sweep kernel, so the choice
-    // never changes the result.
+    // never changes the result.  (A call without any knob takes lists for these shapes, see make_list_plan; the
+    // automatic choice below is for calls that set another knob.)
     bool one_sweep = path == 3;
     if (path == 3) path = 1;
     // (k up to 512 on rows of 64K keys up: the bound then comes from a sample of the row and is checked afterwards --

@@ -1,12 +1,12 @@
-// Selection through a list: the automatic choice for rows of 8192 keys up while k is at most 0.4 n.
+// Selection through a list: the automatic choice for most calls (make_list_plan has the rules).
 //
 // selectBin (paper Section 2.3.1) applied to a sample of the row gives a key T that very probably lies at or below the
 // k-th key.  ONE sweep over X then does nothing but compare every element with T and append the few that are not below
 // it to a list; whenever the list holds at least k elements it contains the k-th key and is the top of the row,
 // exactly, so everything that follows (countBin, selectBin, filter, and the order of the output) works on the list.
 // Nothing is counted in the sweep, no digit decides what is kept, and the only thing that many workgroups have to
-// agree on is T.  The result never depends on the sample: a list that comes out short (the sample misled), or longer
-// than half the row, has the row done again by one workgroup that selects the k-th key from all of X (k_list_redo).
+// agree on is T.  The result never depends on the sample: a list that comes out short (the sample misled), or of which more
+// than half the row would have to be kept, has the row done again by one workgroup that selects the k-th key from all of X.
 //
 //   k_list_held     rows of up to 256 KB: one workgroup per row, which holds the row in registers and needs no sample
 //   k_list_part     few rows and a small k: several workgroups hold a row and list their stretches' best (k_list_finish follows)
@@ -16,14 +16,15 @@
 //   k_list_finish   (short lists) one workgroup per row: the list, best first, is the output
 //   k_list_scatter  (long lists) many workgroups per row: the list into buckets of about 2048 ranks each,
 //   k_list_buckets  and one workgroup per bucket puts its ranks in order
-//   k_list_redo     rows whose list was no use (normally none: the launch finds nothing to do)
+//   k_list_redo     lists and buckets too long for one workgroup, which several put in order, and rows whose list was no use
+//                   (normally none of either: the launch finds nothing to do)
 //
 // List entries are 64-bit numbers, distinct within a row, whose descending order is the order of the output: the
 // ordered key (direction applied, 16 or 32 bits) above the inverted index (as many bits as n needs).  An entry holds
 // all there is to know about an element but a NaN's payload.
 //
-// Rows with very many elements equal to T (most of the row one value) would make a long list for nothing.  The sample
-// shows that; the sweep then keeps only what is better than T and counts the equal elements of every tile, and
+// Rows with very many elements equal to T (most of the row one value, or enough of it) would make a long list for nothing.  The
+// sample shows that; the sweep then keeps only what is better than T and counts the equal elements of every tile, and
 // the ones with the lowest positions are read from X again, straight into the output (ties_of_row).
 #include "rtopk_kernels.inl"
 
@@ -332,6 +333,7 @@ __device__ __forceinline__ u32 rank_by_one_wave(u32 value, u32 rank, u32 lo, u32
     return result[0];
 }
 
+// An integer hash; the multipliers are those of "lowbias32" (Chris Wellons, hash-prospector).
 __device__ __forceinline__ u32 mix32(u32 z) {
     z ^= z >> 16; z *= 0x7feb352du;
     z ^= z >> 15; z *= 0x846ca68bu;
@@ -920,6 +922,8 @@ __device__ __forceinline__ void sweep_row(const Source& src, u32 wg, u32 G, cons
     }
 }
 
+// (The compiler keeps 30 to 60 scalar registers of the fp32 sweeps, and up to 190 of the 16-bit ones and of the row kernels, in lanes of a
+// vector register; the sweeps are at the rate of memory all the same.)
 // X -> list.  A wave takes one noted element per lane at a time until no lane has any left, stages them in LDS, and writes
 // a full stage to the workgroup's segment.
 // NT: the input is far larger than the last-level cache.  LONG: the list's histogram is counted as it is written; then one
@@ -1936,7 +1940,7 @@ __global__ void __launch_bounds__(B, 4) k_list_held(Params P, ListPlan L) {
         return;
     }
     const u32 listed = hold_and_list<DT, B, NV>(P, rs, 0u, true, kCap, sm, [&]() __attribute__((always_inline)) { init_row<DT>(P, row, st, rs); });
-    if (tid == 0) list_record(st, rs, listed, 4u);
+    if (tid == 0) list_record(st, rs, listed, 6u);
     if (listed > kCap) {  // never expected: the k-th key bounds the list
         if (tid == 0) st->error |= 4u;
     } else if (listed <= 8u * OB) {
@@ -2030,7 +2034,7 @@ __global__ void __launch_bounds__(B, 4) k_list_row(Params P, ListPlan L) {
         }
         return;
     }
-    if (tid == 0) list_record(st, rs, total, 4u);
+    if (tid == 0) list_record(st, rs, total, 6u);
     if (total > kCap) {
         for (u32 i = tid; i < kCap; i += B) list[i] = sm.ord.buf[i];
         if (tid == 0) {

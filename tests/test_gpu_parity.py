@@ -242,8 +242,8 @@ def test_one_sweep_kernel_with_a_sampled_bound():
                 trs = _run_and_check("sampled bound", bits.reshape(5, 70001), dtype, k, largest, tuning=T)
                 if dtype == F32:
                     assert all(short(t) and t.redo_why == 0 for t in trs)
-    # the automatic choice takes this way for such batches (a few rows of the benchmark's shape)
-    trs = _run_and_check("sampled bound logits", W.llm_logits(100, 131072, 142), BF16, 300, True)
+    # a few rows of the benchmark's shape: most of them are finished this way
+    trs = _run_and_check("sampled bound logits", W.llm_logits(100, 131072, 142), BF16, 300, True, tuning=T)
     assert sum(short(t) for t in trs) >= 80
     # a sample that misleads: the 250 largest elements all sit in sampled tiles (tile 0, 4, 8, ... of 8192 elements),
     # so the bound taken from the sample lies above the k-th key and the list comes out short: reason 8, handed over
@@ -589,10 +589,26 @@ def test_kernels_stay_inside_the_workspace_and_the_outputs():
         (W.llm_logits(5, 70001, 91), BF16, 400, dict(path=3)),                                       # sampled bound
         (W.normal(100003, 92).view(np.uint32), F32, 20000, dict(path=2, sorted=True)),                # radix sort on the grid
         (W.normal(3 * 20001, 93).view(np.uint32).reshape(3, 20001), F32, 8192, dict(path=1, sorted=True)),   # sort in LDS
+        # automatic calls, list kernels: held rows, stretches, one workgroup per row, short lists, long ones (sorted and not), an odd row
+        # with crowds of ties, lists that are too long, bins between splitters
+        (W.normal(5 * 4097, 94).view(np.uint32).reshape(5, 4097), F32, 100, dict(lists=True)),
+        (W.normal(5 * 4000, 94).view(np.uint32).reshape(5, 4000), F32, 4000, dict(lists=True, sorted=True)),
+        (W.llm_logits(3, 200000, 95), BF16, 48, dict(lists=True, sorted=True)),
+        (W.llm_logits(7, 70001, 96), BF16, 700, dict(lists=True)),
+        (W.normal(300007, 97).view(np.uint32), F32, 300, dict(lists=True)),
+        (W.normal(300007, 98).view(np.uint32), F32, 100000, dict(lists=True, sorted=True)),
+        (W.normal(2 * 1000003, 99).astype(np.float16).view(np.uint16).reshape(2, 1000003), F16, 300000, dict(lists=True, sorted=True)),
+        (W.duplicates(300007, 100).view(np.uint32), F32, 100000, dict(lists=True, sorted=True)),
+        (np.linspace(1.0, -1.0, 1 << 20, dtype=np.float32).view(np.uint32), F32, 1000, dict(lists=True)),
+        (np.linspace(1.0, -1.0, 1 << 20, dtype=np.float32).view(np.uint32), F32, 300000, dict(lists=True, sorted=True)),
+        (np.where(W.uniform01(1 << 21, 101) < 5e-4, np.float32(3e38), W.normal(1 << 21, 102)).astype(np.float32).view(np.uint32), F32, 200000,
+         dict(lists=True, sorted=True)),
     ]
     for bits, dtype, k, tuning in cases:
         tuning = dict(tuning) if tuning else None
         sorted_out = bool(tuning.pop("sorted", False)) if tuning else False
+        by_list = bool(tuning.pop("lists", False)) if tuning else False
+        tuning = tuning or None
         for scaling in ((False, True) if dtype == F32 and not (tuning or {}).get("prefilter") else (False,)):
             _say("guards:", bits.shape, dtype, k, tuning, "scaling", scaling, "sorted", sorted_out)
             x = to_device(bits, dtype)
@@ -615,7 +631,9 @@ def test_kernels_stay_inside_the_workspace_and_the_outputs():
                 assert bool((buf[guard + size:] == 0xA5).all()), "%s: bytes after the buffer were written" % name
             gv = vals.view(torch.int32 if dtype == F32 else torch.int16).cpu().numpy().view(bits.dtype)
             b2 = bits.reshape(1, -1) if bits.ndim == 1 else bits
-            _check_rows(b2, dtype, k, True, gv, idx.cpu().numpy(), B.read_trace(ws, batch))
+            trs = B.read_trace(ws, batch)
+            _check_rows(b2, dtype, k, True, gv, idx.cpu().numpy(), trs)
+            assert not by_list or all(t.passes[0].where in (5, 6) for t in trs)
 
 
 def _check_sorted(name, bits, dtype, k, largest, tuning=None, scaling=False):
@@ -768,7 +786,7 @@ def test_streamed_row_whose_prefilter_declines():
     xd = to_device(bits, F32)
     for largest in (True, False):
         _say("narrow 2^27 largest", largest)
-        gv, gi, tr, _ = gpu_topk(xd, F32, k, largest)
+        gv, gi, tr, _ = gpu_topk(xd, F32, k, largest, tuning=dict(path=2, prefilter=1))
         assert tr[0].error == 0 and tr[0].done
         assert tr[0].pre_missed == 2 and tr[0].pre_kept == 0 and tr[0].passes[0].cand_before == n
         verify.check_topk_properties(bits, F32, k, largest, gv[0], gi[0])
