@@ -523,13 +523,15 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
     };
     bool elements = false;  // T is ranked among the elements
     bool alike = true;      // runs may be fewer draws than they have elements
+    u32 by_lanes = 0;       // T was ranked among the lanes' best: how many of those are not below it
     if (whole) {
     } else if (rank <= lanes / 4u) {
         T = rank_by_one_wave<B, GATHER>(lmax >> ksh, rank, low >> ksh, top >> ksh, sm.hist, sm.selv, &exact);
         if constexpr (GATHER) {
-            const float c = (float)sm.selv[2];
+            by_lanes = sm.selv[2];
+            const float c = (float)by_lanes;
             alike = (float)sm.selv[3] > (2.0f + c / (float)(lanes / kRun)) * c;
-            if (sm.selv[2] > lanes / 2u)  // (T is what most of the sample equals)
+            if (by_lanes > lanes / 2u)  // (T is what most of the sample equals)
                 while ((runs >> thin) > kLeastThinned) ++thin;
         }
     } else if (rank <= vecs / 4u) {
@@ -647,9 +649,13 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
                 continue;
             }
             // how many of them equal T, the sum of the runs' squares, and how many lie in each of a long list's bins
-            u32 sq = 0;
+            u32 sq = 0, rich = 0;  // rich: runs of which a quarter counts, and above that how many of them the next run does not follow
             eq_got = most = 0;
-            for (u32 r = tid; r < runs; r += B) sq += sl->run[r] * sl->run[r];
+            for (u32 r = tid; r < runs; r += B) {
+                const u32 c = sl->run[r], next = r + 1u < runs ? sl->run[r + 1u] : 0u;
+                sq += c * c;
+                if (c >= kRun * E / 4u) rich += next >= kRun * E / 4u ? 1u : 0x10001u;
+            }
             lo = (u64)(T >> ent.kshift) << ent.ib;
             sh = even_shift(lo);
             for (u32 i = tid; i < got; i += B) {
@@ -662,12 +668,14 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
             }
             eq_got = wave_inclusive_scan(eq_got);
             sq = wave_inclusive_scan(sq);
+            rich = wave_inclusive_scan(rich);
             most = wave_reduce(most, MaxOf());
-            if (lane == 63u) { red[3 * wave] = eq_got; red[3 * wave + 1] = sq; red[3 * wave + 2] = most; }
+            if (lane == 63u) { red[4 * wave] = eq_got; red[4 * wave + 1] = sq; red[4 * wave + 2] = most; red[4 * wave + 3] = rich; }
             __syncthreads();
-            eq_got = sum_of_waves<B>(red, 3);
-            sq = sum_of_waves<B>(red + 1, 3);
-            most = best_of_waves<B>(red + 2, 3, MaxOf());
+            eq_got = sum_of_waves<B>(red, 4);
+            sq = sum_of_waves<B>(red + 1, 4);
+            most = best_of_waves<B>(red + 2, 4, MaxOf());
+            rich = sum_of_waves<B>(red + 3, 4);
             cnt = got << thin;
             eq = eq_got << thin;
             const float v = got != 0u ? (float)sq / (float)got - (float)cnt / (float)runs : 0.0f;
@@ -677,11 +685,21 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
                 continue;
             }
             // (a list holds at least what the sample has of it: nothing can go wrong from k on, twice k where runs meet)
-            const float need = ks + 4.0f * __builtin_sqrtf(ks * v) + 3.0f * v;
+            // (Rich runs that all follow one another are a trend: one run from every stretch then misses by one at either end at most.
+            // A ramp of 13.6 million fp32 keys with infinities, k = 5676: 105 us with the margin of independent runs.)
+            const float need = ks + ((rich >> 16) == 1u && (rich & 0xffffu) >= 3u ? 2.0f * v : 4.0f * __builtin_sqrtf(ks * v) + 3.0f * v);
             const u32 have = thin == 0u ? cnt : rank;  // (thinned, cnt is an estimate; it is no less than the rank)
             if (whole || again || !(v > 2.0f) || !((float)have < need) || have >= 2u * rs.k) break;
             rank = need < (float)elems ? (u32)need : elems;
-            elements = fresh = again = true;
+            fresh = again = true;
+            // (so many lanes have that many such elements, if the next ones have as many each: one wave finds that out sooner)
+            const float more = need * (float)by_lanes / (float)got * 1.25f + 2.0f;
+            if (by_lanes != 0u && thin == 0u && more < (float)(lanes / 2u)) {
+                __syncthreads();
+                T = rank_by_one_wave<B>(lmax >> ksh, (u32)more, 0u, top >> ksh, sm.hist, sm.selv, &exact) << ksh;
+            } else {
+                elements = true;
+            }
         }
     }
     // Most of the row may equal T, or so much that the list would be longer than half the row or than what is put in order in
@@ -695,7 +713,9 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
     }
     bool split = false;
     if constexpr (GATHER) if (bins) {
-        if (!tied && most < eq_got) most = eq_got;  // (so many with one key)
+        // (those equal to T: one key's share of the bins is by position)
+        const u32 ties = eq_got >> (ent.ib > sh ? ent.ib - sh : 0u);
+        if (!tied && most < ties) most = ties;
         // (a bin of several buckets' ranks -- up to there k_list_redo has it in order in no time -- and more of them than fall together by
         // chance: 4096 bins, 2^28 keys, k = 2^20: about 400 draws)
         split = most > 5u && ((u64)most << thin) * rs.n / elems > 8192u;
@@ -758,7 +778,7 @@ template <int DT, int B, int V>
 __global__ void __launch_bounds__(B) k_list_bound(Params P, ListPlan L) {
     __shared__ RankShared sm;
     __shared__ SampleList sl;
-    __shared__ u32 red[3 * (B / 64)];
+    __shared__ u32 red[4 * (B / 64)];
     const int row = blockIdx.x;
     const RowShape rs = row_shape_scalar<DT>(P, row);
     ListSource<DT, false> src;  // (the smaller of the two sweeps' tiles: the larger number of them)
@@ -995,7 +1015,7 @@ __global__ void __launch_bounds__(LONG ? kLongBlock : kGridBlock, LONG ? 4 : DT 
 // over the number of entries per thread (equal keys; one key far from the others), the bins are laid anew between 255 of the entries themselves: equal keys then
 // differ by their positions, and no distance between keys matters.  Only entries that defeat that as well (more than
 // kSplitCrowd in one bin) go through a bitonic network.
-constexpr u32 kOrderCrowd = 256, kSplitCrowd = 256;
+constexpr u32 kOrderCrowd = 128, kSplitCrowd = 256;
 template <int B>
 struct OrderShared {
     u64 buf[8 * B + 4];  // (four more: they are compared four at a time)
@@ -1146,7 +1166,8 @@ __device__ __forceinline__ void order_in_lds(const Params& P, int row, const Row
     for (int j = 0; j < 8; ++j)
         if (tid + (u32)j * B < C) atomicAdd(&sm.hist[(u32)((mx - e[j]) >> sh) + 1u], 1u);  // (the bins' counts, one place up)
     __syncthreads();
-    order_scan<B>(sm.hist + 1, want, kOrderCrowd / ((C + (u32)B - 1u) / (u32)B), sorted, sm);
+    const u32 per = (C + (u32)B - 1u) / (u32)B;  // entries per thread
+    order_scan<B>(sm.hist + 1, want, per < 4u ? kOrderCrowd / per : kOrderCrowd / 4u, sorted, sm);
     // entry j's rank, if it is wanted, among the entries of its bin, which are buf[from .. to); then every one to its place
     auto rank_and_place = [&](auto&& from, auto&& to) __attribute__((always_inline)) {
         u32 rank[4];  // two to a word
@@ -1190,29 +1211,32 @@ __device__ __forceinline__ void order_in_lds(const Params& P, int row, const Row
         order_output<DT, B>(P, row, rs, sm, want, rank0, ent);
         return;
     }
-    // crowded: bins between splitters, which are taken from the entries at equal distances
+    // crowded: bins between splitters, which are taken from the entries at equal distances (8 us; two entries per thread are through
+    // the network in less)
     typedef SplitBins<B> Split;
     __syncthreads();  // (everybody has seen the flag)
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        if (tid + (u32)j * B < C) sm.buf[tid + (u32)j * B] = e[j];
-    for (u32 j = tid; j < 4u * B + 2u; j += B) sm.hist[j] = 0;
-    if (tid == 0) sm.flag = 0;
-    __syncthreads();
-    const u64 mine = tid < (u32)Split::N ? sm.buf[(u32)((u64)tid * C / (u32)Split::N)] : 0ull;
-    __syncthreads();
-    make_edges<B>(sm.buf, mine, mx, mn);
     u32 at[8];  // bin, and which of its entries this one is
+    if (per > 2u) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        at[j] = 0;
-        if (tid + (u32)j * B < C) {
-            const u32 bin = Split::bin(sm.buf, e[j]);
-            at[j] = bin << 16 | atomicAdd(&sm.hist[bin], 1u);
+        for (int j = 0; j < 8; ++j)
+            if (tid + (u32)j * B < C) sm.buf[tid + (u32)j * B] = e[j];
+        for (u32 j = tid; j < 4u * B + 2u; j += B) sm.hist[j] = 0;
+        if (tid == 0) sm.flag = 0;
+        __syncthreads();
+        const u64 mine = tid < (u32)Split::N ? sm.buf[(u32)((u64)tid * C / (u32)Split::N)] : 0ull;
+        __syncthreads();
+        make_edges<B>(sm.buf, mine, mx, mn);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            at[j] = 0;
+            if (tid + (u32)j * B < C) {
+                const u32 bin = Split::bin(sm.buf, e[j]);
+                at[j] = bin << 16 | atomicAdd(&sm.hist[bin], 1u);
+            }
         }
+        __syncthreads();
+        order_scan<B>(sm.hist, want, kSplitCrowd, sorted, sm);
     }
-    __syncthreads();
-    order_scan<B>(sm.hist, want, kSplitCrowd, sorted, sm);
     if (sm.flag == 0u) {
         const u32 last = sm.sp;
         if (tid == 0) sm.hist[4 * B] = C;

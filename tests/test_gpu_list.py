@@ -361,3 +361,14 @@ def test_unsorted_calls_of_a_large_part_of_a_row_take_digit_passes():
                 tr = _check("unsorted", x, dtype, k, largest, batch=2, sorted=False)
                 assert all((t.passes[0].where in LIST) == (k == inside) for t in tr), (n, k, [t.passes[0].where for t in tr])
                 _check("sorted", x, dtype, k, largest, batch=2)
+
+
+def test_a_trend_has_a_short_list():
+    # the sample has one run from every stretch of the row, so a trend's k-th key is known to a stretch or two: no margin for
+    # independent runs, and a lane's best element does not stand for sixteen neighbouring stretches
+    n = 1 << 22  # 2048 stretches
+    x = np.linspace(1.0e6, -1.0e6, n, dtype=np.float32)
+    for k in (16, 1000, 5000, 30000):
+        for largest in (True, False):
+            tr = _check("trend", x, F32, k, largest)
+            assert k <= tr[0].pre_kept < 1.6 * k + 12 * 2048 and tr[0].redo & 1 == 0, tr[0].pre_kept
