@@ -132,6 +132,7 @@ struct ListEntry {
     __device__ __forceinline__ u64 of(u32 key, u32 idx) const { return ((u64)(key >> kshift) << ib) | (u64)(idx_max - idx); }
     __device__ __forceinline__ u32 idx(u64 e) const { return idx_max - ((u32)e & idx_max); }
     __device__ __forceinline__ u32 key(u64 e) const { return (u32)(e >> ib) << kshift; }
+    __device__ __forceinline__ u64 end() const { return 1ull << (32u - kshift + ib); }  // above every entry
 };
 template <int DT>
 __device__ __forceinline__ ListEntry list_entry(const Params& P) {
@@ -722,7 +723,7 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
         if (split) {
             static_assert(sizeof(sm.hist) >= kListSplits * 8, "room for the candidates");
             u64* cand = (u64*)sm.hist;
-            if (tid < kListSplits) cand[tid] = ~0ull >> 1;
+            if (tid < kListSplits) cand[tid] = ent.end();
             __syncthreads();
             const u32 total = tied ? got - eq_got : got;
             for (u32 i = tid; i < got; i += B) {
@@ -743,7 +744,7 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
                 if (r != 0u) edge[r] = c;
                 if (tid == 0) {
                     edge[0] = lo;
-                    edge[kListSplits] = 1ull << 63;
+                    edge[kListSplits] = ent.end();
                 }
             }
         }
@@ -1478,8 +1479,9 @@ __device__ __forceinline__ void order_shared(const Params& P, int row, const Row
         if (part == 0u) order_in_lds<DT, B>(P, row, rs, sm, count, rank0, [&](u32 i) __attribute__((always_inline)) { return src[i]; });
         return;
     }
-    // (the ends: nothing is known of the best and the worst entry but that they fit)
-    make_edges<B>(sp.edge, tid < (u32)Split::N ? src[(u64)tid * count / (u32)Split::N] : 0ull, (1ull << 63) - 1u, 0ull);
+    // (the ends: nothing is known of the best and the worst entry but that they are entries)
+    const u64 end = list_entry<DT>(P).end();
+    make_edges<B>(sp.edge, tid < (u32)Split::N ? src[(u64)tid * count / (u32)Split::N] : 0ull, end - 1u, 0ull);
     for (u32 done = 0;;) {
         for (u32 j = tid; j < 4u * B + 2u; j += B) sm.hist[j] = 0;
         __syncthreads();
@@ -1512,7 +1514,7 @@ __device__ __forceinline__ void order_shared(const Params& P, int row, const Row
             const u64 r64 = (u64)part + (u64)(done + i) * parts;
             if (r64 < nrun) {
                 const u32 r = (u32)r64, b0 = sp.bin[r], b1 = r + 1u < nrun ? sp.bin[r + 1u] - 1u : last;
-                sp.hi[i] = b0 == 0u ? 1ull << 63 : Split::floor_of(sp.edge, b0 - 1u);
+                sp.hi[i] = b0 == 0u ? end : Split::floor_of(sp.edge, b0 - 1u);
                 sp.lo[i] = Split::floor_of(sp.edge, b1);
                 sp.start[i] = sm.hist[b0];
                 sp.size[i] = sm.hist[b1 + 1u] - sm.hist[b0];
