@@ -943,7 +943,7 @@ __device__ __forceinline__ void sweep_row(const Source& src, u32 wg, u32 G, cons
     }
 }
 
-// (The compiler keeps 30 to 60 scalar registers of the fp32 sweeps, and up to 190 of the 16-bit ones and of the row kernels, in lanes of a
+// (The compiler keeps 30 to 60 scalar registers of the fp32 sweeps, and up to 200 of the 16-bit ones and of the row kernels, in lanes of a
 // vector register; the sweeps are at the rate of memory all the same.)
 // X -> list.  A wave takes one noted element per lane at a time until no lane has any left, stages them in LDS, and writes
 // a full stage to the workgroup's segment.
