@@ -95,7 +95,7 @@ class RtopkError(RuntimeError):
 
 
 _SOURCES = ("rtopk_api.hip", "rtopk_f32.hip", "rtopk_f16.hip", "rtopk_bf16.hip", "rtopk_list_f32.hip", "rtopk_list_f16.hip",
-            "rtopk_list_bf16.hip")
+            "rtopk_list_bf16.hip", "rtopk_rows_f32.hip", "rtopk_rows_f16.hip", "rtopk_rows_bf16.hip")
 _HEADERS = ("rtopk_device.h", "rtopk_host.h", "rtopk_kernels.inl", "rtopk_sort.inl", "rtopk_list.inl")
 
 

@@ -43,6 +43,9 @@ struct ListPlan {
     u32 bucket_shift; // ... of 2^bucket_shift ranks
     u32 hist_off, cursor_off, first_off, split_off, seg_off, tile_off, stack_off;
 };
+void launch_list_rows_f32(const Params& P, const ListPlan& L, hipStream_t st);  // (the kernels of L.row_block alone)
+void launch_list_rows_f16(const Params& P, const ListPlan& L, hipStream_t st);
+void launch_list_rows_bf16(const Params& P, const ListPlan& L, hipStream_t st);
 rtopk_status launch_list_f32(const Params& P, const ListPlan& L, hipStream_t st, void* const* events);
 rtopk_status launch_list_f16(const Params& P, const ListPlan& L, hipStream_t st, void* const* events);
 rtopk_status launch_list_bf16(const Params& P, const ListPlan& L, hipStream_t st, void* const* events);

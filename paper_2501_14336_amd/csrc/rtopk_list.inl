@@ -2391,8 +2391,9 @@ __global__ void __launch_bounds__(kListBucketBlock) k_list_redo(Params P, ListPl
 }
 
 // ------------------------------------------------------------------------------------------------
+// The kernels of a row that one workgroup takes alone, and those of rows that many share, are compiled apart (launch_list_rows_*, launch_list_*).
 template <int DT, bool NT>
-static void launch_list_row(const Params& P, const ListPlan& L, hipStream_t st) {
+static void launch_row(const Params& P, const ListPlan& L, hipStream_t st) {
     const dim3 rows((unsigned)P.batch);
     if (L.row_block == 1024) hipLaunchKernelGGL((k_list_row<DT, 1024, 1, NT>), rows, dim3(1024), 0, st, P, L);
     else if (L.row_block == 512 && L.sample == 1) hipLaunchKernelGGL((k_list_row<DT, 512, 2, NT>), rows, dim3(512), 0, st, P, L);
@@ -2401,7 +2402,21 @@ static void launch_list_row(const Params& P, const ListPlan& L, hipStream_t st) 
     else hipLaunchKernelGGL((k_list_row<DT, 256, 2, NT>), rows, dim3(256), 0, st, P, L);
 }
 template <int DT>
-static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStream_t st, void* const* events) {
+static void launch_rows(const Params& P, const ListPlan& L, hipStream_t st) {
+    const dim3 rows((unsigned)P.batch);
+    if (L.held == 0) {
+        if (L.stream) launch_row<DT, true>(P, L, st);
+        else launch_row<DT, false>(P, L, st);
+    } else if (L.row_block == 128) hipLaunchKernelGGL((k_list_held<DT, 128, 4>), rows, dim3(128), 0, st, P, L);
+    else if (L.row_block == 256 && L.held == 4) hipLaunchKernelGGL((k_list_held<DT, 256, 4>), rows, dim3(256), 0, st, P, L);
+    else if (L.row_block == 256) hipLaunchKernelGGL((k_list_held<DT, 256, 8>), rows, dim3(256), 0, st, P, L);
+    else if (L.row_block == 512 && L.held == 8) hipLaunchKernelGGL((k_list_held<DT, 512, 8>), rows, dim3(512), 0, st, P, L);
+    else if (L.row_block == 512) hipLaunchKernelGGL((k_list_held<DT, 512, 16>), rows, dim3(512), 0, st, P, L);
+    else hipLaunchKernelGGL((k_list_held<DT, 1024, 16>), rows, dim3(1024), 0, st, P, L);
+}
+template <int DT>
+static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStream_t st, void* const* events,
+                                    void (*rows_alone)(const Params&, const ListPlan&, hipStream_t)) {
     mark(events, 0, st);
     mark(events, 1, st);
     const dim3 rows((unsigned)P.batch);
@@ -2409,21 +2424,8 @@ static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStrea
     if (L.row_block != 0) {
         mark(events, 2, st);
         mark(events, 3, st);
-    }
-    if (L.held != 0) {
-        if (L.row_block == 128) hipLaunchKernelGGL((k_list_held<DT, 128, 4>), rows, dim3(128), 0, st, P, L);
-        else if (L.row_block == 256 && L.held == 4) hipLaunchKernelGGL((k_list_held<DT, 256, 4>), rows, dim3(256), 0, st, P, L);
-        else if (L.row_block == 256) hipLaunchKernelGGL((k_list_held<DT, 256, 8>), rows, dim3(256), 0, st, P, L);
-        else if (L.row_block == 512 && L.held == 8) hipLaunchKernelGGL((k_list_held<DT, 512, 8>), rows, dim3(512), 0, st, P, L);
-        else if (L.row_block == 512) hipLaunchKernelGGL((k_list_held<DT, 512, 16>), rows, dim3(512), 0, st, P, L);
-        else hipLaunchKernelGGL((k_list_held<DT, 1024, 16>), rows, dim3(1024), 0, st, P, L);
-        mark(events, 4, st);
-        return hipGetLastError() == hipSuccess ? RTOPK_OK : RTOPK_ERR_HIP;
-    }
-    if (L.row_block != 0) {
-        if (L.stream) launch_list_row<DT, true>(P, L, st);
-        else launch_list_row<DT, false>(P, L, st);
-        hipLaunchKernelGGL((k_list_redo<DT>), dim3(redo), dim3(kListBucketBlock), 0, st, P, L);
+        rows_alone(P, L, st);
+        if (L.held == 0) hipLaunchKernelGGL((k_list_redo<DT>), dim3(redo), dim3(kListBucketBlock), 0, st, P, L);
         mark(events, 4, st);
         return hipGetLastError() == hipSuccess ? RTOPK_OK : RTOPK_ERR_HIP;
     }

@@ -1,0 +1,6 @@
+// List kernels of rows that one workgroup takes alone, for RTOPK_F32 keys.
+#include "rtopk_list.inl"
+
+namespace rtopk {
+void launch_list_rows_f32(const Params& P, const ListPlan& L, hipStream_t st) { launch_rows<RTOPK_F32>(P, L, st); }
+}  // namespace rtopk
