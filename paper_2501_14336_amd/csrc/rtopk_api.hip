@@ -238,7 +238,7 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
             L->G = (int)G;
             L->seg_stride = (u32)stride;
             L->finish = G * stride <= 2048 ? 256 : 1024;
-            L->seg_off = 256;
+            L->seg_off = kListMetaBytes;
             return true;
         }
     }
@@ -280,13 +280,14 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     const bool by_row = n * eb <= (256 << 10) || (batch >= 256 && n * eb <= (1 << 20));
     if (by_row && L->sample > 1) L->sample = 1;
     double listed = 0.0, room = 0.0;  // expected length of the list, and with a margin
-    auto expect = [&]() {
-        const double elems = (double)((L->sample == 4 ? (eb == 4 ? 16384 : 8192) : L->sample == 3 ? 4096 : 512 << L->sample) * E);
+    auto expect = [&](int64_t sampled) {
+        const double elems = (double)(sampled * E);
         const double ks = (double)k * elems / (double)n;
         listed = (ks + 6.0 * __builtin_sqrt(ks) + 7.0) * 1.08 * (double)n / elems;
         room = listed * 1.08 + 64.0;
     };
-    expect();
+    auto sample_vecs = [&]() { return L->sample == 4 ? (eb == 4 ? 16384 : 8192) : L->sample == 3 ? 4096 : 512 << L->sample; };
+    expect(sample_vecs());
     if (by_row) {
         // (a list that does not fit is put in order by k_list_redo: better a little too much room)
         L->row_block = batch > 256 && room * 1.2 <= 2048.0 ? 256 : batch > 256 && room * 1.2 <= 4096.0 ? 512 : room <= 8192.0 ? 1024 : 0;
@@ -296,26 +297,51 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
         if (vecs < 4096) return false;
         L->sample = 2;
     }
-    expect();
+    // Short lists of few rows: sample and sweep in one launch (k_list_stream), with half the sample, while one workgroup puts in order what that lists
+    // (up to twice as much as it should be, 16384 entries at most).  us, two launches / one, normal keys: one fp32 row of 1.5 million, k = 16, 300 and 3000,
+    // 22.2 / 20.0, 25.1 / 21.5, 30.9 / 27.4; of 8 million 34.3 / 24.7, 35.8 / 27.7, 46.6 / 46.5 (a long list either way); of 24 million 41.7 / 35.3,
+    // 44.3 / 43.0.  fp16 rows of 2 million 22.4 / 21.0, 26.5 / 21.8, 33.3 / 28.6.  Shorter rows have less than a tile to a wave, and a sample that is a large
+    // part of what a workgroup sweeps: one bf16 row of 400001, k = 1000, 24.9 / 29.5, of 700003, k = 100, 23.2 / 24.5, one fp16 row of
+    // 1 million, k = 3000, 30.1 / 32.3; eleven fp32 rows of 135112, k = 615, 22.5 / 30.2.  Longer 16-bit rows keep eight waves per compute unit busy
+    // where ties are counted: one bf16 row of 16 million, nine in ten equal, 30.7 / 32.8.
+    bool stream = false;
+    if (L->row_block == 0 && batch <= 32 && n * eb >= ((int64_t)(eb == 4 ? 1 : 3) << 20) &&
+        (eb == 4 || n * eb <= ((int64_t)24 << 20))) {
+        expect(L->sample == 4 && eb == 4 ? 8192 : 4096);
+        stream = room <= 8192.0 && listed * 1.1 <= 0.5 * (double)n;
+    }
+    if (!stream) expect(sample_vecs());
     if (listed * 1.1 > 0.5 * (double)n) return false;
-    const bool is_long = L->row_block == 0 && room > 8192.0;
+    const bool is_long = L->row_block == 0 && !stream && room > 8192.0;
     // A long list is put in order whether that was asked for or not.  Unsorted output pays for it where keys lie in order
     // along the row and crowd the bins: a ramp with infinities, us, digit passes / list: 2^22 fp32 keys, k = 2^13, 75 / 105,
     // k = 2^20, 77 / 159; 2^26 fp16 keys, k = 2^16, 162 / 234, k = 2^20, 154 / 388.  Long fp32 rows gain more than they can
     // lose: 2^26 keys, k = 2^16, uniform 149 / 104, the ramp 154 / 162.
     if (is_long && !sorted && (eb != 4 || n < ((int64_t)1 << 25))) return false;
-    // one workgroup of 1024 threads per compute unit where the list's histogram is counted, else four of 512 (three for 16-bit keys)
+    // k_list_stream: a workgroup of 512 threads per compute unit; k_list_sweep: one of 1024 where the list's histogram is counted, else four
+    // of 512 (three for 16-bit keys)
     const int64_t tile_elems = (int64_t)(is_long ? 1024 : kHostGridBlock) * 64 / eb;
     const int64_t ntiles = (n + E - 1 + tile_elems - 1) / tile_elems;
-    int64_t G = (is_long ? 256 : eb == 4 ? 1024 : 768) / batch;
+    const int64_t wave_tiles = (n + E - 1 + 256 * E - 1) / (256 * E);  // (k_list_stream's)
+    int64_t G = (stream || is_long ? 256 : eb == 4 ? 1024 : 768) / batch;
     if (G < 1) G = 1;
-    if (G > ntiles) G = ntiles;
+    if (G > (stream ? wave_tiles : ntiles)) G = stream ? wave_tiles : ntiles;
+    if (!is_long && G > 256) G = 256;  // (a finishing workgroup has a thread per segment)
     L->G = (int)G;
+    L->stream_block = stream ? 512 : 0;
     // (one sweep: nothing is read twice.  2^26 fp32 keys, k = n / 100 as a mask, 133 us with ordinary loads, 121 past the
     // caches; 1024 rows of 2^17 bf16 keys, k = 50, 64 against 57.5; 2^24 fp32 keys, which the last-level cache holds, 36.7
     // against 37.8)
     L->stream = batch * n * eb > ((int64_t)128 << 20);
-    L->finish = room > 2048.0 ? 1024 : 256;
+    // (256 segments to read keep 1024 threads busy: one fp16 row of 6 million, k = 16, 256 threads 25.9, k = 100, 1024 threads 23.3)
+    L->finish = room > 2048.0 || stream ? 1024 : 256;
+    L->room = (u32)L->finish * 8u;
+    const double twice = 2.0 * room < 2.0 * L->room ? 2.0 * room : 2.0 * L->room;
+    L->most = twice > L->room ? (u32)twice : L->room;
+    // (twice the average segment's entries, no more than 16 places per thread, and not most of the row's working memory)
+    L->slots = 8;
+    while ((double)L->slots * (double)G < 2.0 * room && (int64_t)L->slots * 2 * G <= (int64_t)L->finish * 16 && (int64_t)L->slots * 16 * G <= n * 2) L->slots *= 2;
+    if (is_long || L->row_block != 0) L->slots = 0;
     L->bucket_shift = 11;
     while ((k >> L->bucket_shift) + 1 > (int64_t)kListMaxBuckets) ++L->bucket_shift;
     L->nb = is_long ? (u32)((k >> L->bucket_shift) + 1) : 0u;
@@ -326,14 +352,16 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     L->redo_wgs = L->row_block != 0 || batch >= 256 ? 1 : (int)(256 / batch);
     if (!is_long && L->redo_wgs > 4) L->redo_wgs = 4;  // (a short list's k ranks are at most so many parts)
     if (batch * ((int64_t)L->nb + 1 + ties) >= ((int64_t)1 << 22) || batch * G >= ((int64_t)1 << 22)) return false;  // grid sizes
-    u64 off = 256;
-    auto take = [&](u64 bytes) { const u64 at = off; off = align_up(off + bytes, 16); return (u32)at; };
+    u64 off = kListMetaBytes;
+    // (whole cache lines: a wave's adds to 64 neighbouring counters fall on two of them, not three -- 4 million fp16 keys, k = 2^20, 64.8 / 62.3 us)
+    auto take = [&](u64 bytes) { const u64 at = off; off = align_up(off + bytes, 128); return (u32)at; };
+    L->front_off = take((u64)G * L->slots * 8);
+    L->seg_off = take((u64)G * 4);
     L->hist_off = take(is_long ? kMaxBins * 4 : 0);
     L->cursor_off = take((u64)L->nb * 4);
     L->first_off = take((u64)L->nb * 8);
     L->split_off = take(is_long ? (kListSplits + 1) * 8 : 0);
-    L->seg_off = take((u64)G * 4);
-    L->tile_off = take((u64)((n + E - 1) / (kHostGridBlock * 64 / eb) + 1) * 4);  // (the smaller tiles' number)
+    L->tile_off = take((u64)(stream ? wave_tiles + 2 : (n + E - 1) / (kHostGridBlock * 64 / eb) + 2) * 4);  // (the smallest tiles' number)
     L->stack_off = take(((u64)n / 256 + 64 + 16 * (u64)L->nb) * 16);
     return off + 256 + 8 <= (u64)n * 4;  // (the upper half of a candidate array)
 }

@@ -29,11 +29,13 @@ rtopk_status launch_bf16(const Params& P, const Config& c, bool scaled, hipStrea
 constexpr unsigned kListMaxBuckets = 4096;
 constexpr unsigned kListSplits = 256;                  // intervals between splitters
 constexpr int kListPartBlock = 256, kListPartVecs = 8;  // a stretch of a row that one workgroup holds: 32 KB
+constexpr unsigned kListMetaBytes = 256;  // a row's records before the plan's first offset
 struct ListPlan {
     int G;            // workgroups per row in the sweep
     int row_block;    // one workgroup per row does everything: its threads (0: many workgroups per row)
     int held;         // ... holding the row in registers: 16-byte vectors per thread (0: the row is swept)
-    int sample;       // which size of sample: 512, 1024, 2048, 4096 or 16384 (16-bit keys: 8192) vectors of 16 bytes
+    int sample;       // which size of sample: 512, 1024, 2048, 4096 or 16384 (16-bit keys: 8192) vectors of 16 bytes; k_list_stream's: 4096 and 8192 (4096)
+    int stream_block; // short lists of few rows: threads of k_list_stream's workgroups, which take the sample themselves (0: k_list_bound does)
     int stream;       // the input is too large for the caches to keep: read past them
     int finish;       // short lists: threads of the workgroup that puts a row's list in order
     int ties;         // workgroups per row that fetch elements equal to the bound, where those are very many
@@ -41,7 +43,9 @@ struct ListPlan {
     u32 seg_stride;   // the row's stretches are held by G workgroups that list at most this many each (0: the row is swept)
     u32 nb;           // long lists: buckets per row (0: short lists)
     u32 bucket_shift; // ... of 2^bucket_shift ranks
-    u32 hist_off, cursor_off, first_off, split_off, seg_off, tile_off, stack_off;
+    u32 slots;        // short lists: a power of two: so many entries of each segment lie together at front_off
+    u32 room, most;   // ... so many in all are put in order in LDS, and so many there are cut down to that first
+    u32 front_off, hist_off, cursor_off, first_off, split_off, seg_off, tile_off, stack_off;
 };
 void launch_list_rows_f32(const Params& P, const ListPlan& L, hipStream_t st);  // (the kernels of L.row_block alone)
 void launch_list_rows_f16(const Params& P, const ListPlan& L, hipStream_t st);

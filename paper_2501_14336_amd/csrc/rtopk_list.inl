@@ -9,10 +9,12 @@
 // than half the row would have to be kept, has the row done again by one workgroup that selects the k-th key from all of X.
 //
 //   k_list_held     rows of up to 256 KB: one workgroup per row, which holds the row in registers and needs no sample
-//   k_list_part     few rows and a small k: several workgroups hold a row and list their stretches' best (k_list_finish follows)
+//   k_list_part     few rows and a small k: several workgroups hold a row and list their stretches' best
+//   k_part_finish   ... one workgroup per row puts those in order
 //   k_list_row      longer rows, or many: one workgroup per row does all of the following
-//   k_list_bound    one workgroup per row: sample, T
-//   k_list_sweep    many workgroups per row: X -> list, one segment per workgroup
+//   k_list_stream   (short lists, few rows) many workgroups per row, each of which takes the sample and T for itself: X -> list
+//   k_list_bound    (the other calls) one workgroup per row: sample, T
+//   k_list_sweep    many workgroups per row: X -> list
 //   k_list_finish   (short lists) one workgroup per row: the list, best first, is the output
 //   k_list_scatter  (long lists) many workgroups per row: the list into buckets of about 2048 ranks each,
 //   k_list_buckets  and one workgroup per bucket puts its ranks in order
@@ -39,6 +41,7 @@ constexpr u32 kListTies = 16384;                // equal elements from which on 
 
 // How a sweep deals a row: tiles of four 16-byte vectors per thread (16 elements, or 32 of 16 bits).
 constexpr int kLongBlock = 1024;                // threads per workgroup of a long list's sweep (one workgroup per compute unit)
+constexpr int kSharedBlock = 512;               // ... of the sweep of few rows
 template <int DT, bool LONG, bool NT = false>
 using ListSource = KeySource<DT, LONG ? kLongBlock : kGridBlock, 4, NT>;
 
@@ -64,7 +67,7 @@ struct ListDone {
     u32 pad;
 };
 constexpr u32 kListDoneOff = 128;
-static_assert(sizeof(ListRow) <= kListDoneOff && kListDoneOff + sizeof(ListDone) <= 256, "both lie before the plan's first offset");
+static_assert(sizeof(ListRow) <= kListDoneOff && kListDoneOff + sizeof(ListDone) <= kListMetaBytes, "both lie before the plan's first offset");
 // Bits of rtopk_row_trace::redo that the list kernels set and k_list_redo looks at: the list is no use; it was too long to
 // put in order in LDS (it is all in array `end`); so were some of its buckets.
 enum : u32 { kRedoRow = 1, kRedoList = 2, kRedoBuckets = 4 };
@@ -81,6 +84,9 @@ __device__ __forceinline__ RowShape row_shape_scalar(const Params& P, int row) {
     return r;
 }
 
+// (explicitly global: a wait for a flat operation's result waits for every load under way)
+__device__ __forceinline__ u32 add_of_agent(u32* p, u32 n) { return __hip_atomic_fetch_add((Glb<u32>*)p, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
 // A row's decision, read into scalar registers (it is the same for every lane, which a load does not know).
 __device__ __forceinline__ ListRow list_row_scalar(const ListRow* p) {
     ListRow r;
@@ -91,7 +97,6 @@ __device__ __forceinline__ ListRow list_row_scalar(const ListRow* p) {
     __builtin_memcpy(&r, w, sizeof(r));
     return r;
 }
-
 // Bin of an entry of a long list, in the entries' order.  The bins divide the range of what the sample showed evenly, one shift per
 // entry; where the sample shows a crowd in one of those bins (equal keys, or one key far above the others: infinities, a mask
 // value), they lie between 255 entries of the sample at equal ranks, 16 to an interval: equal keys then differ by position, and
@@ -274,13 +279,18 @@ __device__ __forceinline__ u32 sample_rank(Each&& each, u32 rank, u32 lo, u32 hi
     }
 }
 
-// The same for one value per thread, in LDS: the first wave halves [lo, hi] until the values from lo up are at least `rank`
-// and few more, counting with a compare and a scalar population count per 64 of them -- no barriers among many waves
-// (1024 values: 1.3 us against 4.4 with sample_rank).  At least `rank` values are not below lo.  Contains two barriers; `v`
-// may be written again after it.  RUNS: result[2] is how many values that are, result[3] the sum of squares of how many every eight
+// The same for one value per thread, in LDS, by the first wave alone -- no barriers among many waves (1024 values: 4.4 us with sample_rank): until
+// the values from lo up are at least `rank` and few more.  At least `rank` values are not below lo.  Contains two barriers; `v`
+// (RankShared::hist) may be written again after it.  RUNS: result[2] is how many values that are, result[3] the sum of squares of how many every eight
 // neighbouring threads have.
-template <int B, bool RUNS = false>
+// Bound by the latency of one wave.  [lo, hi] is divided into 512 bins, again and again, a bin being one LDS add (300 rows of 30011 fp16 keys, k = 100,
+// halved 16.0 us, so 15.6; 16 rows of 2^17 bf16 keys 15.9 / 15.0).  HALVE: it is halved, with a compare and a scalar population count per 64 values:
+// better where several workgroups of four waves share a compute unit and its LDS (1024 rows of 2^17 bf16 keys, k = 50, 54.7 / 55.5),
+// and for a few of 256 values (four fp16 rows of 89250, k = 2, 12.7 / 13.6).
+template <int B, bool RUNS = false, bool HALVE = false>
 __device__ __forceinline__ u32 rank_by_one_wave(u32 value, u32 rank, u32 lo, u32 hi, u32* v, u32* result, bool* exact) {
+    constexpr u32 kBins = 512, kMine = kBins / 64;
+    static_assert(B + kBins <= 2 * 2049 && B % 4 == 0, "bins behind the values");
     const u32 tid = threadIdx.x;
     v[tid] = value;
     __syncthreads();
@@ -290,22 +300,63 @@ __device__ __forceinline__ u32 rank_by_one_wave(u32 value, u32 rank, u32 lo, u32
 #pragma unroll
         for (int i = 0; i < kPer; ++i) mine[i] = v[i * 64 + tid];
         const u32 slack = rank + 1u + rank / 16u;
-        u32 end = hi;  // fewer than `rank` values lie above it
-        while (lo < end) {
-            const u32 mid = end - (end - lo) / 2u;
-            u32 c = 0;
+        bool one = lo >= hi;
+        if (HALVE || (kPer <= 4 && rank < 8u)) {
+            u32 end = hi;  // fewer than `rank` values lie above it
+            while (lo < end) {
+                const u32 mid = end - (end - lo) / 2u;
+                u32 c = 0;
 #pragma unroll
-            for (int i = 0; i < kPer; ++i) c += (u32)__popcll(ballot64(mine[i] >= mid));
-            if (c >= rank) {
-                lo = mid;
-                if (c <= slack) break;
-            } else {
-                end = mid - 1u;
+                for (int i = 0; i < kPer; ++i) c += (u32)__popcll(ballot64(mine[i] >= mid));
+                if (c >= rank) {
+                    lo = mid;
+                    if (c <= slack) break;
+                } else {
+                    end = mid - 1u;
+                }
+            }
+            one = lo == end;
+        } else {
+            u32* bins = v + B;
+            u32 above = 0;  // values above hi: fewer than `rank`
+            while (!one) {
+                const u32 width = 32u - (u32)__builtin_clz(hi - lo), sh = width > 9u ? width - 9u : 0u;
+                // (bin 0 is the best; a lane's bins are neighbours)
+#pragma unroll
+                for (u32 j = 0; j < kMine; j += 4u) *(uint4*)&bins[tid * kMine + j] = make_uint4(0, 0, 0, 0);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+                for (int i = 0; i < kPer; ++i) {
+                    if (mine[i] >= lo && mine[i] <= hi) atomicAdd(&bins[(hi - mine[i]) >> sh], 1u);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                u32 c[kMine], s = 0;
+#pragma unroll
+                for (u32 j = 0; j < kMine; ++j) {
+                    c[j] = bins[tid * kMine + j];
+                    s += c[j];
+                }
+                u32 run = above + wave_inclusive_scan(s) - s, bin = 0, before = 0, upto = 0;
+#pragma unroll
+                for (u32 j = 0; j < kMine; ++j) {
+                    if (run < rank && rank <= run + c[j]) { bin = tid * kMine + j; before = run; upto = run + c[j]; }
+                    run += c[j];
+                }
+                const u64 who = ballot64(upto != 0u);
+                if (who == 0u) break;  // (never: at least `rank` values lie in [lo, hi] or above)
+                const int l = (int)__builtin_ctzll(who);
+                bin = (u32)__builtin_amdgcn_readlane((int)bin, l);
+                above = (u32)__builtin_amdgcn_readlane((int)before, l);
+                upto = (u32)__builtin_amdgcn_readlane((int)upto, l);
+                hi -= bin << sh;
+                lo = hi - lo > (1u << sh) - 1u ? hi - ((1u << sh) - 1u) : lo;  // (the last bin may reach beyond the range)
+                one = lo == hi;
+                if (upto <= slack) break;
             }
         }
         if (tid == 0) {
             result[0] = lo;
-            result[1] = lo == end ? 1u : 0u;
+            result[1] = one ? 1u : 0u;
         }
         if constexpr (RUNS) {
             u32 word = 0, sq = 0;  // lane 2 i, 2 i + 1: which of the values i * 64 .. i * 64 + 63 they are
@@ -403,9 +454,11 @@ struct SampleList {
     u32 bin[kListBins];  // how many of them, of those better than T, lie in each bin of a long list
     u32 n, next;
 };
-template <int DT, int B, int V, bool GATHER>
+// record: this workgroup writes the row's record.  after_load(): what may be done once the sample's loads are under way.
+template <int DT, int B, int V, bool GATHER, class AfterLoad>
 __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L, int row, const RowShape& rs, rtopk_row_trace* st,
-                                             ListRow* lr, u32* te, u32 nt, u32 room, RankShared& sm, SampleList* sl, u32* red) {
+                                             ListRow* lr, u32* te, u32 nt, u32 room, RankShared& sm, SampleList* sl, u32* red, bool record,
+                                             AfterLoad&& after_load) {
     constexpr int E = 16 / KeyOf<DT>::kBytes;
     constexpr u32 kRun = 8, kRuns = (u32)(B * V) / kRun, kLeastRuns = 16;
     const u32 tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
@@ -439,7 +492,8 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
             q[u] = load16<false>(src.abase + vector_of(run_of(tid, (u32)u) & (runs - 1u), tid % kRun));
         }
     }
-    init_row<DT>(P, row, st, rs);
+    if (record) init_row<DT>(P, row, st, rs);
+    after_load();
     if (rs.k == 0) {
         if (tid == 0) lr->mode = kListSkip;
         return;
@@ -452,7 +506,7 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
     }
     if (bins) {  // its histogram and the buckets' write positions
         u32* gh = list_part<u32>(P, row, L.hist_off);
-        for (u32 j = tid; j < kListBins; j += B) gh[j] = 0;
+        for (u32 j = tid; j < kListBins; j += B) gh[j] = 0u;
         u32* cur = list_part<u32>(P, row, L.cursor_off);
         for (u32 j = tid; j < L.nb; j += B) cur[j] = 0;
     }
@@ -527,7 +581,7 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
     u32 by_lanes = 0;       // T was ranked among the lanes' best: how many of those are not below it
     if (whole) {
     } else if (rank <= lanes / 4u) {
-        T = rank_by_one_wave<B, GATHER>(lmax >> ksh, rank, low >> ksh, top >> ksh, sm.hist, sm.selv, &exact);
+        T = rank_by_one_wave<B, GATHER, (B <= 256)>(lmax >> ksh, rank, low >> ksh, top >> ksh, sm.hist, sm.selv, &exact);
         if constexpr (GATHER) {
             by_lanes = sm.selv[2];
             const float c = (float)by_lanes;
@@ -770,8 +824,10 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
         lr->lo = lo;
         lr->sh = sh;
         lr->split = split ? 1u : 0u;
-        st->pre_elems = elems;
-        st->pre_bound = T >> (32u - P.pass[0].bits);
+        if (record) {
+            st->pre_elems = elems;
+            st->pre_bound = T >> (32u - P.pass[0].bits);
+        }
     }
 }
 
@@ -785,29 +841,18 @@ __global__ void __launch_bounds__(B) k_list_bound(Params P, ListPlan L) {
     ListSource<DT, false> src;  // (the smaller of the two sweeps' tiles: the larger number of them)
     src.init(rs);
     bound_of_row<DT, B, V, true>(P, L, row, rs, row_state(P, row), list_row_out(P, row), list_part<u32>(P, row, L.tile_off), src.ntiles(),
-                           L.nb != 0u ? ~0u : 8u * (u32)L.finish, sm, &sl, red);
+                           L.nb != 0u ? ~0u : L.room, sm, &sl, red, true, [] {});
 }
 
 // ------------------------------------------------------------------------------------------------
 // the sweep
 // ------------------------------------------------------------------------------------------------
 
-// Where workgroup wg's segment of the list begins: as many entries in as the tiles of the workgroups before it have
-// elements (tiles are dealt round-robin; the first and the last of a row may be short).
-template <class Source>
-__device__ __forceinline__ u32 list_segment(const Source& src, u32 wg, u32 G, u32 ntiles) {
-    const u32 te = (u32)Source::kTileVecs * (u32)Source::E;
-    const u32 q = ntiles / G, r = ntiles % G;
-    u64 at = (u64)(wg * q + (wg < r ? wg : r)) * te;
-    if (wg > 0) at -= src.lead;
-    if (ntiles > 0 && (ntiles - 1u) % G < wg) at -= (u64)ntiles * te - src.lead - src.n;  // (the last tile's missing end)
-    return (u32)at;
-}
-
-// Staged (raw bits, index) pairs -> entries at the workgroup's next free positions; LONG: counted into the histogram.
-// (Expanded in place: around a call the compiler keeps the tiles in flight in memory.)
+// Staged (raw bits, index) pairs -> entries at the workgroup's next free places; LONG: counted into the histogram.  (Expanded in place: around a call
+// the compiler keeps the tiles in flight in memory.)  The first `slots` of a workgroup's entries go to `front`
+// (short lists).
 template <int DT, bool LONG>
-__device__ __forceinline__ void list_flush(u64* seg, Lds<u64>* buf, Lds<u32>* run, u32 fill, Lds<u32>* hist, const u64* split,
+__device__ __forceinline__ void list_flush(u64* seg, u64* front, u32 slots, Lds<u64>* buf, Lds<u32>* run, u32 fill, Lds<u32>* hist, const u64* split,
                                            const ListEntry& c, const ListRow& lr, u32 lane) {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     u32 base = 0;
@@ -816,13 +861,39 @@ __device__ __forceinline__ void list_flush(u64* seg, Lds<u64>* buf, Lds<u32>* ru
     for (u32 i = lane; i < fill; i += 64) {
         const u64 v = buf[i];
         const u64 e = c.of(KeyOf<DT>::key((u32)v) ^ c.dirmask, (u32)(v >> 32));
-        ((Glb<u64>*)seg)[base + i] = e;
+        if (LONG) {
+            ((Glb<u64>*)seg)[base + i] = e;
+        } else {
+            u64* at = base + i < slots ? front : seg;
+            ((Glb<u64>*)at)[base + i] = e;
+        }
         if (LONG) {
             __hip_atomic_fetch_add(hist + (lr.split != 0u ? list_bin_split(e, split) : list_bin(e, lr.lo, lr.sh)), 1u, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_WORKGROUP);
         }
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+// Where workgroup wg's part of the list begins: as many entries in as the units before it have elements that are dealt to the workgroups before it.
+// Unit c (of `unit` vectors, a power of two) is workgroup c % G's; the first and the last of a row may be short.
+template <int DT>
+__device__ __forceinline__ u32 list_segment(const RowShape& rs, u32 wg, u32 G, u32 unit) {
+    KeySource<DT, 64, 4, false> src;
+    src.init(rs);
+    const u32 ue = unit * (u32)decltype(src)::E;
+    const u32 units = (u32)((src.nvec + unit - 1u) >> (31u - (u32)__builtin_clz(unit))), q = units / G, r = units % G;
+    u64 at = (u64)(wg * q + (wg < r ? wg : r)) * ue;
+    if (wg > 0) at -= src.lead;
+    if (units > 0 && (units - 1u) % G < wg) at -= (u64)units * ue - src.lead - src.n;  // (the last unit's missing end)
+    return (u32)at;
+}
+// k_list_stream: tiles of 4 KB, which are dealt to the waves one by one, or where every wave has as many, four neighbours at a time.
+constexpr u32 kWaveVecs = 256, kSharedWaves = kSharedBlock / 64;
+template <int DT>
+__device__ __forceinline__ u32 wave_unit(const RowShape& rs, u32 G) {
+    KeySource<DT, 64, 4, false> src;
+    src.init(rs);
+    return src.nvec >= (u64)4u * kWaveVecs * kSharedWaves * G ? 4u * kWaveVecs : kWaveVecs;
 }
 
 // Element s (0 .. kSlots - 1, different in every lane) of a tile that is held in registers: a tree of selects.  (An index
@@ -945,15 +1016,50 @@ __device__ __forceinline__ void sweep_row(const Source& src, u32 wg, u32 G, cons
 
 // (The compiler keeps 30 to 60 scalar registers of the fp32 sweeps, and up to 200 of the 16-bit ones and of the row kernels, in lanes of a
 // vector register; the sweeps are at the rate of memory all the same.)
-// X -> list.  A wave takes one noted element per lane at a time until no lane has any left, stages them in LDS, and writes
-// a full stage to the workgroup's segment.
+template <bool LONG, int B>
+constexpr u32 list_stage() { return !LONG ? kListStage : B == kSharedBlock ? 2 * kListStageLong : kListStageLong; }
+// A wave takes one noted element per lane at a time until no lane has any left, stages them in LDS, and writes
+// a full stage to the workgroup's part of the list.
+template <int DT, bool LONG, class Source>
+struct ListWriter {
+    static constexpr u32 ST = LONG ? kListStageLong : kListStage;
+    ListEntry ent;
+    u64 *seg, *front;
+    u32 slots;
+    uint2* buf;       // this wave's stage
+    u32* run;         // entries of the workgroup so far
+    u32* hist;        // LONG
+    const u64* split;
+    u32 fill;
+    __device__ __forceinline__ void flush(const ListRow& lr) {
+        list_flush<DT, LONG>(seg, front, slots, lds_words(buf), lds_word(run), fill, lds_word(hist), split, ent, lr, lane_id());
+        fill = 0;
+    }
+    // index(s): position in the row of this lane's element s
+    template <class Index>
+    __device__ __forceinline__ void append(const typename Source::Tile& cur, u32 m, const ListRow& lr, Index&& index) {
+        for (;;) {
+            const u64 have = ballot64(m != 0u);
+            if (have == 0) break;
+            if (fill > ST - 64u) flush(lr);
+            if (m != 0u) {
+                const u32 bit = 31u - (u32)__builtin_clz(m), s = (u32)Source::kSlots - 1u - bit;
+                m ^= 1u << bit;
+                buf[fill + mbcnt64(have)] = make_uint2(pick<Source>(cur, s), index(s));
+            }
+            fill += (u32)__popcll(have);
+        }
+    }
+};
+
+// X -> list, one segment per workgroup.
 // NT: the input is far larger than the last-level cache.  LONG: the list's histogram is counted as it is written; then one
 // workgroup of 1024 threads has a compute unit, so that there are no more than 256 histograms to add up (512
 // workgroups of 512: adding up took longer than it saved).
 template <int DT, bool NT, bool LONG>
 __global__ void __launch_bounds__(LONG ? kLongBlock : kGridBlock, LONG ? 4 : DT == RTOPK_F32 ? 8 : 6) k_list_sweep(Params P, ListPlan L) {
-    constexpr int B = LONG ? kLongBlock : kGridBlock, ST = LONG ? kListStageLong : kListStage;
-    __shared__ uint2 stage[B / 64][ST];
+    constexpr int B = LONG ? kLongBlock : kGridBlock;
+    __shared__ uint2 stage[B / 64][LONG ? kListStageLong : kListStage];
     __shared__ u32 hist[LONG ? kListBins : 1];
     __shared__ u64 split[LONG ? kListSplits + 1 : 1];
     __shared__ u32 run;
@@ -966,35 +1072,19 @@ __global__ void __launch_bounds__(LONG ? kLongBlock : kGridBlock, LONG ? 4 : DT 
     const RowShape rs = row_shape_scalar<DT>(P, row);
     Source src;
     src.init(rs);
-    const u32 tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-    u64* seg = list_array(P, 1u, row) + list_segment(src, wg, G, src.ntiles());
+    const u32 tid = threadIdx.x;
     if (LONG) {
         for (u32 j = tid; j < kListBins; j += B) hist[j] = 0;
         if (lr.split != 0u && tid <= kListSplits) split[tid] = list_part<u64>(P, row, L.split_off)[tid];
     }
     if (tid == 0) run = 0;
     __syncthreads();
-    const ListEntry ent = list_entry<DT>(P);
-    uint2* buf = stage[wave];
-    u32 fill = 0;
-    auto flush = [&]() __attribute__((always_inline)) {
-        list_flush<DT, LONG>(seg, lds_words(buf), lds_word(&run), fill, lds_word(hist), split, ent, lr, lane);
-        fill = 0;
-    };
+    ListWriter<DT, LONG, Source> w{list_entry<DT>(P), list_array(P, 1u, row) + list_segment<DT>(rs, wg, G, (u32)Source::kTileVecs),
+                                   list_part<u64>(P, row, L.front_off) + (size_t)wg * L.slots, L.slots, stage[tid >> 6], &run, hist, split, 0u};
     sweep_row<DT>(src, wg, G, lr, list_part<u32>(P, row, L.tile_off), P.dirmask, [&](const typename Source::Tile& cur, u32 m) __attribute__((always_inline)) {
-        for (;;) {
-            const u64 have = ballot64(m != 0u);
-            if (have == 0) break;
-            if (fill > (u32)(ST - 64)) flush();
-            if (m != 0u) {
-                const u32 bit = 31u - (u32)__builtin_clz(m), s = (u32)Source::kSlots - 1u - bit;
-                m ^= 1u << bit;
-                buf[fill + mbcnt64(have)] = make_uint2(pick<Source>(cur, s), element_index(src, cur.tile, s));
-            }
-            fill += (u32)__popcll(have);
-        }
+        w.append(cur, m, lr, [&](u32 s) __attribute__((always_inline)) { return element_index(src, cur.tile, s); });
     });
-    if (fill != 0u) flush();
+    if (w.fill != 0u) w.flush(lr);
     __syncthreads();
     if (tid == 0) list_part<u32>(P, row, L.seg_off)[wg] = run;
     if (LONG) {
@@ -1004,6 +1094,157 @@ __global__ void __launch_bounds__(LONG ? kLongBlock : kGridBlock, LONG ? 4 : DT 
             if (c) atomicAdd(&gh[j], c);
         }
     }
+}
+
+// Sample, T and X -> list in one launch, for few rows and short lists.  Every workgroup takes the same sample and comes to the same T by itself (the
+// sample, 64 or 128 KB, comes from its XCD's cache for all but the first of them), while its first tiles are on their way: nobody waits for
+// anybody, and no word of memory has to be cleared by an earlier launch.
+// Every wave works by itself, on tiles of 4 KB that are dealt evenly to all of them (wave_unit); four of them are in registers, and each is loaded anew as soon
+// as it is done with, so that 12 to 16 KB per wave and 128 KB per compute unit are in flight.  (1 GiB read and compared: tiles of 64 KB of a workgroup of
+// 1024, two in turn, 162 us; by waves 155; dealt by counters, eight workgroups on eight XCDs to each, 175.  One fp16 row of
+// 12 million, k = 1000, 33 us with four neighbouring tiles to a wave at a time, 35.5 with single ones; but a short row would then have few waves at work,
+// and a ramp one that writes most of the list: one bf16 row of 6 million, k = 1024, a ramp, 94 / 74.)
+template <int DT, bool NT>
+using WaveSource = KeySource<DT, 64, 4, NT>;
+template <int DT, class Source, class Bound, class Append>
+__device__ __forceinline__ void sweep_by_waves(const Source& src, u32 first, u32 step, bool by_four, u32* te, u32 dirmask, Bound&& bound, Append&& append) {
+    typedef typename Source::Tile Tile;
+    constexpr u32 E = Source::E, kRing = 4;
+    constexpr u32 kAll = 0xffffffffu >> (32 - Source::kSlots);
+    const u32 lane = lane_id(), ntiles = src.ntiles();
+    const u32 nvec = (u32)src.nvec, last = nvec - 1u;
+    u32 f0, f1;  // tiles [f0, f1) are full
+    src.full_range(f0, f1);
+    const u32 begin = by_four ? kRing * first : first, apart = by_four ? 1u : step;  // a round of this wave: tiles cur, cur + apart, ..., the next begins kRing * step on
+    Tile t[kRing];
+    auto load = [&](u32 tile, Tile& x) __attribute__((always_inline)) {  // (beyond the row's end: its last vector, which is nobody's)
+        x.tile = tile;
+#pragma unroll
+        for (u32 u = 0; u < 4u; ++u) {
+            const u32 v = tile * (u32)Source::kTileVecs + u * 64u + lane;
+            x.r[u] = load16<Source::kStreams>(src.abase + (v < last ? v : last));
+        }
+    };
+    ListRow lr;
+    if (!bound([&]() __attribute__((always_inline)) {
+            if (begin < ntiles) static_for<0, (int)kRing>([&](auto c) __attribute__((always_inline)) { load(begin + (u32)decltype(c)::value * apart, t[decltype(c)::value]); });
+        }, lr)) return;
+    const bool tied = lr.mode == kListTied, largest = dirmask == 0;
+    const u32 T = lr.T;
+    const float thr = lr.t;
+    // (a tile is one wave's alone: nothing to add to, and nothing to be cleared before)
+    auto note_ties = [&](u32 tile, u32 eq) __attribute__((always_inline)) {
+        eq = wave_inclusive_scan(eq);
+        if (lane == 63u) te[tile] = eq;
+    };
+    // short tiles, and every tile where T is not a number to compare with
+    auto by_key = [&](const Tile& x) __attribute__((always_inline)) {
+        u32 m = 0, eq = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            uint4 v = x.r[u];
+            keys_of_vector<DT>(v, dirmask);
+            const u32 idx = (x.tile * (u32)Source::kTileVecs + (u32)u * 64u + lane) * E - src.lead;  // (a lead-in element's wraps to a huge number)
+#pragma unroll
+            for (u32 j = 0; j < E; ++j) {
+                const u32 key = key_in_vector<DT>(v, (int)j);
+                const bool valid = idx + j < src.n;
+                m = m + m + ((valid && (tied ? key > T : key >= T)) ? 1u : 0u);
+                eq += (valid && key == T) ? 1u : 0u;
+            }
+            __builtin_amdgcn_sched_barrier(0);  // (one vector's keys at a time: registers)
+        }
+        append(x, m, lr);
+        if (tied) note_ties(x.tile, eq);
+    };
+    auto all_tiles = [&](auto&& one) __attribute__((always_inline)) {
+        for (u32 cur = begin; cur < ntiles; cur += kRing * step) {
+            if (ntiles - cur <= kRing * step) {
+                static_for<0, (int)kRing>([&](auto c) __attribute__((always_inline)) { one(t[decltype(c)::value]); });
+                break;
+            }
+            static_for<0, (int)kRing>([&](auto c) __attribute__((always_inline)) {
+                one(t[decltype(c)::value]);
+                load(cur + kRing * step + (u32)decltype(c)::value * apart, t[decltype(c)::value]);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        }
+    };
+    if (lr.exact == 0u && !tied) {
+        const u32 flip = largest ? kAll : 0u;
+        all_tiles([&](const Tile& x) __attribute__((always_inline)) {
+            if (x.tile >= f0 && x.tile < f1) append(x, below_mask(src, x, thr) ^ flip, lr);
+        });
+    } else if (lr.exact == 0u) {
+        // better than t, and how many equal it: "largest" notes what is not (x <= t), which a NaN is, "smallest" what is x < t
+        all_tiles([&](const Tile& x) __attribute__((always_inline)) {
+            if (x.tile < f0 || x.tile >= f1) return;
+            u32 m = 0, eq = 0;
+#pragma unroll
+            for (int s = 0; s < Source::kSlots; ++s) {
+                const float v = src.template value<SRC_KEY>(x, s, 0.0f);
+                m = largest ? shift_in_not_above(m, v, thr) : shift_in_below(m, v, thr);
+                eq = shift_in_equal(eq, v, thr);
+            }
+            append(x, m ^ (largest ? kAll : 0u), lr);
+            note_ties(x.tile, (u32)__builtin_popcount(eq));
+        });
+    }
+    if (lr.exact != 0u) {
+#pragma unroll 1
+        for (u32 cur = begin; cur < ntiles; cur += kRing * step) {
+#pragma unroll 1
+            for (u32 tile = cur; tile < ntiles && tile - cur < kRing * apart; tile += apart) {
+                load(tile, t[0]);
+                by_key(t[0]);
+            }
+        }
+    } else {
+        // the row's first and last tile, if they are short
+#pragma unroll 1
+        for (u32 e = 0; e < 2u; ++e) {
+            const u32 tile = e == 0u ? 0u : f1;
+            if ((e == 0u ? f0 == 0u : tile >= ntiles) || (by_four ? tile / kRing : tile) % step != first) continue;
+            load(tile, t[0]);
+            by_key(t[0]);
+        }
+    }
+}
+
+template <int DT, int V, bool NT>
+__global__ void __launch_bounds__(kSharedBlock) k_list_stream(Params P, ListPlan L) {
+    constexpr int B = kSharedBlock;
+    struct BoundShared { RankShared rank; SampleList list; u32 red[4 * (B / 64)]; };
+    __shared__ union { BoundShared bound; uint2 stage[B / 64][kListStage]; } sm;
+    __shared__ ListRow decided;
+    __shared__ u32 run, none[1];
+    typedef WaveSource<DT, NT> Source;
+    const u32 G = (u32)L.G, tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row = (int)(blockIdx.x / G);
+    const u32 wg = blockIdx.x % G;
+    const RowShape rs = row_shape_scalar<DT>(P, row);
+    Source src;
+    src.init(rs);
+    ListWriter<DT, false, Source> w{list_entry<DT>(P), list_array(P, 1u, row) + list_segment<DT>(rs, wg, G, wave_unit<DT>(rs, G)),
+                                    list_part<u64>(P, row, L.front_off) + (size_t)wg * L.slots, L.slots, sm.stage[wave], &run, none, nullptr, 0u};
+    sweep_by_waves<DT>(src, wave * G + wg, G * (u32)(B / 64), wave_unit<DT>(rs, G) != kWaveVecs, list_part<u32>(P, row, L.tile_off), P.dirmask,
+                     [&](auto&& load_first, ListRow& lr) __attribute__((always_inline)) {
+                         bound_of_row<DT, B, V, true>(P, L, row, rs, row_state(P, row), &decided, nullptr, 0u, L.room, sm.bound.rank, &sm.bound.list,
+                                                      sm.bound.red, wg == 0u, [&]() __attribute__((always_inline)) { if (rs.k != 0u) load_first(); });
+                         if (tid == 0) run = 0;
+                         __syncthreads();
+                         lr = list_row_scalar(&decided);
+                         if (wg == 0u && tid == 0) *list_row_out(P, row) = lr;
+                         return lr.mode != kListSkip;
+                     },
+                     [&](const typename Source::Tile& x, u32 m, const ListRow& lr) __attribute__((always_inline)) {
+                         w.append(x, m, lr, [&](u32 s) __attribute__((always_inline)) {
+                             return (x.tile * (u32)Source::kTileVecs + (s / (u32)Source::E) * 64u + lane_id()) * (u32)Source::E + s % (u32)Source::E - src.lead;
+                         });
+                     });
+    if (w.fill != 0u) w.flush(decided);
+    __syncthreads();
+    if (tid == 0) list_part<u32>(P, row, L.seg_off)[wg] = run;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1553,11 +1794,21 @@ __device__ __forceinline__ void list_record(rtopk_row_trace* st, const RowShape&
     st->pre_kept = listed;
 }
 
+template <int DT>
+__device__ __forceinline__ u64 src_vectors(const RowShape& rs) {
+    KeySource<DT, 64, 4, false> src;
+    src.init(rs);
+    return src.nvec;
+}
+// Elements that equal T, by tile.  (Counted by atomics: read past the vector cache, which does not see those.)
+struct TileCounts {
+    const u32* te;
+    __device__ __forceinline__ u32 operator()(u32 i) const { return __hip_atomic_load(&te[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+};
 // Elements equal to T, lowest positions first, to the output behind the `listed` better ones.  Workgroup w of nw takes the
-// tiles w, w + nw, ... as far as they are needed.  te: how many every tile has (counted by atomics, and read past the
-// vector cache, which does not see those).  Returns false if the row has too few of them.
-template <int DT, int B, class Source>
-__device__ __forceinline__ bool ties_of_row(const Params& P, const u32* te, int row, const RowShape& rs, u32 listed, u32 T, u32 w, u32 nw,
+// tiles w, w + nw, ... as far as they are needed.  te(i): how many tile i has.  Returns false if the row has too few of them.
+template <int DT, int B, class Source, class Counts>
+__device__ __forceinline__ bool ties_of_row(const Params& P, Counts&& te, int row, const RowShape& rs, u32 listed, u32 T, u32 w, u32 nw,
                             u32* before, u32* wsum) {
     constexpr u32 E = Source::E, kStep = 2;
     static_assert(Source::kTileVecs % (kStep * B) == 0, "whole steps");
@@ -1568,7 +1819,7 @@ __device__ __forceinline__ bool ties_of_row(const Params& P, const u32* te, int 
     long long* out_i = P.out_indices + (size_t)row * (size_t)P.k;
     u32 base = 0;  // equal elements in the tiles before this block of B tiles
     for (u32 t0 = 0; t0 < ntiles; t0 += B) {
-        const u32 c = t0 + tid < ntiles ? __hip_atomic_load(&te[t0 + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        const u32 c = t0 + tid < ntiles ? te(t0 + tid) : 0u;
         __syncthreads();
         const u32 incl = block_scan<B>(c, wsum);
         before[tid] = base + incl - c;
@@ -1614,53 +1865,121 @@ __device__ __forceinline__ bool ties_of_row(const Params& P, const u32* te, int 
     return false;
 }
 
+// sm.buf[0 .. total), at most 8 B entries, into the output, by as few waves as hold them (barriers).  Begins with a barrier.
+template <int DT, int B>
+__device__ __forceinline__ void order_list(const Params& P, int row, const RowShape& rs, OrderShared<B>& sm, u32 total) {
+    __syncthreads();
+    auto listed = [&](u32 i) __attribute__((always_inline)) { return sm.buf[i]; };
+    if (B > 256 && total <= 8u * 256u) {
+        if (threadIdx.x >= 256u) return;
+        order_in_lds<DT, 256>(P, row, rs, *(OrderShared<256>*)&sm, total, 0u, listed);
+    } else if (B > 512 && total <= 8u * 512u) {
+        if (threadIdx.x >= 512u) return;
+        order_in_lds<DT, 512>(P, row, rs, *(OrderShared<512>*)&sm, total, 0u, listed);
+    } else {
+        order_in_lds<DT, B>(P, row, rs, sm, total, 0u, listed);
+    }
+}
+
+// e[j], ~0 where there is none: those that may be among the best `want` go to sm.buf (a bin's entries together, up to the bin that rank want - 1
+// lies in); returns how many that are, or 0 if they do not fit.  Ends with a barrier.
+template <int B, u32 N>
+__device__ __forceinline__ u32 keep_best(const u64 (&e)[N], u32 total, u32 want, OrderShared<B>& sm) {
+    const u32 tid = threadIdx.x;
+    u64 mn = ~0ull, mx = 0;
+    for (u32 j = tid; j < 4u * B; j += B) sm.hist[j] = 0;
+#pragma unroll
+    for (u32 j = 0; j < N; ++j) {
+        if (e[j] == ~0ull) continue;
+        mn = mn < e[j] ? mn : e[j];
+        mx = mx > e[j] ? mx : e[j];
+    }
+    order_range<B>(mn, mx, sm);
+    const u32 sh = order_shift<B>(mx - mn);
+#pragma unroll
+    for (u32 j = 0; j < N; ++j)
+        if (e[j] != ~0ull) atomicAdd(&sm.hist[(u32)((mx - e[j]) >> sh)], 1u);
+    __syncthreads();
+    order_scan<B>(sm.hist, want, ~0u, false, sm);
+    const u32 last = sm.sp, end = last + 1u < 4u * B ? sm.hist[last + 1u] : total;
+    __syncthreads();
+    if (end > 8u * B) return 0;
+#pragma unroll
+    for (u32 j = 0; j < N; ++j) {
+        const u32 bin = (u32)((mx - e[j]) >> sh);
+        if (e[j] != ~0ull && bin <= last) sm.buf[atomicAdd(&sm.hist[bin], 1u)] = e[j];
+    }
+    __syncthreads();
+    return end;
+}
+
 // The list of one row into the output.  Blocks [0, batch): a row each.  Blocks beyond: L.ties per row, for rows whose
 // equal elements were counted, and for lists that one workgroup cannot put in order in LDS.
+// Bound by latency.  The first entries of every segment lie together (L.slots of each) and are read before it is known how many there are: a search by
+// every entry for the segment that holds it, and 1024 segments all over the list array, took 6.2 us for 3300 entries; this 3.3 for 5800.  (Ordered from
+// the registers they are read to, 16 places per thread, they need not be put together first, but every phase takes longer: 12 / 15.5 us in all.)
 template <int DT, int B>
 __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
+    constexpr u32 kMost = 16;  // places per thread
     __shared__ OrderShared<B> sm;
-    __shared__ u32 segs[1025];
-    const u32 tid = threadIdx.x;
+    __shared__ u32 segs[257];
+    const u32 tid = threadIdx.x, G = (u32)L.G, slots = L.slots, log = 31u - (u32)__builtin_clz(slots);
     const bool for_ties = blockIdx.x >= (u32)P.batch;
     const int row = for_ties ? (int)((blockIdx.x - (u32)P.batch) / (u32)L.ties) : (int)blockIdx.x;
+    const u32 places = G * slots;  // (at most kMost * B)
+    const u64* front = list_part<u64>(P, row, L.front_off);
+    // (k_list_sweep's few long segments: entries look for theirs, where the list is short, or so long that all waves are needed to order it.  One
+    // row of 1048869 fp16 keys, k = 3990, 34.7 us, put together first 37.0; 41 fp32 rows of 74007, k = 28, 20.7 / 21.5; but eleven of 135112, k = 615, 24.9 / 22.5.)
+    const bool few = L.stream_block == 0;
+    u64 e[kMost] = {};
+    if (!for_ties && !(few && B <= 256)) {
+#pragma unroll
+        for (u32 j = 0; j < kMost; ++j) {
+            if (tid + j * (u32)B < places) e[j] = front[tid + j * (u32)B];
+        }
+    }
+    const u32 c = tid < G ? list_part<u32>(P, row, L.seg_off)[tid] : 0u;  // (G is at most 256)
     const ListRow* lr = list_row(P, row);
     const u32 mode = lr->mode;
     if (mode == kListSkip) return;
     const RowShape rs = row_shape_scalar<DT>(P, row);
     rtopk_row_trace* st = row_state(P, row);
-    // the segments' beginnings in the list
-    const u32* counts = list_part<u32>(P, row, L.seg_off);
-    u32 total = 0;
-    for (u32 s0 = 0; s0 < (u32)L.G; s0 += B) {
-        const u32 c = s0 + tid < (u32)L.G ? counts[s0 + tid] : 0u;
-        const u32 incl = block_scan<B>(c, sm.wsum);
-        if (s0 + tid < (u32)L.G) segs[s0 + tid] = total + incl - c;
-        if (tid == B - 1) segs[1024] = total + incl;
-        __syncthreads();
-        total = segs[1024];
-        __syncthreads();
-    }
+    const u32 incl = block_scan<B>(c, sm.wsum);
+    if (tid < G) segs[tid] = incl - c;
+    if (tid == B - 1) segs[G] = incl;
+    const bool over = __syncthreads_or(c > slots ? 1 : 0) != 0;
+    const u32 total = segs[G];
     const bool useless = (mode == kListPlain && total < rs.k) || total > (u32)((P.n + 1) / 2);
-    ListSource<DT, false> src;
-    src.init(rs);
-    const u32 ntiles = src.ntiles();
-    u64* dst = list_array(P, 0u, row);
     const u64* from = list_array(P, 1u, row);
     auto entry = [&](u32 i) __attribute__((always_inline)) {
-        u32 a = 0, b = (u32)L.G;  // the segment that holds entry i: the last one that begins at or before it
+        u32 a = 0, b = G;  // the segment that holds entry i: the last one that begins at or before it
         while (b - a > 1u) {
             const u32 m = (a + b) / 2u;
             if (segs[m] <= i) a = m; else b = m;
         }
-        const u32 at = L.seg_stride != 0u ? a * L.seg_stride : list_segment(src, a, (u32)L.G, ntiles);
-        return from[at + (i - segs[a])];
+        const u32 l = i - segs[a];
+        if (l < slots) return front[a * slots + l];
+        const u32 at = L.stream_block != 0 ? list_segment<DT>(rs, a, G, wave_unit<DT>(rs, G)) : list_segment<DT>(rs, a, G, (u32)ListSource<DT, false>::kTileVecs);
+        return from[at + l];
     };
     if (for_ties) {
         const u32 w = (blockIdx.x - (u32)P.batch) % (u32)L.ties;
-        if (total > 8u * B && !useless)  // more than LDS holds: the segments are put together for k_list_redo
+        if (total > 8u * B && !useless) {  // (perhaps) more than LDS holds: the segments are put together for k_list_redo
+            u64* dst = list_array(P, 0u, row);
             for (u32 i = w * B + tid; i < total; i += (u32)L.ties * B) dst[i] = entry(i);
-        if (mode == kListTied && total < rs.k && !ties_of_row<DT, B, ListSource<DT, false>>(P, list_part<u32>(P, row, L.tile_off), row, rs, total, lr->T, w, (u32)L.ties,
-                                                               sm.hist, sm.wsum) && w == 0 && tid == 0) {
+        }
+        if (mode != kListTied || total >= rs.k) return;
+        const TileCounts tiles{list_part<u32>(P, row, L.tile_off)};
+        constexpr u32 kParts = (u32)ListSource<DT, false>::kTileVecs / kWaveVecs;
+        const u32 parts = (u32)((src_vectors<DT>(rs) + kWaveVecs - 1u) / kWaveVecs);
+        auto count = [&](u32 i) __attribute__((always_inline)) {  // (k_list_stream's tiles are smaller)
+            if (L.stream_block == 0) return tiles(i);
+            u32 n = 0;
+#pragma unroll
+            for (u32 c = 0; c < kParts; ++c) n += kParts * i + c < parts ? tiles(kParts * i + c) : 0u;
+            return n;
+        };
+        if (!ties_of_row<DT, B, ListSource<DT, false>>(P, count, row, rs, total, lr->T, w, (u32)L.ties, sm.hist, sm.wsum) && w == 0 && tid == 0) {
             st->redo_why = 8u;
             atomicOr(&st->redo, kRedoRow);
         }
@@ -1675,21 +1994,87 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     }
     if (tid == 0) list_record(st, rs, total, 5u);
     if (total == 0) return;
+    u32 n = total;
+    // (A list that LDS does not hold, though not much longer than expected, is cut down first.  Not every one that is much longer than what is wanted of it: 5800 entries, k = 256, 12.0 / 15.8 us.)
+    if (few && (B <= 256 || total > 4096u) && total <= 8u * B) {
+        order_in_lds<DT, B>(P, row, rs, sm, total, 0u, entry);
+        return;
+    }
+    if (total > 8u * B) {
+        n = 0;
+        if (total <= L.most) {  // (at most kMost * B)
+#pragma unroll
+            for (u32 j = 0; j < kMost; ++j) {
+                const u32 i = tid + j * (u32)B, a = i >> log, l = i & (slots - 1u);
+                if (over || few) e[j] = i < total ? entry(i) : ~0ull;  // (a segment of more than its places: entries look for themselves)
+                else if (i >= places || l >= segs[a + 1u] - segs[a]) e[j] = ~0ull;
+            }
+            n = keep_best<B>(e, total, rs.k < total ? rs.k : total, sm);
+        }
+        if (n == 0u) {
+            if (tid == 0) {
+                list_done(P, row)->total = total;
+                list_done(P, row)->end = 0u;
+                atomicOr(&st->redo, kRedoList);
+            }
+            return;
+        }
+    } else if (over) {
+        for (u32 i = tid; i < total; i += B) sm.buf[i] = entry(i);
+    } else {
+#pragma unroll
+        for (u32 j = 0; j < kMost; ++j) {
+            const u32 i = tid + j * (u32)B, a = i >> log, l = i & (slots - 1u);
+            if (i < places && l < segs[a + 1u] - segs[a]) sm.buf[segs[a] + l] = e[j];
+        }
+    }
+    order_list<DT, B>(P, row, rs, sm, n);
+}
+
+// k_list_part's lists: L.G of at most L.seg_stride entries, 8 B in all at most.  (Places and lengths read together, and the entries then put together in
+// LDS: 6.2 us for one row of 2^16 fp32 keys; so 5.6.)
+template <int DT, int B>
+__global__ void __launch_bounds__(B) k_part_finish(Params P, ListPlan L) {
+    __shared__ OrderShared<B> sm;
+    __shared__ u32 segs[1025];
+    const u32 tid = threadIdx.x, G = (u32)L.G;
+    const int row = (int)blockIdx.x;
+    if (list_row(P, row)->mode == kListSkip) return;
+    const RowShape rs = row_shape_scalar<DT>(P, row);
+    const u32* counts = list_part<u32>(P, row, L.seg_off);
+    u32 total = 0;
+    for (u32 s0 = 0; s0 < G; s0 += B) {
+        const u32 c = s0 + tid < G ? counts[s0 + tid] : 0u;
+        const u32 incl = block_scan<B>(c, sm.wsum);
+        if (s0 + tid < G) segs[s0 + tid] = total + incl - c;
+        if (tid == B - 1) segs[1024] = total + incl;
+        __syncthreads();
+        total = segs[1024];
+        __syncthreads();
+    }
+    const u64* from = list_array(P, 1u, row);
+    if (tid == 0) segs[G] = total;  // (at most 1024 of them)
+    __syncthreads();
+    const float per = (float)G / (float)total;
+    auto entry = [&](u32 i) __attribute__((always_inline)) {  // (the lists are about equally long)
+        u32 a = (u32)((float)i * per);
+        a = a < G ? a : G - 1u;
+        while (segs[a] > i) --a;
+        while (segs[a + 1u] <= i) ++a;
+        return from[a * L.seg_stride + (i - segs[a])];
+    };
+    rtopk_row_trace* st = row_state(P, row);
+    if (tid == 0) list_record(st, rs, total, 5u);
+    if (total < rs.k || total > 8u * B) {  // never expected: every stretch lists its k best
+        if (tid == 0) st->error |= 4u;
+        return;
+    }
     // (a list that fewer waves can put in order is left to them: barriers)
     if (B > 256 && total <= 8u * 256u) {
         if (tid >= 256u) return;
         order_in_lds<DT, 256>(P, row, rs, *(OrderShared<256>*)&sm, total, 0u, entry);
-    } else if (B > 512 && total <= 8u * 512u) {
-        if (tid >= 512u) return;
-        order_in_lds<DT, 512>(P, row, rs, *(OrderShared<512>*)&sm, total, 0u, entry);
-    } else if (total <= 8u * B) {
-        order_in_lds<DT, B>(P, row, rs, sm, total, 0u, entry);
     } else {
-        if (tid == 0) {
-            list_done(P, row)->total = total;
-            list_done(P, row)->end = 0u;
-            atomicOr(&st->redo, kRedoList);
-        }
+        order_in_lds<DT, B>(P, row, rs, sm, total, 0u, entry);
     }
 }
 
@@ -2027,7 +2412,7 @@ __global__ void __launch_bounds__(B, 4) k_list_row(Params P, ListPlan L) {
     rtopk_row_trace* st = row_state(P, row);
     Source src;
     src.init(rs);
-    bound_of_row<DT, B, V, false>(P, L, row, rs, st, &lr, te, src.ntiles(), kCap, sm.rank, nullptr, red);
+    bound_of_row<DT, B, V, false>(P, L, row, rs, st, &lr, te, src.ntiles(), kCap, sm.rank, nullptr, red, true, [] {});
     if (tid == 0) run = 0;
     __syncthreads();
     if (lr.mode == kListSkip) return;
@@ -2076,7 +2461,7 @@ __global__ void __launch_bounds__(B, 4) k_list_row(Params P, ListPlan L) {
     }
     if (b.mode == kListTied && total < rs.k) {
         __syncthreads();
-        if (!ties_of_row<DT, B, Source>(P, te, row, rs, total, b.T, 0u, 1u, sm.ord.hist, sm.ord.wsum) && tid == 0) {
+        if (!ties_of_row<DT, B, Source>(P, TileCounts{te}, row, rs, total, b.T, 0u, 1u, sm.ord.hist, sm.ord.wsum) && tid == 0) {
             st->redo_why = 8u;
             atomicOr(&st->redo, kRedoRow);
         }
@@ -2110,9 +2495,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     const u64 lo = lr->lo;
     const u32 sh = lr->sh, by_split = __builtin_amdgcn_readfirstlane(lr->split);
     if (by_split != 0u && tid <= kListSplits) split[tid] = list_part<u64>(P, row, L.split_off)[tid];
-    ListSource<DT, true> src;
-    src.init(rs);
-    const u64* from = list_array(P, 1u, row) + list_segment(src, wg, G, src.ntiles());
+    const u64* from = list_array(P, 1u, row) + list_segment<DT>(rs, wg, G, (u32)ListSource<DT, true>::kTileVecs);
     const u32 mine = list_part<u32>(P, row, L.seg_off)[wg];
     constexpr int kHeld = 8;
     u64 held[kHeld];
@@ -2239,7 +2622,7 @@ __global__ void __launch_bounds__(kListBucketBlock) k_list_buckets(Params P, Lis
     const RowShape rs = row_shape_scalar<DT>(P, row);
     if (j >= L.nb) {
         if (mode != kListTied || done.total >= rs.k) return;
-        if (!ties_of_row<DT, B, ListSource<DT, true>>(P, list_part<u32>(P, row, L.tile_off), row, rs, done.total, lr->T, j - L.nb,
+        if (!ties_of_row<DT, B, ListSource<DT, true>>(P, TileCounts{list_part<u32>(P, row, L.tile_off)}, row, rs, done.total, lr->T, j - L.nb,
                                                       (u32)L.ties, sm.hist, sm.wsum) && j == L.nb && tid == 0) {
             rtopk_row_trace* st = row_state(P, row);
             st->redo_why = 8u;
@@ -2318,7 +2701,7 @@ __device__ __forceinline__ void redo_row(const Params& P, const ListPlan& L, int
     if (tid == 0) list_record(st, rs, listed, 5u);
     if (listed < rs.k) {
         __syncthreads();
-        ties_of_row<DT, B, Source>(P, te, row, rs, listed, T, 0u, 1u, hist, wsum);
+        ties_of_row<DT, B, Source>(P, TileCounts{te}, row, rs, listed, T, 0u, 1u, hist, wsum);
         __syncthreads();
     }
     *listed_out = listed;
@@ -2433,23 +2816,31 @@ static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStrea
         hipLaunchKernelGGL((k_list_part<DT>), dim3((unsigned)P.batch * (unsigned)L.G), dim3(kPartBlock), 0, st, P, L);
         mark(events, 2, st);
         mark(events, 3, st);
-        if (L.finish == 256) hipLaunchKernelGGL((k_list_finish<DT, 256>), rows, dim3(256), 0, st, P, L);
-        else hipLaunchKernelGGL((k_list_finish<DT, 1024>), rows, dim3(1024), 0, st, P, L);
+        if (L.finish == 256) hipLaunchKernelGGL((k_part_finish<DT, 256>), rows, dim3(256), 0, st, P, L);
+        else hipLaunchKernelGGL((k_part_finish<DT, 1024>), rows, dim3(1024), 0, st, P, L);
         mark(events, 4, st);
         return hipGetLastError() == hipSuccess ? RTOPK_OK : RTOPK_ERR_HIP;
     }
-    switch (L.sample) {
-        case 2: hipLaunchKernelGGL((k_list_bound<DT, 512, 4>), rows, dim3(512), 0, st, P, L); break;
-        case 3: hipLaunchKernelGGL((k_list_bound<DT, 1024, 4>), rows, dim3(1024), 0, st, P, L); break;
-        default: hipLaunchKernelGGL((k_list_bound<DT, 1024, DT == RTOPK_F32 ? 16 : 8>), rows, dim3(1024), 0, st, P, L); break;
-    }
-    mark(events, 2, st);
     const bool nt = L.stream != 0, is_long = L.nb != 0;
-    const dim3 grid((unsigned)P.batch * (unsigned)L.G), block(is_long ? kLongBlock : kGridBlock);
-    if (is_long && nt) hipLaunchKernelGGL((k_list_sweep<DT, true, true>), grid, block, 0, st, P, L);
-    else if (is_long) hipLaunchKernelGGL((k_list_sweep<DT, false, true>), grid, block, 0, st, P, L);
-    else if (nt) hipLaunchKernelGGL((k_list_sweep<DT, true, false>), grid, block, 0, st, P, L);
-    else hipLaunchKernelGGL((k_list_sweep<DT, false, false>), grid, block, 0, st, P, L);
+    const dim3 grid((unsigned)P.batch * (unsigned)L.G), block(L.stream_block != 0 ? L.stream_block : is_long ? kLongBlock : kGridBlock);
+    if (L.stream_block != 0) {
+        mark(events, 2, st);
+        constexpr int kMost = DT == RTOPK_F32 ? 16 : 8;  // vectors per thread of the larger sample (16-bit keys: 16 do not fit the registers)
+        auto sweep = [&](auto v) {
+            if (nt) hipLaunchKernelGGL((k_list_stream<DT, decltype(v)::value, true>), grid, block, 0, st, P, L);
+            else hipLaunchKernelGGL((k_list_stream<DT, decltype(v)::value, false>), grid, block, 0, st, P, L);
+        };
+        if (L.sample == 3) sweep(std::integral_constant<int, 8>{});
+        else sweep(std::integral_constant<int, kMost>{});
+    } else {
+        if (L.sample == 2) hipLaunchKernelGGL((k_list_bound<DT, 512, 4>), rows, dim3(512), 0, st, P, L);
+        else if (L.sample == 3) hipLaunchKernelGGL((k_list_bound<DT, 1024, 4>), rows, dim3(1024), 0, st, P, L);
+        else hipLaunchKernelGGL((k_list_bound<DT, 1024, DT == RTOPK_F32 ? 16 : 8>), rows, dim3(1024), 0, st, P, L);
+        mark(events, 2, st);
+        auto sweep = [&](auto nt_, auto long_) { hipLaunchKernelGGL((k_list_sweep<DT, decltype(nt_)::value, decltype(long_)::value>), grid, block, 0, st, P, L); };
+        if (nt) is_long ? sweep(std::true_type{}, std::true_type{}) : sweep(std::true_type{}, std::false_type{});
+        else is_long ? sweep(std::false_type{}, std::true_type{}) : sweep(std::false_type{}, std::false_type{});
+    }
     mark(events, 3, st);
     if (is_long) {
         hipLaunchKernelGGL((k_list_scatter<DT>), grid, block, 0, st, P, L);

@@ -376,3 +376,40 @@ def test_a_trend_has_a_short_list():
             ks = k / 64
             bound = 4 * 64 * (ks + 6 * ks ** 0.5 + 6) + 2 * 4 * 2048
             assert k <= tr[0].pre_kept < bound and tr[0].redo & 1 == 0, (tr[0].pre_kept, bound)
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+def test_rows_swept_by_waves(dtype):
+    # short lists of few rows: tiles of 4 KB, a wave each; rows that end just before, at and after a tile, rows that begin
+    # between 16-byte boundaries, batches on both sides of the rule's line, ties counted by tile (as numbers; zeros and NaNs by key)
+    tile = 1024 if dtype == F32 else 2048
+    for n in (16 * tile * 16, 16 * tile * 16 + 1, 17 * tile * 16 - 1, 16 * tile * 16 + 5 * tile - 9) if dtype == F32 else (2048 * tile + 1,):
+        for batch in (1, 3) if dtype == F32 else (1,):
+            x = W.normal(batch * n, seed=n, sigma=3.0)
+            u = W.uniform01(batch * n, 3)
+            for k in (70, 1500):
+                _check("by waves", x, dtype, k, largest=k != 70, batch=batch, sorted=k != 70)
+            for value in (2.5, 0.0, np.nan) if batch == 1 else (2.5,):
+                y = np.where(u < 0.8, np.float32(value), x).astype(np.float32)
+                _check("by waves, %g" % value, y, dtype, n // 3, value != 2.5, batch=batch)
+                _check("by waves, %g" % value, y, dtype, 100, value == 2.5, batch=batch)
+    if dtype == F32:
+        for batch in (32, 33):
+            x = W.normal(batch * 256 * tile, seed=batch, sigma=3.0)
+            _check("batch", x, dtype, 200, batch=batch)
+            y = np.where(W.uniform01(len(x), 4) < 0.9, np.float32(1.0), x).astype(np.float32)
+            _check("batch, duplicates", y, dtype, 64 * tile, batch=batch)
+
+
+def test_lists_a_little_too_long_are_cut_down():
+    # a list of more than one workgroup orders in LDS, but no more than twice as long as expected, needs no second kernel; nor does one
+    # whose segments have more entries than the places that are read at once
+    n, k = 1 << 20, 3000
+    hidden = np.setdiff1d(np.arange(n), _sampled(n, 4096, 4))
+    for where in (hidden[:: len(hidden) // 5000][:5000], hidden[100000:105000]):
+        x = W.normal(n, 51)
+        x[where] = 9.0 + W.uniform01(len(where), 52)
+        for largest in (True, False):
+            for srt in (True, False):
+                tr = _check("a little too long", x if largest else -x, F32, k, largest, sorted=srt)
+                assert tr[0].redo == 0 and 8192 < tr[0].pre_kept <= 16384, (tr[0].redo, tr[0].pre_kept)
