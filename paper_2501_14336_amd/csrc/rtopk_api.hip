@@ -344,7 +344,7 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     if (is_long || L->row_block != 0) L->slots = 0;
     L->bucket_shift = 11;
     while ((k >> L->bucket_shift) + 1 > (int64_t)kListMaxBuckets) ++L->bucket_shift;
-    L->nb = is_long ? (u32)((k >> L->bucket_shift) + 1) : 0u;
+    L->nb = !is_long ? 0u : sorted ? (u32)((k >> L->bucket_shift) + 1) : 1u;  // (unsorted: one, for the bin that rank k lies in)
     int64_t ties = 128 / batch;
     if (ties < 1) ties = 1;
     if (ties > ntiles) ties = ntiles;
@@ -358,7 +358,7 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     L->front_off = take((u64)G * L->slots * 8);
     L->seg_off = take((u64)G * 4);
     L->hist_off = take(is_long ? kMaxBins * 4 : 0);
-    L->cursor_off = take((u64)L->nb * 4);
+    L->cursor_off = take((u64)(L->nb + 1) * 4);
     L->first_off = take((u64)L->nb * 8);
     L->split_off = take(is_long ? (kListSplits + 1) * 8 : 0);
     L->tile_off = take((u64)(stream ? wave_tiles + 2 : (n + E - 1) / (kHostGridBlock * 64 / eb) + 2) * 4);  // (the smallest tiles' number)

@@ -16,7 +16,8 @@
 //   k_list_bound    (the other calls) one workgroup per row: sample, T
 //   k_list_sweep    many workgroups per row: X -> list
 //   k_list_finish   (short lists) one workgroup per row: the list, best first, is the output
-//   k_list_scatter  (long lists) many workgroups per row: the list into buckets of about 2048 ranks each,
+//   k_list_emit     (long lists, unsorted output) many workgroups per row: what lies in better bins than rank k is output as it comes; its bin is a bucket,
+//   k_list_scatter  (long lists, sorted) many workgroups per row: the list into buckets of about 2048 ranks each,
 //   k_list_buckets  and one workgroup per bucket puts its ranks in order
 //   k_list_redo     lists and buckets too long for one workgroup, which several put in order, and rows whose list was no use
 //                   (normally none of either: the launch finds nothing to do)
@@ -508,7 +509,7 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
         u32* gh = list_part<u32>(P, row, L.hist_off);
         for (u32 j = tid; j < kListBins; j += B) gh[j] = 0u;
         u32* cur = list_part<u32>(P, row, L.cursor_off);
-        for (u32 j = tid; j < L.nb; j += B) cur[j] = 0;
+        for (u32 j = tid; j < L.nb + 1u; j += B) cur[j] = 0;  // (k_list_emit counts two things)
     }
     if (whole && !(bins && sampled)) {
         if (tid == 0) {
@@ -2597,6 +2598,122 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     }
 }
 
+// Unsorted output.  Workgroup w writes segment w: entries of better bins than the one rank k - 1 lies in go straight to the output, in whatever order they
+// are in, those of that bin to the row's only bucket, which k_list_buckets takes the missing ones from.  One atomic per workgroup reserves its places.
+// (2^26 fp32 keys, k = n / 100, through the buckets, every one of which is then put in order: 14.1 + 10.0 us; so 8.9 + 5.4, and what the caller
+// does with positions that lie near one another is faster, too.)
+template <int DT>
+__global__ void __launch_bounds__(kLongBlock) k_list_emit(Params P, ListPlan L) {
+    constexpr int B = kLongBlock, kPer = kListBins / B, kHeld = 8;
+    __shared__ u64 split[kListSplits + 1], s_base;
+    __shared__ u32 wsum[B / 64], counts[2 * (B / 64)], s_bin, s_rank, s_end;
+    const u32 G = (u32)L.G, tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    const int row = (int)(blockIdx.x / G);
+    const u32 wg = blockIdx.x % G;
+    const ListRow* lr = list_row(P, row);
+    const u32 mode = lr->mode;
+    if (mode == kListSkip) return;
+    const RowShape rs = row_shape_scalar<DT>(P, row);
+    rtopk_row_trace* st = row_state(P, row);
+    const u64 lo = lr->lo;
+    const u32 sh = lr->sh, by_split = __builtin_amdgcn_readfirstlane(lr->split);
+    if (by_split != 0u && tid <= kListSplits) split[tid] = list_part<u64>(P, row, L.split_off)[tid];
+    const u64* from = list_array(P, 1u, row) + list_segment<DT>(rs, wg, G, (u32)ListSource<DT, true>::kTileVecs);
+    const u32 mine = list_part<u32>(P, row, L.seg_off)[wg];
+    u64 held[kHeld];
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i) held[i] = tid + (u32)i * B < mine ? from[tid + (u32)i * B] : 0ull;
+    const u32* gh = list_part<u32>(P, row, L.hist_off);
+    u32 c[kPer], s = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        c[i] = gh[kListBins - 1u - (tid * kPer + i)];  // from the best bin down
+        s += c[i];
+    }
+    if (tid == 0) s_bin = 0xffffffffu;
+    const u32 incl = block_scan<B>(s, wsum);
+    {
+        u32 r = incl - s;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            if (r < rs.k && r + c[i] >= rs.k) {
+                s_bin = kListBins - 1u - (tid * kPer + i);
+                s_rank = r;
+                s_end = r + c[i];
+            }
+            r += c[i];
+        }
+        if (tid == B - 1) counts[0] = r;
+    }
+    __syncthreads();
+    const u32 total = counts[0], bin = s_bin;  // (fewer than k in all: 0xffffffff, and every entry is output)
+    const bool few = bin == 0xffffffffu;
+    const u32 rank = few ? total : s_rank, end = few ? total : s_end;
+    const bool drop = (mode == kListPlain && few) || end > (u32)((P.n + 1) / 2);  // (the bucket has its place in half a candidate array)
+    if (wg == 0 && tid == 0) {
+        *list_done(P, row) = ListDone{total, end, drop ? 1u : 0u, 0u};
+        u32* first = list_part<u32>(P, row, L.first_off);
+        first[0] = few ? 0xffffffffu : rank;
+        first[1] = end - rank;
+        if (drop) {
+            st->redo_why = few ? 8u : 5u;
+            atomicOr(&st->redo, kRedoRow);
+        } else {
+            list_record(st, rs, total, 5u);
+        }
+    }
+    if (drop) return;
+    __syncthreads();  // (everybody has read the total)
+    // 0: not wanted; 1: of the bin; 2: output
+    auto what = [&](u64 e) __attribute__((always_inline)) {
+        const u32 b = by_split != 0u ? list_bin_split(e, split) : list_bin(e, lo, sh);
+        return few || b > bin ? 2u : b == bin ? 1u : 0u;
+    };
+    u32 is[kHeld], out = 0, in = 0;  // (of the wave: counts)
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i) {
+        is[i] = tid + (u32)i * B < mine ? what(held[i]) : 0u;
+        out += (u32)__popcll(ballot64(is[i] == 2u));
+        in += (u32)__popcll(ballot64(is[i] == 1u));
+    }
+    for (u32 i0 = wave * 64u + kHeld * B; i0 < mine; i0 += B) {  // (what the registers do not hold is read twice)
+        const u32 w = i0 + lane < mine ? what(from[i0 + lane]) : 0u;
+        out += (u32)__popcll(ballot64(w == 2u));
+        in += (u32)__popcll(ballot64(w == 1u));
+    }
+    if (lane == 0) { counts[2 * wave] = out; counts[2 * wave + 1] = in; }
+    __syncthreads();
+    const u32 so = wave_inclusive_scan(lane < (u32)(B / 64) ? counts[2 * (lane % (u32)(B / 64))] : 0u);
+    const u32 si = wave_inclusive_scan(lane < (u32)(B / 64) ? counts[2 * (lane % (u32)(B / 64)) + 1] : 0u);
+    if (tid == 0) {
+        const u64 n = (u64)(u32)__builtin_amdgcn_readlane((int)si, 63) << 32 | (u32)__builtin_amdgcn_readlane((int)so, 63);
+        s_base = n != 0u ? atomicAdd((unsigned long long*)list_part<u64>(P, row, L.cursor_off), (unsigned long long)n) : 0u;
+    }
+    __syncthreads();
+    u32 at_out = (u32)s_base + (u32)__shfl((int)so, (int)wave, 64) - out, at_in = rank + (u32)(s_base >> 32) + (u32)__shfl((int)si, (int)wave, 64) - in;
+    const ListEntry ent = list_entry<DT>(P);
+    char* out_v = (char*)P.out_values + (size_t)row * (size_t)P.k * KeyOf<DT>::kBytes;
+    long long* out_i = P.out_indices + (size_t)row * (size_t)P.k;
+    u64* dst = list_array(P, 0u, row);
+    auto put = [&](u64 e, u32 w) __attribute__((always_inline)) {
+        const u64 o = ballot64(w == 2u), b = ballot64(w == 1u);
+        if (w == 2u) {
+            const u32 p = at_out + mbcnt64(o), idx = ent.idx(e);
+            out_i[p] = (long long)idx;
+            store_value<DT>(out_v, p, raw_of_key<DT>(ent.key(e), idx, rs, P.dirmask));
+        }
+        if (w == 1u) dst[at_in + mbcnt64(b)] = e;
+        at_out += (u32)__popcll(o);
+        at_in += (u32)__popcll(b);
+    };
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i) put(held[i], is[i]);
+    for (u32 i0 = wave * 64u + kHeld * B; i0 < mine; i0 += B) {
+        const u64 e = i0 + lane < mine ? from[i0 + lane] : 0ull;
+        put(e, i0 + lane < mine ? what(e) : 0u);
+    }
+}
+
 // Where bucket j of a row begins and how many entries it has; false if there is no such bucket, or nothing is wanted from it.
 __device__ __forceinline__ bool bucket_range(const Params& P, const ListPlan& L, int row, const RowShape& rs, u32 j, u32* at, u32* count) {
     const uint2 f = list_part<uint2>(P, row, L.first_off)[j];
@@ -2843,7 +2960,8 @@ static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStrea
     }
     mark(events, 3, st);
     if (is_long) {
-        hipLaunchKernelGGL((k_list_scatter<DT>), grid, block, 0, st, P, L);
+        if (P.flags & RTOPK_FLAG_SORTED) hipLaunchKernelGGL((k_list_scatter<DT>), grid, block, 0, st, P, L);
+        else hipLaunchKernelGGL((k_list_emit<DT>), grid, block, 0, st, P, L);
         hipLaunchKernelGGL((k_list_buckets<DT>), dim3((unsigned)P.batch * (L.nb + (unsigned)L.ties)), dim3(kListBucketBlock), 0, st, P, L);
     } else {
         const dim3 g((unsigned)P.batch * (1u + (unsigned)L.ties));

@@ -413,3 +413,24 @@ def test_lists_a_little_too_long_are_cut_down():
             for srt in (True, False):
                 tr = _check("a little too long", x if largest else -x, F32, k, largest, sorted=srt)
                 assert tr[0].redo == 0 and 8192 < tr[0].pre_kept <= 16384, (tr[0].redo, tr[0].pre_kept)
+
+
+@pytest.mark.parametrize("k", [70000, (1 << 25) // 100])
+def test_unsorted_long_lists(k):
+    # better bins go to the output as they come, and the bin of rank k is ordered: keys of many values, duplicates (ties counted), a crowd in that
+    # bin, and a row that ends inside a tile
+    n = (1 << 25) + 5
+    x = W.normal(n, 55)
+    crowd = np.sort(x)[n - k]
+    for name, y in (("normal", x), ("duplicates", W.duplicates(n, 56)),
+                    ("crowd", np.where(W.uniform01(n, 57) < 0.0003, crowd, x))):
+        bits = _bits(y.astype(np.float32), F32).reshape(1, -1)
+        for largest in (True, False):
+            print("unsorted:", name, k, largest, flush=True)
+            gv, gi, tr, _ = gpu_topk(to_device(bits, F32), F32, k, largest, sorted=False)
+            assert tr[0].error == 0 and tr[0].done and tr[0].passes[0].where == 5
+            key = y if largest else -y
+            order = np.argpartition(-key, k - 1)
+            edge = key[order[k - 1]]
+            want = np.concatenate([np.flatnonzero(key > edge), np.flatnonzero(key == edge)[: k - int((key > edge).sum())]])
+            assert np.array_equal(np.sort(gi[0]), np.sort(want)) and np.array_equal(bits[0][gi[0]], gv[0])
