@@ -431,7 +431,7 @@ __device__ __forceinline__ u32 best_of_waves(const u32* v, u32 stride, Op&& op) 
 }
 
 // Bound by latency: V independent loads per lane, then a few phases with barriers, on one compute unit.  The sample is
-// B * V vectors of 16 bytes, in runs of 8 (one 128-byte line), one run from a hashed place in each of B * V / 8 equal
+// B * V vectors of 16 bytes, in runs of RUN (8: one 128-byte line), one run from a hashed place in each of B * V / RUN equal
 // stretches of the row: a trend along the row, or any period in it, cannot line up with that.  (A stretch is at least 1.5 runs
 // long and may begin inside one, so that neighbours meet in one run now and then, at most once in nine: it then counts twice.)
 // A row that is too short for that has a smaller sample, half as many runs until they fit.
@@ -448,7 +448,7 @@ __device__ __forceinline__ u32 best_of_waves(const u32* v, u32 stride, Op&& op) 
 // in LDS.  Thread 0 fills in *lr.
 constexpr u32 kSampleList = 8192, kLeastThinned = 128;
 struct SampleList {
-    // place: (run * 8 + vector of the run) * elements per vector + element
+    // place: (run * RUN + vector of the run) * elements per vector + element
     // (two arrays: a 64-bit store of both would put a loaded vector's words into register pairs, and the kernel into scratch memory)
     u32 key[kSampleList], place[kSampleList];
     u32 run[2048];       // how many of them each run has
@@ -456,12 +456,12 @@ struct SampleList {
     u32 n, next;
 };
 // record: this workgroup writes the row's record.  after_load(): what may be done once the sample's loads are under way.
-template <int DT, int B, int V, bool GATHER, class AfterLoad>
+template <int DT, int B, int V, bool GATHER, int RUN, class AfterLoad>
 __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L, int row, const RowShape& rs, rtopk_row_trace* st,
                                              ListRow* lr, u32* te, u32 nt, u32 room, RankShared& sm, SampleList* sl, u32* red, bool record,
                                              AfterLoad&& after_load) {
     constexpr int E = 16 / KeyOf<DT>::kBytes;
-    constexpr u32 kRun = 8, kRuns = (u32)(B * V) / kRun, kLeastRuns = 16;
+    constexpr u32 kRun = (u32)RUN, kRuns = (u32)(B * V) / kRun, kLeastRuns = 16;
     const u32 tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     KeySource<DT, kGridBlock, key_vecs<DT>(), false> src;
     src.init(rs);
@@ -476,7 +476,7 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
     // (where more than 0.4 of the row is wanted -- ragged batches -- everything is listed)
     const bool whole = !sampled || (u64)rs.k * 5u > (u64)rs.n * 2u;
     const bool bins = GATHER && L.nb != 0u;  // a long list
-    // Lane t's vector u is the t % 8-th of this run: the runs of a lane lie far apart (its best element would else stand for
+    // Lane t's vector u is the t % RUN-th of this run: the runs of a lane lie far apart (its best element would else stand for
     // V neighbouring runs where the row has a trend), and so do the runs of any u.
     static_assert((V & (V - 1)) == 0 && (B & (B - 1)) == 0, "one to one");
     auto run_of = [&](u32 t, u32 u) __attribute__((always_inline)) { return t / kRun + (u32)B / kRun * ((u + t / kRun) % (u32)V); };
@@ -586,7 +586,7 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
         if constexpr (GATHER) {
             by_lanes = sm.selv[2];
             const float c = (float)by_lanes;
-            alike = (float)sm.selv[3] > (2.0f + c / (float)(lanes / kRun)) * c;
+            alike = (float)sm.selv[3] > (2.0f + c / (float)(lanes / 8u)) * c;
             if (by_lanes > lanes / 2u)  // (T is what most of the sample equals)
                 while ((runs >> thin) > kLeastThinned) ++thin;
         }
@@ -681,7 +681,7 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
                     u32 r = c;
                     r += (u32)__builtin_amdgcn_update_dpp(0, (int)r, 0xb1, 0xf, 0xf, false);   // the neighbour's
                     r += (u32)__builtin_amdgcn_update_dpp(0, (int)r, 0x4e, 0xf, 0xf, false);   // the other pair's
-                    r += (u32)__builtin_amdgcn_update_dpp(0, (int)r, 0x141, 0xf, 0xf, false);  // the other four's
+                    if constexpr (kRun == 8) r += (u32)__builtin_amdgcn_update_dpp(0, (int)r, 0x141, 0xf, 0xf, false);  // the other four's
                     if (lane % kRun == 0u && r != 0u) sl->run[run] = r;
 #pragma unroll
                     for (int j = 0; j < E; ++j) {
@@ -841,7 +841,7 @@ __global__ void __launch_bounds__(B) k_list_bound(Params P, ListPlan L) {
     const RowShape rs = row_shape_scalar<DT>(P, row);
     ListSource<DT, false> src;  // (the smaller of the two sweeps' tiles: the larger number of them)
     src.init(rs);
-    bound_of_row<DT, B, V, true>(P, L, row, rs, row_state(P, row), list_row_out(P, row), list_part<u32>(P, row, L.tile_off), src.ntiles(),
+    bound_of_row<DT, B, V, true, 8>(P, L, row, rs, row_state(P, row), list_row_out(P, row), list_part<u32>(P, row, L.tile_off), src.ntiles(),
                            L.nb != 0u ? ~0u : L.room, sm, &sl, red, true, [] {});
 }
 
@@ -888,14 +888,8 @@ __device__ __forceinline__ u32 list_segment(const RowShape& rs, u32 wg, u32 G, u
     if (units > 0 && (units - 1u) % G < wg) at -= (u64)units * ue - src.lead - src.n;  // (the last unit's missing end)
     return (u32)at;
 }
-// k_list_stream: tiles of 4 KB, which are dealt to the waves one by one, or where every wave has as many, four neighbours at a time.
+// k_list_stream: tiles of 4 KB, which are dealt to the waves one by one.
 constexpr u32 kWaveVecs = 256, kSharedWaves = kSharedBlock / 64;
-template <int DT>
-__device__ __forceinline__ u32 wave_unit(const RowShape& rs, u32 G) {
-    KeySource<DT, 64, 4, false> src;
-    src.init(rs);
-    return src.nvec >= (u64)4u * kWaveVecs * kSharedWaves * G ? 4u * kWaveVecs : kWaveVecs;
-}
 
 // Element s (0 .. kSlots - 1, different in every lane) of a tile that is held in registers: a tree of selects.  (An index
 // that varies would put the tile into scratch memory.)
@@ -1100,15 +1094,14 @@ __global__ void __launch_bounds__(LONG ? kLongBlock : kGridBlock, LONG ? 4 : DT 
 // Sample, T and X -> list in one launch, for few rows and short lists.  Every workgroup takes the same sample and comes to the same T by itself (the
 // sample, 64 or 128 KB, comes from its XCD's cache for all but the first of them), while its first tiles are on their way: nobody waits for
 // anybody, and no word of memory has to be cleared by an earlier launch.
-// Every wave works by itself, on tiles of 4 KB that are dealt evenly to all of them (wave_unit); four of them are in registers, and each is loaded anew as soon
+// Every wave works by itself, on tiles of 4 KB that are dealt evenly to all of them; four of them are in registers, and each is loaded anew as soon
 // as it is done with, so that 12 to 16 KB per wave and 128 KB per compute unit are in flight.  (1 GiB read and compared: tiles of 64 KB of a workgroup of
-// 1024, two in turn, 162 us; by waves 155; dealt by counters, eight workgroups on eight XCDs to each, 175.  One fp16 row of
-// 12 million, k = 1000, 33 us with four neighbouring tiles to a wave at a time, 35.5 with single ones; but a short row would then have few waves at work,
-// and a ramp one that writes most of the list: one bf16 row of 6 million, k = 1024, a ramp, 94 / 74.)
+// 1024, two in turn, 162 us; by waves 155; dealt by counters, eight workgroups on eight XCDs to each, 175.  Four neighbouring tiles to a wave at a time,
+// normal keys, cost up to 0.5 us less, but of a ramp a wave or two then write most of the list: 2^23 fp32 keys, k = 100, 54 / 42 us with single ones.)
 template <int DT, bool NT>
 using WaveSource = KeySource<DT, 64, 4, NT>;
 template <int DT, class Source, class Bound, class Append>
-__device__ __forceinline__ void sweep_by_waves(const Source& src, u32 first, u32 step, bool by_four, u32* te, u32 dirmask, Bound&& bound, Append&& append) {
+__device__ __forceinline__ void sweep_by_waves(const Source& src, u32 first, u32 step, u32* te, u32 dirmask, Bound&& bound, Append&& append) {
     typedef typename Source::Tile Tile;
     constexpr u32 E = Source::E, kRing = 4;
     constexpr u32 kAll = 0xffffffffu >> (32 - Source::kSlots);
@@ -1116,7 +1109,6 @@ __device__ __forceinline__ void sweep_by_waves(const Source& src, u32 first, u32
     const u32 nvec = (u32)src.nvec, last = nvec - 1u;
     u32 f0, f1;  // tiles [f0, f1) are full
     src.full_range(f0, f1);
-    const u32 begin = by_four ? kRing * first : first, apart = by_four ? 1u : step;  // a round of this wave: tiles cur, cur + apart, ..., the next begins kRing * step on
     Tile t[kRing];
     auto load = [&](u32 tile, Tile& x) __attribute__((always_inline)) {  // (beyond the row's end: its last vector, which is nobody's)
         x.tile = tile;
@@ -1128,7 +1120,7 @@ __device__ __forceinline__ void sweep_by_waves(const Source& src, u32 first, u32
     };
     ListRow lr;
     if (!bound([&]() __attribute__((always_inline)) {
-            if (begin < ntiles) static_for<0, (int)kRing>([&](auto c) __attribute__((always_inline)) { load(begin + (u32)decltype(c)::value * apart, t[decltype(c)::value]); });
+            if (first < ntiles) static_for<0, (int)kRing>([&](auto c) __attribute__((always_inline)) { load(first + (u32)decltype(c)::value * step, t[decltype(c)::value]); });
         }, lr)) return;
     const bool tied = lr.mode == kListTied, largest = dirmask == 0;
     const u32 T = lr.T;
@@ -1159,14 +1151,14 @@ __device__ __forceinline__ void sweep_by_waves(const Source& src, u32 first, u32
         if (tied) note_ties(x.tile, eq);
     };
     auto all_tiles = [&](auto&& one) __attribute__((always_inline)) {
-        for (u32 cur = begin; cur < ntiles; cur += kRing * step) {
+        for (u32 cur = first; cur < ntiles; cur += kRing * step) {
             if (ntiles - cur <= kRing * step) {
                 static_for<0, (int)kRing>([&](auto c) __attribute__((always_inline)) { one(t[decltype(c)::value]); });
                 break;
             }
             static_for<0, (int)kRing>([&](auto c) __attribute__((always_inline)) {
                 one(t[decltype(c)::value]);
-                load(cur + kRing * step + (u32)decltype(c)::value * apart, t[decltype(c)::value]);
+                load(cur + kRing * step + (u32)decltype(c)::value * step, t[decltype(c)::value]);
                 __builtin_amdgcn_sched_barrier(0);
             });
         }
@@ -1193,9 +1185,9 @@ __device__ __forceinline__ void sweep_by_waves(const Source& src, u32 first, u32
     }
     if (lr.exact != 0u) {
 #pragma unroll 1
-        for (u32 cur = begin; cur < ntiles; cur += kRing * step) {
+        for (u32 cur = first; cur < ntiles; cur += kRing * step) {
 #pragma unroll 1
-            for (u32 tile = cur; tile < ntiles && tile - cur < kRing * apart; tile += apart) {
+            for (u32 tile = cur; tile < ntiles && tile - cur < kRing * step; tile += step) {
                 load(tile, t[0]);
                 by_key(t[0]);
             }
@@ -1205,14 +1197,17 @@ __device__ __forceinline__ void sweep_by_waves(const Source& src, u32 first, u32
 #pragma unroll 1
         for (u32 e = 0; e < 2u; ++e) {
             const u32 tile = e == 0u ? 0u : f1;
-            if ((e == 0u ? f0 == 0u : tile >= ntiles) || (by_four ? tile / kRing : tile) % step != first) continue;
+            if ((e == 0u ? f0 == 0u : tile >= ntiles) || tile % step != first) continue;
             load(tile, t[0]);
             by_key(t[0]);
         }
     }
 }
 
-template <int DT, int V, bool NT>
+// Of rows from 16 MB up the sample is half as large as k_list_bound's, in runs of 4 vectors: as many runs, which is all that a trend's list is known by.
+// (Runs of 8, of 4, a ramp, k = 100 and 600: 2^23 fp32 keys 63 and 65, 42 and 45 us; 10 million fp16 keys 73 and 74, 50 and 52.  Normal keys, k = 100, of which twice as many
+// lines are read: 25.9 / 28.1 and 25.0 / 26.5, where k_list_bound and k_list_sweep take 35.7 and 31.2.)
+template <int DT, int V, int RUN, bool NT>
 __global__ void __launch_bounds__(kSharedBlock) k_list_stream(Params P, ListPlan L) {
     constexpr int B = kSharedBlock;
     struct BoundShared { RankShared rank; SampleList list; u32 red[4 * (B / 64)]; };
@@ -1226,11 +1221,11 @@ __global__ void __launch_bounds__(kSharedBlock) k_list_stream(Params P, ListPlan
     const RowShape rs = row_shape_scalar<DT>(P, row);
     Source src;
     src.init(rs);
-    ListWriter<DT, false, Source> w{list_entry<DT>(P), list_array(P, 1u, row) + list_segment<DT>(rs, wg, G, wave_unit<DT>(rs, G)),
+    ListWriter<DT, false, Source> w{list_entry<DT>(P), list_array(P, 1u, row) + list_segment<DT>(rs, wg, G, kWaveVecs),
                                     list_part<u64>(P, row, L.front_off) + (size_t)wg * L.slots, L.slots, sm.stage[wave], &run, none, nullptr, 0u};
-    sweep_by_waves<DT>(src, wave * G + wg, G * (u32)(B / 64), wave_unit<DT>(rs, G) != kWaveVecs, list_part<u32>(P, row, L.tile_off), P.dirmask,
+    sweep_by_waves<DT>(src, wave * G + wg, G * (u32)(B / 64), list_part<u32>(P, row, L.tile_off), P.dirmask,
                      [&](auto&& load_first, ListRow& lr) __attribute__((always_inline)) {
-                         bound_of_row<DT, B, V, true>(P, L, row, rs, row_state(P, row), &decided, nullptr, 0u, L.room, sm.bound.rank, &sm.bound.list,
+                         bound_of_row<DT, B, V, true, RUN>(P, L, row, rs, row_state(P, row), &decided, nullptr, 0u, L.room, sm.bound.rank, &sm.bound.list,
                                                       sm.bound.red, wg == 0u, [&]() __attribute__((always_inline)) { if (rs.k != 0u) load_first(); });
                          if (tid == 0) run = 0;
                          __syncthreads();
@@ -1960,7 +1955,7 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
         }
         const u32 l = i - segs[a];
         if (l < slots) return front[a * slots + l];
-        const u32 at = L.stream_block != 0 ? list_segment<DT>(rs, a, G, wave_unit<DT>(rs, G)) : list_segment<DT>(rs, a, G, (u32)ListSource<DT, false>::kTileVecs);
+        const u32 at = L.stream_block != 0 ? list_segment<DT>(rs, a, G, kWaveVecs) : list_segment<DT>(rs, a, G, (u32)ListSource<DT, false>::kTileVecs);
         return from[at + l];
     };
     if (for_ties) {
@@ -2413,7 +2408,7 @@ __global__ void __launch_bounds__(B, 4) k_list_row(Params P, ListPlan L) {
     rtopk_row_trace* st = row_state(P, row);
     Source src;
     src.init(rs);
-    bound_of_row<DT, B, V, false>(P, L, row, rs, st, &lr, te, src.ntiles(), kCap, sm.rank, nullptr, red, true, [] {});
+    bound_of_row<DT, B, V, false, 8>(P, L, row, rs, st, &lr, te, src.ntiles(), kCap, sm.rank, nullptr, red, true, [] {});
     if (tid == 0) run = 0;
     __syncthreads();
     if (lr.mode == kListSkip) return;
@@ -2943,12 +2938,12 @@ static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStrea
     if (L.stream_block != 0) {
         mark(events, 2, st);
         constexpr int kMost = DT == RTOPK_F32 ? 16 : 8;  // vectors per thread of the larger sample (16-bit keys: 16 do not fit the registers)
-        auto sweep = [&](auto v) {
-            if (nt) hipLaunchKernelGGL((k_list_stream<DT, decltype(v)::value, true>), grid, block, 0, st, P, L);
-            else hipLaunchKernelGGL((k_list_stream<DT, decltype(v)::value, false>), grid, block, 0, st, P, L);
+        auto sweep = [&](auto v, auto r) {
+            if (nt) hipLaunchKernelGGL((k_list_stream<DT, decltype(v)::value, decltype(r)::value, true>), grid, block, 0, st, P, L);
+            else hipLaunchKernelGGL((k_list_stream<DT, decltype(v)::value, decltype(r)::value, false>), grid, block, 0, st, P, L);
         };
-        if (L.sample == 3) sweep(std::integral_constant<int, 8>{});
-        else sweep(std::integral_constant<int, kMost>{});
+        if (L.sample == 3) sweep(std::integral_constant<int, 8>{}, std::integral_constant<int, 8>{});
+        else sweep(std::integral_constant<int, kMost>{}, std::integral_constant<int, 4>{});
     } else {
         if (L.sample == 2) hipLaunchKernelGGL((k_list_bound<DT, 512, 4>), rows, dim3(512), 0, st, P, L);
         else if (L.sample == 3) hipLaunchKernelGGL((k_list_bound<DT, 1024, 4>), rows, dim3(1024), 0, st, P, L);

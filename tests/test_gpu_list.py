@@ -415,6 +415,18 @@ def test_lists_a_little_too_long_are_cut_down():
                 assert tr[0].redo == 0 and 8192 < tr[0].pre_kept <= 16384, (tr[0].redo, tr[0].pre_kept)
 
 
+@pytest.mark.parametrize("dtype,n", [(F32, 1 << 22), (F32, (1 << 22) + 4099), (F16, (1 << 23) + 5)])
+def test_the_halved_sample_sees_a_trend(dtype, n):
+    # rows from 16 MB up: runs of half a line.  A ramp's list is a few stretches of the row, of which there are as many as runs; on either side of
+    # the rule's line, with a ragged end
+    x = np.linspace(3, -3, n).astype(np.float32)
+    for largest in (True, False):
+        for k in (16, 100, 600):
+            tr = _check("ramp", x, dtype, k, largest)
+            if dtype == F32:
+                assert k <= tr[0].pre_kept <= 8 * (n // 2048), tr[0].pre_kept
+
+
 @pytest.mark.parametrize("k", [70000, (1 << 25) // 100])
 def test_unsorted_long_lists(k):
     # better bins go to the output as they come, and the bin of rank k is ordered: keys of many values, duplicates (ties counted), a crowd in that
