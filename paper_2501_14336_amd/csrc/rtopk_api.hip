@@ -299,8 +299,8 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     }
     // Short lists of few rows: sample and sweep in one launch (k_list_stream), with half the sample, while one workgroup puts in order what that lists
     // (up to twice as much as it should be, 16384 entries at most).  us, two launches / one, normal keys: one fp32 row of 1.5 million, k = 16, 300 and 3000,
-    // 22.2 / 20.0, 25.1 / 21.5, 30.9 / 27.4; of 8 million 34.3 / 24.7, 35.8 / 27.7, 46.6 / 46.5 (a long list either way); of 24 million 41.7 / 35.3,
-    // 44.3 / 43.0.  fp16 rows of 2 million 22.4 / 21.0, 26.5 / 21.8, 33.3 / 28.6.  Shorter rows have less than a tile to a wave, and a sample that is a large
+    // 22.2 / 20.0, 25.1 / 21.5, 30.9 / 27.4; of 2^23 keys, k = 16, 100 and 256, 34.7 / 26.6, 36.3 / 28.0, 33.6 / 29.3; of 24 million 42.3 / 37.0,
+    // 44.4 / 38.9, 44.2 / 42.6.  fp16 rows of 2 million 22.4 / 21.0, 26.5 / 21.8, 33.3 / 28.6.  Shorter rows have less than a tile to a wave, and a sample that is a large
     // part of what a workgroup sweeps: one bf16 row of 400001, k = 1000, 24.9 / 29.5, of 700003, k = 100, 23.2 / 24.5, one fp16 row of
     // 1 million, k = 3000, 30.1 / 32.3; eleven fp32 rows of 135112, k = 615, 22.5 / 30.2.  Longer 16-bit rows keep eight waves per compute unit busy
     // where ties are counted: one bf16 row of 16 million, nine in ten equal, 30.7 / 32.8.
