@@ -281,11 +281,13 @@ __device__ __forceinline__ u32 sample_rank(Each&& each, u32 rank, u32 lo, u32 hi
 }
 
 // The same for one value per thread, in LDS, by the first wave alone -- no barriers among many waves (1024 values: 4.4 us with sample_rank): until
-// the values from lo up are at least `rank` and few more.  At least `rank` values are not below lo.  Contains two barriers; `v`
-// (RankShared::hist) may be written again after it.  RUNS: result[2] is how many values that are, result[3] the sum of squares of how many every eight
+// the values from lo up are at least `rank` and few more, or lo is one value that a crowd has (*exact).  At least `rank` values are not below lo.
+// Contains two barriers; `v` (RankShared::hist) may be written again after it.  RUNS: result[2] is how many values that are, result[3] the sum of squares of how many every eight
 // neighbouring threads have.
 // Bound by the latency of one wave.  [lo, hi] is divided into 512 bins, again and again, a bin being one LDS add (300 rows of 30011 fp16 keys, k = 100,
-// halved 16.0 us, so 15.6; 16 rows of 2^17 bf16 keys 15.9 / 15.0).  HALVE: it is halved, with a compare and a scalar population count per 64 values:
+// halved 16.0 us, so 15.6; 16 rows of 2^17 bf16 keys 15.9 / 15.0).  Bins of 16-bit keys are mostly one value each, and a bin
+// of few is no crowd: whoever takes it for one counts the whole sample's equal elements for nothing (1024 rows of 2^17 bf16 logits, k = 1024, halved 69.9, with bins
+// 70.9, so 69.8).  HALVE: it is halved, with a compare and a scalar population count per 64 values:
 // better where several workgroups of four waves share a compute unit and its LDS (1024 rows of 2^17 bf16 keys, k = 50, 54.7 / 55.5),
 // and for a few of 256 values (four fp16 rows of 89250, k = 2, 12.7 / 13.6).
 template <int B, bool RUNS = false, bool HALVE = false>
@@ -351,8 +353,8 @@ __device__ __forceinline__ u32 rank_by_one_wave(u32 value, u32 rank, u32 lo, u32
                 upto = (u32)__builtin_amdgcn_readlane((int)upto, l);
                 hi -= bin << sh;
                 lo = hi - lo > (1u << sh) - 1u ? hi - ((1u << sh) - 1u) : lo;  // (the last bin may reach beyond the range)
-                one = lo == hi;
                 if (upto <= slack) break;
+                one = lo == hi;
             }
         }
         if (tid == 0) {
