@@ -2029,30 +2029,25 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     order_list<DT, B>(P, row, rs, sm, n);
 }
 
-// k_list_part's lists: L.G of at most L.seg_stride entries, 8 B in all at most.  (Places and lengths read together, and the entries then put together in
-// LDS: 6.2 us for one row of 2^16 fp32 keys; so 5.6.)
+// k_list_part's lists: L.G of at most L.seg_stride entries, 8 B in all at most (so fewer than B lists).
+// Bound by latency: the lists' lengths and the row's record come in one trip to memory.  In two, one row of 2^18 fp32 keys, k = 3 and 32, took 12.3 and 14.2 us;
+// so 12.0 and 13.6.  An entry's list is guessed from their average length (found by halving, k = 48, 16.2 / 14.8).  Places and lengths read together, and
+// the entries then put together in LDS, took 0.6 us more.
 template <int DT, int B>
 __global__ void __launch_bounds__(B) k_part_finish(Params P, ListPlan L) {
     __shared__ OrderShared<B> sm;
-    __shared__ u32 segs[1025];
+    __shared__ u32 segs[B + 1];
     const u32 tid = threadIdx.x, G = (u32)L.G;
     const int row = (int)blockIdx.x;
+    const u32 c = tid < G ? list_part<u32>(P, row, L.seg_off)[tid] : 0u;
     if (list_row(P, row)->mode == kListSkip) return;
     const RowShape rs = row_shape_scalar<DT>(P, row);
-    const u32* counts = list_part<u32>(P, row, L.seg_off);
-    u32 total = 0;
-    for (u32 s0 = 0; s0 < G; s0 += B) {
-        const u32 c = s0 + tid < G ? counts[s0 + tid] : 0u;
-        const u32 incl = block_scan<B>(c, sm.wsum);
-        if (s0 + tid < G) segs[s0 + tid] = total + incl - c;
-        if (tid == B - 1) segs[1024] = total + incl;
-        __syncthreads();
-        total = segs[1024];
-        __syncthreads();
-    }
-    const u64* from = list_array(P, 1u, row);
-    if (tid == 0) segs[G] = total;  // (at most 1024 of them)
+    const u32 incl = block_scan<B>(c, sm.wsum);
+    segs[tid] = incl - c;
+    if (tid == B - 1) segs[B] = incl;
     __syncthreads();
+    const u32 total = segs[B];
+    const u64* from = list_array(P, 1u, row);
     const float per = (float)G / (float)total;
     auto entry = [&](u32 i) __attribute__((always_inline)) {  // (the lists are about equally long)
         u32 a = (u32)((float)i * per);
@@ -2360,7 +2355,7 @@ __global__ void __launch_bounds__(B, 4) k_list_held(Params P, ListPlan L) {
     }
 }
 
-// Few rows, small k: a row's stretches of 32 KB are held by a workgroup each, which list their best k; k_list_finish puts a
+// Few rows, small k: a row's stretches of 32 KB are held by a workgroup each, which list their best k; k_part_finish puts a
 // row's L.G lists of at most L.seg_stride entries in order.  Two launches, no sample, no row left over.
 constexpr int kPartBlock = kListPartBlock, kPartVecs = kListPartVecs;
 template <int DT>
