@@ -1929,6 +1929,11 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     // (k_list_sweep's few long segments: entries look for theirs, where the list is short, or so long that all waves are needed to order it.  One
     // row of 1048869 fp16 keys, k = 3990, 34.7 us, put together first 37.0; 41 fp32 rows of 74007, k = 28, 20.7 / 21.5; but eleven of 135112, k = 615, 24.9 / 22.5.)
     const bool few = L.stream_block == 0;
+    // (the lengths and the decision before the entries: what counts of a row with ties does not wait for the places)
+    const u32 c = tid < G ? list_part<u32>(P, row, L.seg_off)[tid] : 0u;  // (G is at most 256)
+    const ListRow* lr = list_row(P, row);
+    const u32 mode = lr->mode;
+    __builtin_amdgcn_sched_barrier(0);
     u64 e[kMost] = {};
     if (!for_ties && !(few && B <= 256)) {
 #pragma unroll
@@ -1936,9 +1941,6 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
             if (tid + j * (u32)B < places) e[j] = front[tid + j * (u32)B];
         }
     }
-    const u32 c = tid < G ? list_part<u32>(P, row, L.seg_off)[tid] : 0u;  // (G is at most 256)
-    const ListRow* lr = list_row(P, row);
-    const u32 mode = lr->mode;
     if (mode == kListSkip) return;
     const RowShape rs = row_shape_scalar<DT>(P, row);
     rtopk_row_trace* st = row_state(P, row);
