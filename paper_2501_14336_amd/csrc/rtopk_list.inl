@@ -455,6 +455,7 @@ struct SampleList {
     u32 key[kSampleList], place[kSampleList];
     u32 run[2048];       // how many of them each run has
     u32 bin[kListBins];  // how many of them, of those better than T, lie in each bin of a long list
+    u32 from[16], got[16];  // which of them every wave has: the waves come in any order
     u32 n, next;
 };
 // record: this workgroup writes the row's record.  after_load(): what may be done once the sample's loads are under way.
@@ -657,6 +658,7 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
             // (what follows from these is worked out here and not kept for the whole kernel: registers)
             asm volatile("" : "+v"(t0));
             forget();
+            if (lane == 63u) sl->got[wave] = 0;
             if (ballot64(lmax >= T) != 0u) {
                 // f(vector, how many of its elements are not below T) for the runs that are kept
                 auto kept = [&](auto&& f) __attribute__((always_inline)) {
@@ -674,7 +676,11 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
                 kept([&](auto, u32 c) __attribute__((always_inline)) { mine += c; });
                 const u32 incl = wave_inclusive_scan(mine);
                 u32 at = 0;
-                if (lane == 63u) at = atomicAdd(&sl->n, incl);
+                if (lane == 63u) {
+                    at = atomicAdd(&sl->n, incl);
+                    sl->from[wave] = at;
+                    sl->got[wave] = incl;
+                }
                 at = (u32)__builtin_amdgcn_readlane((int)at, 63) + incl - mine;
                 kept([&](auto uc, u32 c) __attribute__((always_inline)) {
                     constexpr int u = decltype(uc)::value;
@@ -780,16 +786,30 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
         if (split) {
             static_assert(sizeof(sm.hist) >= kListSplits * 8, "room for the candidates");
             u64* cand = (u64*)sm.hist;
-            if (tid < kListSplits) cand[tid] = ent.end();
-            __syncthreads();
+            // every total / 256-th of them, in the order of the waves, in which they did not come: the same row has the same splitters every time.
+            // (Those that are better than a crowd are not counted by wave, and taken as they came.)
             const u32 total = tied ? got - eq_got : got;
-            for (u32 i = tid; i < got; i += B) {
-                if (tied && sl->key[i] == T) continue;
-                // every total / 256-th
-                const u32 pos = atomicAdd(&sl->next, 1u);
-                const u32 s0 = total > kListSplits ? pos * kListSplits / total : pos;
-                const u32 s1 = total > kListSplits ? (pos + 1u) * kListSplits / total : pos + 1u;
-                if (s0 != s1) cand[s0] = entry_at(i);
+            if (tid < kListSplits) {
+                cand[tid] = ent.end();
+                const u32 pos = total > kListSplits ? ((tid + 1u) * total - 1u) / kListSplits : tid;
+                u32 before = 0, at = 0;
+#pragma unroll
+                for (u32 w = 0; w < (u32)(B / 64); ++w) {
+                    const u32 c = sl->got[w], l = pos - before;
+                    at = l < c ? sl->from[w] + l : at;
+                    before += c;
+                }
+                if (!tied && pos < total) cand[tid] = entry_at(at);
+            }
+            __syncthreads();
+            if (tied) {
+                for (u32 i = tid; i < got; i += B) {
+                    if (sl->key[i] == T) continue;
+                    const u32 pos = atomicAdd(&sl->next, 1u);
+                    const u32 s0 = total > kListSplits ? pos * kListSplits / total : pos;
+                    const u32 s1 = total > kListSplits ? (pos + 1u) * kListSplits / total : pos + 1u;
+                    if (s0 != s1) cand[s0] = entry_at(i);
+                }
             }
             __syncthreads();
             if (tid < kListSplits) {
@@ -2468,17 +2488,18 @@ __global__ void __launch_bounds__(B, 4) k_list_row(Params P, ListPlan L) {
 // ------------------------------------------------------------------------------------------------
 
 // Workgroup w moves segment w into buckets.  A bin's rank is the number of entries in better bins; a bucket is the run of
-// bins whose ranks share rank >> L.bucket_shift, its place in the array its first bin's rank.  Bins that begin at rank k or
+// bins whose ranks share rank >> L.bucket_shift, its place in the array its first bin's rank.  A bin that ends beyond the ranks of the next bucket, which is
+// then left without any, is that one alone: else its bucket, with what begins before it, would be longer than one workgroup puts in order.  Bins that begin at rank k or
 // beyond are dropped.  One atomic per bucket reserves all of a workgroup's places in it; what the registers do not hold
 // of a segment is read twice.
 template <int DT>
 __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan L) {
     constexpr int B = kLongBlock, kPer = kListBins / B;
-    __shared__ u32 start[kListBins];         // rank of every bin
+    __shared__ u32 bucket[kListBins];        // of every bin, or ~0
     __shared__ u32 place[kListMaxBuckets];   // of every bucket: this workgroup's entries, then their next place
     __shared__ u64 split[kListSplits + 1];
     __shared__ u32 wsum[B / 64];
-    __shared__ u32 s_end;
+    __shared__ u32 s_end, s_total;
     const u32 G = (u32)L.G, tid = threadIdx.x;
     const int row = (int)(blockIdx.x / G);
     const u32 wg = blockIdx.x % G;
@@ -2498,7 +2519,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     for (int i = 0; i < kHeld; ++i) held[i] = tid + (u32)i * B < mine ? from[tid + (u32)i * B] : 0ull;
     const u32* gh = list_part<u32>(P, row, L.hist_off);
     const u32 bs = L.bucket_shift, nb = L.nb;
-    u32 c[kPer], s = 0;
+    u32 c[kPer], s = 0, rank[kPer];
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
         c[i] = gh[kListBins - 1u - (tid * kPer + i)];  // from the best bin down
@@ -2507,19 +2528,28 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     for (u32 j = tid; j < nb; j += B) place[j] = 0;
     if (tid == 0) s_end = 0;
     const u32 incl = block_scan<B>(s, wsum);
-    u32 total = 0;
     {
         u32 r = incl - s;
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
-            start[kListBins - 1u - (tid * kPer + i)] = r;
+            const u32 j = (r >> bs) + 1u;
+            bucket[kListBins - 1u - (tid * kPer + i)] = r >= rs.k ? 0xffffffffu : j < nb && r + c[i] > ((j + 1u) << bs) ? j : j - 1u;
+            rank[i] = r;
             if (r < rs.k && r + c[i] >= rs.k) s_end = r + c[i];
             r += c[i];
         }
+        if (tid == B - 1) s_total = r;
     }
+    // f(bucket, rank) for this thread's bins that begin one
+    auto first_bins = [&](auto&& f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const u32 q = tid * kPer + i, b = bucket[kListBins - 1u - q];
+            if (b != 0xffffffffu && (q == 0u || b != bucket[kListBins - q])) f(b, rank[i]);
+        }
+    };
     __syncthreads();
-    // (start[0] is the worst bin's rank: its end is the total)
-    total = start[0] + gh[0];
+    const u32 total = s_total;
     const bool few = total < rs.k;
     const u32 end = few ? total : s_end;
     const bool drop = (mode == kListPlain && few) || end > (u32)((P.n + 1) / 2);  // (the buckets have half a candidate array)
@@ -2537,10 +2567,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
         u32* first = list_part<u32>(P, row, L.first_off);
         for (u32 j = tid; j < nb; j += B) place[j] = 0xffffffffu;
         __syncthreads();
-        for (u32 j = tid; j < kListBins; j += B) {  // j counts from the best bin
-            const u32 r = start[kListBins - 1u - j];
-            if (r < end && (j == 0 || (r >> bs) > (start[kListBins - j] >> bs))) place[r >> bs] = r;
-        }
+        first_bins([&](u32 b, u32 r) __attribute__((always_inline)) { place[b] = r; });
         __syncthreads();
         for (u32 j = tid; j < nb; j += B) {
             u32 i = j + 1u;
@@ -2552,10 +2579,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
         for (u32 j = tid; j < nb; j += B) place[j] = 0;
         __syncthreads();
     }
-    auto bucket_of = [&](u64 e) __attribute__((always_inline)) {
-        const u32 r = start[by_split != 0u ? list_bin_split(e, split) : list_bin(e, lo, sh)];
-        return r < end ? r >> bs : 0xffffffffu;
-    };
+    auto bucket_of = [&](u64 e) __attribute__((always_inline)) { return bucket[by_split != 0u ? list_bin_split(e, split) : list_bin(e, lo, sh)]; };
     // (what the registers hold of the segment is on its way before the ranks are known)
     u32 bk[kHeld];
 #pragma unroll
@@ -2576,10 +2600,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
         if (n != 0) place[j] = atomicAdd(&cursor[j], n);
     }
     __syncthreads();
-    for (u32 j = tid; j < kListBins; j += B) {
-        const u32 r = start[kListBins - 1u - j];
-        if (r < end && (j == 0 || (r >> bs) > (start[kListBins - j] >> bs))) place[r >> bs] += r;
-    }
+    first_bins([&](u32 b, u32 r) __attribute__((always_inline)) { place[b] += r; });
     __syncthreads();
     u64* dst = list_array(P, 0u, row);
 #pragma unroll
@@ -2713,7 +2734,7 @@ __device__ __forceinline__ bool bucket_range(const Params& P, const ListPlan& L,
     const uint2 f = list_part<uint2>(P, row, L.first_off)[j];
     *at = f.x;
     *count = f.y;
-    return f.x != 0xffffffffu && f.x < rs.k;
+    return f.x != 0xffffffffu && f.x < rs.k && f.y != 0u;  // (empty bins alone may begin one)
 }
 
 // One workgroup per bucket (blocks [0, nb) of a row) puts its entries in order; the other L.ties blocks of the row are for

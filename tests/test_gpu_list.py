@@ -303,6 +303,19 @@ def test_bins_do_not_follow_the_distance_to_a_few_keys(far):
                 assert tr[0].redo == 0, tr[0].redo
 
 
+def test_splitters_are_the_same_every_time():
+    # one key in 200 is a NaN, far above the rest: the interval between the last number's splitter and the first NaN's has its entries at its two
+    # ends.  The waves that gather the sample come in any order; the row is put in order the same way all the same, without a bucket too long
+    n, k = 1 << 22, 1 << 18
+    x = np.where(W.uniform01(n, 72) < 1 / 200, np.float32(np.nan), W.uniform01(n, 73)).astype(np.float32)
+    _check("far NaNs", x, F32, k)
+    d = to_device(_bits(x, F32), F32)
+    first = gpu_topk(d, F32, k, True, sorted=True)
+    for i in range(40):
+        gv, gi, tr, _ = gpu_topk(d, F32, k, True, sorted=True)
+        assert tr[0].redo == 0 and np.array_equal(gi, first[1]) and np.array_equal(gv, first[0]), (i, tr[0].redo)
+
+
 def test_crowd_of_nans_at_the_top_is_counted():
     # more NaNs than k: T is the NaNs' key, the last there is (the last of an even division's bins reaches beyond 32 bits)
     n = 1 << 22
