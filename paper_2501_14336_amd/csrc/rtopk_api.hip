@@ -319,14 +319,19 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     // lose: 2^26 keys, k = 2^16, uniform 149 / 104, the ramp 154 / 162.
     if (is_long && !sorted && (eb != 4 || n < ((int64_t)1 << 25))) return false;
     // k_list_stream: a workgroup of 512 threads per compute unit; k_list_sweep: one of 1024 where the list's histogram is counted, else four
-    // of 512 (three for 16-bit keys)
+    // of 512 (three for 16-bit keys), but no more than 256 to a row, 512 for 16-bit keys up to 128 MB.  The more there are, the more segments have to be put together, and the
+    // fewer, the less is there to hide the arithmetic of counting ties behind, of which 16-bit keys have twice as much.
+    // us, 1024 (16-bit keys: 768) / 512 / 256 to a row: one fp32 row of 2^25, k = 16 and 300, 51.5 / 50.1 / 49.5 and 50.9 / 50.7 / 50.6, of 3 * 2^24, k = 16, 59.1 / 58.0 /
+    // 56.4; one of 2^25 fp16 keys, k = 100, 41.1 / 38.5 / 37.9, nine in ten equal 42.5 / 43.6 / 48.1; of 14 million, nine in ten equal, 34.6 / 34.9 / 38.4;
+    // of 2^24 bf16 keys, a ramp, k = 100, 55.4 / 56.7 / 58.4; of 2^26, k = 300, nine in ten equal, 62.7 / 64.7 / 64.2.
     const int64_t tile_elems = (int64_t)(is_long ? 1024 : kHostGridBlock) * 64 / eb;
     const int64_t ntiles = (n + E - 1 + tile_elems - 1) / tile_elems;
     const int64_t wave_tiles = (n + E - 1 + 256 * E - 1) / (256 * E);  // (k_list_stream's)
     int64_t G = (stream || is_long ? 256 : eb == 4 ? 1024 : 768) / batch;
     if (G < 1) G = 1;
     if (G > (stream ? wave_tiles : ntiles)) G = stream ? wave_tiles : ntiles;
-    if (!is_long && G > 256) G = 256;  // (a finishing workgroup has a thread per segment)
+    const int64_t most_wgs = eb == 2 && batch * n * eb < ((int64_t)128 << 20) ? 512 : 256;
+    if (!is_long && G > most_wgs) G = most_wgs;
     L->G = (int)G;
     L->stream_block = stream ? 512 : 0;
     // (one sweep: nothing is read twice.  2^26 fp32 keys, k = n / 100 as a mask, 133 us with ordinary loads, 121 past the
@@ -334,7 +339,7 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     // against 37.8)
     L->stream = batch * n * eb > ((int64_t)128 << 20);
     // (256 segments to read keep 1024 threads busy: one fp16 row of 6 million, k = 16, 256 threads 25.9, k = 100, 1024 threads 23.3)
-    L->finish = room > 2048.0 || stream ? 1024 : 256;
+    L->finish = room > 2048.0 || stream || G > 256 ? 1024 : 256;  // (and a thread per segment)
     L->room = (u32)L->finish * 8u;
     const double twice = 2.0 * room < 2.0 * L->room ? 2.0 * room : 2.0 * L->room;
     L->most = twice > L->room ? (u32)twice : L->room;

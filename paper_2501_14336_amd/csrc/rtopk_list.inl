@@ -1940,7 +1940,7 @@ template <int DT, int B>
 __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     constexpr u32 kMost = 16;  // places per thread
     __shared__ OrderShared<B> sm;
-    __shared__ u32 segs[257];
+    __shared__ u32 segs[B + 1];
     const u32 tid = threadIdx.x, G = (u32)L.G, slots = L.slots, log = 31u - (u32)__builtin_clz(slots);
     const bool for_ties = blockIdx.x >= (u32)P.batch;
     const int row = for_ties ? (int)((blockIdx.x - (u32)P.batch) / (u32)L.ties) : (int)blockIdx.x;
@@ -1950,7 +1950,7 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     // row of 1048869 fp16 keys, k = 3990, 34.7 us, put together first 37.0; 41 fp32 rows of 74007, k = 28, 20.7 / 21.5; but eleven of 135112, k = 615, 24.9 / 22.5.)
     const bool few = L.stream_block == 0;
     // (the lengths and the decision before the entries: what counts of a row with ties does not wait for the places)
-    const u32 c = tid < G ? list_part<u32>(P, row, L.seg_off)[tid] : 0u;  // (G is at most 256)
+    const u32 c = tid < G ? list_part<u32>(P, row, L.seg_off)[tid] : 0u;  // (G is at most B)
     const ListRow* lr = list_row(P, row);
     const u32 mode = lr->mode;
     __builtin_amdgcn_sched_barrier(0);
@@ -1967,10 +1967,11 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     const u32 incl = block_scan<B>(c, sm.wsum);
     if (tid < G) segs[tid] = incl - c;
     if (tid == B - 1) segs[G] = incl;
-    const bool over = __syncthreads_or(c > slots ? 1 : 0) != 0;
+    const bool over = __syncthreads_or(c > slots + (few ? 8u : 0u) ? 1 : 0) != 0;  // (a segment has more than its places, or many more)
     const u32 total = segs[G];
     const bool useless = (mode == kListPlain && total < rs.k) || total > (u32)((P.n + 1) / 2);
     const u64* from = list_array(P, 1u, row);
+    const u32 unit = few ? (u32)ListSource<DT, false>::kTileVecs : kWaveVecs;
     auto entry = [&](u32 i) __attribute__((always_inline)) {
         u32 a = 0, b = G;  // the segment that holds entry i: the last one that begins at or before it
         while (b - a > 1u) {
@@ -1979,8 +1980,7 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
         }
         const u32 l = i - segs[a];
         if (l < slots) return front[a * slots + l];
-        const u32 at = L.stream_block != 0 ? list_segment<DT>(rs, a, G, kWaveVecs) : list_segment<DT>(rs, a, G, (u32)ListSource<DT, false>::kTileVecs);
-        return from[at + l];
+        return from[list_segment<DT>(rs, a, G, unit) + l];
     };
     if (for_ties) {
         const u32 w = (blockIdx.x - (u32)P.batch) % (u32)L.ties;
@@ -2023,10 +2023,11 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     if (total > 8u * B) {
         n = 0;
         if (total <= L.most) {  // (at most kMost * B)
+            const bool held = !few && __syncthreads_or(c > slots ? 1 : 0) == 0;  // (every segment has places enough; else entries look for themselves)
 #pragma unroll
             for (u32 j = 0; j < kMost; ++j) {
                 const u32 i = tid + j * (u32)B, a = i >> log, l = i & (slots - 1u);
-                if (over || few) e[j] = i < total ? entry(i) : ~0ull;  // (a segment of more than its places: entries look for themselves)
+                if (!held) e[j] = i < total ? entry(i) : ~0ull;
                 else if (i >= places || l >= segs[a + 1u] - segs[a]) e[j] = ~0ull;
             }
             n = keep_best<B>(e, total, rs.k < total ? rs.k : total, sm);
@@ -2046,6 +2047,11 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
         for (u32 j = 0; j < kMost; ++j) {
             const u32 i = tid + j * (u32)B, a = i >> log, l = i & (slots - 1u);
             if (i < places && l < segs[a + 1u] - segs[a]) sm.buf[segs[a] + l] = e[j];
+        }
+        // (k_list_sweep's 512 segments: one of them has a little more than its places in every other row.  k_list_stream's have not, and 0.15 us to lose here.)
+        if (few && ballot64(c > slots) != 0u) {
+            const u32 at = list_segment<DT>(rs, tid, G, unit);
+            for (u32 l = slots; l < c; ++l) sm.buf[segs[tid] + l] = from[at + l];
         }
     }
     order_list<DT, B>(P, row, rs, sm, n);

@@ -459,3 +459,17 @@ def test_unsorted_long_lists(k):
             edge = key[order[k - 1]]
             want = np.concatenate([np.flatnonzero(key > edge), np.flatnonzero(key == edge)[: k - int((key > edge).sum())]])
             assert np.array_equal(np.sort(gi[0]), np.sort(want)) and np.array_equal(bits[0][gi[0]], gv[0])
+
+
+@pytest.mark.parametrize("dtype", [F16, BF16])
+def test_short_lists_in_many_segments(dtype):
+    # one 16-bit row above 24 MB: 512 segments, of which a few have a little more than the places that are read at once, or (a ramp) one has nearly all; and a
+    # row of which most is one value, so that next to nothing is listed
+    n = 13000001
+    x = W.normal(n, 91, sigma=3.0)
+    for k in (16, 300, 1000):
+        tr = _check("many segments", x, dtype, k, largest=k != 300)
+        assert tr[0].redo == 0 and tr[0].pre_kept < 8192
+    y = np.where(W.uniform01(n, 92) < 0.9, np.float32(0.5), x / 16).astype(np.float32)
+    _check("many segments, ties", y, dtype, 1000, largest=True)
+    _check("many segments, ramp", np.linspace(-3, 3, n).astype(np.float32), dtype, 100)
