@@ -280,28 +280,33 @@ __device__ __forceinline__ u32 sample_rank(Each&& each, u32 rank, u32 lo, u32 hi
     }
 }
 
-// The same for one value per thread, in LDS, by the first wave alone -- no barriers among many waves (1024 values: 4.4 us with sample_rank): until
+// The same for N values in LDS (v[0 .. N), written by the threads), by the first wave alone -- no barriers among many waves (1024 values: 4.4 us with sample_rank): until
 // the values from lo up are at least `rank` and few more, or lo is one value that a crowd has (*exact).  At least `rank` values are not below lo.
-// Contains two barriers; `v` (RankShared::hist) may be written again after it.  RUNS: result[2] is how many values that are, result[3] the sum of squares of how many every eight
-// neighbouring threads have.
+// half: only the first N / 2 are there.  Begins and ends with a barrier; `v` (RankShared::hist) may be written again after it.  RUNS: result[2] is how many values that are, result[3] the sum of squares of how many every eight
+// neighbours have.
 // Bound by the latency of one wave.  [lo, hi] is divided into 512 bins, again and again, a bin being one LDS add (300 rows of 30011 fp16 keys, k = 100,
 // halved 16.0 us, so 15.6; 16 rows of 2^17 bf16 keys 15.9 / 15.0).  Bins of 16-bit keys are mostly one value each, and a bin
 // of few is no crowd: whoever takes it for one counts the whole sample's equal elements for nothing (1024 rows of 2^17 bf16 logits, k = 1024, halved 69.9, with bins
 // 70.9, so 69.8).  HALVE: it is halved, with a compare and a scalar population count per 64 values:
 // better where several workgroups of four waves share a compute unit and its LDS (1024 rows of 2^17 bf16 keys, k = 50, 54.7 / 55.5),
 // and for a few of 256 values (four fp16 rows of 89250, k = 2, 12.7 / 13.6).
-template <int B, bool RUNS = false, bool HALVE = false>
-__device__ __forceinline__ u32 rank_by_one_wave(u32 value, u32 rank, u32 lo, u32 hi, u32* v, u32* result, bool* exact) {
+template <int N, bool RUNS = false, bool HALVE = false>
+__device__ __forceinline__ u32 rank_by_one_wave(u32 rank, u32 lo, u32 hi, u32* v, u32* result, bool* exact, bool half = false) {
     constexpr u32 kBins = 512, kMine = kBins / 64;
-    static_assert(B + kBins <= 2 * 2049 && B % 4 == 0, "bins behind the values");
+    static_assert(N + kBins <= 2 * 2049 && N % 4 == 0, "bins behind the values");
     const u32 tid = threadIdx.x;
-    v[tid] = value;
     __syncthreads();
     if (tid < 64u) {
-        constexpr int kPer = B / 64;
+        constexpr int kPer = N / 64;
         u32 mine[kPer];
+        auto each = [&](auto&& f) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < kPer; ++i) mine[i] = v[i * 64 + tid];
+            for (int i = 0; i < (kPer + 1) / 2; ++i) f(i);
+            if (half) return;
+#pragma unroll
+            for (int i = (kPer + 1) / 2; i < kPer; ++i) f(i);
+        };
+        each([&](int i) __attribute__((always_inline)) { mine[i] = v[i * 64 + tid]; });
         const u32 slack = rank + 1u + rank / 16u;
         bool one = lo >= hi;
         if (HALVE || (kPer <= 4 && rank < 8u)) {
@@ -309,8 +314,7 @@ __device__ __forceinline__ u32 rank_by_one_wave(u32 value, u32 rank, u32 lo, u32
             while (lo < end) {
                 const u32 mid = end - (end - lo) / 2u;
                 u32 c = 0;
-#pragma unroll
-                for (int i = 0; i < kPer; ++i) c += (u32)__popcll(ballot64(mine[i] >= mid));
+                each([&](int i) __attribute__((always_inline)) { c += (u32)__popcll(ballot64(mine[i] >= mid)); });
                 if (c >= rank) {
                     lo = mid;
                     if (c <= slack) break;
@@ -320,7 +324,7 @@ __device__ __forceinline__ u32 rank_by_one_wave(u32 value, u32 rank, u32 lo, u32
             }
             one = lo == end;
         } else {
-            u32* bins = v + B;
+            u32* bins = v + N;
             u32 above = 0;  // values above hi: fewer than `rank`
             while (!one) {
                 const u32 width = 32u - (u32)__builtin_clz(hi - lo), sh = width > 9u ? width - 9u : 0u;
@@ -328,10 +332,9 @@ __device__ __forceinline__ u32 rank_by_one_wave(u32 value, u32 rank, u32 lo, u32
 #pragma unroll
                 for (u32 j = 0; j < kMine; j += 4u) *(uint4*)&bins[tid * kMine + j] = make_uint4(0, 0, 0, 0);
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-#pragma unroll
-                for (int i = 0; i < kPer; ++i) {
+                each([&](int i) __attribute__((always_inline)) {
                     if (mine[i] >= lo && mine[i] <= hi) atomicAdd(&bins[(hi - mine[i]) >> sh], 1u);
-                }
+                });
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 u32 c[kMine], s = 0;
 #pragma unroll
@@ -363,12 +366,11 @@ __device__ __forceinline__ u32 rank_by_one_wave(u32 value, u32 rank, u32 lo, u32
         }
         if constexpr (RUNS) {
             u32 word = 0, sq = 0;  // lane 2 i, 2 i + 1: which of the values i * 64 .. i * 64 + 63 they are
-#pragma unroll
-            for (int i = 0; i < kPer; ++i) {
+            each([&](int i) __attribute__((always_inline)) {
                 const u64 m = ballot64(mine[i] >= lo);
                 word = tid == 2u * (u32)i ? (u32)m : word;
                 word = tid == 2u * (u32)i + 1u ? (u32)(m >> 32) : word;
-            }
+            });
             u32 all = (u32)__builtin_popcount(word);
 #pragma unroll
             for (u32 b = 0; b < 32u; b += 8u) {
@@ -539,22 +541,37 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
         }
         return m;
     };
-    u32 lmax = 0;
+    // (16-bit keys are ranked on the 16 bits they have: fewer rounds)
+    constexpr u32 ksh = DT == RTOPK_F32 ? 0u : 16u;
+    // One wave can rank a quarter as many values as there are.  Where 512 lanes have eight vectors and more each, a larger rank is found among two values per lane, the
+    // best of either half of its vectors (eight fp32 rows of 524288, nine in ten equal, k = 3000, rank 158: 32.8 us with sample_rank, 26.9 so; two values for every
+    // rank: 8 rows, k = 1000, 24.5 / 25.3).
+    constexpr u32 W = GATHER && B == 512 && V >= 8 ? 2u : 1u;
+    const bool two = W == 2u && rank > lanes / 4u;
+    const u32 vals = !two ? lanes : vecs < 2u * (u32)B ? vecs : 2u * (u32)B;
+    u32 best[W] = {}, lmax = 0;
 #pragma unroll
     for (int u = 0; u < V; ++u) {
         keys_of_vector<DT>(q[u], P.dirmask);
         const u32 m = best_of(q[u]);
-        lmax = lmax > m ? lmax : m;
+        best[u * W / V] = best[u * W / V] > m ? best[u * W / V] : m;
     }
     if (runs != kRuns) {  // (beyond a smaller sample: no key is below these)
-        lmax = 0;
+#pragma unroll
+        for (u32 w = 0; w < W; ++w) best[w] = 0;
 #pragma unroll
         for (int u = 0; u < V; ++u) {
             if (run_of(tid, (u32)u) >= runs) q[u] = make_uint4(0, 0, 0, 0);
             const u32 m = best_of(q[u]);
-            lmax = lmax > m ? lmax : m;
+            best[u * W / V] = best[u * W / V] > m ? best[u * W / V] : m;
         }
     }
+#pragma unroll
+    for (u32 w = 0; w < W; ++w) lmax = lmax > best[w] ? lmax : best[w];
+    auto put_values = [&]() __attribute__((always_inline)) {
+        sm.hist[tid] = (two ? best[0] : lmax) >> ksh;
+        if (two) sm.hist[(u32)B + tid] = best[W - 1u] >> ksh;
+    };
     auto forget = [&]() __attribute__((always_inline)) {  // (nothing worked out from the elements is kept: registers)
 #pragma unroll
         for (int u = 0; u < V; ++u) asm volatile("" : "+v"(q[u].x), "+v"(q[u].y), "+v"(q[u].z), "+v"(q[u].w));
@@ -570,8 +587,6 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
     top = best_of_waves<B>(red, 2, MaxOf());
     low = best_of_waves<B>(red + 1, 2, MinOf());
     __syncthreads();
-    // (16-bit keys are ranked on the 16 bits they have: fewer rounds)
-    constexpr u32 ksh = DT == RTOPK_F32 ? 0u : 16u;
     u32 T = 0, cnt = 0, eq = 0, thin = 0, got = 0, eq_got = 0;
     bool exact = false;
     auto all = [&](auto&& f) __attribute__((always_inline)) {
@@ -582,15 +597,16 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
     };
     bool elements = false;  // T is ranked among the elements
     bool alike = true;      // runs may be fewer draws than they have elements
-    u32 by_lanes = 0;       // T was ranked among the lanes' best: how many of those are not below it
+    u32 by_lanes = 0;       // T was ranked among the lanes' best: how many of those values are not below it
     if (whole) {
-    } else if (rank <= lanes / 4u) {
-        T = rank_by_one_wave<B, GATHER, (B <= 256)>(lmax >> ksh, rank, low >> ksh, top >> ksh, sm.hist, sm.selv, &exact);
+    } else if (rank <= vals / 4u) {
+        put_values();
+        T = rank_by_one_wave<(int)W * B, GATHER, (B <= 256)>(rank, low >> ksh, top >> ksh, sm.hist, sm.selv, &exact, W == 2u && !two);
         if constexpr (GATHER) {
             by_lanes = sm.selv[2];
             const float c = (float)by_lanes;
-            alike = (float)sm.selv[3] > (2.0f + c / (float)(lanes / 8u)) * c;
-            if (by_lanes > lanes / 2u)  // (T is what most of the sample equals)
+            alike = (float)sm.selv[3] > (2.0f + c / (float)(vals / 8u)) * c;
+            if (by_lanes > vals / 2u)  // (T is what most of the sample equals)
                 while ((runs >> thin) > kLeastThinned) ++thin;
         }
     } else if (rank <= vecs / 4u) {
@@ -758,9 +774,10 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
             fresh = again = true;
             // (so many lanes have that many such elements, if the next ones have as many each: one wave finds that out sooner)
             const float more = need * (float)by_lanes / (float)got * 1.25f + 2.0f;
-            if (by_lanes != 0u && thin == 0u && more < (float)(lanes / 2u)) {
+            if (by_lanes != 0u && thin == 0u && more < (float)(vals / 2u)) {
                 __syncthreads();
-                T = rank_by_one_wave<B>(lmax >> ksh, (u32)more, 0u, top >> ksh, sm.hist, sm.selv, &exact) << ksh;
+                put_values();
+                T = rank_by_one_wave<(int)W * B>((u32)more, 0u, top >> ksh, sm.hist, sm.selv, &exact, W == 2u && !two) << ksh;
             } else {
                 elements = true;
             }
@@ -2202,7 +2219,8 @@ __device__ __forceinline__ u32 hold_and_list(const Params& P, const RowShape& rs
         }
         __syncthreads();
         if (rs.k <= (u32)B / 2u) {
-            T = rank_by_one_wave<B>(lmax, rs.k, low, top, sm.rank.hist, sm.rank.selv, &exact);
+            sm.rank.hist[tid] = lmax;
+            T = rank_by_one_wave<B>(rs.k, low, top, sm.rank.hist, sm.rank.selv, &exact);
         } else if (NV < 16 && rs.k <= (u32)(B * NV) / 2u) {  // (with 16 vectors the registers do not allow it)
             T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) {
                 static_for<0, kGroups>([&](auto gc) __attribute__((always_inline)) {

@@ -473,3 +473,17 @@ def test_short_lists_in_many_segments(dtype):
     y = np.where(W.uniform01(n, 92) < 0.9, np.float32(0.5), x / 16).astype(np.float32)
     _check("many segments, ties", y, dtype, 1000, largest=True)
     _check("many segments, ramp", np.linspace(-3, 3, n).astype(np.float32), dtype, 100)
+
+
+@pytest.mark.parametrize("dtype,n", [(F32, 300000), (F32, 524288 + 3), (F16, (1 << 21) + 9), (F32, (1 << 22) + 1)])
+def test_ranks_on_both_sides_of_what_one_value_per_lane_holds(dtype, n):
+    # the sample's rank of the k-th key is found among one value per lane, among two, and among vectors: k around 128 and 256 of 512 and 1024 values, with
+    # crowds and in blocks, where a second, lower rank is looked for
+    elems = 16384 if dtype == F32 and n < (1 << 22) else 32768  # of the sample
+    for rank in (120, 136, 250, 264):
+        s = (-6 + (36 + 4 * (rank - 6)) ** 0.5) / 2
+        k = int(s * s * n / elems)
+        x = W.normal(n, rank, sigma=3.0)
+        for name, y in (("normal", x), ("nine in ten", np.where(W.uniform01(n, 5) < 0.9, np.float32(1.5), x)), ("blocks", np.repeat(x[: n // 64 + 1], 64)[:n])):
+            tr = _check("rank %d, %s" % (rank, name), y.astype(np.float32), dtype, k, largest=rank != 136, by_list=True)
+            assert tr[0].redo & 1 == 0
