@@ -300,13 +300,20 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     // Short lists of few rows: sample and sweep in one launch (k_list_stream), with half the sample, while one workgroup puts in order what that lists
     // (up to twice as much as it should be, 16384 entries at most).  us, two launches / one, normal keys: one fp32 row of 1.5 million, k = 16, 300 and 3000,
     // 22.2 / 20.0, 25.1 / 21.5, 30.9 / 27.4; of 2^23 keys, k = 16, 100 and 256, 34.7 / 26.6, 36.3 / 28.0, 33.6 / 29.3; of 24 million 42.3 / 37.0,
-    // 44.4 / 38.9, 44.2 / 42.6.  fp16 rows of 2 million 22.4 / 21.0, 26.5 / 21.8, 33.3 / 28.6.  Shorter rows have less than a tile to a wave, and a sample that is a large
-    // part of what a workgroup sweeps: one bf16 row of 400001, k = 1000, 24.9 / 29.5, of 700003, k = 100, 23.2 / 24.5, one fp16 row of
-    // 1 million, k = 3000, 30.1 / 32.3; eleven fp32 rows of 135112, k = 615, 22.5 / 30.2.  Longer 16-bit rows keep eight waves per compute unit busy
-    // where ties are counted: one bf16 row of 16 million, nine in ten equal, 30.7 / 32.8.
+    // 44.4 / 38.9, 44.2 / 42.6.  fp16 rows of 2 million 22.4 / 21.0, 26.5 / 21.8, 33.3 / 28.6.
+    // Rows below 1 MB have a sample of 2048 vectors in a launch of its own, half of the one that is taken here, which every workgroup has to rank: fp32 rows of 2^17, k = 300,
+    // one 21.1 / 21.0, 8 20.3 / 23.4, 24 23.4 / 30.1; of 200000, k = 300 and 1500, one 21.5 / 21.8, 24.8 / 28.1, 8 22.9 / 23.6, 25.8 / 34.4; of 2^18 one 22.5 / 20.5, 25.5 /
+    // 23.3, 8 23.2 / 21.1, 26.8 / 24.7; eleven of 135112, k = 615, 22.5 / 30.2.  16-bit rows of 1 MB gain as much with normal keys (one of 2^19 22.5 / 19.9), but not
+    // a ramp with infinities (42 / 56); from 3 MB on that is gone (1.6 million 52.9 / 52.2).
+    // 16-bit keys have twice the arithmetic per byte, and the two launches twice the waves to hide it behind, where ties are counted above all: one bf16 row of 16 million, nine
+    // in ten equal, 30.7 / 32.8; 32 rows of 1.7 million fp16 keys, k = 16, normal 38.4 / 38.9, nine in ten equal 45.5 / 51.0, uniform, k = 300, 56.9 / 43.4; 30 of 2^21
+    // 41.2 / 44.2, 40.9 / 44.4, 57.0 / 46.1; 32 of 2^21 43.2 / 47.8, 50.7 / 60.9, 58.1 / 51.3.
+    // More than 32 rows have so few workgroups each that they take the sample for little: 24 fp32 rows of 2^18, k = 300, 27.5 / 24.6, 32 27.6 / 26.8, 40 29.6 / 27.5, 64
+    // 31.2 / 32.2; of 2^19 32 33.5 / 31.9, 64 43.9 / 50.6.  (32 fp32 rows of 2^20, 4 MB apart, eight workgroups each: k = 16 44.1 / 46.0, k = 300 54.0 / 48.4; 28 rows 39.5 / 36.4,
+    // 48.4 / 38.7, 32 of 10^6 38.9 / 38.7, 47.4 / 41.4.)
     bool stream = false;
     if (L->row_block == 0 && batch <= 32 && n * eb >= ((int64_t)(eb == 4 ? 1 : 3) << 20) &&
-        (eb == 4 || n * eb <= ((int64_t)24 << 20))) {
+        (eb == 4 || (n * eb <= ((int64_t)24 << 20) && batch * n * eb <= ((int64_t)112 << 20)))) {
         expect(L->sample == 4 && eb == 4 ? 8192 : 4096);
         stream = room <= 8192.0 && listed * 1.1 <= 0.5 * (double)n;
     }
