@@ -345,8 +345,9 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     // caches; 1024 rows of 2^17 bf16 keys, k = 50, 64 against 57.5; 2^24 fp32 keys, which the last-level cache holds, 36.7
     // against 37.8)
     L->stream = batch * n * eb > ((int64_t)128 << 20);
-    // (256 segments to read keep 1024 threads busy: one fp16 row of 6 million, k = 16, 256 threads 25.9, k = 100, 1024 threads 23.3)
-    L->finish = room > 2048.0 || stream || G > 256 ? 1024 : 256;  // (and a thread per segment)
+    // (256 segments to read keep 1024 threads busy: one fp16 row of 6 million, k = 16, 256 threads 25.9, k = 100, 1024 threads 23.3.  A list that 256 threads
+    // cannot hold goes to k_list_redo, so a little too much room here as well: 32 rows of 2^21 fp16 keys, k = 300, room for 1907 entries, 54.7 / 50.1)
+    L->finish = room * 1.2 > 2048.0 || stream || G > 256 ? 1024 : 256;  // (and a thread per segment)
     L->room = (u32)L->finish * 8u;
     const double twice = 2.0 * room < 2.0 * L->room ? 2.0 * room : 2.0 * L->room;
     L->most = twice > L->room ? (u32)twice : L->room;
