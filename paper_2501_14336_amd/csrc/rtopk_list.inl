@@ -85,9 +85,6 @@ __device__ __forceinline__ RowShape row_shape_scalar(const Params& P, int row) {
     return r;
 }
 
-// (explicitly global: a wait for a flat operation's result waits for every load under way)
-__device__ __forceinline__ u32 add_of_agent(u32* p, u32 n) { return __hip_atomic_fetch_add((Glb<u32>*)p, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
 // A row's decision, read into scalar registers (it is the same for every lane, which a load does not know).
 __device__ __forceinline__ ListRow list_row_scalar(const ListRow* p) {
     ListRow r;
@@ -928,7 +925,7 @@ __device__ __forceinline__ u32 list_segment(const RowShape& rs, u32 wg, u32 G, u
     return (u32)at;
 }
 // k_list_stream: tiles of 4 KB, which are dealt to the waves one by one.
-constexpr u32 kWaveVecs = 256, kSharedWaves = kSharedBlock / 64;
+constexpr u32 kWaveVecs = 256;
 
 // Element s (0 .. kSlots - 1, different in every lane) of a tile that is held in registers: a tree of selects.  (An index
 // that varies would put the tile into scratch memory.)
@@ -1050,8 +1047,6 @@ __device__ __forceinline__ void sweep_row(const Source& src, u32 wg, u32 G, cons
 
 // (The compiler keeps 30 to 60 scalar registers of the fp32 sweeps, and up to 200 of the 16-bit ones and of the row kernels, in lanes of a
 // vector register; the sweeps are at the rate of memory all the same.)
-template <bool LONG, int B>
-constexpr u32 list_stage() { return !LONG ? kListStage : B == kSharedBlock ? 2 * kListStageLong : kListStageLong; }
 // A wave takes one noted element per lane at a time until no lane has any left, stages them in LDS, and writes
 // a full stage to the workgroup's part of the list.
 template <int DT, bool LONG, class Source>
