@@ -190,6 +190,22 @@ def test_rows_whose_sample_misleads_are_done_again(k):
             _check("misled", x if largest else -x, F32, k, largest, srt, why=8)
 
 
+def test_misled_short_lists_of_two_launches():
+    # the same where the sample is a launch of its own: one row too short for the sweep that takes it along (a sample of 2048 vectors; lists for 256
+    # and for 1024 threads to put in order), and more rows than that takes
+    for n, batch, vectors, k in ((200000, 1, 2048, 300), (200000, 1, 2048, 3500), (400000, 33, 4096, 300)):
+        pos = _sampled(n, vectors, 4)
+        hidden = np.setdiff1d(np.arange(n), pos)
+        for largest in (True, False):
+            x = W.normal(batch * n, 36).reshape(batch, n)
+            y = x.copy()
+            x[:, pos] = 100.0 + W.uniform01(len(pos), 37)
+            y[:, hidden[W.uniform01(len(hidden), 64) < 0.65]] = 9.0
+            _check("misled", x if largest else -x, F32, k, largest, batch=batch, why=8)
+            tr = _check("hidden majority", y if largest else -y, F32, k, largest, batch=batch, why=5)
+            assert all(t.redo & 1 for t in tr)
+
+
 def test_misled_rows_beside_others():
     # long lists, several workgroups per row, and every second row's list is no use: its buckets stay empty, its record says so,
     # and the rows beside it are not touched
@@ -428,16 +444,65 @@ def test_lists_a_little_too_long_are_cut_down():
                 assert tr[0].redo == 0 and 8192 < tr[0].pre_kept <= 16384, (tr[0].redo, tr[0].pre_kept)
 
 
-@pytest.mark.parametrize("dtype,n", [(F32, 1 << 22), (F32, (1 << 22) + 4099), (F16, (1 << 23) + 5)])
-def test_the_halved_sample_sees_a_trend(dtype, n):
-    # rows from 16 MB up: runs of half a line.  A ramp's list is a few stretches of the row, of which there are as many as runs; on either side of
-    # the rule's line, with a ragged end
+@pytest.mark.parametrize("k,most", [(300, 2048 + 150), (3500, 8192 + 1500)])
+def test_lists_a_little_too_long_are_cut_down_after_two_launches(k, most):
+    # the same where sample and sweep are two launches, and a list's entries look for their segment: 256 threads (2048 entries, up to 2424 cut down)
+    # and 1024 threads (8192, up to 12788).  The bound is the sample's alone: so many more elements above it lengthen the list by just as many
+    n = 200000
+    hidden = np.setdiff1d(np.arange(n), _sampled(n, 2048, 4))
+    x = W.normal(n, 51)
+    below = hidden[x[hidden] < 0]
+    for largest in (True, False):
+        base = _check("as expected", x if largest else -x, F32, k, largest)[0].pre_kept
+        more = most - base
+        assert 0 < more < len(below)
+        y = x.copy()
+        y[below[:: len(below) // more][:more]] = 9.0 + W.uniform01(more, 52)
+        for srt in (True, False):
+            tr = _check("a little too long", y if largest else -y, F32, k, largest, sorted=srt)
+            assert tr[0].redo == 0 and tr[0].pre_kept == most, (tr[0].redo, tr[0].pre_kept, base)
+
+
+@pytest.mark.parametrize("dtype,n,runs", [(F32, (1 << 22) - 4099, 512), (F32, 1 << 22, 2048), (F32, (1 << 22) + 4099, 2048),
+                                          (F16, (1 << 23) - 4099, 512), (F16, (1 << 23) + 5, 1024), (BF16, (1 << 23) + 5, 1024)])
+def test_the_halved_sample_sees_a_trend(dtype, n, runs):
+    # rows from 16 MB up: runs of half a line, and as many as there were.  A ramp's list is a few stretches of the row, of which there are as many as runs; on
+    # either side of the rule's line, with a ragged end.  k = 600 is rank 25 of the sample at most, which seven of its best runs of four vectors
+    # hold, one vector to a lane; 16-bit keys that equal the bound are listed with it, or counted (bf16: a value is up to n / 384 of the row)
     x = np.linspace(3, -3, n).astype(np.float32)
     for largest in (True, False):
         for k in (16, 100, 600):
             tr = _check("ramp", x, dtype, k, largest)
-            if dtype == F32:
-                assert k <= tr[0].pre_kept <= 8 * (n // 2048), tr[0].pre_kept
+            assert (k if dtype == F32 else 0) <= tr[0].pre_kept <= 8 * (n // runs) + (0 if dtype == F32 else n // 384), tr[0].pre_kept
+
+
+def _assert_best(x, bits, k, largest, gv, gi):
+    key = x if largest else -x
+    edge = np.partition(key, len(key) - k)[len(key) - k]
+    want = np.concatenate([np.flatnonzero(key > edge), np.flatnonzero(key == edge)[: k - int((key > edge).sum())]])
+    assert np.array_equal(np.sort(gi), np.sort(want)) and np.array_equal(bits[gi], gv)
+
+
+def test_unsorted_long_lists_of_several_rows():
+    # positions are reserved row by row: a batch, and a ragged one whose rows are empty, shorter than k, listed whole, or have k near their end
+    n, k = 1 << 25, 70000
+    x = np.stack([W.normal(n, 58), W.duplicates(n, 59)])
+    for largest in (True, False):
+        print("unsorted, two rows:", largest, flush=True)
+        gv, gi, tr, _ = gpu_topk(to_device(x.view(np.uint32), F32), F32, k, largest, sorted=False)
+        for r in range(2):
+            assert tr[r].error == 0 and tr[r].done and tr[r].redo & 1 == 0 and tr[r].passes[0].where == 5
+            _assert_best(x[r], x[r].view(np.uint32), k, largest, gv[r], gi[r])
+    lens, ks = [n + 5, 0, 70000, 100001, 200003, 3000001, 1 << 20], [70000, 0, 70000, 70000, 69999, 1, 9000]
+    rows = [W.normal(m, 60 + r) if r != 6 else W.duplicates(m, 66) for r, m in enumerate(lens)]
+    for largest in (True, False):
+        print("unsorted, ragged:", largest, flush=True)
+        gv, gi, tr = _run_ragged([r.view(np.uint32) for r in rows], F32, ks, largest)
+        for r, (row, kk) in enumerate(zip(rows, ks)):
+            assert np.all(gi[r, kk:] == -1) and tr[r].error == 0
+            if kk:
+                assert tr[r].done and tr[r].passes[0].where in LIST
+                _assert_best(row, row.view(np.uint32), kk, largest, gv[r, :kk], gi[r, :kk])
 
 
 @pytest.mark.parametrize("k", [70000, (1 << 25) // 100])
@@ -454,11 +519,7 @@ def test_unsorted_long_lists(k):
             print("unsorted:", name, k, largest, flush=True)
             gv, gi, tr, _ = gpu_topk(to_device(bits, F32), F32, k, largest, sorted=False)
             assert tr[0].error == 0 and tr[0].done and tr[0].passes[0].where == 5
-            key = y if largest else -y
-            order = np.argpartition(-key, k - 1)
-            edge = key[order[k - 1]]
-            want = np.concatenate([np.flatnonzero(key > edge), np.flatnonzero(key == edge)[: k - int((key > edge).sum())]])
-            assert np.array_equal(np.sort(gi[0]), np.sort(want)) and np.array_equal(bits[0][gi[0]], gv[0])
+            _assert_best(y, bits[0], k, largest, gv[0], gi[0])
 
 
 @pytest.mark.parametrize("dtype", [F16, BF16])
