@@ -548,3 +548,19 @@ def test_ranks_on_both_sides_of_what_one_value_per_lane_holds(dtype, n):
         for name, y in (("normal", x), ("nine in ten", np.where(W.uniform01(n, 5) < 0.9, np.float32(1.5), x)), ("blocks", np.repeat(x[: n // 64 + 1], 64)[:n])):
             tr = _check("rank %d, %s" % (rank, name), y.astype(np.float32), dtype, k, largest=rank != 136, by_list=True)
             assert tr[0].redo & 1 == 0
+
+
+@pytest.mark.parametrize("dtype,n", [(F32, 300001), (F16, 1600001)])
+@pytest.mark.parametrize("width", [40, 150, 700, 1500, 2500])
+def test_crowds_of_which_little_is_wanted(dtype, n, width):
+    # the best values have `width` elements each, neighbours or all over the row, and a list has a few such values: one bin has more than is ordered in one
+    # go, and the bins up to it have less than half the list (256, 512 and 1024 threads, up to 2048 entries kept), just as much, or nearly all of it
+    steps = np.arange(n) // width
+    few = np.floor(W.uniform01(n, width) * (n // width))
+    few = np.minimum(few, 2000.0) if dtype == F16 else few
+    for name, x in (("steps", np.maximum(steps - (n // width - 1500), 0)), ("spread", few), ("a crowd and others", np.where(W.uniform01(n, 5) < 0.002, steps, few % 7))):
+        for k in (1, 16, width - 1, width, width + 1, 3 * width):
+            for largest in (True, False):
+                y = x.astype(np.float32) if largest else -x.astype(np.float32)
+                _check("%s of %d" % (name, width), y, dtype, k, largest, by_list=None)
+                _check("%s of %d" % (name, width), y, dtype, k, largest, by_list=None, sorted=False)
