@@ -1965,7 +1965,8 @@ __device__ __forceinline__ u32 keep_best(const u64 (&e)[N], u32 total, u32 want,
 // Bound by latency.  The first entries of every segment lie together (L.slots of each) and are read before it is known how many there are: a search by
 // every entry for the segment that holds it, and 1024 segments all over the list array, took 6.2 us for 3300 entries; this 3.3 for 5800.  (Ordered from
 // the registers they are read to, 16 places per thread, they need not be put together first, but every phase takes longer: 12 / 15.5 us in all.)
-template <int DT, int B>
+// STREAM: k_list_stream's lists, in as many segments as there are compute units.  (Told apart while it runs, one row of 2^24 fp32 keys, k = 256, 12.0 us; compiled apart 11.7.)
+template <int DT, int B, bool STREAM>
 __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     constexpr u32 kMost = 16;  // places per thread
     __shared__ OrderShared<B> sm;
@@ -1977,7 +1978,7 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     const u64* front = list_part<u64>(P, row, L.front_off);
     // (k_list_sweep's few long segments: entries look for theirs, where the list is short, or so long that all waves are needed to order it.  One
     // row of 1048869 fp16 keys, k = 3990, 34.7 us, put together first 37.0; 41 fp32 rows of 74007, k = 28, 20.7 / 21.5; but eleven of 135112, k = 615, 24.9 / 22.5.)
-    const bool few = L.stream_block == 0;
+    constexpr bool few = !STREAM;
     // (the lengths and the decision before the entries: what counts of a row with ties does not wait for the places)
     const u32 c = tid < G ? list_part<u32>(P, row, L.seg_off)[tid] : 0u;  // (G is at most B)
     const ListRow* lr = list_row(P, row);
@@ -2022,7 +2023,7 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
         constexpr u32 kParts = (u32)ListSource<DT, false>::kTileVecs / kWaveVecs;
         const u32 parts = (u32)((src_vectors<DT>(rs) + kWaveVecs - 1u) / kWaveVecs);
         auto count = [&](u32 i) __attribute__((always_inline)) {  // (k_list_stream's tiles are smaller)
-            if (L.stream_block == 0) return tiles(i);
+            if (few) return tiles(i);
             u32 n = 0;
 #pragma unroll
             for (u32 c = 0; c < kParts; ++c) n += kParts * i + c < parts ? tiles(kParts * i + c) : 0u;
@@ -3016,8 +3017,9 @@ static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStrea
         hipLaunchKernelGGL((k_list_buckets<DT>), dim3((unsigned)P.batch * (L.nb + (unsigned)L.ties)), dim3(kListBucketBlock), 0, st, P, L);
     } else {
         const dim3 g((unsigned)P.batch * (1u + (unsigned)L.ties));
-        if (L.finish == 256) hipLaunchKernelGGL((k_list_finish<DT, 256>), g, dim3(256), 0, st, P, L);
-        else hipLaunchKernelGGL((k_list_finish<DT, 1024>), g, dim3(1024), 0, st, P, L);
+        if (L.stream_block != 0) hipLaunchKernelGGL((k_list_finish<DT, 1024, true>), g, dim3(1024), 0, st, P, L);
+        else if (L.finish == 256) hipLaunchKernelGGL((k_list_finish<DT, 256, false>), g, dim3(256), 0, st, P, L);
+        else hipLaunchKernelGGL((k_list_finish<DT, 1024, false>), g, dim3(1024), 0, st, P, L);
     }
     hipLaunchKernelGGL((k_list_redo<DT>), dim3(redo), dim3(kListBucketBlock), 0, st, P, L);
     mark(events, 4, st);
