@@ -289,7 +289,7 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     auto sample_vecs = [&]() { return L->sample == 4 ? (eb == 4 ? 16384 : 8192) : L->sample == 3 ? 4096 : 512 << L->sample; };
     expect(sample_vecs());
     if (by_row) {
-        // (a list that does not fit is put in order by k_list_redo: better a little too much room)
+        // (a list that does not fit is put in order part by part: better a little too much room)
         L->row_block = batch > 256 && room * 1.2 <= 2048.0 ? 256 : batch > 256 && room * 1.2 <= 4096.0 ? 512 : room <= 8192.0 ? 1024 : 0;
         if (L->row_block == 1024 && L->sample == 0) L->sample = 1;
     }
@@ -346,7 +346,7 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     // against 37.8)
     L->stream = batch * n * eb > ((int64_t)128 << 20);
     // (256 segments to read keep 1024 threads busy: one fp16 row of 6 million, k = 16, 256 threads 25.9, k = 100, 1024 threads 23.3.  A list that 256 threads
-    // cannot hold goes to k_list_redo, so a little too much room here as well: 32 rows of 2^21 fp16 keys, k = 300, room for 1907 entries, 54.7 / 50.1)
+    // cannot hold is put in order part by part, so a little too much room here as well: 32 rows of 2^21 fp16 keys, k = 300, room for 1907 entries, 54.7 / 50.1)
     L->finish = room * 1.2 > 2048.0 || stream || G > 256 ? 1024 : 256;  // (and a thread per segment)
     L->room = (u32)L->finish * 8u;
     const double twice = 2.0 * room < 2.0 * L->room ? 2.0 * room : 2.0 * L->room;
@@ -365,14 +365,12 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     if (ties < 1) ties = 1;
     if (ties > ntiles) ties = ntiles;
     L->ties = (int)ties;
-    L->redo_wgs = L->row_block != 0 || batch >= 256 ? 1 : (int)(256 / batch);
-    if (!is_long && L->redo_wgs > 4) L->redo_wgs = 4;  // (a short list's k ranks are at most so many parts)
     if (batch * ((int64_t)L->nb + 1 + ties) >= ((int64_t)1 << 22) || batch * G >= ((int64_t)1 << 22)) return false;  // grid sizes
     u64 off = kListMetaBytes;
     // (whole cache lines: a wave's adds to 64 neighbouring counters fall on two of them, not three -- 4 million fp16 keys, k = 2^20, 64.8 / 62.3 us)
     auto take = [&](u64 bytes) { const u64 at = off; off = align_up(off + bytes, 128); return (u32)at; };
     L->front_off = take((u64)G * L->slots * 8);
-    L->seg_off = take((u64)G * 4);
+    L->seg_off = take((u64)G * 8);
     L->hist_off = take(is_long ? kMaxBins * 4 : 0);
     L->cursor_off = take((u64)(L->nb + 1) * 4);
     L->first_off = take((u64)L->nb * 8);

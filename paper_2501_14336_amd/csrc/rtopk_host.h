@@ -39,12 +39,11 @@ struct ListPlan {
     int stream;       // the input is too large for the caches to keep: read past them
     int finish;       // short lists: threads of the workgroup that puts a row's list in order
     int ties;         // workgroups per row that fetch elements equal to the bound, where those are very many
-    int redo_wgs;     // workgroups per row of the kernel that does what the others leave over
     u32 seg_stride;   // the row's stretches are held by G workgroups that list at most this many each (0: the row is swept)
     u32 nb;           // long lists: buckets per row (0: short lists)
     u32 bucket_shift; // ... of 2^bucket_shift ranks
     u32 slots;        // short lists: a power of two: so many entries of each segment lie together at front_off
-    u32 room, most;   // ... so many in all are put in order in LDS, and so many there are cut down to that first
+    u32 room, most;   // ... so many in all are put in order in LDS (and twice as many cut down to that first); the record says so from `most` on
     u32 front_off, hist_off, cursor_off, first_off, split_off, seg_off, tile_off, stack_off;
 };
 void launch_list_rows_f32(const Params& P, const ListPlan& L, hipStream_t st);  // (the kernels of L.row_block alone)

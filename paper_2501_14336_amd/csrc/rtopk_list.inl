@@ -19,8 +19,10 @@
 //   k_list_emit     (long lists, unsorted output) many workgroups per row: what lies in better bins than rank k is output as it comes; its bin is a bucket,
 //   k_list_scatter  (long lists, sorted) many workgroups per row: the list into buckets of about 2048 ranks each,
 //   k_list_buckets  and one workgroup per bucket puts its ranks in order
-//   k_list_redo     lists and buckets too long for one workgroup, which several put in order, and rows whose list was no use
-//                   (normally none of either: the launch finds nothing to do)
+//
+// The last kernel of each of these also does what is normally not there to be done: lists and buckets too long for one workgroup, which
+// several put in order, and rows whose list was no use, which one workgroup selects anew.  (A clean-up kernel behind it, which found nothing
+// to do, took 3 to 4.6 us of every call: 1024 rows of 2^17 bf16 keys, k = 50, 54.3 us, so 49.2; one of 2^24 fp32 keys, k = 256, 33.6 / 31.8; of 2^26, nine in ten equal, k = 2^16, 96.0 / 93.0.)
 //
 // List entries are 64-bit numbers, distinct within a row, whose descending order is the order of the output: the
 // ordered key (direction applied, 16 or 32 bits) above the inverted index (as many bits as n needs).  An entry holds
@@ -59,18 +61,17 @@ struct ListRow {
     u32 split;     // long lists, 1: the bins lie between splitters
 };
 static_assert(sizeof(ListRow) % 8 == 0, "read by words");
-// What became of a row's list.  A record of its own: the kernel that writes it has workgroups that still read the decision, and a
+// What became of a row's long list.  A record of its own: the kernel that writes it has workgroups that still read the decision, and a
 // wave that found the decision changed would leave the others of its workgroup alone with sums it never wrote.
 struct ListDone {
-    u32 total;     // entries (long lists, and short ones that do not fit one workgroup's LDS)
-    u32 end;       // long lists: entries in bins that begin below rank k; short ones: the array that holds the list
-    u32 drop;      // long lists: 1: the list was no use, the buckets are not filled
-    u32 pad;
+    u32 total;     // entries
+    u32 end;       // entries in bins that begin below rank k
+    u32 drop;      // the list was no use, the buckets are not filled: why (rtopk_row_trace::redo_why)
+    u32 big;       // ... 1: a bucket has more than one workgroup puts in order
 };
 constexpr u32 kListDoneOff = 128;
 static_assert(sizeof(ListRow) <= kListDoneOff && kListDoneOff + sizeof(ListDone) <= kListMetaBytes, "both lie before the plan's first offset");
-// Bits of rtopk_row_trace::redo that the list kernels set and k_list_redo looks at: the list is no use; it was too long to
-// put in order in LDS (it is all in array `end`); so were some of its buckets.
+// Bits of rtopk_row_trace::redo: the list was no use; it was too long to put in order in LDS; so were some of its buckets.
 enum : u32 { kRedoRow = 1, kRedoList = 2, kRedoBuckets = 4 };
 
 // row_shape, in scalar registers (a ragged batch's comes from memory).
@@ -794,7 +795,7 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
         // (those equal to T: one key's share of the bins is by position)
         const u32 ties = eq_got >> (ent.ib > sh ? ent.ib - sh : 0u);
         if (!tied && most < ties) most = ties;
-        // (a bin of several buckets' ranks -- up to there k_list_redo has it in order in no time -- and more of them than fall together by
+        // (a bin of several buckets' ranks -- up to there its parts are shared out in no time -- and more of them than fall together by
         // chance: 4096 bins, 2^28 keys, k = 2^20: about 400 draws)
         split = most > 5u && ((u64)most << thin) * rs.n / elems > 8192u;
         if (split) {
@@ -978,7 +979,7 @@ __device__ __forceinline__ u32 element_index(const Source& src, u32 tile, u32 s)
 }
 
 // Workgroup wg of the G that share the row: what is not below the row's bound goes to append(tile, mask), bit
-// kSlots - 1 - s of a lane's mask standing for its element s; where ties are counted, tile j's go to te[j].
+// kSlots - 1 - s of a lane's mask standing for its element s; where ties are counted, tile j's go to te[j], and lane 63 returns how many its wave saw.
 // Bound by HBM.  Per element: a compare and an add-with-carry (and the unpacking of a 16-bit key), into one mask per lane
 // and tile; another pair where ties are counted.  A branch per 64 elements, or a store, would cost more than the row's trip from
 // memory (see stream_tile).  Full tiles go through the load pipeline of for_each_tile, whose loads in the steady state are
@@ -986,14 +987,16 @@ __device__ __forceinline__ u32 element_index(const Source& src, u32 tile, u32 s)
 // rows of 2^17 bf16 keys, k = 50, 57.2 / 55.2.  Ties by key, tiles loaded one after the other / by number in the pipeline: 2^26
 // fp32 keys, nine in ten equal, k = 2^16, 114.9 / 93.1.
 template <int DT, class Source, class Append>
-__device__ __forceinline__ void sweep_row(const Source& src, u32 wg, u32 G, const ListRow& lr, u32* te, u32 dirmask, Append&& append) {
+__device__ __forceinline__ u32 sweep_row(const Source& src, u32 wg, u32 G, const ListRow& lr, u32* te, u32 dirmask, Append&& append) {
     typedef typename Source::Tile Tile;
+    u32 ties = 0;
     const u32 ntiles = src.ntiles(), lane = lane_id(), T = lr.T;
     const bool tied = lr.mode == kListTied, largest = dirmask == 0;
     constexpr u32 kAll = 0xffffffffu >> (32 - Source::kSlots);
     const float t = lr.t;
     auto count_ties = [&](u32 tile, u32 eq) __attribute__((always_inline)) {
         eq = wave_inclusive_scan(eq);
+        ties += eq;
         if (lane == 63u && eq != 0u) atomicAdd(&te[tile], eq);
     };
     // short tiles, and every tile where T is not a number to compare with
@@ -1043,6 +1046,7 @@ __device__ __forceinline__ void sweep_row(const Source& src, u32 wg, u32 G, cons
             by_key(cur);
         }
     }
+    return ties;
 }
 
 // (The compiler keeps 30 to 60 scalar registers of the fp32 sweeps, and up to 200 of the 16-bit ones and of the row kernels, in lanes of a
@@ -1091,7 +1095,7 @@ __global__ void __launch_bounds__(LONG ? kLongBlock : kGridBlock, LONG ? 4 : DT 
     __shared__ uint2 stage[B / 64][LONG ? kListStageLong : kListStage];
     __shared__ u32 hist[LONG ? kListBins : 1];
     __shared__ u64 split[LONG ? kListSplits + 1 : 1];
-    __shared__ u32 run;
+    __shared__ u32 run, all_ties;
     typedef ListSource<DT, LONG, NT> Source;
     const u32 G = (u32)L.G;
     const int row = (int)(blockIdx.x / G);
@@ -1106,16 +1110,17 @@ __global__ void __launch_bounds__(LONG ? kLongBlock : kGridBlock, LONG ? 4 : DT 
         for (u32 j = tid; j < kListBins; j += B) hist[j] = 0;
         if (lr.split != 0u && tid <= kListSplits) split[tid] = list_part<u64>(P, row, L.split_off)[tid];
     }
-    if (tid == 0) run = 0;
+    if (tid == 0) run = all_ties = 0;
     __syncthreads();
     ListWriter<DT, LONG, Source> w{list_entry<DT>(P), list_array(P, 1u, row) + list_segment<DT>(rs, wg, G, (u32)Source::kTileVecs),
                                    list_part<u64>(P, row, L.front_off) + (size_t)wg * L.slots, L.slots, stage[tid >> 6], &run, hist, split, 0u};
-    sweep_row<DT>(src, wg, G, lr, list_part<u32>(P, row, L.tile_off), P.dirmask, [&](const typename Source::Tile& cur, u32 m) __attribute__((always_inline)) {
+    const u32 ties = sweep_row<DT>(src, wg, G, lr, list_part<u32>(P, row, L.tile_off), P.dirmask, [&](const typename Source::Tile& cur, u32 m) __attribute__((always_inline)) {
         w.append(cur, m, lr, [&](u32 s) __attribute__((always_inline)) { return element_index(src, cur.tile, s); });
     });
     if (w.fill != 0u) w.flush(lr);
+    if (lane_id() == 63u && ties != 0u) atomicAdd(&all_ties, ties);
     __syncthreads();
-    if (tid == 0) list_part<u32>(P, row, L.seg_off)[wg] = run;
+    if (tid == 0) list_part<uint2>(P, row, L.seg_off)[wg] = make_uint2(run, all_ties);
     if (LONG) {
         u32* gh = list_part<u32>(P, row, L.hist_off);
         for (u32 j = tid; j < kListBins; j += B) {
@@ -1135,8 +1140,9 @@ __global__ void __launch_bounds__(LONG ? kLongBlock : kGridBlock, LONG ? 4 : DT 
 template <int DT, bool NT>
 using WaveSource = KeySource<DT, 64, 4, NT>;
 template <int DT, class Source, class Bound, class Append>
-__device__ __forceinline__ void sweep_by_waves(const Source& src, u32 first, u32 step, u32* te, u32 dirmask, Bound&& bound, Append&& append) {
+__device__ __forceinline__ u32 sweep_by_waves(const Source& src, u32 first, u32 step, u32* te, u32 dirmask, Bound&& bound, Append&& append) {
     typedef typename Source::Tile Tile;
+    u32 ties = 0;  // (in lane 63)
     constexpr u32 E = Source::E, kRing = 4;
     constexpr u32 kAll = 0xffffffffu >> (32 - Source::kSlots);
     const u32 lane = lane_id(), ntiles = src.ntiles();
@@ -1155,13 +1161,14 @@ __device__ __forceinline__ void sweep_by_waves(const Source& src, u32 first, u32
     ListRow lr;
     if (!bound([&]() __attribute__((always_inline)) {
             if (first < ntiles) static_for<0, (int)kRing>([&](auto c) __attribute__((always_inline)) { load(first + (u32)decltype(c)::value * step, t[decltype(c)::value]); });
-        }, lr)) return;
+        }, lr)) return 0;
     const bool tied = lr.mode == kListTied, largest = dirmask == 0;
     const u32 T = lr.T;
     const float thr = lr.t;
     // (a tile is one wave's alone: nothing to add to, and nothing to be cleared before)
     auto note_ties = [&](u32 tile, u32 eq) __attribute__((always_inline)) {
         eq = wave_inclusive_scan(eq);
+        ties += eq;
         if (lane == 63u) te[tile] = eq;
     };
     // short tiles, and every tile where T is not a number to compare with
@@ -1236,6 +1243,7 @@ __device__ __forceinline__ void sweep_by_waves(const Source& src, u32 first, u32
             by_key(t[0]);
         }
     }
+    return ties;
 }
 
 // Of rows from 16 MB up the sample is half as large as k_list_bound's, in runs of 4 vectors: as many runs, which is all that a trend's list is known by.
@@ -1247,7 +1255,7 @@ __global__ void __launch_bounds__(kSharedBlock) k_list_stream(Params P, ListPlan
     struct BoundShared { RankShared rank; SampleList list; u32 red[4 * (B / 64)]; };
     __shared__ union { BoundShared bound; uint2 stage[B / 64][kListStage]; } sm;
     __shared__ ListRow decided;
-    __shared__ u32 run, none[1];
+    __shared__ u32 run, all_ties, none[1];
     typedef WaveSource<DT, NT> Source;
     const u32 G = (u32)L.G, tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row = (int)(blockIdx.x / G);
@@ -1257,11 +1265,11 @@ __global__ void __launch_bounds__(kSharedBlock) k_list_stream(Params P, ListPlan
     src.init(rs);
     ListWriter<DT, false, Source> w{list_entry<DT>(P), list_array(P, 1u, row) + list_segment<DT>(rs, wg, G, kWaveVecs),
                                     list_part<u64>(P, row, L.front_off) + (size_t)wg * L.slots, L.slots, sm.stage[wave], &run, none, nullptr, 0u};
-    sweep_by_waves<DT>(src, wave * G + wg, G * (u32)(B / 64), list_part<u32>(P, row, L.tile_off), P.dirmask,
+    const u32 ties = sweep_by_waves<DT>(src, wave * G + wg, G * (u32)(B / 64), list_part<u32>(P, row, L.tile_off), P.dirmask,
                      [&](auto&& load_first, ListRow& lr) __attribute__((always_inline)) {
                          bound_of_row<DT, B, V, true, RUN>(P, L, row, rs, row_state(P, row), &decided, nullptr, 0u, L.room, sm.bound.rank, &sm.bound.list,
                                                       sm.bound.red, wg == 0u, [&]() __attribute__((always_inline)) { if (rs.k != 0u) load_first(); });
-                         if (tid == 0) run = 0;
+                         if (tid == 0) run = all_ties = 0;
                          __syncthreads();
                          lr = list_row_scalar(&decided);
                          if (wg == 0u && tid == 0) *list_row_out(P, row) = lr;
@@ -1273,8 +1281,9 @@ __global__ void __launch_bounds__(kSharedBlock) k_list_stream(Params P, ListPlan
                          });
                      });
     if (w.fill != 0u) w.flush(decided);
+    if (lane_id() == 63u && ties != 0u) atomicAdd(&all_ties, ties);
     __syncthreads();
-    if (tid == 0) list_part<u32>(P, row, L.seg_off)[wg] = run;
+    if (tid == 0) list_part<uint2>(P, row, L.seg_off)[wg] = make_uint2(run, all_ties);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1391,6 +1400,19 @@ __device__ __forceinline__ void order_scan(u32* h, u32 want, u32 crowd, bool sor
     __syncthreads();
 }
 
+// One more in hist[bin]; lanes whose bin is the first lane's add together where they are many.  (Most of a crowd falls into one bin, and a wave's adds to one word are made one after the
+// other: keep_best of 10308 entries, a ramp with infinities, 20.6 us, so 13.9.)
+__device__ __forceinline__ void count_alike(u32* hist, u32 bin) {
+    const u32 first = __builtin_amdgcn_readfirstlane(bin);
+    const u64 alike = ballot64(bin == first);
+    const u32 n = (u32)__popcll(alike);
+    if (n >= 12u && bin == first) {
+        if (mbcnt64(alike) == 0u) atomicAdd(&hist[bin], n);
+    } else {
+        atomicAdd(&hist[bin], 1u);
+    }
+}
+
 // buf[0 .. want) to the row's output, from rank0 on.
 template <int DT, int B>
 __device__ __forceinline__ void order_output(const Params& P, int row, const RowShape& rs, const OrderShared<B>& sm, u32 want, u32 rank0,
@@ -1413,7 +1435,8 @@ __device__ __forceinline__ void order_output(const Params& P, int row, const Row
 template <int DT, int B, bool CUT = false, class Load>
 __device__ __forceinline__ void order_in_lds(const Params& P, int row, const RowShape& rs, OrderShared<B>& sm, u32 C, u32 rank0,
                                              Load&& load) {
-    const u32 tid = threadIdx.x;
+    u32 tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
     const u32 want = rs.k - rank0 < C ? rs.k - rank0 : C;
     const bool sorted = (P.flags & RTOPK_FLAG_SORTED) != 0u;
     const ListEntry ent = list_entry<DT>(P);
@@ -1630,37 +1653,48 @@ __device__ __forceinline__ void order_entries(const Params& P, int row, const Ro
     }
 }
 
-// f(entry, of(entry)) for all of src[0 .. count), eight loads in flight per thread (and eight chains of what `of` looks up in LDS).
-template <int B, class Of, class F>
-__device__ __forceinline__ void order_pass(const u64* src, u32 count, Of&& of, F&& f) {
-    constexpr u32 kAhead = 8;
-    u32 i = threadIdx.x;
+// sm.buf[0 .. total), at most 8 B entries, into the output, by as few waves as hold them (barriers).  Begins with a barrier.
+template <int DT, int B>
+__device__ __forceinline__ void order_list(const Params& P, int row, const RowShape& rs, OrderShared<B>& sm, u32 total) {
+    __syncthreads();
+    auto listed = [&](u32 i) __attribute__((always_inline)) { return sm.buf[i]; };
+    if (B > 256 && total <= 8u * 256u) {
+        if (threadIdx.x >= 256u) return;
+        order_in_lds<DT, 256, true>(P, row, rs, *(OrderShared<256>*)&sm, total, 0u, listed);
+    } else if (B > 512 && total <= 8u * 512u) {
+        if (threadIdx.x >= 512u) return;
+        order_in_lds<DT, 512, true>(P, row, rs, *(OrderShared<512>*)&sm, total, 0u, listed);
+    } else {
+        order_in_lds<DT, B, true>(P, row, rs, sm, total, 0u, listed);
+    }
+}
+
+// f(entry, of(entry)) for all entries src(0) .. src(count - 1), kAhead loads in flight per thread (and as many chains of what `src` and `of` look up in LDS).
+template <int B, u32 kAhead, class Src, class Of, class F>
+__device__ __forceinline__ void order_pass(const Src& src, u32 count, Of&& of, F&& f) {
 #pragma unroll 1
-    for (; (u64)i + (kAhead - 1u) * B < count; i += kAhead * B) {
+    for (u32 i = threadIdx.x; i < count; i += kAhead * B) {  // (beyond the end: the last entry, which is not looked at)
         u64 e[kAhead];
 #pragma unroll
-        for (u32 j = 0; j < kAhead; ++j) e[j] = src[i + j * B];
+        for (u32 j = 0; j < kAhead; ++j) e[j] = src(i + j * B < count ? i + j * B : count - 1u);
         u32 x[kAhead];
 #pragma unroll
         for (u32 j = 0; j < kAhead; ++j) x[j] = of(e[j]);
 #pragma unroll
-        for (u32 j = 0; j < kAhead; ++j) f(e[j], x[j]);
-    }
-#pragma unroll 1
-    for (; i < count; i += B) {
-        const u64 e = src[i];
-        f(e, of(e));
+        for (u32 j = 0; j < kAhead; ++j)
+            if (i + j * B < count) f(e[j], x[j]);
+        if (count - i <= kAhead * B) break;
     }
 }
 
-// Entries of src[0 .. count) in [lo, hi) to buf; returns how many there are (up to 8 B are kept).  Begins and ends with a barrier.
-template <int B>
-__device__ __forceinline__ u32 order_gather(const u64* src, u32 count, u64 lo, u64 hi, OrderShared<B>& sm, u32* run) {
+// Those of src's `count` entries that lie in [lo, hi) to buf; returns how many there are (up to 8 B are kept).  Begins and ends with a barrier.
+template <int B, u32 kAhead, class Src>
+__device__ __forceinline__ u32 order_gather(const Src& src, u32 count, u64 lo, u64 hi, OrderShared<B>& sm, u32* run) {
     const u32 tid = threadIdx.x;
     __syncthreads();
     if (tid == 0) *run = 0;
     __syncthreads();
-    order_pass<B>(src, count, [](u64) { return 0u; }, [&](u64 e, u32) __attribute__((always_inline)) {
+    order_pass<B, kAhead>(src, count, [](u64) { return 0u; }, [&](u64 e, u32) __attribute__((always_inline)) {
         if (e >= lo && e < hi) {
             const u32 at = atomicAdd(run, 1u);
             if (at < 8u * B) sm.buf[at] = e;
@@ -1672,8 +1706,8 @@ __device__ __forceinline__ u32 order_gather(const u64* src, u32 count, u64 lo, u
 
 // The entries of src in [lo, hi), which are the row's ranks from rank0 on, a chunk that LDS holds after the other; where the
 // chunk ends is found by dividing the range evenly, as often as it takes (entries are distinct).
-template <int DT, int B>
-__device__ __forceinline__ void order_in_chunks(const Params& P, int row, const RowShape& rs, OrderShared<B>& sm, const u64* src, u32 count,
+template <int DT, int B, u32 kAhead, class Src>
+__device__ __forceinline__ void order_in_chunks(const Params& P, int row, const RowShape& rs, OrderShared<B>& sm, const Src& src, u32 count,
                                                 u32 rank0, u64 lo, u64 hi, u32* run) {
     const u32 tid = threadIdx.x;
     while (hi > lo && rank0 < rs.k) {
@@ -1684,7 +1718,7 @@ __device__ __forceinline__ void order_in_chunks(const Params& P, int row, const 
             for (u32 j = tid; j < 4u * B; j += B) sm.hist[j] = 0;
             if (tid == 0) sm.sp = 4u * B;
             __syncthreads();
-            order_pass<B>(src, count, [](u64) { return 0u; }, [&](u64 e, u32) __attribute__((always_inline)) {
+            order_pass<B, kAhead>(src, count, [](u64) { return 0u; }, [&](u64 e, u32) __attribute__((always_inline)) {
                 if (e >= a && e < hi) atomicAdd(&sm.hist[(u32)((hi - 1u - e) >> sh)], 1u);
             });
             __syncthreads();
@@ -1695,31 +1729,30 @@ __device__ __forceinline__ void order_in_chunks(const Params& P, int row, const 
             if (bins != 0u) break;
             if (hi - a > (1ull << sh)) a = hi - (1ull << sh);
         }
-        const u32 n = order_gather<B>(src, count, cut, hi, sm, run);
+        const u32 n = order_gather<B, kAhead>(src, count, cut, hi, sm, run);
         if (n != 0u) order_in_lds<DT, B>(P, row, rs, sm, n, rank0, [&](u32 i) __attribute__((always_inline)) { return sm.buf[i]; });
         rank0 += n;
         hi = cut;
     }
 }
 
-// One of `parts` workgroups that put src[0 .. count) in order, the row's ranks from rank0 on.  Each reads all of it once and counts
+// One of `parts` workgroups that put src's `count` entries in order, the row's ranks from rank0 on.  Each reads all of it once and counts
 // it into bins between splitters, which are entries at equal distances, so that all of them see the same bins; runs of bins that LDS
 // holds are dealt to them, and each reads all of it again for every run of its own.  Nobody waits for anybody and
-// nothing is moved in memory.  One workgroup reads about 0.1 TB/s, so 2^20 entries take 256 of them about 0.2 ms.
+// nothing is moved in memory.  LAST: rank0 is 0, and the workgroup has nothing else to do afterwards.  One workgroup reads about 0.1 TB/s, so 2^20 entries take 256 of them about 0.2 ms.
 constexpr u32 kOrderRuns = 128;  // runs that a workgroup notes at a time
 template <int B>
 struct OrderParts {
     u64 edge[SplitBins<B>::N + 1];
     u64 lo[kOrderRuns], hi[kOrderRuns];
     u32 start[kOrderRuns], size[kOrderRuns];
-    u32 bin[4 * B];  // the runs' first bins
     u32 nrun, run;
 };
-template <int DT, int B>
-__device__ __forceinline__ void order_shared(const Params& P, int row, const RowShape& rs, OrderShared<B>& sm, OrderParts<B>& sp, const u64* src,
+template <int DT, int B, bool LAST = false, class Src>
+__device__ __forceinline__ void order_shared(const Params& P, int row, const RowShape& rs, OrderShared<B>& sm, OrderParts<B>& sp, const Src& src,
                                              u32 count, u32 rank0, u32 part, u32 parts) {
     typedef SplitBins<B> Split;
-    constexpr u32 kCap = 8 * B, kRun = kCap * 3 / 4, kBig = kCap / 4;
+    constexpr u32 kCap = 8 * B, kRun = kCap * 3 / 4, kBig = kCap / 4, kAhead = LAST ? 8 : 4;  // (registers)
     const u32 tid = threadIdx.x, want = rs.k - rank0 < count ? rs.k - rank0 : count;
     __syncthreads();
     // Little is wanted of much: a bound from 8 B entries at equal distances, and one pass that gathers what is not below it.
@@ -1730,7 +1763,7 @@ __device__ __forceinline__ void order_shared(const Params& P, int row, const Row
             if (part != 0u) return;
             u64 e[8], lo = ~0ull, hi = 0;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) e[j] = src[(u64)(tid + (u32)j * B) * count / kCap];
+            for (int j = 0; j < 8; ++j) e[j] = src((u32)((u64)(tid + (u32)j * B) * count / kCap));
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 lo = lo < e[j] ? lo : e[j];
@@ -1745,7 +1778,7 @@ __device__ __forceinline__ void order_shared(const Params& P, int row, const Row
                 __syncthreads();
 #pragma unroll
                 for (int j = 0; j < 8; ++j)
-                    if (e[j] >= lo && e[j] <= hi) atomicAdd(&sm.hist[(u32)((hi - e[j]) >> sh)], 1u);
+                    if (e[j] >= lo && e[j] <= hi) count_alike(sm.hist, (u32)((hi - e[j]) >> sh));
                 __syncthreads();
                 order_scan<B>(sm.hist, left, ~0u, false, sm);
                 const u32 b = sm.sp, s0 = sm.hist[b], inside = b + 1u < 4u * B ? sm.hist[b + 1u] - s0 : 0u;
@@ -1754,9 +1787,10 @@ __device__ __forceinline__ void order_shared(const Params& P, int row, const Row
                 lo = hi - lo > (1ull << sh) - 1u ? hi - ((1ull << sh) - 1u) : lo;
                 if (sh == 0u || (b + 1u < 4u * B && inside <= 4u + rank / 8u)) break;
             }
-            const u32 n = order_gather<B>(src, count, lo, ~0ull, sm, &sp.run);
+            const u32 n = order_gather<B, kAhead>(src, count, lo, ~0ull, sm, &sp.run);
             if (n >= want && n <= kCap) {
-                order_in_lds<DT, B>(P, row, rs, sm, n, rank0, [&](u32 i) __attribute__((always_inline)) { return sm.buf[i]; });
+                if constexpr (LAST) order_list<DT, B>(P, row, rs, sm, n);
+                else order_in_lds<DT, B>(P, row, rs, sm, n, rank0, [&](u32 i) __attribute__((always_inline)) { return sm.buf[i]; });
                 return;
             }
             __syncthreads();
@@ -1764,16 +1798,16 @@ __device__ __forceinline__ void order_shared(const Params& P, int row, const Row
         }
     }
     if (count <= kCap) {
-        if (part == 0u) order_in_lds<DT, B>(P, row, rs, sm, count, rank0, [&](u32 i) __attribute__((always_inline)) { return src[i]; });
+        if (part == 0u) order_in_lds<DT, B>(P, row, rs, sm, count, rank0, [&](u32 i) __attribute__((always_inline)) { return src(i); });
         return;
     }
     // (the ends: nothing is known of the best and the worst entry but that they are entries)
     const u64 end = list_entry<DT>(P).end();
-    make_edges<B>(sp.edge, tid < (u32)Split::N ? src[(u64)tid * count / (u32)Split::N] : 0ull, end - 1u, 0ull);
+    make_edges<B>(sp.edge, tid < (u32)Split::N ? src((u32)((u64)tid * count / (u32)Split::N)) : 0ull, end - 1u, 0ull);
     for (u32 done = 0;;) {
         for (u32 j = tid; j < 4u * B + 2u; j += B) sm.hist[j] = 0;
         __syncthreads();
-        order_pass<B>(src, count, [&](u64 e) __attribute__((always_inline)) { return Split::bin(sp.edge, e); },
+        order_pass<B, kAhead>(src, count, [&](u64 e) __attribute__((always_inline)) { return Split::bin(sp.edge, e); },
                       [&](u64, u32 bin) __attribute__((always_inline)) { atomicAdd(&sm.hist[bin], 1u); });
         __syncthreads();
         order_scan<B>(sm.hist, want, ~0u, false, sm);
@@ -1791,9 +1825,10 @@ __device__ __forceinline__ void order_shared(const Params& P, int row, const Row
         }
         u32 slot = block_scan<B>(begins, sm.wsum) - begins;
         const u32 last = sm.sp;
+        u32* first_bin = (u32*)sm.buf;  // of every run (nothing else is there yet)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            if ((mask >> i) & 1u) sp.bin[slot++] = 4 * tid + i;
+            if ((mask >> i) & 1u) first_bin[slot++] = 4 * tid + i;
         if (tid == B - 1) sp.nrun = slot;
         __syncthreads();
         const u32 nrun = sp.nrun;
@@ -1801,7 +1836,7 @@ __device__ __forceinline__ void order_shared(const Params& P, int row, const Row
         for (u32 i = tid; i < kOrderRuns; i += B) {
             const u64 r64 = (u64)part + (u64)(done + i) * parts;
             if (r64 < nrun) {
-                const u32 r = (u32)r64, b0 = sp.bin[r], b1 = r + 1u < nrun ? sp.bin[r + 1u] - 1u : last;
+                const u32 r = (u32)r64, b0 = first_bin[r], b1 = r + 1u < nrun ? first_bin[r + 1u] - 1u : last;
                 sp.hi[i] = b0 == 0u ? end : Split::floor_of(sp.edge, b0 - 1u);
                 sp.lo[i] = Split::floor_of(sp.edge, b1);
                 sp.start[i] = sm.hist[b0];
@@ -1813,9 +1848,9 @@ __device__ __forceinline__ void order_shared(const Params& P, int row, const Row
             if ((u64)part + (u64)(done + i) * parts >= nrun) return;
             const u32 n = sp.size[i], r0 = rank0 + sp.start[i];
             if (n > kCap) {
-                order_in_chunks<DT, B>(P, row, rs, sm, src, count, r0, sp.lo[i], sp.hi[i], &sp.run);
+                order_in_chunks<DT, B, kAhead>(P, row, rs, sm, src, count, r0, sp.lo[i], sp.hi[i], &sp.run);
             } else if (n != 0u) {
-                order_gather<B>(src, count, sp.lo[i], sp.hi[i], sm, &sp.run);
+                order_gather<B, kAhead>(src, count, sp.lo[i], sp.hi[i], sm, &sp.run);
                 order_in_lds<DT, B>(P, row, rs, sm, n, r0, [&](u32 i) __attribute__((always_inline)) { return sm.buf[i]; });
             }
         }
@@ -1912,29 +1947,13 @@ __device__ __forceinline__ bool ties_of_row(const Params& P, Counts&& te, int ro
     return false;
 }
 
-// sm.buf[0 .. total), at most 8 B entries, into the output, by as few waves as hold them (barriers).  Begins with a barrier.
-template <int DT, int B>
-__device__ __forceinline__ void order_list(const Params& P, int row, const RowShape& rs, OrderShared<B>& sm, u32 total) {
-    __syncthreads();
-    auto listed = [&](u32 i) __attribute__((always_inline)) { return sm.buf[i]; };
-    if (B > 256 && total <= 8u * 256u) {
-        if (threadIdx.x >= 256u) return;
-        order_in_lds<DT, 256, true>(P, row, rs, *(OrderShared<256>*)&sm, total, 0u, listed);
-    } else if (B > 512 && total <= 8u * 512u) {
-        if (threadIdx.x >= 512u) return;
-        order_in_lds<DT, 512, true>(P, row, rs, *(OrderShared<512>*)&sm, total, 0u, listed);
-    } else {
-        order_in_lds<DT, B, true>(P, row, rs, sm, total, 0u, listed);
-    }
-}
-
-// e[j], ~0 where there is none: those that may be among the best `want` go to sm.buf (a bin's entries together, up to the bin that rank want - 1
-// lies in); returns how many that are, or 0 if they do not fit.  Ends with a barrier.
+// e[j], ~0 where there is none: those that may be among the best `want`, at most 8 B, go to sm.buf, in any order; returns how many that are.  *crowd: the bins that divide
+// the entries' range evenly had to be laid again, inside the one that rank want - 1 lies in, because it held too many.  (Entries are distinct: at some point it does not.  A row of
+// 2^20 fp32 keys, a ramp with infinities, k = 1000, 10308 entries, which order_shared put in order otherwise, 57.4 us, so 51.0.)  Ends with a barrier.
 template <int B, u32 N>
-__device__ __forceinline__ u32 keep_best(const u64 (&e)[N], u32 total, u32 want, OrderShared<B>& sm) {
+__device__ __forceinline__ u32 keep_best(const u64 (&e)[N], u32 total, u32 want, OrderShared<B>& sm, bool* crowd) {
     const u32 tid = threadIdx.x;
     u64 mn = ~0ull, mx = 0;
-    for (u32 j = tid; j < 4u * B; j += B) sm.hist[j] = 0;
 #pragma unroll
     for (u32 j = 0; j < N; ++j) {
         if (e[j] == ~0ull) continue;
@@ -1942,26 +1961,128 @@ __device__ __forceinline__ u32 keep_best(const u64 (&e)[N], u32 total, u32 want,
         mx = mx > e[j] ? mx : e[j];
     }
     order_range<B>(mn, mx, sm);
-    const u32 sh = order_shift<B>(mx - mn);
+    u32 left = want, above = 0;  // entries above mx
+    *crowd = false;
+#pragma unroll 1
+    for (;;) {
+        const u32 sh = order_shift<B>(mx - mn);
+        for (u32 j = tid; j < 4u * B; j += B) sm.hist[j] = 0;
+        __syncthreads();
 #pragma unroll
-    for (u32 j = 0; j < N; ++j)
-        if (e[j] != ~0ull) atomicAdd(&sm.hist[(u32)((mx - e[j]) >> sh)], 1u);
-    __syncthreads();
-    order_scan<B>(sm.hist, want, ~0u, false, sm);
-    const u32 last = sm.sp, end = last + 1u < 4u * B ? sm.hist[last + 1u] : total;
-    __syncthreads();
-    if (end > 8u * B) return 0;
+        for (u32 j = 0; j < N; ++j)
+            if (e[j] >= mn && e[j] <= mx) count_alike(sm.hist, (u32)((mx - e[j]) >> sh));
+        __syncthreads();
+        order_scan<B>(sm.hist, left, ~0u, false, sm);
+        const u32 last = sm.sp, before = sm.hist[last], upto = last + 1u < 4u * B ? sm.hist[last + 1u] : total - above;
+        if (tid == 0) sm.flag = 0;
+        __syncthreads();
+        const u64 floor = mx - mn > ((u64)(last + 1u) << sh) - 1u ? mx - (((u64)(last + 1u) << sh) - 1u) : mn;
+        if (above + upto <= 8u * B && (above + upto <= 2048u || above + upto <= want + want / 4u)) {
+            mn = floor;
+            above += upto;
+            break;
+        }
+        mx -= (u64)last << sh;
+        mn = floor;
+        above += before;
+        left -= before;
+        *crowd = true;
+    }
+    // (a lane's places by the wave, a wave's by the workgroup: bins would be places, too, but not those of what lies above them)
 #pragma unroll
     for (u32 j = 0; j < N; ++j) {
-        const u32 bin = (u32)((mx - e[j]) >> sh);
-        if (e[j] != ~0ull && bin <= last) sm.buf[atomicAdd(&sm.hist[bin], 1u)] = e[j];
+        const bool is = e[j] >= mn && e[j] != ~0ull;
+        const u64 have = ballot64(is);
+        if (have == 0) continue;
+        u32 at = 0;
+        if (lane_id() == 0) at = atomicAdd(&sm.flag, (u32)__popcll(have));
+        at = __builtin_amdgcn_readfirstlane(at) + mbcnt64(have);
+        if (is) sm.buf[at] = e[j];
     }
     __syncthreads();
-    return end;
+    return above;
+}
+
+// ------------------------------------------------------------------------------------------------
+// rows whose list was no use
+// ------------------------------------------------------------------------------------------------
+// One workgroup selects the row's k-th key from all of X (three or four sweeps), lists what is better, counts what
+// is equal, and goes on as usual.
+template <int DT, int B>
+__device__ __forceinline__ u32 list_anew(const Params& P, const ListPlan& L, int row, const RowShape& rs, rtopk_row_trace* st,
+                                         RankShared& rank, u32* run, u32* hist, u32* wsum) {
+    typedef ListSource<DT, false> Source;
+    constexpr u32 E = Source::E;
+    const u32 tid = threadIdx.x, lane = lane_id();
+    Source src;
+    src.init(rs);
+    const u32 nvec = (u32)src.nvec;
+    bool exact;
+    const u32 T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) {
+        for (u32 v = tid; v < nvec; v += B) {
+            uint4 q = load16<false>(src.abase + v);
+            keys_of_vector<DT>(q, P.dirmask);
+#pragma unroll
+            for (u32 j = 0; j < E; ++j)
+                if (v * E + j - src.lead < rs.n) f(key_in_vector<DT>(q, (int)j));
+        }
+    }, rs.k, 0u, 0xffffffffu, rank, &exact);
+    u32* te = list_part<u32>(P, row, L.tile_off);
+    const u32 nt = src.ntiles();
+    for (u32 j = tid; j < nt; j += B) te[j] = 0;
+    if (tid == 0) *run = 0;
+    __syncthreads();
+    const ListEntry ent = list_entry<DT>(P);
+    u64* list = list_array(P, 1u, row);
+    const u32 room = (u32)((P.n + 1) / 2);
+    for (u32 b = 0; b < nvec; b += B) {  // (whole waves: a wave's 64 vectors lie in one tile)
+        const u32 v = b + tid;
+        uint4 q = v < nvec ? load16<false>(src.abase + v) : make_uint4(0, 0, 0, 0);
+        keys_of_vector<DT>(q, P.dirmask);
+        u32 eq = 0;
+#pragma unroll
+        for (u32 j = 0; j < E; ++j) {
+            const u32 key = key_in_vector<DT>(q, (int)j), idx = v * E + j - src.lead;
+            const bool valid = v < nvec && idx < rs.n;
+            eq += valid && key == T ? 1u : 0u;
+            if (valid && key > T) {
+                const u32 at = atomicAdd(run, 1u);
+                if (at < room) list[at] = ent.of(key, idx);
+            }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) eq += __shfl_down(eq, o, 64);
+        if (lane == 0 && eq != 0u) atomicAdd(&te[v / (u32)Source::kTileVecs], eq);
+    }
+    __syncthreads();
+    const u32 listed = *run;
+    if (listed > room) {
+        if (tid == 0) st->error |= 4u;  // never expected: little more than k are better than T
+        return 0;
+    }
+    if (tid == 0) list_record(st, rs, listed, 5u);
+    if (listed < rs.k) {
+        __syncthreads();
+        ties_of_row<DT, B, Source>(P, TileCounts{te}, row, rs, listed, T, 0u, 1u, hist, wsum);
+        __syncthreads();
+    }
+    return listed;
+}
+template <int DT, int B>
+__device__ __forceinline__ void redo_row(const Params& P, const ListPlan& L, int row, const RowShape& rs, rtopk_row_trace* st, u32 why,
+                                         OrderShared<B>& ord, RankShared& rank, u32* run) {
+    if (threadIdx.x == 0) {
+        st->redo_why = why;
+        st->redo |= kRedoRow;
+    }
+    __syncthreads();
+    const u32 count = list_anew<DT, B>(P, L, row, rs, st, rank, run, ord.hist, ord.wsum);
+    __syncthreads();
+    if (count != 0u) order_entries<DT, B>(P, row, rs, ord, 0u, count, 1u, list_part<OrderRange>(P, row, L.stack_off));
 }
 
 // The list of one row into the output.  Blocks [0, batch): a row each.  Blocks beyond: L.ties per row, for rows whose
-// equal elements were counted, and for lists that one workgroup cannot put in order in LDS.
+// equal elements were counted; the first of them also help with lists that one workgroup cannot put in order in LDS.
 // Bound by latency.  The first entries of every segment lie together (L.slots of each) and are read before it is known how many there are: a search by
 // every entry for the segment that holds it, and 1024 segments all over the list array, took 6.2 us for 3300 entries; this 3.3 for 5800.  (Ordered from
 // the registers they are read to, 16 places per thread, they need not be put together first, but every phase takes longer: 12 / 15.5 us in all.)
@@ -1969,8 +2090,11 @@ __device__ __forceinline__ u32 keep_best(const u64 (&e)[N], u32 total, u32 want,
 template <int DT, int B, bool STREAM>
 __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     constexpr u32 kMost = 16;  // places per thread
-    __shared__ OrderShared<B> sm;
-    __shared__ u32 segs[B + 1];
+    constexpr u32 kMostSegments = B < 512 ? 256 : 512;
+    __shared__ union { OrderShared<B> ord; RankShared rank; } lds;
+    __shared__ OrderParts<B> shared;
+    __shared__ u32 segs[B + 1], place[B];
+    OrderShared<B>& sm = lds.ord;
     const u32 tid = threadIdx.x, G = (u32)L.G, slots = L.slots, log = 31u - (u32)__builtin_clz(slots);
     const bool for_ties = blockIdx.x >= (u32)P.batch;
     const int row = for_ties ? (int)((blockIdx.x - (u32)P.batch) / (u32)L.ties) : (int)blockIdx.x;
@@ -1980,7 +2104,8 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     // row of 1048869 fp16 keys, k = 3990, 34.7 us, put together first 37.0; 41 fp32 rows of 74007, k = 28, 20.7 / 21.5; but eleven of 135112, k = 615, 24.9 / 22.5.)
     constexpr bool few = !STREAM;
     // (the lengths and the decision before the entries: what counts of a row with ties does not wait for the places)
-    const u32 c = tid < G ? list_part<u32>(P, row, L.seg_off)[tid] : 0u;  // (G is at most B)
+    const uint2 seg = tid < G ? list_part<uint2>(P, row, L.seg_off)[tid] : make_uint2(0u, 0u);  // (G is at most B)
+    const u32 c = seg.x;
     const ListRow* lr = list_row(P, row);
     const u32 mode = lr->mode;
     __builtin_amdgcn_sched_barrier(0);
@@ -1995,96 +2120,109 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     const RowShape rs = row_shape_scalar<DT>(P, row);
     rtopk_row_trace* st = row_state(P, row);
     const u32 incl = block_scan<B>(c, sm.wsum);
-    if (tid < G) segs[tid] = incl - c;
+    if (tid != G) segs[tid] = tid < G ? incl - c : ~0u;
     if (tid == B - 1) segs[G] = incl;
+    const u32 unit = few ? (u32)ListSource<DT, false>::kTileVecs : kWaveVecs;
+    if (few && tid < G) place[tid] = list_segment<DT>(rs, tid, G, unit) - (incl - c);
     const bool over = __syncthreads_or(c > slots + (few ? 8u : 0u) ? 1 : 0) != 0;  // (a segment has more than its places, or many more)
     const u32 total = segs[G];
-    const bool useless = (mode == kListPlain && total < rs.k) || total > (u32)((P.n + 1) / 2);
+    u32 equal = 0;  // elements that equal T, where they were counted
+    if (mode == kListTied) {
+        (void)block_scan<B>(seg.y, sm.wsum);
+        equal = sum_of_waves<B>(sm.wsum, 1);
+        __syncthreads();
+    }
+    const bool few_in_all = (u64)total + equal < (u64)rs.k, useless = few_in_all || total > (u32)((P.n + 1) / 2);
     const u64* from = list_array(P, 1u, row);
-    const u32 unit = few ? (u32)ListSource<DT, false>::kTileVecs : kWaveVecs;
+    // (No branches: eight entries' searches and loads are under way together.  With loops that end when they have found it, and segments' places worked out for every entry,
+    // one row of 2^20 fp32 keys, a ramp, k = 3000, took 81.7 us, so 71.2; 16 of 2^24, k = 512, of which nothing is too long, 38.6 / 38.0.)
     auto entry = [&](u32 i) __attribute__((always_inline)) {
-        u32 a = 0, b = G;  // the segment that holds entry i: the last one that begins at or before it
-        while (b - a > 1u) {
-            const u32 m = (a + b) / 2u;
-            if (segs[m] <= i) a = m; else b = m;
-        }
+        u32 a = 0;  // the segment that holds entry i: the last one that begins at or before it
+#pragma unroll
+        for (u32 step = kMostSegments / 2u; step > 0; step /= 2u) a += segs[a + step] <= i ? step : 0u;
         const u32 l = i - segs[a];
-        if (l < slots) return front[a * slots + l];
-        return from[list_segment<DT>(rs, a, G, unit) + l];
+        return *(l < slots ? front + (a * slots + l) : from + (place[a] + i));
     };
+    auto find_places = [&]() __attribute__((always_inline)) {  // (k_list_stream's, which are rarely needed)
+        if (few) return;
+        if (tid < G) place[tid] = list_segment<DT>(rs, tid, G, unit) - (incl - c);
+        __syncthreads();
+    };
+    constexpr u32 kHelpers = 3;
+    const u32 helpers = kHelpers < (u32)L.ties ? kHelpers : (u32)L.ties;
+    u32 part = 0, parts = 1u + helpers;  // of a list that is far too long
     if (for_ties) {
         const u32 w = (blockIdx.x - (u32)P.batch) % (u32)L.ties;
-        if (total > 8u * B && !useless) {  // (perhaps) more than LDS holds: the segments are put together for k_list_redo
-            u64* dst = list_array(P, 0u, row);
-            for (u32 i = w * B + tid; i < total; i += (u32)L.ties * B) dst[i] = entry(i);
-        }
-        if (mode != kListTied || total >= rs.k) return;
-        const TileCounts tiles{list_part<u32>(P, row, L.tile_off)};
-        constexpr u32 kParts = (u32)ListSource<DT, false>::kTileVecs / kWaveVecs;
-        const u32 parts = (u32)((src_vectors<DT>(rs) + kWaveVecs - 1u) / kWaveVecs);
-        auto count = [&](u32 i) __attribute__((always_inline)) {  // (k_list_stream's tiles are smaller)
-            if (few) return tiles(i);
-            u32 n = 0;
+        if (useless) return;
+        if (mode == kListTied && total < rs.k) {
+            const TileCounts tiles{list_part<u32>(P, row, L.tile_off)};
+            constexpr u32 kParts = (u32)ListSource<DT, false>::kTileVecs / kWaveVecs;
+            const u32 parts = (u32)((src_vectors<DT>(rs) + kWaveVecs - 1u) / kWaveVecs);
+            auto count = [&](u32 i) __attribute__((always_inline)) {  // (k_list_stream's tiles are smaller)
+                if (few) return tiles(i);
+                u32 n = 0;
 #pragma unroll
-            for (u32 c = 0; c < kParts; ++c) n += kParts * i + c < parts ? tiles(kParts * i + c) : 0u;
-            return n;
-        };
-        if (!ties_of_row<DT, B, ListSource<DT, false>>(P, count, row, rs, total, lr->T, w, (u32)L.ties, sm.hist, sm.wsum) && w == 0 && tid == 0) {
-            st->redo_why = 8u;
-            atomicOr(&st->redo, kRedoRow);
+                for (u32 c = 0; c < kParts; ++c) n += kParts * i + c < parts ? tiles(kParts * i + c) : 0u;
+                return n;
+            };
+            if (!ties_of_row<DT, B, ListSource<DT, false>>(P, count, row, rs, total, lr->T, w, (u32)L.ties, sm.hist, sm.wsum) && w == 0 && tid == 0)
+                st->error |= 4u;  // never expected: there are enough of them
         }
+        if (total <= kMost * B || w >= helpers) return;  // (16 entries per thread: one workgroup cuts that down)
+        part = 1u + w;
+        find_places();
+    } else if (useless) {
+        redo_row<DT, B>(P, L, row, rs, st, few_in_all ? 8u : 5u, sm, lds.rank, &shared.run);
         return;
-    }
-    if (useless) {
-        if (tid == 0) {
-            st->redo_why = total < rs.k ? 8u : 5u;
-            atomicOr(&st->redo, kRedoRow);
+    } else {
+        if (tid == 0) list_record(st, rs, total, 5u);
+        if (total == 0) return;
+        u32 n = total;
+        // (A list that LDS does not hold, though not much longer than expected, is cut down first.  Not every one that is much longer than what is wanted of it: 5800 entries, k = 256, 12.0 / 15.8 us.)
+        if (few && (B <= 256 || total > 4096u) && total <= 8u * B) {
+            order_in_lds<DT, B>(P, row, rs, sm, total, 0u, entry);
+            return;
         }
-        return;
-    }
-    if (tid == 0) list_record(st, rs, total, 5u);
-    if (total == 0) return;
-    u32 n = total;
-    // (A list that LDS does not hold, though not much longer than expected, is cut down first.  Not every one that is much longer than what is wanted of it: 5800 entries, k = 256, 12.0 / 15.8 us.)
-    if (few && (B <= 256 || total > 4096u) && total <= 8u * B) {
-        order_in_lds<DT, B>(P, row, rs, sm, total, 0u, entry);
-        return;
-    }
-    if (total > 8u * B) {
-        n = 0;
-        if (total <= L.most) {  // (at most kMost * B)
-            const bool held = !few && __syncthreads_or(c > slots ? 1 : 0) == 0;  // (every segment has places enough; else entries look for themselves)
+        if (over || total > 8u * B) find_places();
+        if (total > 8u * B) {
+            n = 0;
+            if (total <= kMost * B) {
+                const bool held = !few && __syncthreads_or(c > slots ? 1 : 0) == 0;  // (every segment has places enough; else entries look for themselves)
+#pragma unroll
+                for (u32 j = 0; j < kMost; ++j) {
+                    const u32 i = tid + j * (u32)B, a = i >> log, l = i & (slots - 1u);
+                    if (!held) e[j] = i < total ? entry(i) : ~0ull;
+                    else if (i >= places || l >= segs[a + 1u] - segs[a]) e[j] = ~0ull;
+                }
+                bool crowd;
+                n = keep_best<B>(e, total, rs.k, sm, &crowd);
+                if ((crowd || total > L.most) && tid == 0) st->redo |= kRedoList;
+            } else if (tid == 0) {
+                st->redo |= kRedoList;
+            }
+        } else if (over) {
+            for (u32 i = tid; i < total; i += B) sm.buf[i] = entry(i);
+        } else {
 #pragma unroll
             for (u32 j = 0; j < kMost; ++j) {
                 const u32 i = tid + j * (u32)B, a = i >> log, l = i & (slots - 1u);
-                if (!held) e[j] = i < total ? entry(i) : ~0ull;
-                else if (i >= places || l >= segs[a + 1u] - segs[a]) e[j] = ~0ull;
+                if (i < places && l < segs[a + 1u] - segs[a]) sm.buf[segs[a] + l] = e[j];
             }
-            n = keep_best<B>(e, total, rs.k < total ? rs.k : total, sm);
+            // (k_list_sweep's 512 segments: one of them has a little more than its places in every other row.  k_list_stream's have not, and 0.15 us to lose here.)
+            if (few && ballot64(c > slots) != 0u) {
+                const u32 at = list_segment<DT>(rs, tid, G, unit);
+                for (u32 l = slots; l < c; ++l) sm.buf[segs[tid] + l] = from[at + l];
+            }
         }
-        if (n == 0u) {
-            if (tid == 0) {
-                list_done(P, row)->total = total;
-                list_done(P, row)->end = 0u;
-                atomicOr(&st->redo, kRedoList);
-            }
+        if (n != 0u) {
+            order_list<DT, B>(P, row, rs, sm, n);
             return;
         }
-    } else if (over) {
-        for (u32 i = tid; i < total; i += B) sm.buf[i] = entry(i);
-    } else {
-#pragma unroll
-        for (u32 j = 0; j < kMost; ++j) {
-            const u32 i = tid + j * (u32)B, a = i >> log, l = i & (slots - 1u);
-            if (i < places && l < segs[a + 1u] - segs[a]) sm.buf[segs[a] + l] = e[j];
-        }
-        // (k_list_sweep's 512 segments: one of them has a little more than its places in every other row.  k_list_stream's have not, and 0.15 us to lose here.)
-        if (few && ballot64(c > slots) != 0u) {
-            const u32 at = list_segment<DT>(rs, tid, G, unit);
-            for (u32 l = slots; l < c; ++l) sm.buf[segs[tid] + l] = from[at + l];
-        }
     }
-    order_list<DT, B>(P, row, rs, sm, n);
+    // (nobody puts it together first: every part reads it where it lies)
+    const u32 want = rs.k < total ? rs.k : total, n = (want + 4u * B - 1u) / (4u * B);
+    parts = parts < n ? parts : n;
+    if (part < parts) order_shared<DT, B, true>(P, row, rs, sm, shared, entry, total, 0u, part, parts);
 }
 
 // k_list_part's lists: L.G of at most L.seg_stride entries, 8 B in all at most (so fewer than B lists).
@@ -2447,13 +2585,16 @@ __global__ void __launch_bounds__(kPartBlock, 4) k_list_part(Params P, ListPlan 
     if (tid == 0) list_part<u32>(P, row, L.seg_off)[g] = listed < L.seg_stride ? listed : L.seg_stride;
 }
 
+// (Registers: six waves to a SIMD where a workgroup has eight, which what is normally not there to be done would else make four: 1024 rows of 2^17 bf16 keys, k = 1024, 68.8 us / 63.9.
+// Workgroups of four waves are better four to a compute unit than unevenly more of them: k = 50, six waves 52.4 us, four 49.4.)
 // Bound, sweep and order in one kernel: the list is gathered in LDS (what does not fit there goes to the list array).
 // For rows so short, or so many, that sharing one out gains nothing.  Several of these workgroups share a compute unit, so that one
 // row's trip from memory overlaps the others' ranking.
 template <int DT, int B, int V, bool NT>
-__global__ void __launch_bounds__(B, 4) k_list_row(Params P, ListPlan L) {
+__global__ void __launch_bounds__(B, B == 512 ? 6 : 4) k_list_row(Params P, ListPlan L) {
     constexpr int OB = B < 256 ? B : 256;  // threads that order a short list (see k_list_held)
     __shared__ union { OrderShared<B> ord; OrderShared<OB> few; RankShared rank; } sm;
+    __shared__ OrderParts<B> shared;
     __shared__ ListRow lr;
     __shared__ u32 red[3 * (B / 64)], te[kListRowTiles], run;
     constexpr u32 kCap = 8 * B;
@@ -2471,7 +2612,7 @@ __global__ void __launch_bounds__(B, 4) k_list_row(Params P, ListPlan L) {
     const ListRow b = list_row_scalar(&lr);
     const ListEntry ent = list_entry<DT>(P);
     u64* list = list_array(P, 1u, row);
-    sweep_row<DT>(src, 0u, 1u, b, te, P.dirmask, [&](const typename Source::Tile& cur, u32 m) __attribute__((always_inline)) {
+    (void)sweep_row<DT>(src, 0u, 1u, b, te, P.dirmask, [&](const typename Source::Tile& cur, u32 m) __attribute__((always_inline)) {
         for (;;) {
             const u64 have = ballot64(m != 0u);
             if (have == 0) break;
@@ -2491,20 +2632,14 @@ __global__ void __launch_bounds__(B, 4) k_list_row(Params P, ListPlan L) {
     __syncthreads();
     const u32 total = run;
     if (b.mode == kListPlain && total < rs.k) {
-        if (tid == 0) {
-            st->redo_why = 8u;
-            atomicOr(&st->redo, kRedoRow);
-        }
+        redo_row<DT, B>(P, L, row, rs, st, 8u, sm.ord, sm.rank, &run);
         return;
     }
     if (tid == 0) list_record(st, rs, total, 6u);
     if (total > kCap) {
         for (u32 i = tid; i < kCap; i += B) list[i] = sm.ord.buf[i];
-        if (tid == 0) {
-            list_done(P, row)->total = total;
-            list_done(P, row)->end = 1u;
-            atomicOr(&st->redo, kRedoList);
-        }
+        if (tid == 0) st->redo |= kRedoList;
+        order_shared<DT, B>(P, row, rs, sm.ord, shared, [&](u32 i) __attribute__((always_inline)) { return list[i]; }, total, 0u, 0u, 1u);
     } else if (total != 0u && total <= 8u * OB && b.mode != kListTied) {
         if (tid >= (u32)OB) return;  // (a barrier waits for the waves that are left)
         order_in_lds<DT, OB>(P, row, rs, sm.few, total, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.few.buf[i]; });
@@ -2513,9 +2648,9 @@ __global__ void __launch_bounds__(B, 4) k_list_row(Params P, ListPlan L) {
     }
     if (b.mode == kListTied && total < rs.k) {
         __syncthreads();
-        if (!ties_of_row<DT, B, Source>(P, TileCounts{te}, row, rs, total, b.T, 0u, 1u, sm.ord.hist, sm.ord.wsum) && tid == 0) {
-            st->redo_why = 8u;
-            atomicOr(&st->redo, kRedoRow);
+        if (!ties_of_row<DT, B, Source>(P, TileCounts{te}, row, rs, total, b.T, 0u, 1u, sm.ord.hist, sm.ord.wsum)) {
+            __syncthreads();
+            redo_row<DT, B>(P, L, row, rs, st, 8u, sm.ord, sm.rank, &run);
         }
     }
 }
@@ -2523,6 +2658,15 @@ __global__ void __launch_bounds__(B, 4) k_list_row(Params P, ListPlan L) {
 // ------------------------------------------------------------------------------------------------
 // long lists
 // ------------------------------------------------------------------------------------------------
+
+constexpr u32 kBucketRoom = 8 * kListBucketBlock;  // entries of a bucket that one workgroup puts in order
+
+// The elements equal to T that the row's workgroups counted, into *sum (which has been cleared before a barrier).
+__device__ __forceinline__ void add_ties(u32 mode, u32 mine, u32* sum) {
+    if (mode != kListTied) return;
+    mine = wave_inclusive_scan(mine);
+    if (lane_id() == 63u && mine != 0u) atomicAdd(sum, mine);
+}
 
 // Workgroup w moves segment w into buckets.  A bin's rank is the number of entries in better bins; a bucket is the run of
 // bins whose ranks share rank >> L.bucket_shift, its place in the array its first bin's rank.  A bin that ends beyond the ranks of the next bucket, which is
@@ -2536,7 +2680,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     __shared__ u32 place[kListMaxBuckets];   // of every bucket: this workgroup's entries, then their next place
     __shared__ u64 split[kListSplits + 1];
     __shared__ u32 wsum[B / 64];
-    __shared__ u32 s_end, s_total;
+    __shared__ u32 s_end, s_total, s_equal, s_big;
     const u32 G = (u32)L.G, tid = threadIdx.x;
     const int row = (int)(blockIdx.x / G);
     const u32 wg = blockIdx.x % G;
@@ -2549,7 +2693,9 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     const u32 sh = lr->sh, by_split = __builtin_amdgcn_readfirstlane(lr->split);
     if (by_split != 0u && tid <= kListSplits) split[tid] = list_part<u64>(P, row, L.split_off)[tid];
     const u64* from = list_array(P, 1u, row) + list_segment<DT>(rs, wg, G, (u32)ListSource<DT, true>::kTileVecs);
-    const u32 mine = list_part<u32>(P, row, L.seg_off)[wg];
+    const uint2* segs = list_part<uint2>(P, row, L.seg_off);
+    const u32 mine = segs[wg].x;
+    const u32 equal = mode == kListTied && tid < G ? segs[tid].y : 0u;  // (G is at most 256)
     constexpr int kHeld = 8;
     u64 held[kHeld];
 #pragma unroll
@@ -2563,7 +2709,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
         s += c[i];
     }
     for (u32 j = tid; j < nb; j += B) place[j] = 0;
-    if (tid == 0) s_end = 0;
+    if (tid == 0) s_end = s_equal = s_big = 0;
     const u32 incl = block_scan<B>(s, wsum);
     {
         u32 r = incl - s;
@@ -2577,6 +2723,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
         }
         if (tid == B - 1) s_total = r;
     }
+    add_ties(mode, equal, &s_equal);
     // f(bucket, rank) for this thread's bins that begin one
     auto first_bins = [&](auto&& f) __attribute__((always_inline)) {
 #pragma unroll
@@ -2589,13 +2736,10 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     const u32 total = s_total;
     const bool few = total < rs.k;
     const u32 end = few ? total : s_end;
-    const bool drop = (mode == kListPlain && few) || end > (u32)((P.n + 1) / 2);  // (the buckets have half a candidate array)
-    if (wg == 0 && tid == 0) *list_done(P, row) = ListDone{total, end, drop ? 1u : 0u, 0u};
+    const bool few_in_all = few && (u64)total + s_equal < (u64)rs.k;
+    const bool drop = few_in_all || end > (u32)((P.n + 1) / 2);  // (the buckets have half a candidate array)
     if (drop) {
-        if (wg == 0 && tid == 0) {
-            st->redo_why = few ? 8u : 5u;
-            atomicOr(&st->redo, kRedoRow);
-        }
+        if (wg == 0 && tid == 0) *list_done(P, row) = ListDone{total, end, few_in_all ? 8u : 5u, 0u};
         return;
     }
     if (wg == 0) {
@@ -2609,10 +2753,13 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
         for (u32 j = tid; j < nb; j += B) {
             u32 i = j + 1u;
             while (i < nb && place[i] == 0xffffffffu) ++i;
+            const u32 size = (i < nb ? place[i] : end) - place[j];
             first[2u * j] = place[j];
-            first[2u * j + 1u] = (i < nb ? place[i] : end) - place[j];
+            first[2u * j + 1u] = size;
+            if (place[j] != 0xffffffffu && size > kBucketRoom) s_big = 1u;
         }
         __syncthreads();
+        if (tid == 0) *list_done(P, row) = ListDone{total, end, 0u, s_big};
         for (u32 j = tid; j < nb; j += B) place[j] = 0;
         __syncthreads();
     }
@@ -2658,7 +2805,7 @@ template <int DT>
 __global__ void __launch_bounds__(kLongBlock) k_list_emit(Params P, ListPlan L) {
     constexpr int B = kLongBlock, kPer = kListBins / B, kHeld = 8;
     __shared__ u64 split[kListSplits + 1], s_base;
-    __shared__ u32 wsum[B / 64], counts[2 * (B / 64)], s_bin, s_rank, s_end;
+    __shared__ u32 wsum[B / 64], counts[2 * (B / 64)], s_bin, s_rank, s_end, s_equal;
     const u32 G = (u32)L.G, tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     const int row = (int)(blockIdx.x / G);
     const u32 wg = blockIdx.x % G;
@@ -2671,7 +2818,9 @@ __global__ void __launch_bounds__(kLongBlock) k_list_emit(Params P, ListPlan L) 
     const u32 sh = lr->sh, by_split = __builtin_amdgcn_readfirstlane(lr->split);
     if (by_split != 0u && tid <= kListSplits) split[tid] = list_part<u64>(P, row, L.split_off)[tid];
     const u64* from = list_array(P, 1u, row) + list_segment<DT>(rs, wg, G, (u32)ListSource<DT, true>::kTileVecs);
-    const u32 mine = list_part<u32>(P, row, L.seg_off)[wg];
+    const uint2* segs = list_part<uint2>(P, row, L.seg_off);
+    const u32 mine = segs[wg].x;
+    const u32 equal = mode == kListTied && tid < G ? segs[tid].y : 0u;  // (G is at most 256)
     u64 held[kHeld];
 #pragma unroll
     for (int i = 0; i < kHeld; ++i) held[i] = tid + (u32)i * B < mine ? from[tid + (u32)i * B] : 0ull;
@@ -2682,7 +2831,10 @@ __global__ void __launch_bounds__(kLongBlock) k_list_emit(Params P, ListPlan L) 
         c[i] = gh[kListBins - 1u - (tid * kPer + i)];  // from the best bin down
         s += c[i];
     }
-    if (tid == 0) s_bin = 0xffffffffu;
+    if (tid == 0) {
+        s_bin = 0xffffffffu;
+        s_equal = 0;
+    }
     const u32 incl = block_scan<B>(s, wsum);
     {
         u32 r = incl - s;
@@ -2697,22 +2849,19 @@ __global__ void __launch_bounds__(kLongBlock) k_list_emit(Params P, ListPlan L) 
         }
         if (tid == B - 1) counts[0] = r;
     }
+    add_ties(mode, equal, &s_equal);
     __syncthreads();
     const u32 total = counts[0], bin = s_bin;  // (fewer than k in all: 0xffffffff, and every entry is output)
     const bool few = bin == 0xffffffffu;
     const u32 rank = few ? total : s_rank, end = few ? total : s_end;
-    const bool drop = (mode == kListPlain && few) || end > (u32)((P.n + 1) / 2);  // (the bucket has its place in half a candidate array)
+    const bool few_in_all = few && (u64)total + s_equal < (u64)rs.k;
+    const bool drop = few_in_all || end > (u32)((P.n + 1) / 2);  // (the bucket has its place in half a candidate array)
     if (wg == 0 && tid == 0) {
-        *list_done(P, row) = ListDone{total, end, drop ? 1u : 0u, 0u};
+        *list_done(P, row) = ListDone{total, end, drop ? (few_in_all ? 8u : 5u) : 0u, !few && end - rank > kBucketRoom ? 1u : 0u};
         u32* first = list_part<u32>(P, row, L.first_off);
         first[0] = few ? 0xffffffffu : rank;
         first[1] = end - rank;
-        if (drop) {
-            st->redo_why = few ? 8u : 5u;
-            atomicOr(&st->redo, kRedoRow);
-        } else {
-            list_record(st, rs, total, 5u);
-        }
+        if (!drop) list_record(st, rs, total, 5u);
     }
     if (drop) return;
     __syncthreads();  // (everybody has read the total)
@@ -2775,11 +2924,14 @@ __device__ __forceinline__ bool bucket_range(const Params& P, const ListPlan& L,
 }
 
 // One workgroup per bucket (blocks [0, nb) of a row) puts its entries in order; the other L.ties blocks of the row are for
-// the elements equal to T.
+// the elements equal to T.  Buckets of too many entries are shared out among all of a row's workgroups, and the first has a row whose list was no use.
 template <int DT>
-__global__ void __launch_bounds__(kListBucketBlock) k_list_buckets(Params P, ListPlan L) {
+__global__ void __launch_bounds__(kListBucketBlock, 6) k_list_buckets(Params P, ListPlan L) {
     constexpr int B = kListBucketBlock;
-    __shared__ OrderShared<B> sm;
+    __shared__ union { OrderShared<B> ord; RankShared rank; } lds;
+    __shared__ OrderParts<B> shared;
+    __shared__ u32 before[B], run;
+    OrderShared<B>& sm = lds.ord;
     const u32 per = L.nb + (u32)L.ties, tid = threadIdx.x;
     const int row = (int)(blockIdx.x / per);
     const u32 j = blockIdx.x % per;
@@ -2787,158 +2939,48 @@ __global__ void __launch_bounds__(kListBucketBlock) k_list_buckets(Params P, Lis
     const u32 mode = lr->mode;
     if (mode == kListSkip) return;
     const ListDone done = *list_done(P, row);
-    if (done.drop != 0u) return;
     const RowShape rs = row_shape_scalar<DT>(P, row);
+    rtopk_row_trace* st = row_state(P, row);
+    if (done.drop != 0u) {
+        if (j == 0u) redo_row<DT, B>(P, L, row, rs, st, done.drop, sm, lds.rank, &run);
+        return;
+    }
+    u32 at = 0, count = 0;
+    const u64* list = list_array(P, 0u, row);
     if (j >= L.nb) {
-        if (mode != kListTied || done.total >= rs.k) return;
-        if (!ties_of_row<DT, B, ListSource<DT, true>>(P, TileCounts{list_part<u32>(P, row, L.tile_off)}, row, rs, done.total, lr->T, j - L.nb,
-                                                      (u32)L.ties, sm.hist, sm.wsum) && j == L.nb && tid == 0) {
-            rtopk_row_trace* st = row_state(P, row);
-            st->redo_why = 8u;
-            atomicOr(&st->redo, kRedoRow);
-        }
-        return;
-    }
-    u32 at, count;
-    if (!bucket_range(P, L, row, rs, j, &at, &count)) return;
-    if (count <= 8u * B) {
-        const u64* src = list_array(P, 0u, row) + at;
+        if (mode == kListTied && done.total < rs.k &&
+            !ties_of_row<DT, B, ListSource<DT, true>>(P, TileCounts{list_part<u32>(P, row, L.tile_off)}, row, rs, done.total, lr->T, j - L.nb,
+                                                      (u32)L.ties, sm.hist, sm.wsum) && j == L.nb && tid == 0)
+            st->error |= 4u;  // never expected: there are enough of them
+    } else if (bucket_range(P, L, row, rs, j, &at, &count) && count <= kBucketRoom) {
+        const u64* src = list + at;
         order_in_lds<DT, B>(P, row, rs, sm, count, at, [&](u32 i) __attribute__((always_inline)) { return src[i]; });
-    } else if (tid == 0) {
-        atomicOr(&row_state(P, row)->redo, kRedoBuckets);
     }
-}
-
-// ------------------------------------------------------------------------------------------------
-// rows whose list was no use
-// ------------------------------------------------------------------------------------------------
-// kRedoRow: one workgroup selects the row's k-th key from all of X (three or four sweeps), lists what is better, counts what
-// is equal, and goes on as usual.
-template <int DT, int B>
-__device__ __forceinline__ void redo_row(const Params& P, const ListPlan& L, int row, const RowShape& rs, rtopk_row_trace* st,
-                                         RankShared& rank, u32* run, u32* hist, u32* wsum, u32* listed_out) {
-    typedef ListSource<DT, false> Source;
-    constexpr u32 E = Source::E;
-    const u32 tid = threadIdx.x, lane = lane_id();
-    Source src;
-    src.init(rs);
-    const u32 nvec = (u32)src.nvec;
-    bool exact;
-    const u32 T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) {
-        for (u32 v = tid; v < nvec; v += B) {
-            uint4 q = load16<false>(src.abase + v);
-            keys_of_vector<DT>(q, P.dirmask);
-#pragma unroll
-            for (u32 j = 0; j < E; ++j)
-                if (v * E + j - src.lead < rs.n) f(key_in_vector<DT>(q, (int)j));
-        }
-    }, rs.k, 0u, 0xffffffffu, rank, &exact);
-    u32* te = list_part<u32>(P, row, L.tile_off);
-    const u32 nt = src.ntiles();
-    for (u32 j = tid; j < nt; j += B) te[j] = 0;
-    if (tid == 0) *run = 0;
-    __syncthreads();
-    const ListEntry ent = list_entry<DT>(P);
-    u64* list = list_array(P, 1u, row);
-    const u32 room = (u32)((P.n + 1) / 2);
-    for (u32 b = 0; b < nvec; b += B) {  // (whole waves: a wave's 64 vectors lie in one tile)
-        const u32 v = b + tid;
-        uint4 q = v < nvec ? load16<false>(src.abase + v) : make_uint4(0, 0, 0, 0);
-        keys_of_vector<DT>(q, P.dirmask);
-        u32 eq = 0;
-#pragma unroll
-        for (u32 j = 0; j < E; ++j) {
-            const u32 key = key_in_vector<DT>(q, (int)j), idx = v * E + j - src.lead;
-            const bool valid = v < nvec && idx < rs.n;
-            eq += valid && key == T ? 1u : 0u;
-            if (valid && key > T) {
-                const u32 at = atomicAdd(run, 1u);
-                if (at < room) list[at] = ent.of(key, idx);
+    if (done.big == 0u) return;
+    // every bucket that is too large is cut into parts of about half of what LDS holds; all of the row's parts are dealt to its workgroups
+    if (j == 0u && tid == 0) st->redo |= kRedoBuckets;
+    u32 base = 0;
+    for (u32 j0 = 0; j0 < L.nb; j0 += B) {
+        u32 n = 0;
+        if (j0 + tid < L.nb && bucket_range(P, L, row, rs, j0 + tid, &at, &count) && count > kBucketRoom) n = (count + 4u * B - 1u) / (4u * B);
+        __syncthreads();
+        const u32 incl = block_scan<B>(n, sm.wsum);
+        before[tid] = incl - n;
+        if (tid == B - 1) run = incl;
+        __syncthreads();
+        const u32 total = run;
+        for (u32 s = (j + per - base % per) % per; s < total; s += per) {
+            u32 a = 0, b = B;  // the bucket that part s belongs to: the last one that begins at or before it
+            while (b - a > 1u) {
+                const u32 m = (a + b) / 2u;
+                if (before[m] <= s) a = m; else b = m;
             }
+            bucket_range(P, L, row, rs, j0 + a, &at, &count);
+            const u64* src = list + at;
+            order_shared<DT, B>(P, row, rs, sm, shared, [&](u32 i) __attribute__((always_inline)) { return src[i]; }, count, at, s - before[a],
+                                (count + 4u * B - 1u) / (4u * B));
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) eq += __shfl_down(eq, o, 64);
-        if (lane == 0 && eq != 0u) atomicAdd(&te[v / (u32)Source::kTileVecs], eq);
-    }
-    __syncthreads();
-    const u32 listed = *run;
-    *listed_out = 0;
-    if (listed > room) {
-        if (tid == 0) st->error |= 4u;  // never expected: little more than k are better than T
-        return;
-    }
-    if (tid == 0) list_record(st, rs, listed, 5u);
-    if (listed < rs.k) {
-        __syncthreads();
-        ties_of_row<DT, B, Source>(P, TileCounts{te}, row, rs, listed, T, 0u, 1u, hist, wsum);
-        __syncthreads();
-    }
-    *listed_out = listed;
-}
-
-// What the kernels before left over; normally nothing.  Every row has L.redo_wgs workgroups, which share what has to be put in
-// order; where that is one, a workgroup has several rows.
-template <int DT>
-__global__ void __launch_bounds__(kListBucketBlock) k_list_redo(Params P, ListPlan L) {
-    constexpr int B = kListBucketBlock;
-    __shared__ union { OrderShared<B> ord; RankShared rank; } sm;
-    __shared__ OrderParts<B> parts;
-    __shared__ u32 before[B], run, marked[B], nmarked;
-    const u32 tid = threadIdx.x, W = (u32)L.redo_wgs, w = blockIdx.x % W;
-    const u32 step = gridDim.x / W, first = blockIdx.x / W;  // (the grid is a multiple of W)
-    for (u64 r0 = first; r0 < (u64)P.batch; r0 += (u64)step * B) {
-        const u64 r = r0 + (u64)tid * step;
-        const u32 mark = r < (u64)P.batch ? row_state(P, (int)r)->redo : 0u;
-        if (__syncthreads_or((int)mark) == 0) continue;
-        if (tid == 0) nmarked = 0;
-        __syncthreads();
-        if (mark != 0u) marked[atomicAdd(&nmarked, 1u)] = (u32)r;
-        __syncthreads();
-        const u32 nm = nmarked;
-        for (u32 i = 0; i < nm; ++i) {
-            const int row = (int)marked[i];
-            rtopk_row_trace* st = row_state(P, row);
-            const u32 why = st->redo;
-            const RowShape rs = row_shape_scalar<DT>(P, row);
-            __syncthreads();
-            if (why & kRedoRow) {
-                if (w != 0u) continue;
-                u32 count;
-                redo_row<DT, B>(P, L, row, rs, st, sm.rank, &run, sm.ord.hist, sm.ord.wsum, &count);
-                __syncthreads();
-                if (count != 0u) order_entries<DT, B>(P, row, rs, sm.ord, 0u, count, 1u, list_part<OrderRange>(P, row, L.stack_off));
-            } else if (why & kRedoList) {
-                const ListDone done = *list_done(P, row);
-                const u32 want = rs.k < done.total ? rs.k : done.total, n = (want + 4u * B - 1u) / (4u * B), np = n < W ? n : W;
-                if (w < np) order_shared<DT, B>(P, row, rs, sm.ord, parts, list_array(P, done.end, row), done.total, 0u, w, np);
-            } else {
-                // every bucket that is too large is cut into parts of about half of what LDS holds; all of the row's parts are dealt to its
-                // workgroups
-                u32 base = 0;
-                for (u32 j0 = 0; j0 < L.nb; j0 += B) {
-                    u32 at = 0, count = 0, n = 0;
-                    if (j0 + tid < L.nb && bucket_range(P, L, row, rs, j0 + tid, &at, &count) && count > 8u * B) n = (count + 4u * B - 1u) / (4u * B);
-                    __syncthreads();
-                    const u32 incl = block_scan<B>(n, sm.ord.wsum);
-                    before[tid] = incl - n;
-                    if (tid == B - 1) run = incl;
-                    __syncthreads();
-                    const u32 total = run;
-                    for (u32 s = (w + W - base % W) % W; s < total; s += W) {
-                        u32 a = 0, b = B;  // the bucket that part s belongs to: the last one that begins at or before it
-                        while (b - a > 1u) {
-                            const u32 m = (a + b) / 2u;
-                            if (before[m] <= s) a = m; else b = m;
-                        }
-                        bucket_range(P, L, row, rs, j0 + a, &at, &count);
-                        order_shared<DT, B>(P, row, rs, sm.ord, parts, list_array(P, 0u, row) + at, count, at, s - before[a], (count + 4u * B - 1u) / (4u * B));
-                    }
-                    base += total;
-                }
-            }
-            __syncthreads();
-        }
-        __syncthreads();
+        base += total;
     }
 }
 
@@ -2972,12 +3014,10 @@ static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStrea
     mark(events, 0, st);
     mark(events, 1, st);
     const dim3 rows((unsigned)P.batch);
-    const unsigned redo = (unsigned)((L.redo_wgs > 1 ? P.batch * L.redo_wgs : P.batch < 512 ? P.batch : 512));
     if (L.row_block != 0) {
         mark(events, 2, st);
         mark(events, 3, st);
         rows_alone(P, L, st);
-        if (L.held == 0) hipLaunchKernelGGL((k_list_redo<DT>), dim3(redo), dim3(kListBucketBlock), 0, st, P, L);
         mark(events, 4, st);
         return hipGetLastError() == hipSuccess ? RTOPK_OK : RTOPK_ERR_HIP;
     }
@@ -3021,7 +3061,6 @@ static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStrea
         else if (L.finish == 256) hipLaunchKernelGGL((k_list_finish<DT, 256, false>), g, dim3(256), 0, st, P, L);
         else hipLaunchKernelGGL((k_list_finish<DT, 1024, false>), g, dim3(1024), 0, st, P, L);
     }
-    hipLaunchKernelGGL((k_list_redo<DT>), dim3(redo), dim3(kListBucketBlock), 0, st, P, L);
     mark(events, 4, st);
     return hipGetLastError() == hipSuccess ? RTOPK_OK : RTOPK_ERR_HIP;
 }
