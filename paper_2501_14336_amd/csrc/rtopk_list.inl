@@ -117,8 +117,10 @@ __device__ __forceinline__ u32 list_bin_split(u64 e, const u64* split) {
 // Per-row working memory beside the list: the upper half of the row's first candidate array (the list proper is at
 // most half a row).  Offsets in bytes from its 256-byte-aligned start come from the host (ListPlan).
 __device__ __forceinline__ char* list_meta(const Params& P, int row) {
-    const uintptr_t a = (uintptr_t)(P.cand[0] + (size_t)row * P.cand_stride + (size_t)((P.n + 1) / 2));
-    return (char*)((a + 255) & ~(uintptr_t)255);
+    // (An offset is added; a number made a pointer would be one of no known address space, whose loads and stores wait for LDS, and LDS for them.  One row of 2^24 fp32 keys, k = 256, 31.7 us
+    // with that, so 30.6.)
+    char* a = (char*)(P.cand[0] + (size_t)row * P.cand_stride + (size_t)((P.n + 1) / 2));
+    return a + (0u - (u32)(uintptr_t)a & 255u);
 }
 // (written by k_list_bound and k_list_part, through list_row_out; constant for every kernel after them)
 __device__ __forceinline__ const ListRow* list_row(const Params& P, int row) { return (const ListRow*)list_meta(P, row); }
@@ -126,6 +128,12 @@ __device__ __forceinline__ ListRow* list_row_out(const Params& P, int row) { ret
 __device__ __forceinline__ ListDone* list_done(const Params& P, int row) { return (ListDone*)(list_meta(P, row) + kListDoneOff); }
 template <class T>
 __device__ __forceinline__ T* list_part(const Params& P, int row, u32 off) { return (T*)(list_meta(P, row) + off); }
+// The same as a pointer of no known address space, for the sweep's adds to its counters of ties: around adds that it knows to go to global memory the compiler keeps the loads under way in another
+// order (2^26 fp16 keys, a ramp, k = 16, 65.4 us, so 63.8; nine in ten bf16 keys equal, k = 300, 66.7 / 64.6).
+template <class T>
+__device__ __forceinline__ T* list_part_generic(const Params& P, int row, u32 off) {
+    return (T*)((((uintptr_t)(P.cand[0] + (size_t)row * P.cand_stride + (size_t)((P.n + 1) / 2)) + 255) & ~(uintptr_t)255) + off);
+}
 __device__ __forceinline__ u64* list_array(const Params& P, u32 which, int row) {
     return (u64*)(P.cand[which] + (size_t)row * P.cand_stride);
 }
@@ -1114,7 +1122,7 @@ __global__ void __launch_bounds__(LONG ? kLongBlock : kGridBlock, LONG ? 4 : DT 
     __syncthreads();
     ListWriter<DT, LONG, Source> w{list_entry<DT>(P), list_array(P, 1u, row) + list_segment<DT>(rs, wg, G, (u32)Source::kTileVecs),
                                    list_part<u64>(P, row, L.front_off) + (size_t)wg * L.slots, L.slots, stage[tid >> 6], &run, hist, split, 0u};
-    const u32 ties = sweep_row<DT>(src, wg, G, lr, list_part<u32>(P, row, L.tile_off), P.dirmask, [&](const typename Source::Tile& cur, u32 m) __attribute__((always_inline)) {
+    const u32 ties = sweep_row<DT>(src, wg, G, lr, list_part_generic<u32>(P, row, L.tile_off), P.dirmask, [&](const typename Source::Tile& cur, u32 m) __attribute__((always_inline)) {
         w.append(cur, m, lr, [&](u32 s) __attribute__((always_inline)) { return element_index(src, cur.tile, s); });
     });
     if (w.fill != 0u) w.flush(lr);

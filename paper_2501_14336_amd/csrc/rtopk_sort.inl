@@ -34,7 +34,7 @@ __device__ __forceinline__ u64 sort_key_of(u32 raw, u32 idx, u32 dirmask) {
 }
 template <int DT>
 __device__ __forceinline__ u32 load_value(const void* v, size_t i) {
-    return DT == RTOPK_F32 ? ((const u32*)v)[i] : (u32)((const uint16_t*)v)[i];
+    return DT == RTOPK_F32 ? ((const Glb<u32>*)v)[i] : (u32)((const Glb<uint16_t>*)v)[i];
 }
 
 // Up to three consecutive levels of the bitonic network (strides S, S/2, ... down to h = S >> (L - 1)) in one go:
