@@ -34,7 +34,7 @@ struct ListPlan {
     int G;            // workgroups per row in the sweep
     int row_block;    // one workgroup per row does everything: its threads (0: many workgroups per row)
     int held;         // ... holding the row in registers: 16-byte vectors per thread (0: the row is swept)
-    int sample;       // which size of sample: 512, 1024, 2048, 4096 or 16384 (16-bit keys: 8192) vectors of 16 bytes; k_list_stream's: 4096 and 8192 (4096)
+    int sample;       // which size of sample: 512, 1024, 2048, 4096 or 16384 (16-bit keys, and 5: 8192) vectors of 16 bytes; k_list_stream's: 4096 and 8192 (4096)
     int stream_block; // short lists of few rows: threads of k_list_stream's workgroups, which take the sample themselves (0: k_list_bound does)
     int stream;       // the input is too large for the caches to keep: read past them
     int finish;       // short lists: threads of the workgroup that puts a row's list in order

@@ -564,3 +564,21 @@ def test_crowds_of_which_little_is_wanted(dtype, n, width):
                 y = x.astype(np.float32) if largest else -x.astype(np.float32)
                 _check("%s of %d" % (name, width), y, dtype, k, largest, by_list=None)
                 _check("%s of %d" % (name, width), y, dtype, k, largest, by_list=None, sorted=False)
+
+
+@pytest.mark.parametrize("n", [(1 << 22) - 5, (1 << 22) + 4, (1 << 24) + 3])
+def test_long_lists_bounded_by_half_the_largest_sample(n):
+    # around the first row that has the largest sample at all; from k near the shortest long list's up; crowds right below what is wanted, of
+    # whose betters the sample sees none, one or a few (the bins then reach beyond the best of the sample)
+    x = W.normal(n, 3 + n % 7)
+    for k in (3000, 12000, n // 5):
+        for largest in (True, False):
+            _check("half the largest sample", x, F32, k, largest, why=0)
+    y = np.where(W.uniform01(n, 5) < 0.999, np.float32(1.0), np.float32(2.0) + W.uniform01(n, 6)).astype(np.float32)
+    for k in (9000, n // 1000 - 1500):  # (about n / 1000 are better than the crowd)
+        for sorted in (True, False):
+            _check("few above a crowd", y, F32, k, sorted=sorted, by_list=None)
+    _check("few above a crowd", -y, F32, 9000, largest=False, by_list=None)
+    z = np.linspace(1.0e6, -1.0e6, n, dtype=np.float32)
+    z[W.uniform01(n, 8) < 2.0 ** -11] = np.inf
+    _check("ramp", z, F32, 12000, by_list=None)
