@@ -225,6 +225,9 @@ __device__ __forceinline__ u64 wave_reduce64(u64 v, Op&& op) {
     v = op(v, lane_move64<0x142, 0xa>(v));
     return op(v, lane_move64<0x143, 0xc>(v));
 }
+__device__ __forceinline__ u64 last_lane64(u64 v) {
+    return ((u64)(u32)__builtin_amdgcn_readlane((int)(u32)(v >> 32), 63) << 32) | (u32)__builtin_amdgcn_readlane((int)(u32)v, 63);
+}
 struct MaxOf { template <class T> __device__ __forceinline__ T operator()(T a, T b) const { return a > b ? a : b; } };
 struct MinOf { template <class T> __device__ __forceinline__ T operator()(T a, T b) const { return a < b ? a : b; } };
 
@@ -1372,12 +1375,18 @@ __device__ __forceinline__ void order_range(u64& mn, u64& mx, OrderShared<B>& sm
     mx = wave_reduce64(mx, MaxOf());
     if (lane == 63u) { sm.red[2 * wave] = mn; sm.red[2 * wave + 1] = mx; }
     __syncthreads();
-    mn = sm.red[0];
-    mx = sm.red[1];
+    if constexpr (B > 512) {  // (see sum_of_waves; eight waves' are read as quickly one by one)
+        const u32 w = lane % (u32)(B / 64);
+        mn = last_lane64(wave_reduce64(sm.red[2 * w], MinOf()));
+        mx = last_lane64(wave_reduce64(sm.red[2 * w + 1], MaxOf()));
+    } else {
+        mn = sm.red[0];
+        mx = sm.red[1];
 #pragma unroll
-    for (int w = 1; w < B / 64; ++w) {
-        mn = mn < sm.red[2 * w] ? mn : sm.red[2 * w];
-        mx = mx > sm.red[2 * w + 1] ? mx : sm.red[2 * w + 1];
+        for (int w = 1; w < B / 64; ++w) {
+            mn = mn < sm.red[2 * w] ? mn : sm.red[2 * w];
+            mx = mx > sm.red[2 * w + 1] ? mx : sm.red[2 * w + 1];
+        }
     }
 }
 template <int B>
@@ -1444,7 +1453,11 @@ __device__ __forceinline__ void order_output(const Params& P, int row, const Row
 // CUT: if a bin is crowded and the bins up to the one that rank k lies in have half the entries at most, those are put in order by themselves: their bins, divided
 // again, are even as a rule (16-bit keys that rise along the row: some hundred neighbours to a value).  For k_list_finish, one row of 2^21 fp16 keys, a ramp, 4438 entries:
 // k = 16, between splitters 52.2 us, so 42.5; k = 1, 48.0 / 38.9.
-template <int DT, int B, bool CUT = false, class Load>
+// PART: where no more than half of the entries lie in the bins that matter, those are spread over the threads anew once they are in place, one or two to a thread instead of a few in each of
+// up to eight rounds that most waves have to go through; and who is alone in its bin has nothing to read.  One row of 2^24 fp32 keys, 6500 entries, k = 256, 32.0 us, so 30.3; of 2^20,
+// k = 3000, 24.0 / 21.5.  171 rows of 223482 fp16 keys, k = 512, 37.8 / 35.8.  Where few waves order short lists it adds 0.1 us (300 rows of
+// 30011 fp16 keys, k = 100, 15.25 / 15.4), and to 1024 rows of 2^17 bf16 keys, k = 1024, of which nearly all is wanted, 0.3.
+template <int DT, int B, bool CUT = false, bool PART = CUT || B >= 512, class Load>
 __device__ __forceinline__ void order_in_lds(const Params& P, int row, const RowShape& rs, OrderShared<B>& sm, u32 C, u32 rank0,
                                              Load&& load) {
     u32 tid = threadIdx.x;
@@ -1479,16 +1492,17 @@ __device__ __forceinline__ void order_in_lds(const Params& P, int row, const Row
     const u32 per = (C + (u32)B - 1u) / (u32)B;  // entries per thread
     order_scan<B>(sm.hist + 1, want, per < 4u ? kOrderCrowd / per : kOrderCrowd / 4u, sorted, sm);
     // entry j's rank, if it is wanted, among the entries of its bin, which are buf[from .. to); then every one to its place
+    u32 left = C;  // (this many entries are spread over the threads)
     auto rank_and_place = [&](auto&& from, auto&& to) __attribute__((always_inline)) {
         u32 rank[4];  // two to a word
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             u32 r = 0xffffu;
-            if ((u32)j * B < C && e[j] != ~0ull) {
+            if ((u32)j * B < left && e[j] != ~0ull) {
                 const u32 s0 = from(j), s1 = to(j);
                 r = s0;
 #pragma unroll 1
-                for (u32 i = s0; i < s1; i += 4u) {
+                for (u32 i = PART && s1 - s0 == 1u ? s1 : s0; i < s1; i += 4u) {  // (alone in its bin: nothing to read)
                     u64 b[4];
 #pragma unroll
                     for (u32 x = 0; x < 4u; ++x) b[x] = sm.buf[i + x];
@@ -1516,6 +1530,19 @@ __device__ __forceinline__ void order_in_lds(const Params& P, int row, const Row
             if (!is || (!sorted && bin < last)) e[j] = ~0ull;  // (not an entry: those have at most 63 bits; nothing left to do with it)
         }
         __syncthreads();
+        const u32 end = sm.hist[last + 1u];
+        if (PART && per > 1u && end * 2u <= C) {
+            const u32 first = sorted ? 0u : sm.hist[last];
+            left = end;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                e[j] = ~0ull;
+                if ((u32)j * B < end) {
+                    const u32 i = tid + (u32)j * B;
+                    if (i >= first && i < end) e[j] = sm.buf[i];
+                }
+            }
+        }
         rank_and_place([&](int j) { return sm.hist[(u32)((mx - e[j]) >> sh)]; }, [&](int j) { return sm.hist[(u32)((mx - e[j]) >> sh) + 1u]; });
         __syncthreads();
         order_output<DT, B>(P, row, rs, sm, want, rank0, ent);
@@ -2192,7 +2219,7 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
         u32 n = total;
         // (A list that LDS does not hold, though not much longer than expected, is cut down first.  Not every one that is much longer than what is wanted of it: 5800 entries, k = 256, 12.0 / 15.8 us.)
         if (few && (B <= 256 || total > 4096u) && total <= 8u * B) {
-            order_in_lds<DT, B>(P, row, rs, sm, total, 0u, entry);
+            order_in_lds<DT, B, false, true>(P, row, rs, sm, total, 0u, entry);
             return;
         }
         if (over || total > 8u * B) find_places();
@@ -2656,7 +2683,7 @@ __global__ void __launch_bounds__(B, B == 512 ? 6 : 4) k_list_row(Params P, List
         if (tid >= (u32)OB) return;  // (a barrier waits for the waves that are left)
         order_in_lds<DT, OB>(P, row, rs, sm.few, total, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.few.buf[i]; });
     } else if (total != 0u) {
-        order_in_lds<DT, B>(P, row, rs, sm.ord, total, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.ord.buf[i]; });
+        order_in_lds<DT, B, false, (B > 512)>(P, row, rs, sm.ord, total, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.ord.buf[i]; });
     }
     if (b.mode == kListTied && total < rs.k) {
         __syncthreads();

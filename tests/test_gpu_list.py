@@ -582,3 +582,15 @@ def test_long_lists_bounded_by_half_the_largest_sample(n):
     z = np.linspace(1.0e6, -1.0e6, n, dtype=np.float32)
     z[W.uniform01(n, 8) < 2.0 ** -11] = np.inf
     _check("ramp", z, F32, 12000, by_list=None)
+
+
+@pytest.mark.parametrize("dtype", [F32, F16])
+def test_lists_of_which_half_or_less_is_wanted(dtype):
+    # by 256, 512 and 1024 threads, in one round, a few and all eight, either side of half; alone in a bin, two and many to one
+    for n, batch in ((1 << 21, 1), (1 << 20, 2), (300000, 58), (259335, 4)):
+        x = W.normal(n * batch, n % 11, sigma=2.0)
+        y = (np.round(x * 256.0) / 256.0).astype(np.float32)
+        for k in (1, 40, 300, 1100, 2200, 3300):
+            for sorted in (True, False):
+                _check("normal", x, dtype, k, sorted=sorted, batch=batch, by_list=None)
+        _check("many equal", y, dtype, 900, largest=False, batch=batch, by_list=None)
