@@ -382,7 +382,7 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     L->front_off = take((u64)G * L->slots * 8);
     L->seg_off = take((u64)G * 8);
     L->hist_off = take(is_long ? kMaxBins * 4 : 0);
-    L->cursor_off = take((u64)(L->nb + 1) * 4);
+    L->cursor_off = take(is_long ? (((u64)L->nb + 1 + 31) & ~(u64)31) * 8 : 4);
     L->first_off = take((u64)L->nb * 8);
     L->split_off = take(is_long ? (kListSplits + 1) * 8 : 0);
     L->tile_off = take((u64)(stream ? wave_tiles + 2 : (n + E - 1) / (kHostGridBlock * 64 / eb) + 2) * 4);  // (the smallest tiles' number)

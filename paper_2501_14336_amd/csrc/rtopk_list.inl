@@ -69,6 +69,8 @@ struct ListDone {
     u32 drop;      // the list was no use, the buckets are not filled: why (rtopk_row_trace::redo_why)
     u32 big;       // ... 1: a bucket has more than one workgroup puts in order
 };
+// A bucket's places are taken from its beginning by every other workgroup, and from its end by the rest: two counters each, not of the same cache line.  (k_list_emit counts two things in one.)
+__host__ __device__ constexpr u32 list_cursors(u32 nb) { return (nb + 1u + 31u) & ~31u; }
 constexpr u32 kListDoneOff = 128;
 static_assert(sizeof(ListRow) <= kListDoneOff && kListDoneOff + sizeof(ListDone) <= kListMetaBytes, "both lie before the plan's first offset");
 // Bits of rtopk_row_trace::redo: the list was no use; it was too long to put in order in LDS; so were some of its buckets.
@@ -523,7 +525,7 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
         u32* gh = list_part<u32>(P, row, L.hist_off);
         for (u32 j = tid; j < kListBins; j += B) gh[j] = 0u;
         u32* cur = list_part<u32>(P, row, L.cursor_off);
-        for (u32 j = tid; j < L.nb + 1u; j += B) cur[j] = 0;  // (k_list_emit counts two things)
+        for (u32 j = tid; j < 2u * list_cursors(L.nb); j += B) cur[j] = 0;
     }
     if (whole && !(bins && sampled)) {
         if (tid == 0) {
@@ -2711,7 +2713,11 @@ __device__ __forceinline__ void add_ties(u32 mode, u32 mine, u32* sum) {
 // bins whose ranks share rank >> L.bucket_shift, its place in the array its first bin's rank.  A bin that ends beyond the ranks of the next bucket, which is
 // then left without any, is that one alone: else its bucket, with what begins before it, would be longer than one workgroup puts in order.  Bins that begin at rank k or
 // beyond are dropped.  One atomic per bucket reserves all of a workgroup's places in it; what the registers do not hold
-// of a segment is read twice.
+// of a segment is read twice.  Those atomics are waited for, and the ones to one counter are made one after the other, 11 ns each: of a single row's, every other workgroup takes its
+// places from the bucket's end, with a counter of its own.  A single row has one more workgroup, without a segment, which writes down where the buckets begin while the others move
+// theirs (each bucket's size from its last bin: searched for, the next bucket that has any bins is far where there are few).  Several rows' would share compute units with others: eight rows of
+// 2^19 fp32 keys, k = 52428, 42.0 us, with them 42.4 to 43.4.  us, one counter and workgroup 0 with records and search / so: one fp32 row of 2^28
+// keys, k = 2^20, 218 / 216; of 2^22 + 3 fp16 keys, k = 2^20, 59.2 / 58.2; nine in ten equal, 8.3 million fp16 keys, k = n / 8, 120 / 85, 2^26 fp32 keys, k = 2^16, 86.0 / 84.5.
 template <int DT>
 __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan L) {
     constexpr int B = kLongBlock, kPer = kListBins / B;
@@ -2721,8 +2727,10 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     __shared__ u32 wsum[B / 64];
     __shared__ u32 s_end, s_total, s_equal, s_big;
     const u32 G = (u32)L.G, tid = threadIdx.x;
-    const int row = (int)(blockIdx.x / G);
-    const u32 wg = blockIdx.x % G;
+    const bool alone = P.batch == 1;  // (of several rows: workgroup 0)
+    const int row = alone ? 0 : (int)(blockIdx.x / G);
+    const u32 wg = alone ? blockIdx.x : blockIdx.x % G;
+    const bool records = wg == (alone ? G : 0u);
     const ListRow* lr = list_row(P, row);
     const u32 mode = lr->mode;
     if (mode == kListSkip) return;
@@ -2733,7 +2741,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     if (by_split != 0u && tid <= kListSplits) split[tid] = list_part<u64>(P, row, L.split_off)[tid];
     const u64* from = list_array(P, 1u, row) + list_segment<DT>(rs, wg, G, (u32)ListSource<DT, true>::kTileVecs);
     const uint2* segs = list_part<uint2>(P, row, L.seg_off);
-    const u32 mine = segs[wg].x;
+    const u32 mine = wg == G ? 0u : segs[wg].x;
     const u32 equal = mode == kListTied && tid < G ? segs[tid].y : 0u;  // (G is at most 256)
     constexpr int kHeld = 8;
     u64 held[kHeld];
@@ -2763,12 +2771,19 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
         if (tid == B - 1) s_total = r;
     }
     add_ties(mode, equal, &s_equal);
-    // f(bucket, rank) for this thread's bins that begin one
+    // f(bucket, rank) for this thread's bins that begin one, or end one
     auto first_bins = [&](auto&& f) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
             const u32 q = tid * kPer + i, b = bucket[kListBins - 1u - q];
             if (b != 0xffffffffu && (q == 0u || b != bucket[kListBins - q])) f(b, rank[i]);
+        }
+    };
+    auto last_bins = [&](auto&& f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const u32 q = tid * kPer + i, b = bucket[kListBins - 1u - q];
+            if (b != 0xffffffffu && (q == kListBins - 1u || b != bucket[kListBins - 2u - q])) f(b, rank[i] + c[i]);
         }
     };
     __syncthreads();
@@ -2778,10 +2793,10 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     const bool few_in_all = few && (u64)total + s_equal < (u64)rs.k;
     const bool drop = few_in_all || end > (u32)((P.n + 1) / 2);  // (the buckets have half a candidate array)
     if (drop) {
-        if (wg == 0 && tid == 0) *list_done(P, row) = ListDone{total, end, few_in_all ? 8u : 5u, 0u};
+        if (records && tid == 0) *list_done(P, row) = ListDone{total, end, few_in_all ? 8u : 5u, 0u};
         return;
     }
-    if (wg == 0) {
+    if (records) {
         if (tid == 0) list_record(st, rs, total, 5u);
         // the buckets' first ranks and sizes
         u32* first = list_part<u32>(P, row, L.first_off);
@@ -2789,16 +2804,15 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
         __syncthreads();
         first_bins([&](u32 b, u32 r) __attribute__((always_inline)) { place[b] = r; });
         __syncthreads();
-        for (u32 j = tid; j < nb; j += B) {
-            u32 i = j + 1u;
-            while (i < nb && place[i] == 0xffffffffu) ++i;
-            const u32 size = (i < nb ? place[i] : end) - place[j];
-            first[2u * j] = place[j];
-            first[2u * j + 1u] = size;
-            if (place[j] != 0xffffffffu && size > kBucketRoom) s_big = 1u;
-        }
+        last_bins([&](u32 b, u32 r) __attribute__((always_inline)) {
+            const u32 size = r - place[b];
+            first[2u * b + 1u] = size;
+            if (size > kBucketRoom) s_big = 1u;
+        });
+        for (u32 j = tid; j < nb; j += B) first[2u * j] = place[j];  // (~0: no bin begins it, and it has no size)
         __syncthreads();
         if (tid == 0) *list_done(P, row) = ListDone{total, end, 0u, s_big};
+        if (alone) return;
         for (u32 j = tid; j < nb; j += B) place[j] = 0;
         __syncthreads();
     }
@@ -2816,14 +2830,19 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
         if (b != 0xffffffffu) atomicAdd(&place[b], 1u);
     }
     __syncthreads();
-    u32* cursor = list_part<u32>(P, row, L.cursor_off);
-    // a bucket's own beginning is added by the bin that begins it
+    const u32 back = alone ? wg & 1u : 0u;  // (several rows' have few workgroups each)
+    u32* cursor = list_part<u32>(P, row, L.cursor_off) + back * list_cursors(nb);
+    // a bucket's own beginning is added by the bin that begins it, its end by the one that ends it
     for (u32 j = tid; j < nb; j += B) {
         const u32 n = place[j];
-        if (n != 0) place[j] = atomicAdd(&cursor[j], n);
+        if (n != 0) {
+            const u32 before = atomicAdd(&cursor[j], n);
+            place[j] = back != 0u ? 0u - before - n : before;
+        }
     }
     __syncthreads();
-    first_bins([&](u32 b, u32 r) __attribute__((always_inline)) { place[b] += r; });
+    if (back != 0u) last_bins([&](u32 b, u32 r) __attribute__((always_inline)) { place[b] += r; });
+    else first_bins([&](u32 b, u32 r) __attribute__((always_inline)) { place[b] += r; });
     __syncthreads();
     u64* dst = list_array(P, 0u, row);
 #pragma unroll
@@ -3092,7 +3111,7 @@ static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStrea
     }
     mark(events, 3, st);
     if (is_long) {
-        if (P.flags & RTOPK_FLAG_SORTED) hipLaunchKernelGGL((k_list_scatter<DT>), grid, block, 0, st, P, L);
+        if (P.flags & RTOPK_FLAG_SORTED) hipLaunchKernelGGL((k_list_scatter<DT>), dim3(P.batch == 1 ? (unsigned)L.G + 1u : (unsigned)P.batch * (unsigned)L.G), block, 0, st, P, L);
         else hipLaunchKernelGGL((k_list_emit<DT>), grid, block, 0, st, P, L);
         hipLaunchKernelGGL((k_list_buckets<DT>), dim3((unsigned)P.batch * (L.nb + (unsigned)L.ties)), dim3(kListBucketBlock), 0, st, P, L);
     } else {

@@ -594,3 +594,16 @@ def test_lists_of_which_half_or_less_is_wanted(dtype):
             for sorted in (True, False):
                 _check("normal", x, dtype, k, sorted=sorted, batch=batch, by_list=None)
         _check("many equal", y, dtype, 900, largest=False, batch=batch, by_list=None)
+
+
+@pytest.mark.parametrize("n,k", [(1 << 18, 50000), ((1 << 20) + 1, 20000), ((1 << 22) + 7, 1 << 20)])
+def test_buckets_are_filled_from_both_ends(n, k):
+    # buckets of a few workgroups and of many; empty ones between crowds; and the last one, of which a part is wanted
+    x = W.normal(n, k % 5)
+    y = (np.round(x * 8.0) / 8.0).astype(np.float32)
+    z = np.where(W.uniform01(n, 2) < 0.9, np.float32(0.999), x).astype(np.float32)
+    for dtype in (F32, F16):
+        for largest in (True, False):
+            _check("normal", x, dtype, k, largest)
+            _check("crowds", y, dtype, k, largest, by_list=None)
+            _check("nine in ten equal", z, dtype, k, largest, by_list=None)
