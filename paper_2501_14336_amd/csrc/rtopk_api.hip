@@ -341,7 +341,13 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     // us, 1024 (16-bit keys: 768) / 512 / 256 to a row: one fp32 row of 2^25, k = 16 and 300, 51.5 / 50.1 / 49.5 and 50.9 / 50.7 / 50.6, of 3 * 2^24, k = 16, 59.1 / 58.0 /
     // 56.4; one of 2^25 fp16 keys, k = 100, 41.1 / 38.5 / 37.9, nine in ten equal 42.5 / 43.6 / 48.1; of 14 million, nine in ten equal, 34.6 / 34.9 / 38.4;
     // of 2^24 bf16 keys, a ramp, k = 100, 55.4 / 56.7 / 58.4; of 2^26, k = 300, nine in ten equal, 62.7 / 64.7 / 64.2.
-    const int64_t tile_elems = (int64_t)(is_long ? 1024 : kHostGridBlock) * 64 / eb;
+    // A single row of up to 8.5 MB has no more than 136 tiles of 64 KB for 256 compute units: a long list's sweep takes half as large ones there, and the histograms of then up to 256 workgroups,
+    // which all end together, are added up in four copies (an add to a line of counters takes 11 ns).  us, tiles of 64 KB / of 32, one histogram / so: 2^22 + 3 fp16 keys, k = 2^20,
+    // 58.3 / 55.9 / 54.1; 2^21 fp32 keys, k = 20000 31.9 / 34.1 / 32.2, k = n / 5 41.2 / 42.3 / 40.2; 2^18 fp32 keys, k = n / 5 36.1 / 33.5 / 34.0; ramps, whose list lies in a few tiles, 2^21, k =
+    // 20000, 110 / 80, 2^20 fp16 keys 117 / 94.  Nine in ten equal 2^20 fp32 keys, k = 10000 and n / 4, 34.0 / 35.8 and 57.6 / 59.5.  Above that, where some workgroups have two
+    // tiles and others one: 10 MB of bf16 keys, nine in ten equal, 49.2 / 53.0.
+    L->half = is_long && batch == 1 && n * eb <= ((int64_t)17 << 19) ? 1 : 0;
+    const int64_t tile_elems = (int64_t)(is_long && L->half == 0 ? 1024 : kHostGridBlock) * 64 / eb;
     const int64_t ntiles = (n + E - 1 + tile_elems - 1) / tile_elems;
     const int64_t wave_tiles = (n + E - 1 + 256 * E - 1) / (256 * E);  // (k_list_stream's)
     int64_t G = (stream || is_long ? 256 : eb == 4 ? 1024 : 768) / batch;
@@ -381,7 +387,8 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     auto take = [&](u64 bytes) { const u64 at = off; off = align_up(off + bytes, 128); return (u32)at; };
     L->front_off = take((u64)G * L->slots * 8);
     L->seg_off = take((u64)G * 8);
-    L->hist_off = take(is_long ? kMaxBins * 4 : 0);
+    L->hists = L->half != 0 && G > 64 ? 4u : 1u;
+    L->hist_off = take(is_long ? (u64)L->hists * kMaxBins * 4 : 0);
     L->cursor_off = take(is_long ? (((u64)L->nb + 1 + 31) & ~(u64)31) * 8 : 4);
     L->first_off = take((u64)L->nb * 8);
     L->split_off = take(is_long ? (kListSplits + 1) * 8 : 0);

@@ -41,6 +41,8 @@ struct ListPlan {
     int ties;         // workgroups per row that fetch elements equal to the bound, where those are very many
     u32 seg_stride;   // the row's stretches are held by G workgroups that list at most this many each (0: the row is swept)
     u32 nb;           // long lists: buckets per row (0: short lists)
+    int half;         // ... the sweep's tiles are of 32 KB, not of 64
+    u32 hists;        // ... copies of the list's histogram
     u32 bucket_shift; // ... of 2^bucket_shift ranks
     u32 slots;        // short lists: a power of two: so many entries of each segment lie together at front_off
     u32 room, most;   // ... so many in all are put in order in LDS (and twice as many cut down to that first); the record says so from `most` on

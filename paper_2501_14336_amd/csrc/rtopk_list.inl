@@ -45,8 +45,10 @@ constexpr u32 kListTies = 16384;                // equal elements from which on 
 // How a sweep deals a row: tiles of four 16-byte vectors per thread (16 elements, or 32 of 16 bits).
 constexpr int kLongBlock = 1024;                // threads per workgroup of a long list's sweep (one workgroup per compute unit)
 constexpr int kSharedBlock = 512;               // ... of the sweep of few rows
-template <int DT, bool LONG, bool NT = false>
-using ListSource = KeySource<DT, LONG ? kLongBlock : kGridBlock, 4, NT>;
+template <int DT, bool LONG, bool NT = false, int V = 4>
+using ListSource = KeySource<DT, LONG ? kLongBlock : kGridBlock, V, NT>;
+// Vectors of a tile of a long list's sweep.
+__device__ __forceinline__ u32 long_unit(const ListPlan& L) { return L.half != 0 ? (u32)kLongBlock * 2u : (u32)kLongBlock * 4u; }
 
 enum : u32 { kListSkip = 0, kListPlain = 1, kListTied = 2 };
 
@@ -522,8 +524,8 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
             for (u32 j = tid; j < kListBins; j += B) sl->bin[j] = 0;
     }
     if (bins) {  // its histogram and the buckets' write positions
-        u32* gh = list_part<u32>(P, row, L.hist_off);
-        for (u32 j = tid; j < kListBins; j += B) gh[j] = 0u;
+        uint4* gh = list_part<uint4>(P, row, L.hist_off);
+        for (u32 j = tid; j < L.hists * (kListBins / 4u); j += B) gh[j] = make_uint4(0, 0, 0, 0);
         u32* cur = list_part<u32>(P, row, L.cursor_off);
         for (u32 j = tid; j < 2u * list_cursors(L.nb); j += B) cur[j] = 0;
     }
@@ -954,9 +956,15 @@ __device__ __forceinline__ u32 pick(const typename Source::Tile& t, u32 s) {
         const u32 lo = (w & 1u) ? q.y : q.x, hi = (w & 1u) ? q.w : q.z;
         return (w & 2u) ? hi : lo;
     };
-    const u32 c0 = of4(t.r[0]), c1 = of4(t.r[1]), c2 = of4(t.r[2]), c3 = of4(t.r[3]);
-    const u32 d0 = (w & 4u) ? c1 : c0, d1 = (w & 4u) ? c3 : c2;
-    const u32 x = (w & 8u) ? d1 : d0;
+    u32 x;
+    if constexpr (Source::kSlots / Source::E == 4) {
+        const u32 c0 = of4(t.r[0]), c1 = of4(t.r[1]), c2 = of4(t.r[2]), c3 = of4(t.r[3]);
+        const u32 d0 = (w & 4u) ? c1 : c0, d1 = (w & 4u) ? c3 : c2;
+        x = (w & 8u) ? d1 : d0;
+    } else {
+        const u32 c0 = of4(t.r[0]), c1 = of4(t.r[1]);
+        x = (w & 4u) ? c1 : c0;
+    }
     if constexpr (Source::E == 4) return x;
     else return (s & 1u) ? x >> 16 : x & 0xffffu;
 }
@@ -1106,14 +1114,14 @@ struct ListWriter {
 // NT: the input is far larger than the last-level cache.  LONG: the list's histogram is counted as it is written; then one
 // workgroup of 1024 threads has a compute unit, so that there are no more than 256 histograms to add up (512
 // workgroups of 512: adding up took longer than it saved).
-template <int DT, bool NT, bool LONG>
+template <int DT, bool NT, bool LONG, int V = 4>
 __global__ void __launch_bounds__(LONG ? kLongBlock : kGridBlock, LONG ? 4 : DT == RTOPK_F32 ? 8 : 6) k_list_sweep(Params P, ListPlan L) {
     constexpr int B = LONG ? kLongBlock : kGridBlock;
     __shared__ uint2 stage[B / 64][LONG ? kListStageLong : kListStage];
     __shared__ u32 hist[LONG ? kListBins : 1];
     __shared__ u64 split[LONG ? kListSplits + 1 : 1];
     __shared__ u32 run, all_ties;
-    typedef ListSource<DT, LONG, NT> Source;
+    typedef ListSource<DT, LONG, NT, V> Source;
     const u32 G = (u32)L.G;
     const int row = (int)(blockIdx.x / G);
     const u32 wg = blockIdx.x % G;
@@ -1139,7 +1147,7 @@ __global__ void __launch_bounds__(LONG ? kLongBlock : kGridBlock, LONG ? 4 : DT 
     __syncthreads();
     if (tid == 0) list_part<uint2>(P, row, L.seg_off)[wg] = make_uint2(run, all_ties);
     if (LONG) {
-        u32* gh = list_part<u32>(P, row, L.hist_off);
+        u32* gh = list_part<u32>(P, row, L.hist_off) + (wg & (L.hists - 1u)) * kListBins;
         for (u32 j = tid; j < kListBins; j += B) {
             const u32 c = hist[j];
             if (c) atomicAdd(&gh[j], c);
@@ -2709,6 +2717,21 @@ __device__ __forceinline__ void add_ties(u32 mode, u32 mine, u32* sum) {
     if (lane_id() == 63u && mine != 0u) atomicAdd(sum, mine);
 }
 
+// Thread t's bins of a list's histogram, the 4 t-th best and the three below it, added up over its copies.
+__device__ __forceinline__ void list_counts(const Params& P, const ListPlan& L, int row, u32 (&c)[4]) {
+    static_assert(kListBins == 4 * kLongBlock, "four to a thread");
+    const uint4* gh = list_part<uint4>(P, row, L.hist_off) + (kListBins / 4u - 1u - threadIdx.x);
+    uint4 a = gh[0];
+    if (L.hists == 4u) {
+        const uint4 x = gh[kListBins / 4u], y = gh[2u * (kListBins / 4u)], z = gh[3u * (kListBins / 4u)];
+        a = make_uint4(a.x + x.x + y.x + z.x, a.y + x.y + y.y + z.y, a.z + x.z + y.z + z.z, a.w + x.w + y.w + z.w);
+    }
+    c[0] = a.w;
+    c[1] = a.z;
+    c[2] = a.y;
+    c[3] = a.x;
+}
+
 // Workgroup w moves segment w into buckets.  A bin's rank is the number of entries in better bins; a bucket is the run of
 // bins whose ranks share rank >> L.bucket_shift, its place in the array its first bin's rank.  A bin that ends beyond the ranks of the next bucket, which is
 // then left without any, is that one alone: else its bucket, with what begins before it, would be longer than one workgroup puts in order.  Bins that begin at rank k or
@@ -2739,7 +2762,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     const u64 lo = lr->lo;
     const u32 sh = lr->sh, by_split = __builtin_amdgcn_readfirstlane(lr->split);
     if (by_split != 0u && tid <= kListSplits) split[tid] = list_part<u64>(P, row, L.split_off)[tid];
-    const u64* from = list_array(P, 1u, row) + list_segment<DT>(rs, wg, G, (u32)ListSource<DT, true>::kTileVecs);
+    const u64* from = list_array(P, 1u, row) + list_segment<DT>(rs, wg, G, long_unit(L));
     const uint2* segs = list_part<uint2>(P, row, L.seg_off);
     const u32 mine = wg == G ? 0u : segs[wg].x;
     const u32 equal = mode == kListTied && tid < G ? segs[tid].y : 0u;  // (G is at most 256)
@@ -2747,14 +2770,15 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     u64 held[kHeld];
 #pragma unroll
     for (int i = 0; i < kHeld; ++i) held[i] = tid + (u32)i * B < mine ? from[tid + (u32)i * B] : 0ull;
-    const u32* gh = list_part<u32>(P, row, L.hist_off);
     const u32 bs = L.bucket_shift, nb = L.nb;
     u32 c[kPer], s = 0, rank[kPer];
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-        c[i] = gh[kListBins - 1u - (tid * kPer + i)];  // from the best bin down
-        s += c[i];
+        c[i] = 0;
     }
+    list_counts(P, L, row, c);
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) s += c[i];
     for (u32 j = tid; j < nb; j += B) place[j] = 0;
     if (tid == 0) s_end = s_equal = s_big = 0;
     const u32 incl = block_scan<B>(s, wsum);
@@ -2875,20 +2899,21 @@ __global__ void __launch_bounds__(kLongBlock) k_list_emit(Params P, ListPlan L) 
     const u64 lo = lr->lo;
     const u32 sh = lr->sh, by_split = __builtin_amdgcn_readfirstlane(lr->split);
     if (by_split != 0u && tid <= kListSplits) split[tid] = list_part<u64>(P, row, L.split_off)[tid];
-    const u64* from = list_array(P, 1u, row) + list_segment<DT>(rs, wg, G, (u32)ListSource<DT, true>::kTileVecs);
+    const u64* from = list_array(P, 1u, row) + list_segment<DT>(rs, wg, G, long_unit(L));
     const uint2* segs = list_part<uint2>(P, row, L.seg_off);
     const u32 mine = segs[wg].x;
     const u32 equal = mode == kListTied && tid < G ? segs[tid].y : 0u;  // (G is at most 256)
     u64 held[kHeld];
 #pragma unroll
     for (int i = 0; i < kHeld; ++i) held[i] = tid + (u32)i * B < mine ? from[tid + (u32)i * B] : 0ull;
-    const u32* gh = list_part<u32>(P, row, L.hist_off);
     u32 c[kPer], s = 0;
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-        c[i] = gh[kListBins - 1u - (tid * kPer + i)];  // from the best bin down
-        s += c[i];
+        c[i] = 0;
     }
+    list_counts(P, L, row, c);
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) s += c[i];
     if (tid == 0) {
         s_bin = 0xffffffffu;
         s_equal = 0;
@@ -3006,9 +3031,14 @@ __global__ void __launch_bounds__(kListBucketBlock, 6) k_list_buckets(Params P, 
     u32 at = 0, count = 0;
     const u64* list = list_array(P, 0u, row);
     if (j >= L.nb) {
+        const TileCounts tiles{list_part<u32>(P, row, L.tile_off)};
+        const u32 halves = (u32)((src_vectors<DT>(rs) + 2u * kLongBlock - 1u) / (2u * kLongBlock));
+        auto ties = [&](u32 i) __attribute__((always_inline)) {
+            if (L.half == 0) return tiles(i);
+            return tiles(2u * i) + (2u * i + 1u < halves ? tiles(2u * i + 1u) : 0u);
+        };
         if (mode == kListTied && done.total < rs.k &&
-            !ties_of_row<DT, B, ListSource<DT, true>>(P, TileCounts{list_part<u32>(P, row, L.tile_off)}, row, rs, done.total, lr->T, j - L.nb,
-                                                      (u32)L.ties, sm.hist, sm.wsum) && j == L.nb && tid == 0)
+            !ties_of_row<DT, B, ListSource<DT, true>>(P, ties, row, rs, done.total, lr->T, j - L.nb, (u32)L.ties, sm.hist, sm.wsum) && j == L.nb && tid == 0)
             st->error |= 4u;  // never expected: there are enough of them
     } else if (bucket_range(P, L, row, rs, j, &at, &count) && count <= kBucketRoom) {
         const u64* src = list + at;
@@ -3106,7 +3136,8 @@ static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStrea
         else hipLaunchKernelGGL((k_list_bound<DT, 1024, 8>), rows, dim3(1024), 0, st, P, L);
         mark(events, 2, st);
         auto sweep = [&](auto nt_, auto long_) { hipLaunchKernelGGL((k_list_sweep<DT, decltype(nt_)::value, decltype(long_)::value>), grid, block, 0, st, P, L); };
-        if (nt) is_long ? sweep(std::true_type{}, std::true_type{}) : sweep(std::true_type{}, std::false_type{});
+        if (L.half != 0) hipLaunchKernelGGL((k_list_sweep<DT, false, true, 2>), grid, block, 0, st, P, L);
+        else if (nt) is_long ? sweep(std::true_type{}, std::true_type{}) : sweep(std::true_type{}, std::false_type{});
         else is_long ? sweep(std::false_type{}, std::true_type{}) : sweep(std::false_type{}, std::false_type{});
     }
     mark(events, 3, st);

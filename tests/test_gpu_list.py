@@ -607,3 +607,18 @@ def test_buckets_are_filled_from_both_ends(n, k):
             _check("normal", x, dtype, k, largest)
             _check("crowds", y, dtype, k, largest, by_list=None)
             _check("nine in ten equal", z, dtype, k, largest, by_list=None)
+
+
+@pytest.mark.parametrize("dtype,n", [(F32, 40001), (F32, (1 << 19) + 3), (F32, (17 << 17) + 1), (F32, 17 << 17), (F16, (1 << 22) + 3), (BF16, 17 << 18)])
+def test_long_lists_of_half_tiles(dtype, n):
+    # up to 8.5 MB of a single row, whole and broken last tiles; odd and even numbers of halves for the ties
+    x = W.normal(n, n % 13)
+    y = np.where(W.uniform01(n, 3) < 0.9, np.float32(0.999), W.uniform01(n, 4)).astype(np.float32)
+    z = np.linspace(5.0e4, -5.0e4, n, dtype=np.float32)
+    z[W.uniform01(n, 5) < 2.0 ** -11] = np.inf
+    for k in (8200, n // 5, n // 4 + 1):
+        for largest in (True, False):
+            _check("normal", x, dtype, k, largest, by_list=None)
+            _check("nine in ten equal", y, dtype, k, largest, by_list=None)
+            _check("ramp", z, dtype, k, largest, by_list=None)
+    _check("two rows", np.concatenate([x, y]), dtype, n // 5, batch=2, by_list=None)
