@@ -2335,9 +2335,18 @@ struct HeldShared {
     union { OrderShared<B> ord; OrderShared<OB> few; RankShared rank; };  // (both lists at the same place)
     u32 part[2 * (B / 64)], run;
 };
+// The entry that hold_and_list left at place i of the list.  Where it left places in the row (*places), the elements are fetched from the caches here, all at once (to select one of 64
+// registers by a number takes longer).  Fetched by the lane that noted them, one after the other, two or three trips: us, then / so, one fp32 row of 2^16, k = 32, 11.95 / 11.75, 16 rows of 2^17 bf16
+// keys, k = 50, 14.2 / 14.0, 300 of 30011 fp16 keys, k = 100, 15.25 / 14.9, 512 of 2^14 bf16 keys, k = 628, 20.65 / 19.95.
+template <int DT>
+__device__ __forceinline__ u64 held_entry(const Params& P, const RowShape& rs, const u64* buf, u32 i, bool places) {
+    const u64 v = buf[i];
+    if (!places) return v;
+    return list_entry<DT>(P).of(KeyOf<DT>::key(load_value<DT>(rs.x, (u32)v)) ^ P.dirmask, (u32)v);
+}
 template <int DT, int B, int NV, class AfterLoad>
 __device__ __forceinline__ u32 hold_and_list(const Params& P, const RowShape& rs, u32 p0, bool last, u32 limit, HeldShared<B>& sm,
-                                             AfterLoad&& after_load) {
+                                             bool* places, AfterLoad&& after_load) {
     constexpr int kGroups = NV / 4;  // the stretch as tiles of four vectors per lane
     typedef KeySource<DT, B, 4, false> Source;
     constexpr u32 E = Source::E;
@@ -2364,9 +2373,6 @@ __device__ __forceinline__ u32 hold_and_list(const Params& P, const RowShape& rs
     const u32 before = src.lead != 0u ? (E - src.lead < rs.n ? E - src.lead : rs.n) : 0u;
     const u32 behind = rs.n - before - (v1 > v0 ? (v1 - v0) * E : 0u);
     const u32 head = p0 == 0u ? before : 0u, odd = head + (last ? behind : 0u);
-    const u32 odd_idx = tid < head ? tid : rs.n - odd + tid;
-    u32 odd_raw = 0;
-    if (tid < odd) odd_raw = load_value<DT>(rs.x, odd_idx);
     after_load();
     // (nothing computed from the elements in one phase is worth keeping for the next: unpacked, they would take twice the
     // registers)
@@ -2458,8 +2464,7 @@ __device__ __forceinline__ u32 hold_and_list(const Params& P, const RowShape& rs
     const ListEntry ent = list_entry<DT>(P);
     __syncthreads();  // (the counting arrays are done with)
     if (listed <= limit && bounded) {
-        if (tid < odd) sm.ord.buf[tid] = ent.of(KeyOf<DT>::key(odd_raw) ^ P.dirmask, odd_idx);
-        // (the few are fetched again: to select one of 64 registers by a number takes longer than the caches do)
+        if (tid < odd) sm.ord.buf[tid] = tid < head ? tid : rs.n - odd + tid;
         for (;;) {
             u32 left = 0, group = 0;
             static_for<0, kGroups>([&](auto gc) __attribute__((always_inline)) {
@@ -2472,14 +2477,13 @@ __device__ __forceinline__ u32 hold_and_list(const Params& P, const RowShape& rs
                 constexpr int g = decltype(gc)::value;
                 if (left != 0u && group == (u32)g) m[g] ^= 1u << bit;
             });
-            if (left != 0u) {
-                const u32 idx = element_index(src, p0 / (4u * B) + group, s);
-                sm.ord.buf[pos++] = ent.of(KeyOf<DT>::key(load_value<DT>(rs.x, idx)) ^ P.dirmask, idx);
-            }
+            if (left != 0u) sm.ord.buf[pos++] = element_index(src, p0 / (4u * B) + group, s);
         }
         __syncthreads();
+        *places = true;
         return listed;
     }
+    *places = false;
     // Crowded, or k close to the stretch's size: the k-th key itself, of all elements (which are read again: the caches have
     // them, and the registers stay free of what this rare way needs).
     const u32 pend = last || p0 + (u32)(B * NV) > nvec ? nvec : p0 + (u32)(B * NV);
@@ -2589,15 +2593,16 @@ __global__ void __launch_bounds__(B, 4) k_list_held(Params P, ListPlan L) {
         init_row<DT>(P, row, st, rs);
         return;
     }
-    const u32 listed = hold_and_list<DT, B, NV>(P, rs, 0u, true, kCap, sm, [&]() __attribute__((always_inline)) { init_row<DT>(P, row, st, rs); });
+    bool places;
+    const u32 listed = hold_and_list<DT, B, NV>(P, rs, 0u, true, kCap, sm, &places, [&]() __attribute__((always_inline)) { init_row<DT>(P, row, st, rs); });
     if (tid == 0) list_record(st, rs, listed, 6u);
     if (listed > kCap) {  // never expected: the k-th key bounds the list
         if (tid == 0) st->error |= 4u;
     } else if (listed <= 8u * OB) {
         if (tid >= (u32)OB) return;  // (a barrier waits for the waves that are left)
-        order_in_lds<DT, OB>(P, row, rs, sm.few, listed, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.few.buf[i]; });
+        order_in_lds<DT, OB>(P, row, rs, sm.few, listed, 0u, [&](u32 i) __attribute__((always_inline)) { return held_entry<DT>(P, rs, sm.few.buf, i, places); });
     } else {
-        order_in_lds<DT, B>(P, row, rs, sm.ord, listed, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.ord.buf[i]; });
+        order_in_lds<DT, B>(P, row, rs, sm.ord, listed, 0u, [&](u32 i) __attribute__((always_inline)) { return held_entry<DT>(P, rs, sm.ord.buf, i, places); });
     }
 }
 
@@ -2627,9 +2632,10 @@ __global__ void __launch_bounds__(kPartBlock, 4) k_list_part(Params P, ListPlan 
     if (rs.k == 0u || p0 >= nvec) {
         first();
     } else {
-        listed = hold_and_list<DT, B, kPartVecs>(P, rs, p0, p0 + kHeld >= nvec, L.seg_stride, sm, first);
+        bool places;
+        listed = hold_and_list<DT, B, kPartVecs>(P, rs, p0, p0 + kHeld >= nvec, L.seg_stride, sm, &places, first);
         u64* seg = list_array(P, 1u, row) + (size_t)g * L.seg_stride;
-        for (u32 i = tid; i < listed && i < L.seg_stride; i += B) seg[i] = sm.ord.buf[i];
+        for (u32 i = tid; i < listed && i < L.seg_stride; i += B) seg[i] = held_entry<DT>(P, rs, sm.ord.buf, i, places);
     }
     if (tid == 0) list_part<u32>(P, row, L.seg_off)[g] = listed < L.seg_stride ? listed : L.seg_stride;
 }
