@@ -248,6 +248,21 @@ def test_lists_and_buckets_that_do_not_fit_are_shared_out():
                 assert tr[0].redo == 4
 
 
+@pytest.mark.parametrize("n,batch,k,count", [(400000, 1, 9000, 180000), (400000, 1, 30000, 150000), (300000, 6, 9000, 120000)])
+def test_buckets_of_more_parts_than_the_row_has_workgroups(n, batch, k, count):
+    # parts of 2048 entries, a workgroup for each bucket and each 32 KB of the row at most (several rows: fewer): one part to each workgroup then, and a part
+    # may have several runs of bins, or none
+    hidden = np.setdiff1d(np.arange(n), _sampled(n, 4096, 4))
+    u = W.uniform01(n, 161)
+    where = hidden[u[hidden] < count / len(hidden)]
+    y = W.normal(batch * n, 162).reshape(batch, n)
+    for crowd in (np.full(len(where), np.float32(9.0)), (9.0 + W.uniform01(len(where), 163) * 1e-3).astype(np.float32)):
+        y[:, where] = crowd
+        for largest in (True, False):
+            tr = _check("hidden crowd of many", y if largest else -y, F32, k, largest, batch=batch)
+            assert all(t.redo == 4 and t.pre_kept > len(where) for t in tr), [(t.redo, t.pre_kept) for t in tr]
+
+
 def test_lists_longer_than_half_the_row_are_selected_anew():
     # six elements in ten are one value that the sample does not show: everything listed, reason 5; a short list and a long one
     n = 400000
