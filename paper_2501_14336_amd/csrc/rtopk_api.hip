@@ -321,10 +321,10 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     if (listed * 1.1 > 0.5 * (double)n) return false;
     const bool is_long = L->row_block == 0 && !stream && room > 8192.0;
     // A long list's bound comes from half the largest sample: the one workgroup that takes it needs 6 to 7 us to fetch all of it and as long to rank and gather it, and the row's list
-    // is only a tenth longer where k is large.  us, all of it / half: 2^26 keys, k = n / 100, as a mask 109.3 / 104.7, nine in ten equal, k = 2^16, 89.7 / 86.2; 2^24 keys, k = 20000
-    // 47.7 / 44.6, k = 2^20 70.3 / 63.4; 2^28, k = 20000 196 / 192, k = 2^20 218.0 / 217.1.  (A quarter gains 1 to 3 more there, but 2^28 keys, k = 2^20, uniform 229.5 / 243.4.)  Forty ramps
-    // with infinities, whose list is some of its runs long, take as long on the average, 14 of them less and 12 more by up to a quarter (as many runs, half as long: less on ramps, 0.95, but 2
-    // more everywhere else, 2^28 keys 220).
+    // is only a tenth longer where k is large.  It has as many runs as all of it, half as long: with half as many, trends' lists and bins come out up to twice as long.  240 rows of 2^22 to
+    // 2^27 keys, k from 1000 up, half the runs / this, each against all of the sample's time (geometric mean): normal keys 0.92 / 0.93; nine in ten equal 0.90 / 0.91; a thousand values
+    // 0.95 / 0.97; ramps 1.09 / 0.99; with infinities 0.99 / 0.95; blocks of 64 equal neighbours 1.08 / 0.94; single calls, whose T falls a run lower or higher, up to 1.8 and down to 0.6.  (A quarter
+    // gains 1 to 3 us more on normal keys, but 2^28 uniform ones, k = 2^20, 229.5 / 243.4.)
     if (is_long && L->sample == 4 && eb == 4) {
         expect(8192);
         if (listed * 1.1 > 0.5 * (double)n) expect(sample_vecs());

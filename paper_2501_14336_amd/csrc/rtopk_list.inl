@@ -480,6 +480,7 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
                                              AfterLoad&& after_load) {
     constexpr int E = 16 / KeyOf<DT>::kBytes;
     constexpr u32 kRun = (u32)RUN, kRuns = (u32)(B * V) / kRun, kLeastRuns = 16;
+    constexpr u32 kLeast = (u32)B / kRun > kLeastThinned ? (u32)B / kRun : kLeastThinned;  // (thinned by lanes' vectors: one of V is the least there is)
     const u32 tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     KeySource<DT, kGridBlock, key_vecs<DT>(), false> src;
     src.init(rs);
@@ -620,7 +621,7 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
             const float c = (float)by_lanes;
             alike = (float)sm.selv[3] > (2.0f + c / (float)(vals / 8u)) * c;
             if (by_lanes > vals / 2u)  // (T is what most of the sample equals)
-                while ((runs >> thin) > kLeastThinned) ++thin;
+                while ((runs >> thin) > kLeast) ++thin;
         }
     } else if (rank <= vecs / 4u) {
         T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) {
@@ -668,8 +669,8 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
     }
     if constexpr (GATHER) if (gather) {
         static_assert(kRuns <= sizeof(sl->run) / 4, "a counter per run");
-        static_assert(kLeastThinned * kRun * E <= kSampleList, "thinned far enough");
-        while ((rank >> thin) > 128u && (runs >> thin) > kLeastThinned) ++thin;
+        static_assert(kLeast * kRun * E <= kSampleList, "thinned far enough");
+        while ((rank >> thin) > 128u && (runs >> thin) > kLeast) ++thin;
         bool fresh = true, again = false, dense = false;
 #pragma unroll 1
         for (bool first = true;; first = false) {
@@ -738,7 +739,7 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
             fresh = false;
             if (got > kSampleList) {
                 do { got >>= 1; ++thin; } while (got > kSampleList);
-                while ((runs >> thin) < kLeastThinned) --thin;  // (so many runs always fit: more than this many are left)
+                while ((runs >> thin) < kLeast) --thin;  // (so many runs always fit: more than this many are left)
                 continue;
             }
             // how many of them equal T, the sum of the runs' squares, and how many lie in each of a long list's bins
@@ -888,7 +889,8 @@ __device__ __forceinline__ void bound_of_row(const Params& P, const ListPlan& L,
     }
 }
 
-template <int DT, int B, int V>
+// Half the largest sample (fp32, long lists) is in runs of 4 vectors, so that there are as many runs: a trend's list is known by them alone, to a stretch or two of the row.
+template <int DT, int B, int V, int RUN = 8>
 __global__ void __launch_bounds__(B) k_list_bound(Params P, ListPlan L) {
     __shared__ RankShared sm;
     __shared__ SampleList sl;
@@ -897,7 +899,7 @@ __global__ void __launch_bounds__(B) k_list_bound(Params P, ListPlan L) {
     const RowShape rs = row_shape_scalar<DT>(P, row);
     ListSource<DT, false> src;  // (the smaller of the two sweeps' tiles: the larger number of them)
     src.init(rs);
-    bound_of_row<DT, B, V, true, 8>(P, L, row, rs, row_state(P, row), list_row_out(P, row), list_part<u32>(P, row, L.tile_off), src.ntiles(),
+    bound_of_row<DT, B, V, true, RUN>(P, L, row, rs, row_state(P, row), list_row_out(P, row), list_part<u32>(P, row, L.tile_off), src.ntiles(),
                            L.nb != 0u ? ~0u : L.room, sm, &sl, red, true, [] {});
 }
 
@@ -3142,8 +3144,12 @@ static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStrea
     } else {
         if (L.sample == 2) hipLaunchKernelGGL((k_list_bound<DT, 512, 4>), rows, dim3(512), 0, st, P, L);
         else if (L.sample == 3) hipLaunchKernelGGL((k_list_bound<DT, 1024, 4>), rows, dim3(1024), 0, st, P, L);
-        else if (DT == RTOPK_F32 && L.sample == 4) hipLaunchKernelGGL((k_list_bound<DT, 1024, 16>), rows, dim3(1024), 0, st, P, L);
-        else hipLaunchKernelGGL((k_list_bound<DT, 1024, 8>), rows, dim3(1024), 0, st, P, L);
+        else if constexpr (DT == RTOPK_F32) {  // (16-bit keys: 16 vectors do not fit the registers)
+            if (L.sample == 4) hipLaunchKernelGGL((k_list_bound<DT, 1024, 16>), rows, dim3(1024), 0, st, P, L);
+            else hipLaunchKernelGGL((k_list_bound<DT, 1024, 8, 4>), rows, dim3(1024), 0, st, P, L);
+        } else {
+            hipLaunchKernelGGL((k_list_bound<DT, 1024, 8>), rows, dim3(1024), 0, st, P, L);
+        }
         mark(events, 2, st);
         auto sweep = [&](auto nt_, auto long_) { hipLaunchKernelGGL((k_list_sweep<DT, decltype(nt_)::value, decltype(long_)::value>), grid, block, 0, st, P, L); };
         if (L.half != 0) hipLaunchKernelGGL((k_list_sweep<DT, false, true, 2>), grid, block, 0, st, P, L);

@@ -599,6 +599,18 @@ def test_long_lists_bounded_by_half_the_largest_sample(n):
     _check("ramp", z, F32, 12000, by_list=None)
 
 
+@pytest.mark.parametrize("n", [13600000, 1 << 24, (1 << 24) + 9])
+def test_half_the_largest_sample_has_as_many_runs(n):
+    # a ramp's list is a few dozen of the sample's runs long: with as many runs as all of the sample has, half as long, its bins hold what they should; with half
+    # as many, some hold several times that, and their buckets are shared out
+    for amp in (3.0, 1.0e6):
+        x = np.linspace(amp, -amp, n, dtype=np.float32)
+        for k in (3000, 12000, 100000):
+            for largest in (True, False):
+                tr = _check("ramp", x, F32, k, largest)
+                assert tr[0].redo == 0, (k, tr[0].redo)
+
+
 @pytest.mark.parametrize("dtype", [F32, F16])
 def test_lists_of_which_half_or_less_is_wanted(dtype):
     # by 256, 512 and 1024 threads, in one round, a few and all eight, either side of half; alone in a bin, two and many to one
