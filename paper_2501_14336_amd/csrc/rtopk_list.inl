@@ -2068,14 +2068,26 @@ __device__ __forceinline__ u32 list_anew(const Params& P, const ListPlan& L, int
     Source src;
     src.init(rs);
     const u32 nvec = (u32)src.nvec;
+    constexpr u32 kAhead = 4;  // vectors in flight per thread
+    auto fetch = [&](u32 b, uint4 (&q)[kAhead]) __attribute__((always_inline)) {  // (beyond the end: the last one, which is not looked at)
+#pragma unroll
+        for (u32 c = 0; c < kAhead; ++c) q[c] = load16<false>(src.abase + (b + c * B + tid < nvec ? b + c * B + tid : nvec - 1u));
+#pragma unroll
+        for (u32 c = 0; c < kAhead; ++c) keys_of_vector<DT>(q[c], P.dirmask);
+    };
     bool exact;
     const u32 T = sample_rank<B>([&](auto&& f) __attribute__((always_inline)) {
-        for (u32 v = tid; v < nvec; v += B) {
-            uint4 q = load16<false>(src.abase + v);
-            keys_of_vector<DT>(q, P.dirmask);
+#pragma unroll 1
+        for (u32 b = 0; b < nvec; b += kAhead * B) {
+            uint4 q[kAhead];
+            fetch(b, q);
 #pragma unroll
-            for (u32 j = 0; j < E; ++j)
-                if (v * E + j - src.lead < rs.n) f(key_in_vector<DT>(q, (int)j));
+            for (u32 c = 0; c < kAhead; ++c) {
+                const u32 v = b + c * B + tid;
+#pragma unroll
+                for (u32 j = 0; j < E; ++j)
+                    if (v < nvec && v * E + j - src.lead < rs.n) f(key_in_vector<DT>(q[c], (int)j));
+            }
         }
     }, rs.k, 0u, 0xffffffffu, rank, &exact);
     u32* te = list_part<u32>(P, row, L.tile_off);
@@ -2086,24 +2098,27 @@ __device__ __forceinline__ u32 list_anew(const Params& P, const ListPlan& L, int
     const ListEntry ent = list_entry<DT>(P);
     u64* list = list_array(P, 1u, row);
     const u32 room = (u32)((P.n + 1) / 2);
-    for (u32 b = 0; b < nvec; b += B) {  // (whole waves: a wave's 64 vectors lie in one tile)
-        const u32 v = b + tid;
-        uint4 q = v < nvec ? load16<false>(src.abase + v) : make_uint4(0, 0, 0, 0);
-        keys_of_vector<DT>(q, P.dirmask);
-        u32 eq = 0;
+#pragma unroll 1
+    for (u32 b = 0; b < nvec; b += kAhead * B) {  // (whole waves: a wave's 64 vectors lie in one tile)
+        uint4 q[kAhead];
+        fetch(b, q);
 #pragma unroll
-        for (u32 j = 0; j < E; ++j) {
-            const u32 key = key_in_vector<DT>(q, (int)j), idx = v * E + j - src.lead;
-            const bool valid = v < nvec && idx < rs.n;
-            eq += valid && key == T ? 1u : 0u;
-            if (valid && key > T) {
-                const u32 at = atomicAdd(run, 1u);
-                if (at < room) list[at] = ent.of(key, idx);
+        for (u32 c = 0; c < kAhead; ++c) {
+            const u32 v = b + c * B + tid;
+            u32 eq = 0;
+#pragma unroll
+            for (u32 j = 0; j < E; ++j) {
+                const u32 key = key_in_vector<DT>(q[c], (int)j), idx = v * E + j - src.lead;
+                const bool valid = v < nvec && idx < rs.n;
+                eq += valid && key == T ? 1u : 0u;
+                if (valid && key > T) {
+                    const u32 at = atomicAdd(run, 1u);
+                    if (at < room) list[at] = ent.of(key, idx);
+                }
             }
+            eq = wave_inclusive_scan(eq);
+            if (lane == 63u && eq != 0u) atomicAdd(&te[(v - 63u) / (u32)Source::kTileVecs], eq);
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) eq += __shfl_down(eq, o, 64);
-        if (lane == 0 && eq != 0u) atomicAdd(&te[v / (u32)Source::kTileVecs], eq);
     }
     __syncthreads();
     const u32 listed = *run;
@@ -2119,17 +2134,27 @@ __device__ __forceinline__ u32 list_anew(const Params& P, const ListPlan& L, int
     }
     return listed;
 }
-template <int DT, int B>
-__device__ __forceinline__ void redo_row(const Params& P, const ListPlan& L, int row, const RowShape& rs, rtopk_row_trace* st, u32 why,
-                                         OrderShared<B>& ord, RankShared& rank, u32* run) {
+// All that is missing afterwards is the order of the returned number of entries, in list array 1: fewer than k, so that a short list's are in LDS here (ord.buf).  Ends with a barrier.
+template <int DT, int B, bool LONG>
+__device__ __forceinline__ u32 redo_row(const Params& P, const ListPlan& L, int row, const RowShape& rs, rtopk_row_trace* st, u32 why,
+                                        OrderShared<B>& ord, RankShared& rank, u32* run) {
     if (threadIdx.x == 0) {
         st->redo_why = why;
         st->redo |= kRedoRow;
     }
     __syncthreads();
-    const u32 count = list_anew<DT, B>(P, L, row, rs, st, rank, run, ord.hist, ord.wsum);
+    u32 count = list_anew<DT, B>(P, L, row, rs, st, rank, run, ord.hist, ord.wsum);
     __syncthreads();
-    if (count != 0u) order_entries<DT, B>(P, row, rs, ord, 0u, count, 1u, list_part<OrderRange>(P, row, L.stack_off));
+    if constexpr (!LONG) {
+        if (count > 8u * B) {  // never expected: k is less
+            if (threadIdx.x == 0) st->error |= 4u;
+            count = 0;
+        }
+        const u64* list = list_array(P, 1u, row);
+        for (u32 i = threadIdx.x; i < count; i += B) ord.buf[i] = list[i];
+        __syncthreads();
+    }
+    return __builtin_amdgcn_readfirstlane(count);
 }
 
 // The list of one row into the output.  Blocks [0, batch): a row each.  Blocks beyond: L.ties per row, for rows whose
@@ -2141,7 +2166,7 @@ __device__ __forceinline__ void redo_row(const Params& P, const ListPlan& L, int
 template <int DT, int B, bool STREAM>
 __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     constexpr u32 kMost = 16;  // places per thread
-    constexpr u32 kMostSegments = B < 512 ? 256 : 512;
+    constexpr u32 kMostSegments = B < 1024 ? 256 : 512;
     __shared__ union { OrderShared<B> ord; RankShared rank; } lds;
     __shared__ OrderParts<B> shared;
     __shared__ u32 segs[B + 1], place[B];
@@ -2161,7 +2186,7 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     const u32 mode = lr->mode;
     __builtin_amdgcn_sched_barrier(0);
     u64 e[kMost] = {};
-    if (!for_ties && !(few && B <= 256)) {
+    if (!for_ties && !(few && B <= 512)) {
 #pragma unroll
         for (u32 j = 0; j < kMost; ++j) {
             if (tid + j * (u32)B < places) e[j] = front[tid + j * (u32)B];
@@ -2223,14 +2248,15 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
         part = 1u + w;
         find_places();
     } else if (useless) {
-        redo_row<DT, B>(P, L, row, rs, st, few_in_all ? 8u : 5u, sm, lds.rank, &shared.run);
+        const u32 n = redo_row<DT, B, false>(P, L, row, rs, st, few_in_all ? 8u : 5u, sm, lds.rank, &shared.run);
+        if (n != 0u) order_list<DT, B>(P, row, rs, sm, n);
         return;
     } else {
         if (tid == 0) list_record(st, rs, total, 5u);
         if (total == 0) return;
         u32 n = total;
         // (A list that LDS does not hold, though not much longer than expected, is cut down first.  Not every one that is much longer than what is wanted of it: 5800 entries, k = 256, 12.0 / 15.8 us.)
-        if (few && (B <= 256 || total > 4096u) && total <= 8u * B) {
+        if (few && (B <= 512 || total > 4096u) && total <= 8u * B) {
             order_in_lds<DT, B, false, true>(P, row, rs, sm, total, 0u, entry);
             return;
         }
@@ -2653,7 +2679,7 @@ __global__ void __launch_bounds__(B, B == 512 ? 6 : 4) k_list_row(Params P, List
     __shared__ union { OrderShared<B> ord; OrderShared<OB> few; RankShared rank; } sm;
     __shared__ OrderParts<B> shared;
     __shared__ ListRow lr;
-    __shared__ u32 red[3 * (B / 64)], te[kListRowTiles], run;
+    __shared__ u32 red[3 * (B / 64)], te[kListRowTiles], run, all_ties;
     constexpr u32 kCap = 8 * B;
     typedef KeySource<DT, B, 4, NT> Source;
     const int row = blockIdx.x;
@@ -2663,13 +2689,13 @@ __global__ void __launch_bounds__(B, B == 512 ? 6 : 4) k_list_row(Params P, List
     Source src;
     src.init(rs);
     bound_of_row<DT, B, V, false, 8>(P, L, row, rs, st, &lr, te, src.ntiles(), kCap, sm.rank, nullptr, red, true, [] {});
-    if (tid == 0) run = 0;
+    if (tid == 0) run = all_ties = 0;
     __syncthreads();
     if (lr.mode == kListSkip) return;
     const ListRow b = list_row_scalar(&lr);
     const ListEntry ent = list_entry<DT>(P);
     u64* list = list_array(P, 1u, row);
-    (void)sweep_row<DT>(src, 0u, 1u, b, te, P.dirmask, [&](const typename Source::Tile& cur, u32 m) __attribute__((always_inline)) {
+    const u32 ties = sweep_row<DT>(src, 0u, 1u, b, te, P.dirmask, [&](const typename Source::Tile& cur, u32 m) __attribute__((always_inline)) {
         for (;;) {
             const u64 have = ballot64(m != 0u);
             if (have == 0) break;
@@ -2686,29 +2712,26 @@ __global__ void __launch_bounds__(B, B == 512 ? 6 : 4) k_list_row(Params P, List
             }
         }
     });
+    if (lane == 63u && ties != 0u) atomicAdd(&all_ties, ties);
     __syncthreads();
-    const u32 total = run;
-    if (b.mode == kListPlain && total < rs.k) {
-        redo_row<DT, B>(P, L, row, rs, st, 8u, sm.ord, sm.rank, &run);
-        return;
-    }
-    if (tid == 0) list_record(st, rs, total, 6u);
-    if (total > kCap) {
+    u32 total = __builtin_amdgcn_readfirstlane(run);
+    const bool useless = (u64)total + __builtin_amdgcn_readfirstlane(all_ties) < (u64)rs.k, for_ties = b.mode == kListTied && !useless && total < rs.k;
+    if (__builtin_expect(useless, 0)) total = redo_row<DT, B, false>(P, L, row, rs, st, 8u, sm.ord, sm.rank, &run);
+    else if (tid == 0) list_record(st, rs, total, 6u);
+    if (__builtin_expect(total > kCap, 0)) {
         for (u32 i = tid; i < kCap; i += B) list[i] = sm.ord.buf[i];
         if (tid == 0) st->redo |= kRedoList;
         order_shared<DT, B>(P, row, rs, sm.ord, shared, [&](u32 i) __attribute__((always_inline)) { return list[i]; }, total, 0u, 0u, 1u);
-    } else if (total != 0u && total <= 8u * OB && b.mode != kListTied) {
+    } else if (total != 0u && total <= 8u * OB && !for_ties) {
         if (tid >= (u32)OB) return;  // (a barrier waits for the waves that are left)
         order_in_lds<DT, OB>(P, row, rs, sm.few, total, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.few.buf[i]; });
     } else if (total != 0u) {
         order_in_lds<DT, B, false, (B > 512)>(P, row, rs, sm.ord, total, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.ord.buf[i]; });
     }
-    if (b.mode == kListTied && total < rs.k) {
+    if (for_ties) {
         __syncthreads();
-        if (!ties_of_row<DT, B, Source>(P, TileCounts{te}, row, rs, total, b.T, 0u, 1u, sm.ord.hist, sm.ord.wsum)) {
-            __syncthreads();
-            redo_row<DT, B>(P, L, row, rs, st, 8u, sm.ord, sm.rank, &run);
-        }
+        if (!ties_of_row<DT, B, Source>(P, TileCounts{te}, row, rs, total, b.T, 0u, 1u, sm.ord.hist, sm.ord.wsum) && tid == 0)
+            st->error |= 4u;  // never expected: there are enough of them
     }
 }
 
@@ -3033,7 +3056,9 @@ __global__ void __launch_bounds__(kListBucketBlock, 6) k_list_buckets(Params P, 
     const RowShape rs = row_shape_scalar<DT>(P, row);
     rtopk_row_trace* st = row_state(P, row);
     if (done.drop != 0u) {
-        if (j == 0u) redo_row<DT, B>(P, L, row, rs, st, done.drop, sm, lds.rank, &run);
+        if (j != 0u) return;
+        const u32 n = redo_row<DT, B, true>(P, L, row, rs, st, done.drop, sm, lds.rank, &run);
+        if (n != 0u) order_entries<DT, B>(P, row, rs, sm, 0u, n, 1u, list_part<OrderRange>(P, row, L.stack_off));
         return;
     }
     u32 at = 0, count = 0;
@@ -3164,7 +3189,7 @@ static rtopk_status launch_list_all(const Params& P, const ListPlan& L, hipStrea
     } else {
         const dim3 g((unsigned)P.batch * (1u + (unsigned)L.ties));
         if (L.stream_block != 0) hipLaunchKernelGGL((k_list_finish<DT, 1024, true>), g, dim3(1024), 0, st, P, L);
-        else if (L.finish == 256) hipLaunchKernelGGL((k_list_finish<DT, 256, false>), g, dim3(256), 0, st, P, L);
+        else if (L.finish == 512) hipLaunchKernelGGL((k_list_finish<DT, 512, false>), g, dim3(512), 0, st, P, L);
         else hipLaunchKernelGGL((k_list_finish<DT, 1024, false>), g, dim3(1024), 0, st, P, L);
     }
     mark(events, 4, st);

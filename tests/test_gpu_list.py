@@ -206,6 +206,36 @@ def test_misled_short_lists_of_two_launches():
             assert all(t.redo & 1 for t in tr)
 
 
+@pytest.mark.parametrize("k,n", [(50, 40000), (1000, 40000), (2500, 40000), (1000, 40003)])
+def test_misled_rows_of_one_workgroup(k, n):
+    # more rows than are held in registers: by 256, 512 and 1024 threads, each row selected anew by its own; whole vectors and broken ones
+    batch = 258
+    pos = _sampled(n, 1024, 4)
+    x = W.normal(batch * n, 38).reshape(batch, n)
+    x[::2, pos] = 100.0 + W.uniform01(len(pos), 39)
+    for largest in (True, False):
+        bits = (x if largest else -x).view(np.uint32)
+        print("misled rows of one workgroup:", k, largest, flush=True)
+        gv, gi, tr, _ = gpu_topk(to_device(bits, F32), F32, k, largest, sorted=True)
+        wv, wi = oracle.topk(bits, F32, k, largest)
+        assert np.array_equal(gi, wi) and np.array_equal(gv, wv)
+        # (rows off the 16-byte grid have their sample elsewhere)
+        assert all(t.error == 0 for t in tr) and (n % 4 != 0 or [t.redo & 1 for t in tr] == [1, 0] * (batch // 2))
+
+
+@pytest.mark.parametrize("n,batch,vectors,k,crowd", [(40000, 258, 1024, 1000, 900), (40000, 258, 1024, 2500, 2048), (200000, 1, 2048, 300, 250),
+                                                     (1 << 20, 1, 4096, 3000, 2500), (400000, 33, 4096, 300, 250), (400000, 1, 4096, 9000, 8000)])
+def test_rows_of_fewer_ties_than_the_sample_promises(n, batch, vectors, k, crowd):
+    # the sampled positions hold one value, more often than their share of k and less often than k, and the rest of the row is worse: the equal elements are counted, they
+    # and what is better are fewer than k, and the row is selected anew; by one workgroup, two launches, one, several rows, and a long list
+    pos = _sampled(n, vectors, 4)
+    x = (-10.0 - np.abs(W.normal(batch * n, 131))).astype(np.float32).reshape(batch, n)
+    x[:, np.unique(pos)[:: max(1, len(np.unique(pos)) // crowd)][:crowd]] = 5.0
+    for largest in (True, False):
+        tr = _check("crowd in the sample", x if largest else -x, F32, k, largest, batch=batch, why=8)
+        assert all(t.redo & 1 for t in tr)
+
+
 def test_misled_rows_beside_others():
     # long lists, several workgroups per row, and every second row's list is no use: its buckets stay empty, its record says so,
     # and the rows beside it are not touched
