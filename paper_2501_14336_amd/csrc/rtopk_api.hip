@@ -361,10 +361,11 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     // caches; 1024 rows of 2^17 bf16 keys, k = 50, 64 against 57.5; 2^24 fp32 keys, which the last-level cache holds, 36.7
     // against 37.8)
     L->stream = batch * n * eb > ((int64_t)128 << 20);
-    // (256 segments to read keep 1024 threads busy: one fp16 row of 6 million, k = 16, 256 threads 25.9, k = 100, 1024 threads 23.3.  A list that 256 threads
-    // cannot hold is put in order part by part, so a little too much room here as well: 32 rows of 2^21 fp16 keys, k = 300, room for 1907 entries, 54.7 / 50.1)
-    L->finish = room * 1.2 > 2048.0 || stream || G > 256 ? 1024 : 256;  // (and a thread per segment)
-    L->room = (u32)L->finish * 8u;
+    // (256 segments to read keep 1024 threads busy: one fp16 row of 6 million, k = 16, 256 threads 25.9, k = 100, 1024 threads 23.3.  512 threads take no longer than 256 for a list as
+    // long as expected, 64 rows of 2^18 fp16 keys, k = 300, 21.6 / 21.5, and longer ones in half the time (see k_list_finish).  One of more than 2048 entries is cut down first, so a little
+    // too much room here as well: 32 rows of 2^21 fp16 keys, k = 300, room for 1907 entries, 54.7 / 50.1)
+    L->finish = room * 1.2 > 2048.0 || stream || G > 256 ? 1024 : 512;  // (and a thread per segment)
+    L->room = L->finish == 512 ? 2048u : 8192u;
     const double twice = 2.0 * room < 2.0 * L->room ? 2.0 * room : 2.0 * L->room;
     L->most = twice > L->room ? (u32)twice : L->room;
     // (Twice the average segment's entries; less where they are a hundred and more, whose number varies less: places that stay empty are read for

@@ -45,7 +45,7 @@ struct ListPlan {
     u32 hists;        // ... copies of the list's histogram
     u32 bucket_shift; // ... of 2^bucket_shift ranks
     u32 slots;        // short lists: a power of two: so many entries of each segment lie together at front_off
-    u32 room, most;   // ... so many in all are put in order in LDS (and twice as many cut down to that first); the record says so from `most` on
+    u32 room, most;   // ... so many in all are put in order in LDS, longer ones are cut down first; the record says so from `most` on
     u32 front_off, hist_off, cursor_off, first_off, split_off, seg_off, tile_off, stack_off;
 };
 void launch_list_rows_f32(const Params& P, const ListPlan& L, hipStream_t st);  // (the kernels of L.row_block alone)

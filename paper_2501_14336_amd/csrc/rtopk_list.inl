@@ -1720,23 +1720,126 @@ __device__ __forceinline__ void order_list(const Params& P, int row, const RowSh
     }
 }
 
-// f(entry, of(entry)) for all entries src(0) .. src(count - 1), kAhead loads in flight per thread (and as many chains of what `src` and `of` look up in LDS).
-template <int B, u32 kAhead, class Src, class Of, class F>
-__device__ __forceinline__ void order_pass(const Src& src, u32 count, Of&& of, F&& f) {
+// Where a list's entries are: one by one, a wave's at a time, and all of them -- f(entry, of(entry)) by the B threads, AHEAD loads in flight per thread (and as many chains of what `of` looks
+// up in LDS).
+struct EntriesAt {  // all together
+    const u64* p;
+    __device__ __forceinline__ u64 operator()(u32 i) const { return p[i]; }
+    template <int B, u32 AHEAD, class Of, class F>
+    __device__ __forceinline__ void each(u32 count, Of&& of, F&& f) const {
 #pragma unroll 1
-    for (u32 i = threadIdx.x; i < count; i += kAhead * B) {  // (beyond the end: the last entry, which is not looked at)
-        u64 e[kAhead];
+        for (u32 i = threadIdx.x; i < count; i += AHEAD * B) {  // (beyond the end: the last entry, which is not looked at)
+            u64 e[AHEAD];
 #pragma unroll
-        for (u32 j = 0; j < kAhead; ++j) e[j] = src(i + j * B < count ? i + j * B : count - 1u);
-        u32 x[kAhead];
+            for (u32 j = 0; j < AHEAD; ++j) e[j] = p[i + j * B < count ? i + j * B : count - 1u];
+            u32 x[AHEAD];
 #pragma unroll
-        for (u32 j = 0; j < kAhead; ++j) x[j] = of(e[j]);
+            for (u32 j = 0; j < AHEAD; ++j) x[j] = of(e[j]);
 #pragma unroll
-        for (u32 j = 0; j < kAhead; ++j)
-            if (i + j * B < count) f(e[j], x[j]);
-        if (count - i <= kAhead * B) break;
+            for (u32 j = 0; j < AHEAD; ++j)
+                if (i + j * B < count) f(e[j], x[j]);
+        }
     }
-}
+    template <u32 N>
+    __device__ __forceinline__ void fetch(const u32 (&i)[N], u32, u32, u64 (&e)[N]) const {
+#pragma unroll
+        for (u32 j = 0; j < N; ++j) e[j] = p[i[j]];
+    }
+};
+// In segments, of which begin[a] (in LDS, of at most MOST; ~0 or the list's length behind them) is the first entry's number: the first `slots` of a segment's entries at `front`, all of
+// them in their places from `list` on, place[a] being how far those are from their numbers.  piece[a]: how many pieces of kPiece entries the segments before it have; piece[G]: all.
+template <u32 MOST>
+struct EntriesInSegments {
+    static constexpr u32 kPiece = 256;
+    const u64 *front, *list;
+    const u32 *begin, *place, *piece;
+    u32 slots, G;
+    __device__ __forceinline__ u64 at(u32 a, u32 i) const {
+        const u32 l = i - begin[a];
+        return *(l < slots ? front + (a * slots + l) : list + (place[a] + i));
+    }
+    // (No branches: eight entries' searches and loads are under way together.  With loops that end when they have found it, and segments' places worked out for every entry,
+    // one row of 2^20 fp32 keys, a ramp, k = 3000, took 81.7 us, so 71.2; 16 of 2^24, k = 512, of which nothing is too long, 38.6 / 38.0.)
+    __device__ __forceinline__ u64 operator()(u32 i) const {
+        u32 a = 0;  // the segment that holds entry i: the last one that begins at or before it
+#pragma unroll
+        for (u32 step = MOST / 2u; step > 0; step /= 2u) a += begin[a + step] <= i ? step : 0u;
+        return at(a, i);
+    }
+    // A wave's entries i[.], all of them in [i0, i1].  Lists that are far too long lie in few long segments: those of the ends are counted by all lanes together, and what is left
+    // to be searched between them is a step or two, as a rule none.
+    template <u32 N>
+    __device__ __forceinline__ void fetch(const u32 (&i)[N], u32 i0, u32 i1, u64 (&e)[N]) const {
+        u32 a0 = 0, a1 = 0;
+#pragma unroll
+        for (u32 j = 0; j < MOST / 64u; ++j) {
+            const u32 b = begin[j * 64u + lane_id()];
+            a0 += (u32)__popcll(ballot64(b <= i0));
+            a1 += (u32)__popcll(ballot64(b <= i1));
+        }
+        --a0;  // (begin[0] is 0)
+        --a1;
+        u32 a[N];
+#pragma unroll
+        for (u32 j = 0; j < N; ++j) a[j] = a0;
+#pragma unroll 1
+        for (u32 step = a1 > a0 ? 1u << (31u - (u32)__builtin_clz(a1 - a0)) : 0u; step > 0; step /= 2u) {
+#pragma unroll
+            for (u32 j = 0; j < N; ++j) {
+                const u32 m = a[j] + step;
+                a[j] = m <= a1 && begin[m < a1 ? m : a1] <= i[j] ? m : a[j];
+            }
+        }
+#pragma unroll
+        for (u32 j = 0; j < N; ++j) e[j] = at(a[j], i[j]);
+    }
+    // A wave takes every B / 64-th piece, the next one's loads under way: the segment of a piece is the same for all lanes, and 64 pieces' segments are searched for at once.  (An entry's
+    // segment searched for by its lane, 50 instructions: 53440 entries in 18.5 us.)
+    template <int B, u32 AHEAD, class Of, class F>
+    __device__ __forceinline__ void each(u32, Of&& of, F&& f) const {
+        static_assert(kPiece == 64u * AHEAD, "a piece is what a wave has in flight");
+        constexpr u32 W = (u32)B / 64u;
+        const u32 lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), pieces = __builtin_amdgcn_readfirstlane(piece[G]);
+#pragma unroll 1
+        for (u32 q0 = wave; q0 < pieces; q0 += 64u * W) {
+            const u32 left = (pieces - q0 + W - 1u) / W, n = left < 64u ? left : 64u;
+            const u32 q = q0 + W * (lane < n ? lane : n - 1u);
+            u32 mine = 0;
+#pragma unroll
+            for (u32 step = MOST / 2u; step > 0; step /= 2u) mine += piece[mine + step] <= q ? step : 0u;
+            const u32 l0 = (q - piece[mine]) * kPiece, rest = begin[mine + 1u] - begin[mine] - l0, there = place[mine] + begin[mine];
+            auto load = [&](u32 t, u64 (&e)[AHEAD]) __attribute__((always_inline)) {
+                const u32 a = (u32)__builtin_amdgcn_readlane((int)mine, (int)t), l = (u32)__builtin_amdgcn_readlane((int)l0, (int)t);
+                const u32 c = (u32)__builtin_amdgcn_readlane((int)rest, (int)t);
+                const u64 *head = front + a * slots, *tail = list + (u32)__builtin_amdgcn_readlane((int)there, (int)t);
+#pragma unroll
+                for (u32 j = 0; j < AHEAD; ++j) {
+                    if (j * 64u >= c) break;
+                    const u32 i = l + (j * 64u + lane < c ? j * 64u + lane : c - 1u);
+                    e[j] = *((i < slots ? head : tail) + i);
+                }
+            };
+            auto use = [&](u32 t, const u64 (&e)[AHEAD]) __attribute__((always_inline)) {
+                const u32 c = (u32)__builtin_amdgcn_readlane((int)rest, (int)t);
+                u32 x[AHEAD];
+#pragma unroll
+                for (u32 j = 0; j < AHEAD; ++j) x[j] = of(e[j]);
+#pragma unroll
+                for (u32 j = 0; j < AHEAD; ++j)
+                    if (j * 64u + lane < c) f(e[j], x[j]);
+            };
+            u64 e[2][AHEAD] = {};
+            load(0, e[0]);
+#pragma unroll 1
+            for (u32 t = 0; t < n; t += 2u) {
+                if (t + 1u < n) load(t + 1u, e[1]);
+                use(t, e[0]);
+                if (t + 2u < n) load(t + 2u, e[0]);
+                if (t + 1u < n) use(t + 1u, e[1]);
+            }
+        }
+    }
+};
 
 // Those of src's `count` entries that lie in [lo, hi) to buf; returns how many there are (up to 8 B are kept).  Begins and ends with a barrier.
 template <int B, u32 kAhead, class Src>
@@ -1745,7 +1848,7 @@ __device__ __forceinline__ u32 order_gather(const Src& src, u32 count, u64 lo, u
     __syncthreads();
     if (tid == 0) *run = 0;
     __syncthreads();
-    order_pass<B, kAhead>(src, count, [](u64) { return 0u; }, [&](u64 e, u32) __attribute__((always_inline)) {
+    src.template each<B, kAhead>(count, [](u64) { return 0u; }, [&](u64 e, u32) __attribute__((always_inline)) {
         if (e >= lo && e < hi) {
             const u32 at = atomicAdd(run, 1u);
             if (at < 8u * B) sm.buf[at] = e;
@@ -1769,7 +1872,7 @@ __device__ __forceinline__ void order_in_chunks(const Params& P, int row, const 
             for (u32 j = tid; j < 4u * B; j += B) sm.hist[j] = 0;
             if (tid == 0) sm.sp = 4u * B;
             __syncthreads();
-            order_pass<B, kAhead>(src, count, [](u64) { return 0u; }, [&](u64 e, u32) __attribute__((always_inline)) {
+            src.template each<B, kAhead>(count, [](u64) { return 0u; }, [&](u64 e, u32) __attribute__((always_inline)) {
                 if (e >= a && e < hi) atomicAdd(&sm.hist[(u32)((hi - 1u - e) >> sh)], 1u);
             });
             __syncthreads();
@@ -1790,7 +1893,7 @@ __device__ __forceinline__ void order_in_chunks(const Params& P, int row, const 
 // One of `parts` workgroups that put src's `count` entries in order, the row's ranks from rank0 on.  Each reads all of it once and counts
 // it into bins between splitters, which are entries at equal distances, so that all of them see the same bins; runs of bins that LDS
 // holds are dealt to them, and each reads all of it again for every run of its own.  Nobody waits for anybody and
-// nothing is moved in memory.  LAST: rank0 is 0, and the workgroup has nothing else to do afterwards.  One workgroup reads about 0.1 TB/s, so 2^20 entries take 256 of them about 0.2 ms.
+// nothing is moved in memory.  One workgroup reads about 0.1 TB/s, so 2^20 entries take 256 of them about 0.2 ms.
 constexpr u32 kOrderRuns = 128;  // runs that a workgroup notes at a time
 template <int B>
 struct OrderParts {
@@ -1799,11 +1902,11 @@ struct OrderParts {
     u32 start[kOrderRuns], size[kOrderRuns];
     u32 nrun, run;
 };
-template <int DT, int B, bool LAST = false, class Src>
+template <int DT, int B, class Src>
 __device__ __forceinline__ void order_shared(const Params& P, int row, const RowShape& rs, OrderShared<B>& sm, OrderParts<B>& sp, const Src& src,
                                              u32 count, u32 rank0, u32 part, u32 parts) {
     typedef SplitBins<B> Split;
-    constexpr u32 kCap = 8 * B, kRun = kCap * 3 / 4, kBig = kCap / 4, kAhead = LAST ? 8 : 4;  // (registers)
+    constexpr u32 kCap = 8 * B, kRun = kCap * 3 / 4, kBig = kCap / 4, kAhead = 4;  // (registers)
     const u32 tid = threadIdx.x, want = rs.k - rank0 < count ? rs.k - rank0 : count;
     __syncthreads();
     // Little is wanted of much: a bound from 8 B entries at equal distances, and one pass that gathers what is not below it.
@@ -1813,8 +1916,13 @@ __device__ __forceinline__ void order_shared(const Params& P, int row, const Row
         if (count > kCap && (u64)rank * count < (u64)kCap * (kCap / 8u * 7u)) {
             if (part != 0u) return;
             u64 e[8], lo = ~0ull, hi = 0;
+            {
+                const u32 first = __builtin_amdgcn_readfirstlane(tid >> 6) * 512u;
+                u32 i[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) e[j] = src((u32)((u64)(tid + (u32)j * B) * count / kCap));
+                for (u32 j = 0; j < 8; ++j) i[j] = (u32)((u64)(first + j * 64u + lane_id()) * count / kCap);
+                src.template fetch<8>(i, (u32)((u64)first * count / kCap), (u32)((u64)(first + 511u) * count / kCap), e);
+            }
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 lo = lo < e[j] ? lo : e[j];
@@ -1840,8 +1948,7 @@ __device__ __forceinline__ void order_shared(const Params& P, int row, const Row
             }
             const u32 n = order_gather<B, kAhead>(src, count, lo, ~0ull, sm, &sp.run);
             if (n >= want && n <= kCap) {
-                if constexpr (LAST) order_list<DT, B>(P, row, rs, sm, n);
-                else order_in_lds<DT, B>(P, row, rs, sm, n, rank0, [&](u32 i) __attribute__((always_inline)) { return sm.buf[i]; });
+                order_in_lds<DT, B>(P, row, rs, sm, n, rank0, [&](u32 i) __attribute__((always_inline)) { return sm.buf[i]; });
                 return;
             }
             __syncthreads();
@@ -1858,7 +1965,7 @@ __device__ __forceinline__ void order_shared(const Params& P, int row, const Row
     for (u32 done = 0;;) {
         for (u32 j = tid; j < 4u * B + 2u; j += B) sm.hist[j] = 0;
         __syncthreads();
-        order_pass<B, kAhead>(src, count, [&](u64 e) __attribute__((always_inline)) { return Split::bin(sp.edge, e); },
+        src.template each<B, kAhead>(count, [&](u64 e) __attribute__((always_inline)) { return Split::bin(sp.edge, e); },
                       [&](u64, u32 bin) __attribute__((always_inline)) { atomicAdd(&sm.hist[bin], 1u); });
         __syncthreads();
         order_scan<B>(sm.hist, want, ~0u, false, sm);
@@ -2012,7 +2119,7 @@ __device__ __forceinline__ u32 keep_best(const u64 (&e)[N], u32 total, u32 want,
         mx = mx > e[j] ? mx : e[j];
     }
     order_range<B>(mn, mx, sm);
-    u32 left = want, above = 0;  // entries above mx
+    u32 left = want, above = 0, inside = total;  // entries above mx, and from there down to mn
     *crowd = false;
 #pragma unroll 1
     for (;;) {
@@ -2024,7 +2131,7 @@ __device__ __forceinline__ u32 keep_best(const u64 (&e)[N], u32 total, u32 want,
             if (e[j] >= mn && e[j] <= mx) count_alike(sm.hist, (u32)((mx - e[j]) >> sh));
         __syncthreads();
         order_scan<B>(sm.hist, left, ~0u, false, sm);
-        const u32 last = sm.sp, before = sm.hist[last], upto = last + 1u < 4u * B ? sm.hist[last + 1u] : total - above;
+        const u32 last = sm.sp, before = sm.hist[last], upto = last + 1u < 4u * B ? sm.hist[last + 1u] : inside;
         if (tid == 0) sm.flag = 0;
         __syncthreads();
         const u64 floor = mx - mn > ((u64)(last + 1u) << sh) - 1u ? mx - (((u64)(last + 1u) << sh) - 1u) : mn;
@@ -2037,6 +2144,7 @@ __device__ __forceinline__ u32 keep_best(const u64 (&e)[N], u32 total, u32 want,
         mn = floor;
         above += before;
         left -= before;
+        inside = upto - before;
         *crowd = true;
     }
     // (a lane's places by the wave, a wave's by the workgroup: bins would be places, too, but not those of what lies above them)
@@ -2158,7 +2266,12 @@ __device__ __forceinline__ u32 redo_row(const Params& P, const ListPlan& L, int 
 }
 
 // The list of one row into the output.  Blocks [0, batch): a row each.  Blocks beyond: L.ties per row, for rows whose
-// equal elements were counted; the first of them also help with lists that one workgroup cannot put in order in LDS.
+// equal elements were counted.  A list that LDS does not hold is the one workgroup's, too: little of it is wanted, by the plan's own limit on k, and that takes one bound and
+// one gathering pass, which nobody can share.  (So much is wanted that others could help in 16-bit rows of 1.3 to 1.5 million keys alone, k of 4097 to 4150, of which nearly half is listed; the sample would
+// have to miss that.)
+// Lists that are far too long (trends, blocks of equal neighbours), us, put in order by a kernel of their own, which every call then waited for / by this one, looked through entry by entry / so:
+// 2^24 fp32 keys, blocks, k = 300, 46528 entries, 57 / 83 / 63; four rows of 2^20 fp16 keys, a ramp with infinities, k = 300, 50 / 81 / 53, by 512 threads (256: 70); 33 rows of 400000 fp32 keys, k = 300,
+// 192572 entries, 275 / 1986 / 104.
 // Bound by latency.  The first entries of every segment lie together (L.slots of each) and are read before it is known how many there are: a search by
 // every entry for the segment that holds it, and 1024 segments all over the list array, took 6.2 us for 3300 entries; this 3.3 for 5800.  (Ordered from
 // the registers they are read to, 16 places per thread, they need not be put together first, but every phase takes longer: 12 / 15.5 us in all.)
@@ -2169,11 +2282,11 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     constexpr u32 kMostSegments = B < 1024 ? 256 : 512;
     __shared__ union { OrderShared<B> ord; RankShared rank; } lds;
     __shared__ OrderParts<B> shared;
-    __shared__ u32 segs[B + 1], place[B];
+    __shared__ u32 segs[B + 1], place[B], piece[B + 1];
     OrderShared<B>& sm = lds.ord;
     const u32 tid = threadIdx.x, G = (u32)L.G, slots = L.slots, log = 31u - (u32)__builtin_clz(slots);
     const bool for_ties = blockIdx.x >= (u32)P.batch;
-    const int row = for_ties ? (int)((blockIdx.x - (u32)P.batch) / (u32)L.ties) : (int)blockIdx.x;
+    const int row = __builtin_amdgcn_readfirstlane(for_ties ? (int)((blockIdx.x - (u32)P.batch) / (u32)L.ties) : (int)blockIdx.x);
     const u32 places = G * slots;  // (at most kMost * B)
     const u64* front = list_part<u64>(P, row, L.front_off);
     // (k_list_sweep's few long segments: entries look for theirs, where the list is short, or so long that all waves are needed to order it.  One
@@ -2200,8 +2313,9 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     if (tid == B - 1) segs[G] = incl;
     const u32 unit = few ? (u32)ListSource<DT, false>::kTileVecs : kWaveVecs;
     if (few && tid < G) place[tid] = list_segment<DT>(rs, tid, G, unit) - (incl - c);
-    const bool over = __syncthreads_or(c > slots + (few ? 8u : 0u) ? 1 : 0) != 0;  // (a segment has more than its places, or many more)
-    const u32 total = segs[G];
+    // (as scalars: branches on what the compiler takes to differ by lane are laid one behind the other, with the entries in registers through all of them)
+    const bool over = __builtin_amdgcn_readfirstlane(__syncthreads_or(c > slots + (few ? 8u : 0u) ? 1 : 0)) != 0;  // (a segment has more than its places, or many more)
+    const u32 total = __builtin_amdgcn_readfirstlane(segs[G]);
     u32 equal = 0;  // elements that equal T, where they were counted
     if (mode == kListTied) {
         (void)block_scan<B>(seg.y, sm.wsum);
@@ -2210,96 +2324,83 @@ __global__ void __launch_bounds__(B) k_list_finish(Params P, ListPlan L) {
     }
     const bool few_in_all = (u64)total + equal < (u64)rs.k, useless = few_in_all || total > (u32)((P.n + 1) / 2);
     const u64* from = list_array(P, 1u, row);
-    // (No branches: eight entries' searches and loads are under way together.  With loops that end when they have found it, and segments' places worked out for every entry,
-    // one row of 2^20 fp32 keys, a ramp, k = 3000, took 81.7 us, so 71.2; 16 of 2^24, k = 512, of which nothing is too long, 38.6 / 38.0.)
-    auto entry = [&](u32 i) __attribute__((always_inline)) {
-        u32 a = 0;  // the segment that holds entry i: the last one that begins at or before it
-#pragma unroll
-        for (u32 step = kMostSegments / 2u; step > 0; step /= 2u) a += segs[a + step] <= i ? step : 0u;
-        const u32 l = i - segs[a];
-        return *(l < slots ? front + (a * slots + l) : from + (place[a] + i));
-    };
+    const EntriesInSegments<kMostSegments> entry{front, from, segs, place, piece, slots, G};
     auto find_places = [&]() __attribute__((always_inline)) {  // (k_list_stream's, which are rarely needed)
         if (few) return;
         if (tid < G) place[tid] = list_segment<DT>(rs, tid, G, unit) - (incl - c);
         __syncthreads();
     };
-    constexpr u32 kHelpers = 3;
-    const u32 helpers = kHelpers < (u32)L.ties ? kHelpers : (u32)L.ties;
-    u32 part = 0, parts = 1u + helpers;  // of a list that is far too long
     if (for_ties) {
+        if (useless || mode != kListTied || total >= rs.k) return;
         const u32 w = (blockIdx.x - (u32)P.batch) % (u32)L.ties;
-        if (useless) return;
-        if (mode == kListTied && total < rs.k) {
-            const TileCounts tiles{list_part<u32>(P, row, L.tile_off)};
-            constexpr u32 kParts = (u32)ListSource<DT, false>::kTileVecs / kWaveVecs;
-            const u32 parts = (u32)((src_vectors<DT>(rs) + kWaveVecs - 1u) / kWaveVecs);
-            auto count = [&](u32 i) __attribute__((always_inline)) {  // (k_list_stream's tiles are smaller)
-                if (few) return tiles(i);
-                u32 n = 0;
+        const TileCounts tiles{list_part<u32>(P, row, L.tile_off)};
+        constexpr u32 kParts = (u32)ListSource<DT, false>::kTileVecs / kWaveVecs;
+        const u32 parts = (u32)((src_vectors<DT>(rs) + kWaveVecs - 1u) / kWaveVecs);
+        auto count = [&](u32 i) __attribute__((always_inline)) {  // (k_list_stream's tiles are smaller)
+            if (few) return tiles(i);
+            u32 n = 0;
 #pragma unroll
-                for (u32 c = 0; c < kParts; ++c) n += kParts * i + c < parts ? tiles(kParts * i + c) : 0u;
-                return n;
-            };
-            if (!ties_of_row<DT, B, ListSource<DT, false>>(P, count, row, rs, total, lr->T, w, (u32)L.ties, sm.hist, sm.wsum) && w == 0 && tid == 0)
-                st->error |= 4u;  // never expected: there are enough of them
-        }
-        if (total <= kMost * B || w >= helpers) return;  // (16 entries per thread: one workgroup cuts that down)
-        part = 1u + w;
-        find_places();
-    } else if (useless) {
-        const u32 n = redo_row<DT, B, false>(P, L, row, rs, st, few_in_all ? 8u : 5u, sm, lds.rank, &shared.run);
-        if (n != 0u) order_list<DT, B>(P, row, rs, sm, n);
+            for (u32 c = 0; c < kParts; ++c) n += kParts * i + c < parts ? tiles(kParts * i + c) : 0u;
+            return n;
+        };
+        if (!ties_of_row<DT, B, ListSource<DT, false>>(P, count, row, rs, total, lr->T, w, (u32)L.ties, sm.hist, sm.wsum) && w == 0 && tid == 0)
+            st->error |= 4u;  // never expected: there are enough of them
         return;
-    } else {
-        if (tid == 0) list_record(st, rs, total, 5u);
-        if (total == 0) return;
-        u32 n = total;
-        // (A list that LDS does not hold, though not much longer than expected, is cut down first.  Not every one that is much longer than what is wanted of it: 5800 entries, k = 256, 12.0 / 15.8 us.)
-        if (few && (B <= 512 || total > 4096u) && total <= 8u * B) {
-            order_in_lds<DT, B, false, true>(P, row, rs, sm, total, 0u, entry);
-            return;
-        }
-        if (over || total > 8u * B) find_places();
-        if (total > 8u * B) {
-            n = 0;
-            if (total <= kMost * B) {
-                const bool held = !few && __syncthreads_or(c > slots ? 1 : 0) == 0;  // (every segment has places enough; else entries look for themselves)
-#pragma unroll
-                for (u32 j = 0; j < kMost; ++j) {
-                    const u32 i = tid + j * (u32)B, a = i >> log, l = i & (slots - 1u);
-                    if (!held) e[j] = i < total ? entry(i) : ~0ull;
-                    else if (i >= places || l >= segs[a + 1u] - segs[a]) e[j] = ~0ull;
-                }
-                bool crowd;
-                n = keep_best<B>(e, total, rs.k, sm, &crowd);
-                if ((crowd || total > L.most) && tid == 0) st->redo |= kRedoList;
-            } else if (tid == 0) {
-                st->redo |= kRedoList;
-            }
-        } else if (over) {
-            for (u32 i = tid; i < total; i += B) sm.buf[i] = entry(i);
+    }
+    u32 n = total;
+    if (!useless && tid == 0) list_record(st, rs, total, 5u);
+    if (total == 0 && !useless) return;
+    // (A list that LDS does not hold, though not much longer than expected, is cut down first.  Not every one that is much longer than what is wanted of it: 5800 entries, k = 256, 12.0 / 15.8 us.)
+    // (512 threads: what is longer than four per thread is not what the plan expects, and a crowd as a rule.  16 rows of 2^20 fp16 keys, a ramp, k = 40, 2936 entries: ordered whole 47.1, cut down first 35.8.)
+    constexpr u32 kWhole = B <= 512 ? 4u * B : 8u * B;  // (L.room)
+    if (few && !useless && (B <= 512 || total > 4096u) && total <= kWhole) {
+        order_in_lds<DT, B, false, true>(P, row, rs, sm, total, 0u, entry);
+        return;
+    }
+    // (What is rarely there to be done lies in one place: among the usual steps it costs them 0.3 to 1 us of fetching instructions.)
+    if (__builtin_expect(useless || total > kWhole, 0)) {
+        if (useless) {
+            n = redo_row<DT, B, false>(P, L, row, rs, st, few_in_all ? 8u : 5u, sm, lds.rank, &shared.run);
+            if (n == 0u) return;
         } else {
+            find_places();
+            if (total > kMost * B) {  // nobody puts it together first: it is read where it lies
+                if (tid == 0) st->redo |= kRedoList;
+                const u32 mine = tid < G ? (c + entry.kPiece - 1u) / entry.kPiece : 0u, upto = block_scan<B>(mine, sm.wsum);
+                if (tid != G) piece[tid] = tid < G ? upto - mine : ~0u;
+                if (tid == B - 1) piece[G] = upto;
+                __syncthreads();
+                order_shared<DT, B>(P, row, rs, sm, shared, entry, total, 0u, 0u, 1u);
+                return;
+            }
+            // 16 entries per thread are cut down
+            const bool held = !few && __builtin_amdgcn_readfirstlane(__syncthreads_or(c > slots ? 1 : 0)) == 0;  // (every segment has places enough; else entries look for themselves)
 #pragma unroll
             for (u32 j = 0; j < kMost; ++j) {
                 const u32 i = tid + j * (u32)B, a = i >> log, l = i & (slots - 1u);
-                if (i < places && l < segs[a + 1u] - segs[a]) sm.buf[segs[a] + l] = e[j];
+                if (!held) e[j] = i < total ? entry(i) : ~0ull;
+                else if (i >= places || l >= segs[a + 1u] - segs[a]) e[j] = ~0ull;
             }
-            // (k_list_sweep's 512 segments: one of them has a little more than its places in every other row.  k_list_stream's have not, and 0.15 us to lose here.)
-            if (few && ballot64(c > slots) != 0u) {
-                const u32 at = list_segment<DT>(rs, tid, G, unit);
-                for (u32 l = slots; l < c; ++l) sm.buf[segs[tid] + l] = from[at + l];
-            }
+            bool crowd;
+            n = __builtin_amdgcn_readfirstlane(keep_best<B>(e, total, rs.k, sm, &crowd));
+            if ((crowd || total > L.most) && tid == 0) st->redo |= kRedoList;
         }
-        if (n != 0u) {
-            order_list<DT, B>(P, row, rs, sm, n);
-            return;
+    } else if (__builtin_expect(over, 0)) {
+        find_places();
+        for (u32 i = tid; i < total; i += B) sm.buf[i] = entry(i);
+    } else {
+#pragma unroll
+        for (u32 j = 0; j < kMost; ++j) {
+            const u32 i = tid + j * (u32)B, a = i >> log, l = i & (slots - 1u);
+            if (i < places && l < segs[a + 1u] - segs[a]) sm.buf[segs[a] + l] = e[j];
+        }
+        // (k_list_sweep's 512 segments: one of them has a little more than its places in every other row.  k_list_stream's have not, and 0.15 us to lose here.)
+        if (few && ballot64(c > slots) != 0u) {
+            const u32 at = list_segment<DT>(rs, tid, G, unit);
+            for (u32 l = slots; l < c; ++l) sm.buf[segs[tid] + l] = from[at + l];
         }
     }
-    // (nobody puts it together first: every part reads it where it lies)
-    const u32 want = rs.k < total ? rs.k : total, n = (want + 4u * B - 1u) / (4u * B);
-    parts = parts < n ? parts : n;
-    if (part < parts) order_shared<DT, B, true>(P, row, rs, sm, shared, entry, total, 0u, part, parts);
+    order_list<DT, B>(P, row, rs, sm, n);
 }
 
 // k_list_part's lists: L.G of at most L.seg_stride entries, 8 B in all at most (so fewer than B lists).
@@ -2721,7 +2822,7 @@ __global__ void __launch_bounds__(B, B == 512 ? 6 : 4) k_list_row(Params P, List
     if (__builtin_expect(total > kCap, 0)) {
         for (u32 i = tid; i < kCap; i += B) list[i] = sm.ord.buf[i];
         if (tid == 0) st->redo |= kRedoList;
-        order_shared<DT, B>(P, row, rs, sm.ord, shared, [&](u32 i) __attribute__((always_inline)) { return list[i]; }, total, 0u, 0u, 1u);
+        order_shared<DT, B>(P, row, rs, sm.ord, shared, EntriesAt{list}, total, 0u, 0u, 1u);
     } else if (total != 0u && total <= 8u * OB && !for_ties) {
         if (tid >= (u32)OB) return;  // (a barrier waits for the waves that are left)
         order_in_lds<DT, OB>(P, row, rs, sm.few, total, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.few.buf[i]; });
@@ -3047,8 +3148,8 @@ __global__ void __launch_bounds__(kListBucketBlock, 6) k_list_buckets(Params P, 
     __shared__ u32 before[B], run;
     OrderShared<B>& sm = lds.ord;
     const u32 per = L.nb + (u32)L.ties, tid = threadIdx.x;
-    const int row = (int)(blockIdx.x / per);
-    const u32 j = blockIdx.x % per;
+    const int row = __builtin_amdgcn_readfirstlane((int)(blockIdx.x / per));
+    const u32 j = __builtin_amdgcn_readfirstlane(blockIdx.x % per);
     const ListRow* lr = list_row(P, row);
     const u32 mode = lr->mode;
     if (mode == kListSkip) return;
@@ -3102,8 +3203,7 @@ __global__ void __launch_bounds__(kListBucketBlock, 6) k_list_buckets(Params P, 
                 if (before[m] <= s) a = m; else b = m;
             }
             bucket_range(P, L, row, rs, j0 + a, &at, &count);
-            const u64* src = list + at;
-            order_shared<DT, B>(P, row, rs, sm, shared, [&](u32 i) __attribute__((always_inline)) { return src[i]; }, count, at, s - before[a], parts_of(count));
+            order_shared<DT, B>(P, row, rs, sm, shared, EntriesAt{list + at}, count, at, s - before[a], parts_of(count));
         }
         base += total;
     }

@@ -293,6 +293,30 @@ def test_buckets_of_more_parts_than_the_row_has_workgroups(n, batch, k, count):
             assert all(t.redo == 4 and t.pre_kept > len(where) for t in tr), [(t.redo, t.pre_kept) for t in tr]
 
 
+@pytest.mark.parametrize("dtype,n,batch,k,vectors,counts,threads", [
+    (F32, 200000, 1, 300, 2048, (6000, 9000, 90000), 512), (F32, 400000, 33, 300, 4096, (9000, 100000), 512), (F32, 200000, 1, 3500, 2048, (10000, 17000, 60000), 1024),
+    (F32, 1 << 20, 1, 1000, 4096, (12000, 17000, 300000), 1024), (F32, 600000, 3, 3000, 4096, (17000, 200000), 1024), (F16, 1441792, 1, 4100, 4096, (20000, 695000), 1024)])
+def test_lists_far_longer_than_lds_holds(dtype, n, batch, k, vectors, counts, threads):
+    # what the sample does not show lengthens the list, which one workgroup puts in order: more than 8 entries per thread are cut down to that first, more than 16 are read where they
+    # lie, in two launches (by 512 and by 1024 threads) and in one; segments of a few entries and of many thousands, some of them empty.  The last row's second list is the only kind whose wanted
+    # part is too much for a bound from a sample of it
+    elems = 4 if dtype == F32 else 8
+    hidden = np.setdiff1d(np.arange(n), _sampled(n, vectors, elems))
+    u = W.uniform01(n, 141)
+    for count in counts:
+        chosen = hidden[u[hidden] < count / len(hidden)]
+        for name, where in (("spread", chosen), ("together", hidden[len(hidden) // 3:][:len(chosen)])):
+            x = W.normal(batch * n, 142).reshape(batch, n)
+            x[:, where] = 20.0 + W.uniform01(len(where), 143)
+            for largest in (True, False):
+                for srt in (True, False) if count == counts[0] else (True,):
+                    tr = _check("far too long, " + name, x if largest else -x, dtype, k, largest, sorted=srt, batch=batch, by_list=None)
+                    # (who is spread is in every row, the sample's positions apart; a stretch of its own may hold some of them)
+                    assert all(t.pre_kept > len(where) and t.redo & 1 == 0 for t in tr)
+                    if len(where) > 16 * threads:
+                        assert all(t.redo == 2 for t in tr), [t.redo for t in tr]
+
+
 def test_lists_longer_than_half_the_row_are_selected_anew():
     # six elements in ten are one value that the sample does not show: everything listed, reason 5; a short list and a long one
     n = 400000
@@ -489,10 +513,10 @@ def test_lists_a_little_too_long_are_cut_down():
                 assert tr[0].redo == 0 and 8192 < tr[0].pre_kept <= 16384, (tr[0].redo, tr[0].pre_kept)
 
 
-@pytest.mark.parametrize("k,most", [(300, 2048 + 150), (3500, 8192 + 1500)])
+@pytest.mark.parametrize("k,most", [(300, 2048 + 1), (300, 2048 + 150), (3500, 8192 + 1500)])
 def test_lists_a_little_too_long_are_cut_down_after_two_launches(k, most):
-    # the same where sample and sweep are two launches, and a list's entries look for their segment: 256 threads (2048 entries, up to 2424 cut down)
-    # and 1024 threads (8192, up to 12788).  The bound is the sample's alone: so many more elements above it lengthen the list by just as many
+    # the same where sample and sweep are two launches, and a list's entries look for their segment: 512 threads (2048 entries, up to 2424 cut down
+    # without a record of it) and 1024 threads (8192, up to 12788).  The bound is the sample's alone: so many more elements above it lengthen the list by just as many
     n = 200000
     hidden = np.setdiff1d(np.arange(n), _sampled(n, 2048, 4))
     x = W.normal(n, 51)
