@@ -225,9 +225,10 @@ typedef struct {
     uint32_t redo;             /* 1: the one-sweep row kernel left this row to the two-sweep kernel
                                   (which clears the record, redo_why excepted, when it takes the row
                                   over).  List kernels, bits (any of them): 1 the list was no use and
-                                  the row was selected anew, 2 the list was much too long for one
-                                  workgroup, which cut it down or shared it out, 4 so were some of its
-                                  buckets                                                            */
+                                  the row was selected anew, 2 the list was much longer than one
+                                  workgroup orders in LDS and was cut down first (pre_kept says how
+                                  long it was), 4 some of its buckets were, and were shared out among
+                                  the row's workgroups                                               */
     uint32_t redo_why;         /* diagnostic; non-zero: the one-sweep kernel handed the row over, or
                                   (list kernels: 5 and 8 only) the list was no use.
                                   1 inf/NaN in the part counted first, 2 that part shorter than k,

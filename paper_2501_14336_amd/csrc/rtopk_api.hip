@@ -330,10 +330,10 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
         if (listed * 1.1 > 0.5 * (double)n) expect(sample_vecs());
         else L->sample = 5;
     }
-    // A long list is put in order whether that was asked for or not.  Unsorted output pays for it where keys lie in order
-    // along the row and crowd the bins: a ramp with infinities, us, digit passes / list: 2^22 fp32 keys, k = 2^13, 75 / 105,
-    // k = 2^20, 77 / 159; 2^26 fp16 keys, k = 2^16, 162 / 234, k = 2^20, 154 / 388.  Long fp32 rows gain more than they can
-    // lose: 2^26 keys, k = 2^16, uniform 149 / 104, the ramp 154 / 162.
+    // Unsorted long lists: what lies above rank k's bin is output as it comes, and that bin alone is ordered.  fp32 rows of 2^25 keys and more go that way; the rest is left to the digit passes, a line that was drawn
+    // when all of the list was put in order.  As it is now the list gains wherever keys are in no order, and loses where they lie in order along the row and crowd a few tiles.  One row, us, digit passes / list, k = n /
+    // 1000, n / 100 and n / 16: 2^22 fp32 keys, normal, 42 / 34, 53 / 35, 69 / 41, nine in ten equal 88 / 40, 88 / 52, 88 / 84, ramps with infinities 53 / 70, 56 / 78, 57 / 83; 2^26 fp16 keys, k = n / 1000 and n / 100, 91 /
+    // 57, 119 / 59, equal 249 / 82, 249 / 87, ramps 134 / 170, 127 / 192; 2^24 bf16 keys 62 / 43, 68 / 44, 79 / 59, equal 122 / 53, 123 / 64, 123 / 117, ramps 84 / 168, 85 / 156, 87 / 179.
     if (is_long && !sorted && (eb != 4 || n < ((int64_t)1 << 25))) return false;
     // k_list_stream: a workgroup of 512 threads per compute unit; k_list_sweep: one of 1024 where the list's histogram is counted, else four
     // of 512 (three for 16-bit keys), but no more than 256 to a row, 512 for 16-bit keys up to 128 MB.  The more there are, the more segments have to be put together, and the
@@ -344,8 +344,9 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     // A single row of up to 8.5 MB has no more than 136 tiles of 64 KB for 256 compute units: a long list's sweep takes half as large ones there, and the histograms of then up to 256 workgroups,
     // which all end together, are added up in four copies (an add to a line of counters takes 11 ns).  us, tiles of 64 KB / of 32, one histogram / so: 2^22 + 3 fp16 keys, k = 2^20,
     // 58.3 / 55.9 / 54.1; 2^21 fp32 keys, k = 20000 31.9 / 34.1 / 32.2, k = n / 5 41.2 / 42.3 / 40.2; 2^18 fp32 keys, k = n / 5 36.1 / 33.5 / 34.0; ramps, whose list lies in a few tiles, 2^21, k =
-    // 20000, 110 / 80, 2^20 fp16 keys 117 / 94.  Nine in ten equal 2^20 fp32 keys, k = 10000 and n / 4, 34.0 / 35.8 and 57.6 / 59.5.  Above that, where some workgroups have two
-    // tiles and others one: 10 MB of bf16 keys, nine in ten equal, 49.2 / 53.0.
+    // 20000, 110 / 80, 2^20 fp16 keys 117 / 94.  Nine in ten equal 2^20 fp32 keys, k = 10000 and n / 4, 34.0 / 35.8 and 57.6 / 59.5.  At 8 MB each compute unit has one tile of 32 KB, and the line lies half a megabyte
+    // above that for rows of a power of two and a few more; it is not a sharp one: from 8.1 to 12 MB some workgroups have two tiles and others one, normal keys take the same time either way (2^21 + 2^15 fp32 keys, k =
+    // 20000, 32 / 32, 9 MB of fp16 keys, k = n / 4, 62 / 62), equal ones 2 to 3 us more (40 / 43, 47 / 50) and ramps a quarter less (110 / 82, 158 / 118).
     L->half = is_long && batch == 1 && n * eb <= ((int64_t)17 << 19) ? 1 : 0;
     const int64_t tile_elems = (int64_t)(is_long && L->half == 0 ? 1024 : kHostGridBlock) * 64 / eb;
     const int64_t ntiles = (n + E - 1 + tile_elems - 1) / tile_elems;
@@ -390,7 +391,7 @@ static bool make_list_plan(int64_t batch, int64_t n, int64_t k, rtopk_dtype dt, 
     L->seg_off = take((u64)G * 8);
     L->hists = L->half != 0 && G > 64 ? 4u : 1u;
     L->hist_off = take(is_long ? (u64)L->hists * kMaxBins * 4 : 0);
-    L->cursor_off = take(is_long ? (((u64)L->nb + 1 + 31) & ~(u64)31) * 8 : 4);
+    L->cursor_off = take(is_long ? (u64)list_cursors(L->nb) * 8 : 4);
     L->first_off = take((u64)L->nb * 8);
     L->split_off = take(is_long ? (kListSplits + 1) * 8 : 0);
     L->tile_off = take((u64)(stream ? wave_tiles + 2 : (n + E - 1) / (kHostGridBlock * 64 / eb) + 2) * 4);  // (the smallest tiles' number)

@@ -30,6 +30,9 @@ constexpr unsigned kListMaxBuckets = 4096;
 constexpr unsigned kListSplits = 256;                  // intervals between splitters
 constexpr int kListPartBlock = 256, kListPartVecs = 8;  // a stretch of a row that one workgroup holds: 32 KB
 constexpr unsigned kListMetaBytes = 256;  // a row's records before the plan's first offset
+// A bucket's places are taken from its beginning by every other workgroup, and from its end by the rest: two arrays of so many counters, not of the same cache line.  (k_list_emit counts two things
+// in one.)
+__host__ __device__ constexpr u32 list_cursors(u32 nb) { return (nb + 1u + 31u) & ~31u; }
 struct ListPlan {
     int G;            // workgroups per row in the sweep
     int row_block;    // one workgroup per row does everything: its threads (0: many workgroups per row)

@@ -20,8 +20,8 @@
 //   k_list_scatter  (long lists, sorted) many workgroups per row: the list into buckets of about 2048 ranks each,
 //   k_list_buckets  and one workgroup per bucket puts its ranks in order
 //
-// The last kernel of each of these also does what is normally not there to be done: lists and buckets too long for one workgroup, which
-// several put in order, and rows whose list was no use, which one workgroup selects anew.  (A clean-up kernel behind it, which found nothing
+// The last kernel of each of these also does what is normally not there to be done: lists longer than LDS holds, which one workgroup cuts down first, buckets
+// too long for one workgroup, which several put in order, and rows whose list was no use, which one workgroup selects anew.  (A clean-up kernel behind it, which found nothing
 // to do, took 3 to 4.6 us of every call: 1024 rows of 2^17 bf16 keys, k = 50, 54.3 us, so 49.2; one of 2^24 fp32 keys, k = 256, 33.6 / 31.8; of 2^26, nine in ten equal, k = 2^16, 96.0 / 93.0.)
 //
 // List entries are 64-bit numbers, distinct within a row, whose descending order is the order of the output: the
@@ -67,12 +67,9 @@ static_assert(sizeof(ListRow) % 8 == 0, "read by words");
 // wave that found the decision changed would leave the others of its workgroup alone with sums it never wrote.
 struct ListDone {
     u32 total;     // entries
-    u32 end;       // entries in bins that begin below rank k
     u32 drop;      // the list was no use, the buckets are not filled: why (rtopk_row_trace::redo_why)
-    u32 big;       // ... 1: a bucket has more than one workgroup puts in order
+    u32 big;       // 1: a bucket has more than one workgroup puts in order
 };
-// A bucket's places are taken from its beginning by every other workgroup, and from its end by the rest: two counters each, not of the same cache line.  (k_list_emit counts two things in one.)
-__host__ __device__ constexpr u32 list_cursors(u32 nb) { return (nb + 1u + 31u) & ~31u; }
 constexpr u32 kListDoneOff = 128;
 static_assert(sizeof(ListRow) <= kListDoneOff && kListDoneOff + sizeof(ListDone) <= kListMetaBytes, "both lie before the plan's first offset");
 // Bits of rtopk_row_trace::redo: the list was no use; it was too long to put in order in LDS; so were some of its buckets.
@@ -133,7 +130,7 @@ __device__ __forceinline__ ListDone* list_done(const Params& P, int row) { retur
 template <class T>
 __device__ __forceinline__ T* list_part(const Params& P, int row, u32 off) { return (T*)(list_meta(P, row) + off); }
 // The same as a pointer of no known address space, for the sweep's adds to its counters of ties: around adds that it knows to go to global memory the compiler keeps the loads under way in another
-// order (2^26 fp16 keys, a ramp, k = 16, 65.4 us, so 63.8; nine in ten bf16 keys equal, k = 300, 66.7 / 64.6).
+// order (2^26 fp16 keys, a ramp, k = 16, 65.4 us, so 63.8; nine in ten bf16 keys equal, k = 300, 66.7 / 64.6).  It is the compiler's order that is measured there: with another one, measure again.
 template <class T>
 __device__ __forceinline__ T* list_part_generic(const Params& P, int row, u32 off) {
     return (T*)((((uintptr_t)(P.cand[0] + (size_t)row * P.cand_stride + (size_t)((P.n + 1) / 2)) + 255) & ~(uintptr_t)255) + off);
@@ -1473,7 +1470,7 @@ template <int DT, int B, bool CUT = false, bool PART = CUT || B >= 512, class Lo
 __device__ __forceinline__ void order_in_lds(const Params& P, int row, const RowShape& rs, OrderShared<B>& sm, u32 C, u32 rank0,
                                              Load&& load) {
     u32 tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
+    asm volatile("" : "+v"(tid));  // (what follows from it is worked out here and not kept for the whole kernel: k_list_row by 256 threads 95 registers, 102 without, four waves to a SIMD and not five)
     const u32 want = rs.k - rank0 < C ? rs.k - rank0 : C;
     const bool sorted = (P.flags & RTOPK_FLAG_SORTED) != 0u;
     const ListEntry ent = list_entry<DT>(P);
@@ -2271,7 +2268,7 @@ __device__ __forceinline__ u32 redo_row(const Params& P, const ListPlan& L, int 
 // have to miss that.)
 // Lists that are far too long (trends, blocks of equal neighbours), us, put in order by a kernel of their own, which every call then waited for / by this one, looked through entry by entry / so:
 // 2^24 fp32 keys, blocks, k = 300, 46528 entries, 57 / 83 / 63; four rows of 2^20 fp16 keys, a ramp with infinities, k = 300, 50 / 81 / 53, by 512 threads (256: 70); 33 rows of 400000 fp32 keys, k = 300,
-// 192572 entries, 275 / 1986 / 104.
+// 192572 entries, 275 / 1986 / 132.
 // Bound by latency.  The first entries of every segment lie together (L.slots of each) and are read before it is known how many there are: a search by
 // every entry for the segment that holds it, and 1024 segments all over the list array, took 6.2 us for 3300 entries; this 3.3 for 5800.  (Ordered from
 // the registers they are read to, 16 places per thread, they need not be put together first, but every phase takes longer: 12 / 15.5 us in all.)
@@ -2904,10 +2901,6 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     for (int i = 0; i < kHeld; ++i) held[i] = tid + (u32)i * B < mine ? from[tid + (u32)i * B] : 0ull;
     const u32 bs = L.bucket_shift, nb = L.nb;
     u32 c[kPer], s = 0, rank[kPer];
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        c[i] = 0;
-    }
     list_counts(P, L, row, c);
 #pragma unroll
     for (int i = 0; i < kPer; ++i) s += c[i];
@@ -2949,7 +2942,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
     const bool few_in_all = few && (u64)total + s_equal < (u64)rs.k;
     const bool drop = few_in_all || end > (u32)((P.n + 1) / 2);  // (the buckets have half a candidate array)
     if (drop) {
-        if (records && tid == 0) *list_done(P, row) = ListDone{total, end, few_in_all ? 8u : 5u, 0u};
+        if (records && tid == 0) *list_done(P, row) = ListDone{total, few_in_all ? 8u : 5u, 0u};
         return;
     }
     if (records) {
@@ -2967,7 +2960,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_scatter(Params P, ListPlan 
         });
         for (u32 j = tid; j < nb; j += B) first[2u * j] = place[j];  // (~0: no bin begins it, and it has no size)
         __syncthreads();
-        if (tid == 0) *list_done(P, row) = ListDone{total, end, 0u, s_big};
+        if (tid == 0) *list_done(P, row) = ListDone{total, 0u, s_big};
         if (alone) return;
         for (u32 j = tid; j < nb; j += B) place[j] = 0;
         __syncthreads();
@@ -3031,7 +3024,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_emit(Params P, ListPlan L) 
     const u64 lo = lr->lo;
     const u32 sh = lr->sh, by_split = __builtin_amdgcn_readfirstlane(lr->split);
     if (by_split != 0u && tid <= kListSplits) split[tid] = list_part<u64>(P, row, L.split_off)[tid];
-    const u64* from = list_array(P, 1u, row) + list_segment<DT>(rs, wg, G, long_unit(L));
+    const u64* from = list_array(P, 1u, row) + list_segment<DT>(rs, wg, G, (u32)kLongBlock * 4u);  // (no half tiles: the plan has unsorted lists of rows of 2^25 keys and more)
     const uint2* segs = list_part<uint2>(P, row, L.seg_off);
     const u32 mine = segs[wg].x;
     const u32 equal = mode == kListTied && tid < G ? segs[tid].y : 0u;  // (G is at most 256)
@@ -3039,10 +3032,6 @@ __global__ void __launch_bounds__(kLongBlock) k_list_emit(Params P, ListPlan L) 
 #pragma unroll
     for (int i = 0; i < kHeld; ++i) held[i] = tid + (u32)i * B < mine ? from[tid + (u32)i * B] : 0ull;
     u32 c[kPer], s = 0;
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        c[i] = 0;
-    }
     list_counts(P, L, row, c);
 #pragma unroll
     for (int i = 0; i < kPer; ++i) s += c[i];
@@ -3072,7 +3061,7 @@ __global__ void __launch_bounds__(kLongBlock) k_list_emit(Params P, ListPlan L) 
     const bool few_in_all = few && (u64)total + s_equal < (u64)rs.k;
     const bool drop = few_in_all || end > (u32)((P.n + 1) / 2);  // (the bucket has its place in half a candidate array)
     if (wg == 0 && tid == 0) {
-        *list_done(P, row) = ListDone{total, end, drop ? (few_in_all ? 8u : 5u) : 0u, !few && end - rank > kBucketRoom ? 1u : 0u};
+        *list_done(P, row) = ListDone{total, drop ? (few_in_all ? 8u : 5u) : 0u, !few && end - rank > kBucketRoom ? 1u : 0u};
         u32* first = list_part<u32>(P, row, L.first_off);
         first[0] = few ? 0xffffffffu : rank;
         first[1] = end - rank;
