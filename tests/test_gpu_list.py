@@ -163,19 +163,19 @@ def test_ragged_rows_short_and_long():
                 _check_ragged("list", rows, dtype, ks, False, None, srt)
 
 
-def _sampled(n, vectors, elems):
-    """Positions of a row (starting on a 16-byte boundary) that the sample covers: runs of 8 vectors of 16 bytes."""
+def _sampled(n, vectors, elems, run=8):
+    """Positions of a row (starting on a 16-byte boundary) that the sample covers: runs of 8 vectors of 16 bytes, or of 4."""
     def mix(z):
         z = z.astype(np.uint32)
         z ^= z >> np.uint32(16); z *= np.uint32(0x7feb352d)
         z ^= z >> np.uint32(15); z *= np.uint32(0x846ca68b)
         return z ^ (z >> np.uint32(16))
-    runs, groups = vectors // 8, (n // elems) // 8
+    runs, groups = vectors // run, (n // elems) // run
     c = np.arange(runs, dtype=np.uint64)
     with np.errstate(over="ignore"):
         h = (mix(c) >> np.uint32(16)).astype(np.uint64)
     g = (((c << np.uint64(16)) | h) * np.uint64(groups) // np.uint64(runs)) >> np.uint64(16)
-    return (g[:, None] * np.uint64(8 * elems) + np.arange(8 * elems, dtype=np.uint64)[None, :]).reshape(-1).astype(np.int64)
+    return (g[:, None] * np.uint64(run * elems) + np.arange(run * elems, dtype=np.uint64)[None, :]).reshape(-1).astype(np.int64)
 
 
 @pytest.mark.parametrize("k", [300, 9000])
@@ -236,6 +236,29 @@ def test_rows_of_fewer_ties_than_the_sample_promises(n, batch, vectors, k, crowd
         assert all(t.redo & 1 for t in tr)
 
 
+def test_misled_long_lists_of_the_halved_sample():
+    # rows from 16 MB up: 8192 vectors in runs of 4; sorted, and unsorted, whose kernel hands a row over whose list is no use (fewer than k, more than half the row)
+    for n, k, srt in (((1 << 22) + 4, 12000, True), (1 << 25, 70000, False)):
+        pos = _sampled(n, 8192, 4, run=4)
+        x = W.normal(n, 40)
+        y = x.copy()
+        x[pos] = 100.0 + W.uniform01(len(pos), 41)
+        hidden = W.uniform01(n, 42) < 0.65
+        hidden[pos] = False
+        y[hidden] = 9.0
+        for name, z, why in (("misled", x, 8), ("hidden majority", y, 5)):
+            for largest in (True, False):
+                v = z if largest else -z
+                if srt:
+                    tr = _check(name, v, F32, k, largest, why=why)
+                else:
+                    print("unsorted:", name, largest, flush=True)
+                    gv, gi, tr, _ = gpu_topk(to_device(v.view(np.uint32).reshape(1, -1), F32), F32, k, largest, sorted=False)
+                    assert tr[0].error == 0 and tr[0].done and tr[0].redo_why == why
+                    _assert_best(v, v.view(np.uint32), k, largest, gv[0], gi[0])
+                assert tr[0].redo == 1
+
+
 def test_misled_rows_beside_others():
     # long lists, several workgroups per row, and every second row's list is no use: its buckets stay empty, its record says so,
     # and the rows beside it are not touched
@@ -253,8 +276,8 @@ def test_misled_rows_beside_others():
 
 
 def test_lists_and_buckets_that_do_not_fit_are_shared_out():
-    # a trend along the row: more is listed than one workgroup orders in LDS (bit 2); crowds that the sample does not show: a bucket
-    # that holds most of the list (bit 4), of one value and of neighbouring keys; one workgroup per row, and several
+    # a trend along the row: more is listed than one workgroup orders in LDS, and it is cut down first (bit 2); crowds that the sample does not show: a bucket
+    # that holds most of the list is shared out (bit 4), of one value and of neighbouring keys; one workgroup per row, and several
     n = 1 << 20
     for dtype, k in ((F32, 1000), (F16, 1000), (F32, 3000)):
         x = np.linspace(6.0e4, -6.0e4, n, dtype=np.float32)
