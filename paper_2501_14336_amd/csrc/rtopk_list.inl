@@ -3185,7 +3185,9 @@ __global__ void __launch_bounds__(kListBucketBlock, 6) k_list_buckets(Params P, 
         if (tid == B - 1) run = incl;
         __syncthreads();
         const u32 total = run;
-        for (u32 s = (j + per - base % per) % per; s < total; s += per) {
+        u32 W = per;
+        asm volatile("" : "+s"(W));  // (its reciprocal is worked out here: kept from the kernel's beginning, every thread of every call wrote it to scratch memory, 262 KB of 2^28 keys' call)
+        for (u32 s = (j + W - base % W) % W; s < total; s += W) {
             u32 a = 0, b = B;  // the bucket that part s belongs to: the last one that begins at or before it
             while (b - a > 1u) {
                 const u32 m = (a + b) / 2u;
