@@ -2767,7 +2767,8 @@ __global__ void __launch_bounds__(kPartBlock, 4) k_list_part(Params P, ListPlan 
 }
 
 // (Registers: six waves to a SIMD where a workgroup has eight, which what is normally not there to be done would else make four: 1024 rows of 2^17 bf16 keys, k = 1024, 68.8 us / 63.9.
-// Workgroups of four waves are better four to a compute unit than unevenly more of them: k = 50, six waves 52.4 us, four 49.4.)
+// Workgroups of four waves are better four to a compute unit than unevenly more of them: k = 50, six waves 52.4 us, four 49.4.  Ties are summed up, and a row selected anew, where they are found to be too few:
+// with that known before the list is ordered, as elsewhere, and both ways of ordering behind it, k = 50 49.2 / 49.8 and k = 1024 62.7 / 63.3, 1000 rows of 50257, k = 100, 31.7 / 32.6.)
 // Bound, sweep and order in one kernel: the list is gathered in LDS (what does not fit there goes to the list array).
 // For rows so short, or so many, that sharing one out gains nothing.  Several of these workgroups share a compute unit, so that one
 // row's trip from memory overlaps the others' ranking.
@@ -2777,7 +2778,7 @@ __global__ void __launch_bounds__(B, B == 512 ? 6 : 4) k_list_row(Params P, List
     __shared__ union { OrderShared<B> ord; OrderShared<OB> few; RankShared rank; } sm;
     __shared__ OrderParts<B> shared;
     __shared__ ListRow lr;
-    __shared__ u32 red[3 * (B / 64)], te[kListRowTiles], run, all_ties;
+    __shared__ u32 red[3 * (B / 64)], te[kListRowTiles], run;
     constexpr u32 kCap = 8 * B;
     typedef KeySource<DT, B, 4, NT> Source;
     const int row = blockIdx.x;
@@ -2787,13 +2788,13 @@ __global__ void __launch_bounds__(B, B == 512 ? 6 : 4) k_list_row(Params P, List
     Source src;
     src.init(rs);
     bound_of_row<DT, B, V, false, 8>(P, L, row, rs, st, &lr, te, src.ntiles(), kCap, sm.rank, nullptr, red, true, [] {});
-    if (tid == 0) run = all_ties = 0;
+    if (tid == 0) run = 0;
     __syncthreads();
     if (lr.mode == kListSkip) return;
     const ListRow b = list_row_scalar(&lr);
     const ListEntry ent = list_entry<DT>(P);
     u64* list = list_array(P, 1u, row);
-    const u32 ties = sweep_row<DT>(src, 0u, 1u, b, te, P.dirmask, [&](const typename Source::Tile& cur, u32 m) __attribute__((always_inline)) {
+    (void)sweep_row<DT>(src, 0u, 1u, b, te, P.dirmask, [&](const typename Source::Tile& cur, u32 m) __attribute__((always_inline)) {
         for (;;) {
             const u64 have = ballot64(m != 0u);
             if (have == 0) break;
@@ -2810,26 +2811,31 @@ __global__ void __launch_bounds__(B, B == 512 ? 6 : 4) k_list_row(Params P, List
             }
         }
     });
-    if (lane == 63u && ties != 0u) atomicAdd(&all_ties, ties);
     __syncthreads();
-    u32 total = __builtin_amdgcn_readfirstlane(run);
-    const bool useless = (u64)total + __builtin_amdgcn_readfirstlane(all_ties) < (u64)rs.k, for_ties = b.mode == kListTied && !useless && total < rs.k;
-    if (__builtin_expect(useless, 0)) total = redo_row<DT, B, false>(P, L, row, rs, st, 8u, sm.ord, sm.rank, &run);
-    else if (tid == 0) list_record(st, rs, total, 6u);
-    if (__builtin_expect(total > kCap, 0)) {
+    const u32 total = run;
+    if (b.mode == kListPlain && total < rs.k) {
+        const u32 n = redo_row<DT, B, false>(P, L, row, rs, st, 8u, sm.ord, sm.rank, &run);
+        if (n != 0u) order_in_lds<DT, B>(P, row, rs, sm.ord, n, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.ord.buf[i]; });
+        return;
+    }
+    if (tid == 0) list_record(st, rs, total, 6u);
+    if (total > kCap) {
         for (u32 i = tid; i < kCap; i += B) list[i] = sm.ord.buf[i];
         if (tid == 0) st->redo |= kRedoList;
         order_shared<DT, B>(P, row, rs, sm.ord, shared, EntriesAt{list}, total, 0u, 0u, 1u);
-    } else if (total != 0u && total <= 8u * OB && !for_ties) {
+    } else if (total != 0u && total <= 8u * OB && b.mode != kListTied) {
         if (tid >= (u32)OB) return;  // (a barrier waits for the waves that are left)
         order_in_lds<DT, OB>(P, row, rs, sm.few, total, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.few.buf[i]; });
     } else if (total != 0u) {
         order_in_lds<DT, B, false, (B > 512)>(P, row, rs, sm.ord, total, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.ord.buf[i]; });
     }
-    if (for_ties) {
+    if (b.mode == kListTied && total < rs.k) {
         __syncthreads();
-        if (!ties_of_row<DT, B, Source>(P, TileCounts{te}, row, rs, total, b.T, 0u, 1u, sm.ord.hist, sm.ord.wsum) && tid == 0)
-            st->error |= 4u;  // never expected: there are enough of them
+        if (!ties_of_row<DT, B, Source>(P, TileCounts{te}, row, rs, total, b.T, 0u, 1u, sm.ord.hist, sm.ord.wsum)) {
+            __syncthreads();
+            const u32 n = redo_row<DT, B, false>(P, L, row, rs, st, 8u, sm.ord, sm.rank, &run);
+            if (n != 0u) order_in_lds<DT, B>(P, row, rs, sm.ord, n, 0u, [&](u32 i) __attribute__((always_inline)) { return sm.ord.buf[i]; });
+        }
     }
 }
 
